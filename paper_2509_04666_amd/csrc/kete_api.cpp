@@ -665,10 +665,11 @@ static int64_t cand_capacity(int64_t n_frames, int64_t pairs_cap) {
 // Device counters of the FoV stages: [0] pairs, [1..4] statistics,
 // [5] candidates, [6] wide objects, [8] failed hops, [9] pairs kept after
 // dropping failed objects; from [16] the work-queue cursors of the per-cell
-// join, then those of the wide join.
+// join, then those of the wide join, then the joins' statistics slots.
 constexpr int kFovCursorBase = 16;
 constexpr int kFovWideCursorBase = kFovCursorBase + kJoinCursorWords / 2;
-constexpr int kFovCounters = kFovWideCursorBase + kJoinCursorWords / 2;
+constexpr int kFovStatBase = kFovWideCursorBase + kJoinCursorWords / 2;
+constexpr int kFovCounters = kFovStatBase + kStatSlots * kStatStride;
 
 // Drops the pairs of objects whose hop failed (n_fail > 0): survivors of
 // keys[0..np) go to `out`, and their count is read back (one more
@@ -732,7 +733,7 @@ size_t kete_fov_workspace_size(int64_t n_obj, int64_t n_frames, int64_t n_batch,
     c.take<char>(scan_scratch_bytes(nkeys));
     c.take<int32_t>((size_t)nkeys + 1);             // join work items per key and their starts
     c.take<int32_t>((size_t)nkeys + 1);
-    c.take<unsigned long long>((size_t)fov_item_capacity(nkeys, n_batch * n_obj));
+    c.take<ulonglong2>((size_t)fov_item_capacity(nkeys, n_batch * n_obj));
     c.take<int64_t>((size_t)n_batch + 1);          // batch -> object layout
     c.take<int32_t>((size_t)n_batch);
     c.take<int64_t>((size_t)n_batch);
@@ -809,7 +810,7 @@ int kete_fov_check(const kete_ephem_t* eph, const double* x_epoch, int32_t* stat
     void* oscan = c.take<char>(scan_scratch_bytes(nkeys));
     int32_t* icnt = c.take<int32_t>((size_t)nkeys + 1);
     int32_t* istart = c.take<int32_t>((size_t)nkeys + 1);
-    unsigned long long* items = c.take<unsigned long long>((size_t)fov_item_capacity(nkeys, n_batch * n_obj));
+    ulonglong2* items = c.take<ulonglong2>((size_t)fov_item_capacity(nkeys, n_batch * n_obj));
     int64_t* b_poff = c.take<int64_t>((size_t)n_batch + 1);
     int32_t* b_obj0 = c.take<int32_t>((size_t)n_batch);
     int64_t* b_xoff = c.take<int64_t>((size_t)n_batch);
@@ -850,6 +851,7 @@ int kete_fov_check(const kete_ephem_t* eph, const double* x_epoch, int32_t* stat
     P.n_sub = frames->n_sub;
     P.n_pairs = counters;
     P.stats = counters + 1;
+    P.stat_slots = counters + kFovStatBase;
     P.n_cand = counters + 5;
     P.cap = pairs_cap;
     P.mu = E.gm[0];
@@ -1163,7 +1165,7 @@ struct BatchWs {
     int32_t* perm;
     FovParams P;
     int32_t *qkey, *cnt, *fcnt, *fstart, *okey, *orank, *osorted, *osub, *ostart, *ocnt, *icnt, *istart;
-    unsigned long long* items;
+    ulonglong2* items;
     unsigned long long *counters, *sorted;
     void *scan_scratch, *oscan, *wscan;
     int64_t *b_poff, *b_xoff, *b_koff;
@@ -1203,7 +1205,7 @@ size_t batch_carve(const BatchDims& d, const kete_batch_t* bt, char* base, Batch
     w.oscan = c.take<char>(scan_scratch_bytes(d.nkeys));
     w.icnt = c.take<int32_t>((size_t)d.nkeys + 1);
     w.istart = c.take<int32_t>((size_t)d.nkeys + 1);
-    w.items = c.take<unsigned long long>((size_t)fov_item_capacity(d.nkeys, d.NP));
+    w.items = c.take<ulonglong2>((size_t)fov_item_capacity(d.nkeys, d.NP));
     w.b_poff = c.take<int64_t>((size_t)d.B + 1);
     w.b_obj0 = c.take<int32_t>((size_t)d.B + 1);
     w.b_xoff = c.take<int64_t>((size_t)d.B + 1);
@@ -1326,6 +1328,7 @@ int kete_batch_run(const kete_ephem_t* eph, const kete_batch_t* batch, int64_t p
     P.n_sub = batch->frames.n_sub;
     P.n_pairs = w.counters;
     P.stats = w.counters + 1;
+    P.stat_slots = w.counters + kFovStatBase;
     P.n_cand = w.counters + 5;
     P.n_wide = w.counters + 6;
     P.n_fail = w.counters + 8;

@@ -916,11 +916,83 @@ __global__ void k_item_count(const FovParams p, int32_t* __restrict__ icnt) {
     icnt[key] = narrow_cell ? (p.obj_count[key] + kWave - 1) / kWave : 0;
 }
 
+// An item is {key << 32 | first object, batch << 32 | objects}: its objects
+// are obj_sorted[first ..] and the join needs no search for its batch.
 __global__ void k_item_scatter(const FovParams p, const int32_t* __restrict__ icnt) {
     const int64_t key = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (key >= p.n_keys) return;
-    const int n = icnt[key], s0 = p.item_start[key];
-    for (int c = 0; c < n; ++c) p.items[s0 + c] = ((unsigned long long)key << 32) | (unsigned long long)c;
+    const int n = icnt[key];
+    if (n == 0) return;
+    const int s0 = p.item_start[key], q0 = p.obj_start[key], m = p.obj_count[key];
+    const unsigned long long b = (unsigned long long)batch_of_key(p.b_koff, p.n_batch, key);
+    for (int c = 0; c < n; ++c)
+        p.items[s0 + c] = make_ulonglong2(((unsigned long long)key << 32) | (unsigned)(q0 + c * kWave),
+                                          (b << 32) | (unsigned)min(kWave, m - c * kWave));
+}
+
+// Work is taken from the slices of a list through per-XCD cursors (see
+// kXcds): `per` entries at a time from slice `home` first, then from the
+// others as it runs out.  `tried` counts the slices found empty.  Returns
+// false once all are.  Updates of one cursor are served one after another,
+// about 40 ns each, so the other slices, and every slice of a list shorter
+// than the grid, are looked at with a plain read first (every wavefront
+// passing eight empty slices with atomics took 0.1 ms a call, longer than
+// the join of a few thousand objects); a busy home slice is not, where the
+// read would double the traffic on its line.
+__device__ __forceinline__ bool take_slice(unsigned int* __restrict__ cursors, int n, int per, int home, int& tried,
+                                           int& first, int& end) {
+    while (tried < kXcds) {
+        const int x = (home + tried) % kXcds;
+        const int lo = (int)((int64_t)n * x / kXcds), hi = (int)((int64_t)n * (x + 1) / kXcds);
+        unsigned int* c = cursors + kCursorStride * x;
+        int at = 0;
+        if ((threadIdx.x & 63) == 0) {
+            at = hi - lo;
+            const bool look = tried > 0 || at < (int)(gridDim.x * (blockDim.x / kWave)) / kXcds;
+            if (at > 0 && (!look || (int)__hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < at))
+                at = (int)atomicAdd(c, (unsigned)per);
+        }
+        at = __builtin_amdgcn_readfirstlane(at);
+        if (at < hi - lo) {
+            first = lo + at;
+            end = min(first + per, hi);
+            return true;
+        }
+        ++tried;
+    }
+    return false;
+}
+
+// Entries a wavefront takes from a work list at once: a 32nd of its share of
+// the list, so that the last ones taken are a small part of its work, between
+// one and kSliceStep (at eight the items in flight on an XCD spread over more
+// sky than its L2 holds frames of: 141.8 -> 144.8 ms on 750,000 bodies x
+// 2,000,000 footprints).
+constexpr int kSliceStep = 3;
+__device__ __forceinline__ int slice_step(int n) {
+    return min(max(n / (32 * (int)(gridDim.x * (blockDim.x / kWave))), 1), kSliceStep);
+}
+
+// Adds the block's counts into its statistics slot: one atomic per nonzero
+// count and block (every wavefront of the chip on one counter cost about
+// 0.1 ms a call).  s [4][4] is LDS; the whole block calls it.
+__device__ __forceinline__ void add_stats(const FovParams& p, unsigned long long (*s)[4], unsigned long long a,
+                                          unsigned long long e, unsigned long long over,
+                                          unsigned long long visits) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        a += __shfl_xor(a, off, 64);
+        e += __shfl_xor(e, off, 64);
+    }
+    over = __shfl(over, 0, 64);
+    if (lane == 0) { s[wv][0] = a; s[wv][1] = e; s[wv][2] = over; s[wv][3] = visits; }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        unsigned long long v = 0ull;
+        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) v += s[w][threadIdx.x];
+        if (v) atomicAdd(p.stat_slots + (blockIdx.x % kStatSlots) * kStatStride + threadIdx.x, v);
+    }
 }
 
 // A frame's record for the per-cell join's broadcast loop: cap (centre,
@@ -931,7 +1003,6 @@ struct __align__(16) FrameRec {
 };
 
 constexpr int kLinQueue = 2 * kWave;
-constexpr int kItemChunk = 3;
 
 // Persistent join: every wavefront pops work items until none is left.
 // An item is up to 64 narrow objects of one (batch, cell), one per lane;
@@ -954,6 +1025,7 @@ __global__ __launch_bounds__(256, kJoinWaves) void k_fov_cells(const FovParams p
     __shared__ unsigned long long bufs[4][kBufEntries], pbufs[4][kPairBufEntries];
     __shared__ unsigned long long queue_all[4][kLinQueue];
     __shared__ FrameRec fcap_all[4][kWave];
+    __shared__ unsigned long long s_stat[4][4];
     unsigned long long* buf = bufs[wv];
     unsigned long long* pbuf = pbufs[wv];
     int npbuf = 0;
@@ -962,33 +1034,16 @@ __global__ __launch_bounds__(256, kJoinWaves) void k_fov_cells(const FovParams p
     const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     int nbuf = 0;
     int item = 0, item_end = 0;
+    const int per = slice_step(n_items);
     const int home = (int)(blockIdx.x % kXcds);
     int tried = 0;                            // slices found empty
     for (;;) {
-        // items are taken kItemChunk at a time: one atomic on a slice's
-        // cursor per chunk
-        if (item >= item_end) {
-            while (tried < kXcds) {
-                const int x = (home + tried) % kXcds;
-                const int lo = (int)((int64_t)n_items * x / kXcds), hi = (int)((int64_t)n_items * (x + 1) / kXcds);
-                int first = 0;
-                if (lane == 0) first = (int)atomicAdd(p.item_next + kCursorStride * x, (unsigned)kItemChunk);
-                first = __shfl(first, 0, kWave);
-                if (first < hi - lo) {
-                    item = lo + first;
-                    item_end = min(item + kItemChunk, hi);
-                    break;
-                }
-                ++tried;
-            }
-            if (tried >= kXcds) break;
-        }
-        const unsigned long long it = p.items[item++];
-        const int64_t key = (int64_t)(it >> 32);
-        const int chunk = (int)(it & 0xffffffffull);
-        const int o1 = p.obj_start[key + 1];
-        const int o0 = p.obj_start[key] + chunk * kWave;
-        const int b = batch_of_key(p.b_koff, p.n_batch, key);
+        if (item >= item_end && !take_slice(p.item_next, n_items, per, home, tried, item, item_end)) break;
+        const ulonglong2 it = p.items[item++];
+        const int64_t key = (int64_t)(it.x >> 32);
+        const int o0 = (int)(it.x & 0xffffffffull);
+        const int n_obj_i = (int)(it.y & 0xffffffffull);
+        const int b = (int)(it.y >> 32);
         const int G = p.b_G[b];
         const int64_t base = p.b_koff[b];
         const int cell = (int)(key - base);
@@ -1015,9 +1070,8 @@ __global__ __launch_bounds__(256, kJoinWaves) void k_fov_cells(const FovParams p
         const int excl = incl - my_len;
         const int total = __shfl(incl, 26, kWave);
         if (total == 0) continue;
-        const int q = o0 + lane;
-        const bool has = q < o1;
-        const int64_t j = has ? p.obj_sorted[q] : 0;
+        const bool has = lane < n_obj_i;
+        const int64_t j = has ? p.obj_sorted[o0 + lane] : 0;
         ObjBounds o;
 #pragma unroll
         for (int c = 0; c < 3; ++c) { o.x[c] = 0.0; o.v[c] = 0.0; }
@@ -1151,19 +1205,7 @@ __global__ __launch_bounds__(256, kJoinWaves) void k_fov_cells(const FovParams p
     }
     buf_flush(buf, nbuf, p.cand, p.n_cand, p.cand_cap);
     buf_flush(pbuf, npbuf, p.pairs, p.n_pairs, p.cap);
-    if (p.stats) {
-        unsigned long long a = n_cand, e = n_exact;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            a += __shfl_xor(a, off, 64);
-            e += __shfl_xor(e, off, 64);
-        }
-        if (lane == 0) {
-            atomicAdd(p.stats + 0, a);
-            atomicAdd(p.stats + 1, e);
-            atomicAdd(p.stats + 3, n_visit);
-        }
-    }
+    if (p.stats) add_stats(p, s_stat, n_cand, n_exact, 0ull, n_visit);
 }
 
 // Frame test of the wide join, one frame per lane: the motion-cap test, and
@@ -1225,6 +1267,7 @@ __global__ void k_wide_parts(const FovParams p) {
 __global__ __launch_bounds__(256, kJoinWaves) void k_fov_wide(const FovParams p) {
     const int lane = threadIdx.x & 63, wv = (threadIdx.x >> 6) & 3;
     __shared__ int s_incl[4][kWave], s_base[4][kWave], s_queue[4][2 * kWave];
+    __shared__ unsigned long long s_stat[4][4];
     __shared__ unsigned long long bufs[4][kBufEntries], pbufs[4][kPairBufEntries];
     int* incl_w = s_incl[wv];
     int* base_w = s_base[wv];
@@ -1238,25 +1281,11 @@ __global__ __launch_bounds__(256, kJoinWaves) void k_fov_wide(const FovParams p)
     int nbuf = 0, npbuf = 0;
     unsigned long long n_cand = 0, n_exact = 0, n_over = 0;
     const int home = (int)(blockIdx.x % kXcds);
+    const int per = slice_step(n_parts);
     int tried = 0, part = 0, part_end = 0;
     int w = 0;                                   // object of the previous part
     for (;;) {
-        if (part >= part_end) {
-            while (tried < kXcds) {
-                const int x = (home + tried) % kXcds;
-                const int lo = (int)((int64_t)n_parts * x / kXcds), hi = (int)((int64_t)n_parts * (x + 1) / kXcds);
-                int first = 0;
-                if (lane == 0) first = (int)atomicAdd(p.wide_next + kCursorStride * x, 4u);
-                first = __shfl(first, 0, kWave);
-                if (first < hi - lo) {
-                    part = lo + first;
-                    part_end = min(part + 4, hi);
-                    break;
-                }
-                ++tried;
-            }
-            if (tried >= kXcds) break;
-        }
+        if (part >= part_end && !take_slice(p.wide_next, n_parts, per, home, tried, part, part_end)) break;
         const int pi = part++;
         // object w of part pi: the last w with wide_off[w] <= pi
         if (!(w < n_obj_w && p.wide_off[w] <= pi && pi < p.wide_off[w + 1])) {
@@ -1371,19 +1400,7 @@ __global__ __launch_bounds__(256, kJoinWaves) void k_fov_wide(const FovParams p)
     }
     buf_flush(buf, nbuf, p.cand, p.n_cand, p.cand_cap);
     buf_flush(pbuf, npbuf, p.pairs, p.n_pairs, p.cap);
-    if (p.stats) {
-        unsigned long long a = n_cand, e = n_exact;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            a += __shfl_xor(a, off, 64);
-            e += __shfl_xor(e, off, 64);
-        }
-        if (lane == 0) {
-            atomicAdd(p.stats + 0, a);
-            atomicAdd(p.stats + 1, e);
-            atomicAdd(p.stats + 2, n_over);
-        }
-    }
+    if (p.stats) add_stats(p, s_stat, n_cand, n_exact, n_over, 0ull);
 }
 
 // Sky cell of every (object, batch): direction from the batch's mean
@@ -1615,6 +1632,11 @@ __global__ __launch_bounds__(256) void k_fov_exact(const FovParams p) {
     __shared__ unsigned long long s_buf[4][kPairBufEntries];
     unsigned long long* buf = s_buf[threadIdx.x >> 6];
     int nbuf = 0;
+    if (p.stats && blockIdx.x == 0 && threadIdx.x < 4) {       // the joins' statistics
+        unsigned long long v = 0ull;
+        for (int k = 0; k < kStatSlots; ++k) v += p.stat_slots[k * kStatStride + threadIdx.x];
+        p.stats[threadIdx.x] = v;
+    }
     const unsigned long long nc = *p.n_cand;
     const unsigned long long n = nc < (unsigned long long)p.cand_cap ? nc : (unsigned long long)p.cand_cap;
     const unsigned long long stride = (unsigned long long)gridDim.x * blockDim.x;
@@ -2202,7 +2224,7 @@ hipError_t fill_zero(void* p, size_t bytes, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t fov_candidates(FovParams& p, int32_t* icnt, int32_t* istart, unsigned long long* items,
+hipError_t fov_candidates(FovParams& p, int32_t* icnt, int32_t* istart, ulonglong2* items,
                           unsigned int* item_next, void* scan_scratch, void* wide_scan_scratch, hipStream_t s) {
     if (p.n_pairs_total == 0 || p.n_batch == 0) return hipSuccess;
     p.items = items;

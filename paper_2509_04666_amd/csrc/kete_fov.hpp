@@ -60,7 +60,8 @@ struct FovParams {
     unsigned long long* pairs;  // [cap] packed (frame << 32 | sub << 25 | obj)
     unsigned long long* n_pairs;
     int64_t cap;
-    unsigned long long* stats;  // [4] or null: candidates, exact tests, brute-force objects
+    unsigned long long* stats;  // [4] or null: cap hits, exact tests, brute-force objects, frame visits
+    unsigned long long* stat_slots;     // their partial sums (kStatSlots x kStatStride, zeroed by the caller)
     unsigned long long* cand;   // [cand_cap] keys (frame, sub-frame or kAllSubs, object) for the exact test
     unsigned long long* n_cand;
     int64_t cand_cap;
@@ -84,7 +85,7 @@ struct FovParams {
     const int32_t* obj_sorted;  // [n_pairs_total] local objects of each batch ordered by sky cell
     const int32_t* obj_start;   // [n_keys + 1] start of each key's objects in obj_sorted
     const int32_t* obj_count;   // [n_keys] objects per key
-    unsigned long long* items;  // work items of the per-cell join: key << 32 | object chunk
+    ulonglong2* items;          // work items of the per-cell join (see k_item_scatter)
     const int32_t* item_start;  // [n_keys + 1] exclusive scan of items per key (total at n_keys)
     unsigned int* item_next;    // work-queue cursors, kJoinCursorWords unsigned ints
     unsigned long long* wide;   // [n_pairs_total] (batch << 32 | local obj) of objects with wide motion caps
@@ -127,13 +128,18 @@ constexpr int kXcds = 8;
 constexpr int kCursorStride = 32;
 constexpr int kJoinCursorWords = kXcds * kCursorStride;
 constexpr int kWidePartFrames = 1024;
+// The joins' statistics are summed per block, then over kStatSlots slots
+// kStatStride words (128 bytes) apart, and folded into `stats` by the exact
+// test.
+constexpr int kStatSlots = 32;
+constexpr int kStatStride = 16;
 
 // Candidate generation.  icnt and istart are [n_keys + 1] int32 scratch
 // (istart becomes p.item_start), items holds n_keys + n_pairs_total / 64 + 1
 // entries, scan_scratch >= scan_scratch_bytes(n_keys), wide_scan_scratch >=
 // scan_scratch_bytes(n_pairs_total); p.wide_parts, p.wide_off and
 // p.wide_next must be set.
-hipError_t fov_candidates(FovParams& p, int32_t* icnt, int32_t* istart, unsigned long long* items,
+hipError_t fov_candidates(FovParams& p, int32_t* icnt, int32_t* istart, ulonglong2* items,
                           unsigned int* item_next, void* scan_scratch, void* wide_scan_scratch, hipStream_t s);
 inline int64_t fov_item_capacity(int64_t n_keys, int64_t n_pairs_total) { return n_keys + n_pairs_total / 64 + 1; }
 // Doubles of the frame copies (cell_obs, cell_normals as floats, exact_rec).
