@@ -430,7 +430,7 @@ static int segs_or(const kete_opts_t* o, int dflt) { return o->window_segs > 0 ?
 // blocks of 256 threads share a compute unit's 160 KB of LDS, else smaller
 // blocks.  With landing on every epoch: 128 threads, 2 segments.
 static void auto_integrator_shape(const kete_ephem_t* eph, bool dense, int& block, int& wsegs) {
-    constexpr size_t kBlockLds = 53248;
+    constexpr size_t kBlockLds = 163840 / 3;
     if (!dense) {
         if (block == 0) block = 128;
         if (wsegs <= 0) wsegs = 2;

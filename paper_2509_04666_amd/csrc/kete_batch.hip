@@ -94,7 +94,7 @@ __global__ __launch_bounds__(64, 3) void k_batch_g8(const BatchParams p) {
     load_node_row(p.rc, node, R);
     // dense-output rows and the wavefront's weight slots
     __shared__ double dcoef[kDenseCoefDoubles];
-    __shared__ double dwts[16];
+    __shared__ __align__(16) double dwts[kDenseWeights];
     for (int i = lane; i < kDenseCoefDoubles; i += 64) dcoef[i] = p.dense_coef[i];
     __syncthreads();
     const int W = p.max_win_segs - 1;            // segment lengths per window
@@ -154,25 +154,9 @@ __global__ __launch_bounds__(64, 3) void k_batch_g8(const BatchParams p) {
             const double target = ep[e_end];
             int e_next = e;                              // wave-uniform cursor over e .. e_end - 1
             auto dense_out = [&](double ts, double h, const double dn[3], const G8State& St) {
-                if (e_next >= e_end) return;
-                const double te = ts + h;
-                double tk = ep[e_next];
-                if (!(h > 0.0 ? tk <= te : tk >= te)) return;
-                wave_lds_sync();                        // earlier reads of the exchange rows are done
-                xg[gl] = dn[0];
-                xg[8 + gl] = dn[1];
-                xg[16 + gl] = dn[2];
-                wave_lds_sync();
-                for (;;) {
-                    const double sig = (tk - ts) / h;
-                    dense_weights_wave(dcoef, sig, lane, dwts);
-                    double X[3], V[3];
-                    dense_state_wave(dwts, xg, St.x0, St.v0, St.F0, h, sig, X, V);
-                    put(e_next, state_component(X, V, gl < 6 ? gl : 5), St.active && St.status == 0);
-                    if (++e_next >= e_end) break;
-                    tk = ep[e_next];
-                    if (!(h > 0.0 ? tk <= te : tk >= te)) break;
-                }
+                const bool ok = St.active && St.status == 0;
+                dense_epochs(dcoef, dwts, xg, gl, lane, ts, h, dn, St.x0, St.v0, St.F0, ep, e_next, e_end,
+                             [&](int k, double v) { put(k, v, ok); });
             };
             while (S.t != target) {
                 const Window Wn = next_window(S.t, target, E.t_start, E.seg_days, E.inv_seg, E.n_seg, W);

@@ -188,7 +188,7 @@ __global__ __launch_bounds__(BLOCK, 3) void k_nbody_g8(const NbodyParams p) {
     }
     // dense-output rows, read from LDS at the epochs inside a step
     __shared__ double dcoef[kDenseCoefDoubles];
-    __shared__ double dwts[BLOCK / kWave][16];      // per wavefront: the 14 weights of an epoch
+    __shared__ __align__(16) double dwts[BLOCK / kWave][kDenseWeights];
     if (p.e_first < p.e_land)
         for (int i = tid; i < kDenseCoefDoubles; i += BLOCK) dcoef[i] = p.dense_coef[i];
     __syncthreads();
@@ -229,25 +229,9 @@ __global__ __launch_bounds__(BLOCK, 3) void k_nbody_g8(const NbodyParams p) {
         ++e_next;
     }
     auto dense_out = [&](double ts, double h, const double dn[3], const G8State& St) {
-        if (e_next >= p.e_land) return;
-        const double te = ts + h;
-        double tk = p.t_out[e_next];
-        if (!(h > 0.0 ? tk <= te : tk >= te)) return;
-        wave_lds_sync();                    // earlier reads of the exchange rows are done
-        xg[gl] = dn[0];
-        xg[8 + gl] = dn[1];
-        xg[16 + gl] = dn[2];
-        wave_lds_sync();
-        for (;;) {
-            const double sig = (tk - ts) / h;
-            dense_weights_wave(dcoef, sig, lane, dwts[wid]);
-            double X[3], V[3];
-            dense_state_wave(dwts[wid], xg, St.x0, St.v0, St.F0, h, sig, X, V);
-            put(e_next, state_component(X, V, gl < 6 ? gl : 5), St.active && St.status == 0);
-            if (++e_next >= p.e_land) break;
-            tk = p.t_out[e_next];
-            if (!(h > 0.0 ? tk <= te : tk >= te)) break;
-        }
+        const bool ok = St.active && St.status == 0;
+        dense_epochs(dcoef, dwts[wid], xg, gl, lane, ts, h, dn, St.x0, St.v0, St.F0, p.t_out, e_next, p.e_land,
+                     [&](int e, double v) { put(e, v, ok); });
     };
 
     for (int w = 0; w < p.n_win; ++w) {
@@ -362,7 +346,7 @@ __global__ void k_hpref_init(const double* __restrict__ x0, double* __restrict__
 size_t nbody_g8_lds_bytes(int n_body, int deg1, int max_win_segs, int block) {
     return ((((size_t)n_body * max_win_segs * 3 * deg1 + 1) & ~(size_t)1) +
             (size_t)(block / kWave) * g8_wave_doubles(n_body)) * sizeof(double) +
-           sizeof(NodeRow) * kGroup + kDenseCoefDoubles * sizeof(double);
+           sizeof(NodeRow) * kGroup + (kDenseCoefDoubles + block / kWave * kDenseWeights) * sizeof(double);
 }
 
 hipError_t launch_nbody(const NbodyParams& p, int block, int lanes_per_body, hipStream_t s) {

@@ -866,43 +866,10 @@ __device__ __forceinline__ double state_component(const double x0[3], const doub
 
 // Collocation polynomial at fraction sig of the step (sig = 1: step end),
 // from the monomial weights alpha_m(sig) = sum_k Ap[m][k] sig^(k+2) and
-// beta_m(sig) = sum_k Bp[m][k] sig^(k+1) (m = 1..7, k = 0..7).
-__device__ __forceinline__ void dense_weights(const RadauConst& rc, double sig, double al[7], double be[7]) {
-    // opaque zero row offset: the 112 constants are loaded where used
-    // rather than held in registers across the caller's loops
-    int z;
-    asm volatile("s_mov_b32 %0, 0" : "=s"(z));
-#pragma unroll
-    for (int m = 0; m < 7; ++m) {
-        double a = rc.Ap[m + z][7], b = rc.Bp[m + z][7];
-#pragma unroll
-        for (int k = 6; k >= 0; --k) { a = fma(a, sig, rc.Ap[m + z][k]); b = fma(b, sig, rc.Bp[m + z][k]); }
-        al[m] = a * sig * sig;
-        be[m] = b * sig;
-    }
-}
-
-__device__ __forceinline__ void dense_state(const RadauConst& rc, const double x0[3], const double v0[3],
-                                            const double F0[3], const double D[7][3], double h, double sig,
-                                            double X[3], double V[3]) {
-    double al[7], be[7];
-    dense_weights(rc, sig, al, be);
-    const double hh = h * h;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        double ax = 0.5 * sig * sig * F0[c], av = sig * F0[c];
-#pragma unroll
-        for (int m = 0; m < 7; ++m) { ax = fma(al[m], D[m][c], ax); av = fma(be[m], D[m][c], av); }
-        X[c] = fma(hh, ax, fma(sig * h, v0[c], x0[c]));
-        V[c] = fma(h, av, v0[c]);
-    }
-}
-
-// dense_state with the monomial rows read from a copy in LDS (cw: Ap[7][8]
-// then Bp[7][8]) rather than from the kernel's argument block, and the
-// step's node increments from the group's exchange rows xg (component c of
-// node m + 1 at xg[8 c + m]), one node at a time; sig may differ between
-// groups.
+// beta_m(sig) = sum_k Bp[m][k] sig^(k+1) (m = 1..7, k = 0..7), their rows
+// read from a copy in LDS (cw: Ap[7][8] then Bp[7][8]), and the step's node
+// increments from the group's exchange rows xg (component c of node m + 1 at
+// xg[8 c + m]), one node at a time; sig may differ between groups.
 __device__ __forceinline__ void dense_state_rows(const double* __restrict__ cw, const double* __restrict__ xg,
                                                  const double x0[3], const double v0[3], const double F0[3],
                                                  double h, double sig, double X[3], double V[3]) {
@@ -933,48 +900,84 @@ __device__ __forceinline__ void dense_state_rows(const double* __restrict__ cw, 
     }
 }
 
-// Dense output at fraction sig of a step, in two parts.  The 14 weights
-// alpha_m(sig) = sum_k Ap[m][k] sig^(k+2) and beta_m(sig) = sum_k Bp[m][k]
-// sig^(k+1) are the same for every object of a wavefront (they share the
-// step), so lanes 0..13 evaluate one each from the monomial rows in LDS
-// (cw: Ap[7][8] then Bp[7][8]) into the wavefront's slots wt[14]; then
-// each lane forms its object's state from the weights and the step's node
-// increments in the group's exchange rows xg (component c
-// of node m + 1 at xg[8 c + m]) in dense_state_wave.  The first call is
-// made by the whole wavefront.
-__device__ __forceinline__ void dense_weights_wave(const double* __restrict__ cw, double sig, int lane,
-                                                   double* __restrict__ wt) {
-    wave_lds_sync();                        // earlier reads of wt are done
-    if (lane < 14) {
-        const double* pm = cw + 8 * lane;
+// Dense output of a step for a wavefront's objects: epochs t_out[e_next ..
+// e_end - 1] that lie inside the step [ts, ts + h] are read off its
+// collocation polynomial and put(e, value) gets component gl (0..5) of each
+// object's state; e_next moves past them.  The step is the same for every
+// object, so its weights are too: the 16 lanes of a quarter of the wavefront
+// evaluate one epoch's (slots 0..6 alpha_m(sig) = sum_k Ap[m][k] sig^(k+2)
+// and 7 sig^2 / 2 of the force at the step start; 8..14 beta_m(sig) = sum_k
+// Bp[m][k] sig^(k+1) and 15 sig), four epochs at a time, into the
+// wavefront's slots wt[64]; then each lane forms the one component it
+// writes, eight multiply-adds an epoch, from the weights and the node
+// increments of its group in the exchange rows xg.  (Every lane forming
+// all six components, one epoch's 14 weights at a time, took 250 vector
+// instructions an epoch, a fifth of the integrator's with epochs 3 days apart.)
+constexpr int kDenseRound = 4;              // epochs per round
+constexpr int kDenseWeights = 16 * kDenseRound;
+template <class Put>
+__device__ __forceinline__ void dense_epochs(const double* __restrict__ cw, double* __restrict__ wt,
+                                             double* __restrict__ xg, int gl, int lane, double ts, double h,
+                                             const double dn[3], const double x0[3], const double v0[3],
+                                             const double F0[3], const double* __restrict__ t_out, int& e_next,
+                                             int e_end, Put&& put) {
+    if (e_next >= e_end) return;
+    const double te = ts + h;
+    const double t_first = t_out[e_next];
+    if (!(h > 0.0 ? t_first <= te : t_first >= te)) return;
+    wave_lds_sync();                        // earlier reads of the exchange rows are done
+    xg[gl] = dn[0];
+    xg[8 + gl] = dn[1];
+    xg[16 + gl] = dn[2];
+    wave_lds_sync();
+    // this lane's component: coordinate c of the position or velocity
+    const bool vel = gl >= 3;
+    const int c = vel ? (gl < 6 ? gl - 3 : 2) : gl;
+    double D[8];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const double2 d = *reinterpret_cast<const double2*>(xg + 8 * c + 2 * k);
+        D[2 * k] = d.x;
+        D[2 * k + 1] = d.y;
+    }
+    const double xc = c == 0 ? x0[0] : c == 1 ? x0[1] : x0[2];
+    const double vc = c == 0 ? v0[0] : c == 1 ? v0[1] : v0[2];
+    D[7] = c == 0 ? F0[0] : c == 1 ? F0[1] : F0[2];
+    const double hc = vel ? h : h * h;
+    const int m = lane & 15;
+    const double* pm = cw + 8 * (m < 7 ? m : m < 15 ? m - 1 : 13);
+    for (;;) {
+        const int el = e_next + (lane >> 4);
+        const double tk = t_out[el < e_end ? el : e_end - 1];
+        const int n = __popcll(__ballot(el < e_end && (h > 0.0 ? tk <= te : tk >= te))) >> 4;
+        const double sig = (tk - ts) / h;
         double w = pm[7];
 #pragma unroll
         for (int k = 6; k >= 0; --k) w = fma(w, sig, pm[k]);
-        wt[lane] = w * (lane < 7 ? sig * sig : sig);
-    }
-    wave_lds_sync();
-}
-__device__ __forceinline__ void dense_state_wave(const double* __restrict__ wt, const double* __restrict__ xg,
-                                                 const double x0[3], const double v0[3], const double F0[3],
-                                                 double h, double sig, double X[3], double V[3]) {
-    double ax[3], av[3];
+        w *= m < 8 ? sig * sig : sig;
+        if (m == 7) w = 0.5 * sig * sig;
+        if (m == 15) w = sig;
+        wave_lds_sync();                    // earlier reads of wt are done
+        wt[lane] = w;
+        wave_lds_sync();
 #pragma unroll
-    for (int c = 0; c < 3; ++c) { ax[c] = 0.5 * sig * sig * F0[c]; av[c] = sig * F0[c]; }
-#pragma unroll 1
-    for (int m = 0; m < 7; ++m) {
-        const double a = wt[m], b = wt[7 + m];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const double d = xg[8 * c + m];
-            ax[c] = fma(a, d, ax[c]);
-            av[c] = fma(b, d, av[c]);
+        for (int k = 0; k < kDenseRound; ++k) {
+            if (k >= n) break;
+            const double2* q = reinterpret_cast<const double2*>(wt + 16 * k + (vel ? 8 : 0));
+            const double2 q0 = q[0], q1 = q[1], q2 = q[2], q3 = q[3];
+            double a = q3.y * D[7];
+            a = fma(q0.x, D[0], a);
+            a = fma(q0.y, D[1], a);
+            a = fma(q1.x, D[2], a);
+            a = fma(q1.y, D[3], a);
+            a = fma(q2.x, D[4], a);
+            a = fma(q2.y, D[5], a);
+            a = fma(q3.x, D[6], a);
+            const double sg = wt[16 * k + 15];
+            put(e_next + k, vel ? fma(hc, a, vc) : fma(hc, a, fma(sg * h, vc, xc)));
         }
-    }
-    const double hh = h * h;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        X[c] = fma(hh, ax[c], fma(sig * h, v0[c], x0[c]));
-        V[c] = fma(h, av[c], v0[c]);
+        e_next += n;
+        if (n < kDenseRound || e_next >= e_end) break;
     }
 }
 
