@@ -97,14 +97,12 @@ typedef struct {
     int32_t max_steps;       /* per object per call (2,000,000) */
     int32_t max_iter;        /* corrector iterations per step (12) */
     int32_t n_buckets;       /* step-size buckets (octaves of the predicted step), 1 = none (16) */
-    int32_t block;           /* integrator threads per block: 64/128/256, 0 = auto (0: 256 for the
-                                grouped integrators reading epochs off the step polynomials,
-                                else 128) */
+    int32_t block;           /* integrator threads per block: 64/128/256, 0 = auto (0: 64 for the
+                                grouped integrators, 128 with one lane per body) */
     int32_t rebucket_epochs; /* epochs per integrator launch, 0 = all (0) */
-    int32_t window_segs;     /* Chebyshev segments per staged window, 0 = auto (0: for the grouped
-                                integrators reading epochs off the step polynomials the most, up
-                                to 6, with which three blocks share a compute unit's LDS; for the
-                                adjoint 3; else 2) */
+    int32_t window_segs;     /* Chebyshev segments per integration window; a step ends at every
+                                window's end.  0 = auto (0: no windows for the grouped
+                                integrators and the adjoint, 2 with one lane per body) */
     int32_t lt_iter;         /* light-time updates at most (10) */
     int32_t fov_block;       /* FoV threads per block: 64/128/256 (128) */
     int32_t adj_seg_steps;   /* adjoint: steps stored per checkpoint segment (32) */

@@ -9,8 +9,7 @@
 //
 // Backward: the discrete adjoint of that forward map.  Checkpoint
 // segments are processed last to first: the segment's steps are
-// recomputed from its checkpoint (same windows and step sequence, bit for
-// bit) while each step's start, size and force Jacobians at its 8 nodes
+// recomputed from its checkpoint (same step sequence, bit for bit) while each step's start, size and force Jacobians at its 8 nodes
 // are stored; the steps are then swept in reverse, solving the linear
 // stage equations of the step's transpose by fixed-point iteration.  The
 // recompute of the next segment runs on a second stream during a sweep.  The light-time hop's
@@ -225,14 +224,12 @@ __device__ __forceinline__ void init_lane_state(const AdjParams& p, bool valid, 
 
 template <int NB, int NGR, int DEG1>
 __global__ __launch_bounds__(64, 3) void k_adjoint_fwd(const AdjParams p) {
-    extern __shared__ double smem[];
+    extern __shared__ __align__(16) double smem[];
     const int lane = threadIdx.x;
     const int gl = lane & (kGroup - 1);
     const int node = gl < 7 ? gl + 1 : 7;
     const EphemArgs& E = p.eph;
-    const int bstride = p.max_win_segs * 3 * E.deg1;
-    double* coefL = smem;
-    double* e8 = smem + (((size_t)E.n_body * bstride + 1) & ~(size_t)1);
+    double* e8 = smem;
     g8_table_init(E, lane, e8);
     NodeRow R;
     load_node_row(p.rc, node, R);
@@ -290,16 +287,12 @@ __global__ __launch_bounds__(64, 3) void k_adjoint_fwd(const AdjParams p) {
         }
     };
     if (valid) save_ckpt_g8(p, 0, j, gl, S, S.t);
-    // windows on the fixed grid (aligned_window), so a recompute that starts
-    // at a checkpoint cuts its steps where this run did
-    const int wsegs = p.max_win_segs - 1;
-    int lo = 1, hi = 0;                          // nothing staged yet
-    while (S.t < p.t_end) {
-        const Window W = aligned_window(S.t, p.t_end, E.t_start, E.seg_days, E.inv_seg, E.n_seg, wsegs);
-        ensure_window(E, W.seg_lo, W.seg_hi, lo, hi, coefL, bstride);
-        g8_integrate<NB, NGR, DEG1, kGroup, kStartExtrapolateHeld>(p, R, node, gl, lane / kGroup, lane, coefL, bstride,
-                                                                   e8, lo, hi, W.t_b, S, C, visit);
-    }
+    // (windows, if asked for, end on the fixed grid of aligned_end, so a
+    // recompute that starts at a checkpoint cuts its steps where this run did)
+    while (S.t < p.t_end)
+        g8_integrate<NB, NGR, DEG1, kGroup, kStartExtrapolateHeld>(
+            p, R, node, gl, lane / kGroup, lane, e8,
+            aligned_end(S.t, p.t_end, E.t_start, E.seg_days, E.inv_seg, p.window_segs), S, C, visit);
     // checkpoints no step start reached: the end state
     for (; c_next <= p.n_ckpt; ++c_next)
         if (valid) save_ckpt_g8(p, c_next, j, gl, S, p.t_end);
@@ -399,7 +392,7 @@ __device__ __forceinline__ void fill_node_rows(const RadauConst& rc, int tid, No
 }
 
 // Backward, first half for checkpoint segment c: recompute the segment from
-// its checkpoint with the forward's grouping, windows and step sequence
+// its checkpoint with the forward's grouping and step sequence
 // (one wavefront per block: the checkpoints' times differ between
 // wavefronts), storing each step's start and size and this lane's node
 // Jacobians (lane 7: node 0).  The step count (plus kSegOverflow when the
@@ -409,7 +402,7 @@ static_assert(kAdjLanes == kGroup, "adjoint wavefronts hold 8 objects");
 
 template <int NB, int NGR, int DEG1>
 __global__ __launch_bounds__(64, 2) void k_adj_recompute(const AdjParams p, const int c) {
-    extern __shared__ double smem[];
+    extern __shared__ __align__(16) double smem[];
     const int lane = threadIdx.x;
     const int gl = lane & (kGroup - 1);
     const int node = gl < 7 ? gl + 1 : 7;
@@ -429,9 +422,7 @@ __global__ __launch_bounds__(64, 2) void k_adj_recompute(const AdjParams p, cons
         if (lane == 0) p.seg_ns[wave] = 0;
         return;                                     // the whole block: one wavefront
     }
-    const int bstride = p.max_win_segs * 3 * E.deg1;
-    double* coefL = smem;
-    double* e8 = smem + (((size_t)E.n_body * bstride + 1) & ~(size_t)1);
+    double* e8 = smem;
     g8_table_init(E, lane, e8);
     __shared__ NodeRow rows[kGroup];
     fill_node_rows(p.rc, lane, rows);
@@ -491,16 +482,12 @@ __global__ __launch_bounds__(64, 2) void k_adj_recompute(const AdjParams p, cons
             }
             ++ns;
         };
-    // the forward's windows (aligned_window) from the checkpoint on, until
-    // the step start where the forward took the next checkpoint
-    const int wsegs = p.max_win_segs - 1;
-    int lo = 1, hi = 0;                          // nothing staged yet
-    while (S.t < t_stop) {
-        const Window W = aligned_window(S.t, p.t_end, E.t_start, E.seg_days, E.inv_seg, E.n_seg, wsegs);
-        ensure_window(E, W.seg_lo, W.seg_hi, lo, hi, coefL, bstride);
-        g8_integrate<NB, NGR, DEG1, kGroup, kStartExtrapolateHeld>(p, R, node, gl, lane / kGroup, lane, coefL, bstride,
-                                                                   e8, lo, hi, W.t_b, S, Cn, store, true, t_stop);
-    }
+    // the forward's steps (and windows) from the checkpoint on, until the
+    // step start where the forward took the next checkpoint
+    while (S.t < t_stop)
+        g8_integrate<NB, NGR, DEG1, kGroup, kStartExtrapolateHeld>(
+            p, R, node, gl, lane / kGroup, lane, e8,
+            aligned_end(S.t, p.t_end, E.t_start, E.seg_days, E.inv_seg, p.window_segs), S, Cn, store, true, t_stop);
     if (lane == 0 && wave * kGroup < p.n_obj) p.seg_ns[wave] = min(ns, p.s_max) | (overflow_steps ? kSegOverflow : 0);
 }
 
@@ -728,8 +715,7 @@ __global__ __launch_bounds__(64) void k_adj_sweep(const AdjParams p, const int c
 }  // namespace
 
 size_t adjoint_lds_bytes(const AdjParams& p) {
-    return ((((size_t)p.eph.n_body * p.max_win_segs * 3 * p.eph.deg1 + 1) & ~(size_t)1) +
-            (size_t)g8_wave_doubles(p.eph.n_body)) * sizeof(double);
+    return (size_t)g8_wave_doubles(p.eph.n_body) * sizeof(double);
 }
 
 

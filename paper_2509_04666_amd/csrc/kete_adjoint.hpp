@@ -46,7 +46,7 @@ struct AdjParams {
     double* adj_tab;            // [kAdjTabDoubles] constant rows of the reverse sweep
     double* dense_coef;         // [kDenseCoefDoubles] Ap, Bp of rc (written by the forward launch)
     int32_t s_max;
-    int32_t max_win_segs;
+    int32_t window_segs;        // segments between forced step ends (0: none)
     int32_t max_iter;
     int32_t max_steps;
     double eps, h_min, h_max, h_init, safety;

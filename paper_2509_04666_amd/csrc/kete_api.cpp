@@ -421,33 +421,18 @@ int kete_make_batches(const double* t, int64_t n_frames, double span, int32_t* f
     return KETE_OK;
 }
 
-// window_segs, with 0 (auto) taken as dflt.
-static int segs_or(const kete_opts_t* o, int dflt) { return o->window_segs > 0 ? o->window_segs : dflt; }
+// window_segs, 0 (auto) meaning no forced step ends.
+static int window_segs(const kete_opts_t* o) { return std::max(o->window_segs, 0); }
 
 // Launch shape of the integrator where block or window_segs is 0 (auto).
-// With epochs read off the step polynomials, steps run until a window ends,
-// so windows are long: the longest (up to 6 segments) with which three
-// blocks of 256 threads share a compute unit's 160 KB of LDS, else smaller
-// blocks.  With landing on every epoch: 128 threads, 2 segments.
-static void auto_integrator_shape(const kete_ephem_t* eph, bool dense, int& block, int& wsegs) {
-    constexpr size_t kBlockLds = 163840 / 3;
-    if (!dense) {
-        if (block == 0) block = 128;
-        if (wsegs <= 0) wsegs = 2;
-        return;
-    }
-    for (int b : {256, 128, 64}) {
-        if (block != 0 && b != block) continue;
-        if (wsegs > 0) { block = b; return; }
-        for (int w = 6; w >= 1; --w)
-            if (nbody_g8_lds_bytes(eph->n_body, eph->degree + 1, w + 1, b) <= kBlockLds) {
-                block = b;
-                wsegs = w;
-                return;
-            }
-    }
-    if (block == 0) block = 64;
-    if (wsegs <= 0) wsegs = 1;
+// The grouped kernels share nothing between wavefronts, so a block is one
+// wavefront: it leaves as soon as its own bodies are done.  They read the
+// perturber table from L2, so a window is only where a step must end: the
+// landing epochs (wsegs 0), and segment boundaries if the caller asks.  One
+// lane per body stages its windows in LDS: 128 threads, 2 segments.
+static void auto_integrator_shape(bool grouped, int& block, int& wsegs) {
+    if (block == 0) block = grouped ? 64 : 128;
+    if (wsegs <= 0) wsegs = grouped ? 0 : 2;
 }
 
 // The output epochs and the dense-output rows travel in front of the window
@@ -541,7 +526,7 @@ int kete_propagate_nbody(const kete_ephem_t* eph, const double* x0, double t0, i
     const int ncls = sort_classes(opts);
     const bool dense = !opts->land_epochs && opts->lanes_per_body != 1;
     int block = opts->block, wsegs = opts->window_segs;
-    auto_integrator_shape(eph, dense, block, wsegs);
+    auto_integrator_shape(opts->lanes_per_body != 1, block, wsegs);
 
     // Launches cover runs of rebucket_epochs epochs.  With landing on every
     // epoch each epoch ends a window; otherwise only a launch's last epoch
@@ -908,7 +893,7 @@ int kete_fov_check(const kete_ephem_t* eph, const double* x_epoch, int32_t* stat
 }
 
 // Checkpoint segments of the adjoint: C = ceil((t_end - t0) / ckpt_days).
-// The kernels plan their own windows (aligned_window) and take checkpoint c
+// The kernels plan their own windows (aligned_end) and take checkpoint c
 // at the first step start at or after t0 + c ckpt_days.
 static int adjoint_plan(const kete_ephem_t* eph, double t0, double t_end, double ckpt_days, int64_t& C) {
     if (!std::isfinite(t0) || !std::isfinite(t_end) || !(t_end > t0))
@@ -1018,7 +1003,7 @@ int kete_propagate_adjoint(const kete_ephem_t* eph, int32_t mode, const double* 
     P.seg_ns = seg_ns;
     P.adj_tab = adj_tab;
     P.dense_coef = dense_coef;
-    P.max_win_segs = segs_or(opts, 3) + 1;      // the adjoint's own windows: 3 segments (auto)
+    P.window_segs = window_segs(opts);
     P.max_iter = opts->max_iter;
     P.max_steps = opts->max_steps;
     P.zero_start = opts->zero_start != 0;
@@ -1296,7 +1281,7 @@ int kete_batch_run(const kete_ephem_t* eph, const kete_batch_t* batch, int64_t p
     B.status = status;
     B.perm = w.perm;
     B.n_buckets = bucket_count(opts);
-    B.max_win_segs = segs_or(opts, 2) + 1;
+    B.window_segs = window_segs(opts);
     B.max_iter = opts->max_iter;
     B.max_steps = opts->max_steps;
     B.zero_start = opts->zero_start != 0;

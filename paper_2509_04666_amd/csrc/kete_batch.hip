@@ -1,10 +1,9 @@
 // Many independent propagation jobs of uneven size in one persistent
 // launch.  A job is a set of bodies with a common start epoch and its own
 // list of output epochs.  Its bodies are sorted by predicted step size
-// (stable, per job) and cut into tiles of 8; a grid sized to the device
+// (stable, per job) and cut into tiles of 9; a grid sized to the device
 // pops tiles from a queue ordered longest-first, one wavefront per tile
-// (8 bodies on 8-lane groups, as in the propagation kernel), each with
-// its own LDS window of Chebyshev segments.
+// (9 bodies on 7-lane groups, as in the propagation kernel).
 #include <math.h>
 
 #include "kete_batch.hpp"
@@ -80,15 +79,13 @@ template <int NB, int NGR, int DEG1>
 __global__ __launch_bounds__(64, 3) void k_batch_g8(const BatchParams p) {
     constexpr int G = KETE_BATCH_LANES;
     static_assert(GroupMap<G>::kBodies == KETE_BATCH_TILE, "tile = bodies per wavefront");
-    extern __shared__ double smem[];
+    extern __shared__ __align__(16) double smem[];
     const int lane = threadIdx.x;
     const GroupMap<G> M(lane);
     const int gl = M.gl;
     const int node = gl < 7 ? gl + 1 : 7;
     const EphemArgs& E = p.eph;
-    const int bstride = p.max_win_segs * 3 * E.deg1;
-    double* coefL = smem;
-    double* e8 = smem + (((size_t)E.n_body * bstride + 1) & ~(size_t)1);
+    double* e8 = smem;
     g8_table_init(E, lane, e8);
     NodeRow R;
     load_node_row(p.rc, node, R);
@@ -97,8 +94,6 @@ __global__ __launch_bounds__(64, 3) void k_batch_g8(const BatchParams p) {
     __shared__ __align__(16) double dwts[kDenseWeights];
     for (int i = lane; i < kDenseCoefDoubles; i += 64) dcoef[i] = p.dense_coef[i];
     __syncthreads();
-    const int W = p.max_win_segs - 1;            // segment lengths per window
-    int lo = 1, hi = 0;                          // nothing staged yet
     for (;;) {
         int tile = 0;
         if (lane == 0) tile = (int)atomicAdd(p.tile_counter, 1u);
@@ -159,10 +154,9 @@ __global__ __launch_bounds__(64, 3) void k_batch_g8(const BatchParams p) {
                              [&](int k, double v) { put(k, v, ok); });
             };
             while (S.t != target) {
-                const Window Wn = next_window(S.t, target, E.t_start, E.seg_days, E.inv_seg, E.n_seg, W);
-                ensure_window(E, Wn.seg_lo, Wn.seg_hi, lo, hi, coefL, bstride);
-                g8_integrate<NB, NGR, DEG1, G, kStartExtrapolate>(p, R, node, gl, M.grp, lane, coefL, bstride, e8, lo,
-                                                                  hi, Wn.t_b, S, C, dense_out);
+                const Window Wn = next_window(S.t, target, E.t_start, E.seg_days, E.inv_seg, E.n_seg, p.window_segs);
+                g8_integrate<NB, NGR, DEG1, G, kStartExtrapolate>(p, R, node, gl, M.grp, lane, e8, Wn.t_b, S, C,
+                                                                  dense_out);
                 S.t = Wn.t_b;
             }
             put(e_end, state_component(S.x0, S.v0, gl < 6 ? gl : 5), S.active && S.status == 0);
@@ -175,8 +169,7 @@ __global__ __launch_bounds__(64, 3) void k_batch_g8(const BatchParams p) {
 }  // namespace
 
 size_t batch_lds_bytes(const BatchParams& p) {
-    return ((((size_t)p.eph.n_body * p.max_win_segs * 3 * p.eph.deg1 + 1) & ~(size_t)1) +
-            (size_t)g8_wave_doubles(p.eph.n_body)) * sizeof(double);
+    return (size_t)g8_wave_doubles(p.eph.n_body) * sizeof(double);
 }
 
 // The dense-output rows of the constants into device memory (a tiny kernel,

@@ -26,7 +26,7 @@ struct BatchParams {
     int32_t* status;            // [bodies]
     int32_t* perm;              // [bodies] job-local order of each job's bodies
     int32_t n_buckets;
-    int32_t max_win_segs;
+    int32_t window_segs;        // segments between forced step ends (0: none)
     int32_t max_iter;
     int32_t max_steps;
     int32_t zero_start;         // corrector starts from zero increments (no extrapolation)

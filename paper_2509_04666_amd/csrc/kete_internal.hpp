@@ -51,8 +51,9 @@ __host__ __device__ inline int seg_clamped(double t, double t_start, double inv_
 
 // The next integration window from t toward target: it ends at target or
 // at the segment joint w segment lengths past the start of t's segment,
-// whichever comes first, and reads at most w + 1 consecutive segments
-// (seg_lo..seg_hi), the capacity of the staging buffers.  Every path
+// whichever comes first (w <= 0: at target), and reads at most w + 1
+// consecutive segments (seg_lo..seg_hi), the capacity of the staging buffers
+// of the one-lane-per-body kernel.  Every path
 // (host plans and the persistent kernel) uses this rule, so they window
 // identically.  If t sits on a joint that rounding placed in the earlier
 // segment, the limit moves one segment on so the window never has zero
@@ -61,7 +62,9 @@ __host__ __device__ inline Window next_window(double t, double target, double t_
                                               double inv_seg, int n_seg, int w) {
     const bool fwd = target > t;
     double tb;
-    if (fwd) {
+    if (w <= 0) {
+        tb = target;
+    } else if (fwd) {
         const double kk = floor((t - t_start) * inv_seg);
         double limit = t_start + (kk + w) * seg_days;
         if (!(limit > t)) limit = t_start + (kk + w + 1) * seg_days;
@@ -77,7 +80,7 @@ __host__ __device__ inline Window next_window(double t, double target, double t_
     W.t_b = tb;
     int lo = seg_clamped(fwd ? t : tb, t_start, inv_seg, n_seg);
     int hi = seg_clamped(fwd ? tb : t, t_start, inv_seg, n_seg);
-    if (hi - lo > w) {
+    if (w > 0 && hi - lo > w) {
         if (fwd) hi = lo + w; else lo = hi - w;
     }
     W.seg_lo = lo;
@@ -87,26 +90,18 @@ __host__ __device__ inline Window next_window(double t, double target, double t_
     return W;
 }
 
-// The same, forward in time only, with the window ends on a fixed grid:
-// multiples of w segments from t_start (or the target).  A run that resumes
-// inside a window (from a checkpoint) then ends its windows where the first
-// run did, so both cut their steps at the same times.
-__host__ __device__ inline Window aligned_window(double t, double target, double t_start, double seg_days,
-                                                 double inv_seg, int n_seg, int w) {
+// The end of the window from t, forward in time only, with the window ends on
+// a fixed grid: multiples of w segments from t_start (or the target; w <= 0:
+// the target alone).  A run that resumes inside a window (from a checkpoint)
+// then ends its windows where the first run did, so both cut their steps at
+// the same times.
+__host__ __device__ inline double aligned_end(double t, double target, double t_start, double seg_days,
+                                              double inv_seg, int w) {
+    if (w <= 0) return target;
     const double kk = floor((t - t_start) * inv_seg);
     double limit = t_start + (floor(kk / w) + 1.0) * w * seg_days;
     if (!(limit > t)) limit += w * seg_days;
-    Window W;
-    W.t_a = t;
-    W.t_b = limit < target ? limit : target;
-    const int lo = seg_clamped(t, t_start, inv_seg, n_seg);
-    int hi = seg_clamped(W.t_b, t_start, inv_seg, n_seg);
-    if (hi - lo > w) hi = lo + w;
-    W.seg_lo = lo;
-    W.seg_hi = hi;
-    W.out = -1;
-    W.pad = 0;
-    return W;
+    return limit < target ? limit : target;
 }
 
 struct NbodyParams {
@@ -127,7 +122,7 @@ struct NbodyParams {
     int32_t n_obj;
     int32_t max_iter;
     int32_t max_steps;
-    int32_t max_win_segs;   // LDS capacity in segments
+    int32_t max_win_segs;   // LDS capacity in segments (one lane per object)
     int32_t first_launch;
     int32_t zero_start;     // corrector starts from zero increments (no extrapolation)
     int32_t pad_;
@@ -138,8 +133,6 @@ const RadauConst& radau_const();
 
 // lanes_per_body: 1 (one lane per object) or 8 (an 8-lane group per object).
 hipError_t launch_nbody(const NbodyParams& p, int block, int lanes_per_body, hipStream_t s);
-// LDS of one block of the grouped integrator (dynamic and static).
-size_t nbody_g8_lds_bytes(int n_body, int deg1, int max_win_segs, int block);
 
 // Stable counting sort of objects into step-size buckets.
 // Buckets per octave of the predicted step (the batched jobs' sort), and

@@ -8,8 +8,9 @@
 // objects of a wavefront share the time grid: the step size is the
 // smallest one any of them asks for, so the perturber states at the node
 // times of a step are evaluated once per wavefront and read from LDS.
-// The Chebyshev coefficients of the segments a window needs are staged in
-// LDS once per workgroup.  Objects are sorted by predicted step size
+// k_nbody stages the Chebyshev coefficients of the segments a window needs
+// in LDS once per workgroup; k_nbody_g8 reads them from L2 (see
+// node_ephemeris8).  Objects are sorted by predicted step size
 // before a launch so that the objects of one wavefront want similar steps.
 #include <math.h>
 
@@ -162,21 +163,19 @@ __global__ __launch_bounds__(BLOCK) void k_nbody(const NbodyParams p) {
 // perturber table as above; each sweep evaluates the force at all 7 nodes
 // of an object at once.  Output and counters are per object, as in
 // k_nbody.
-template <int BLOCK, int G, int NB, int NGR, int DEG1>
-__global__ __launch_bounds__(BLOCK, 3) void k_nbody_g8(const NbodyParams p) {
-    extern __shared__ double smem[];
+template <int G, int NB, int NGR, int DEG1>
+__global__ __launch_bounds__(256, 3) void k_nbody_g8(const NbodyParams p) {
+    extern __shared__ __align__(16) double smem[];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
+    const int n_waves = blockDim.x / kWave;
     const GroupMap<G> M(lane);
     const int gl = M.gl;                              // lane within the object's group
     const int node = gl < 7 ? gl + 1 : 7;
     const EphemArgs& E = p.eph;
     const RadauConst& rc = p.rc;
-    const int nb = E.n_body, deg1 = E.deg1;
-    const int cps = 3 * deg1;
-    const int bstride = p.max_win_segs * cps;
-    double* coefL = smem;
-    // the table is read with 16-byte loads: start it on a 16-byte boundary
-    double* e8 = smem + (((size_t)nb * bstride + 1) & ~(size_t)1) + (size_t)wid * g8_wave_doubles(nb);
+    const int nb = E.n_body;
+    double* e8 = smem + (size_t)wid * g8_wave_doubles(nb);
+    double* wt = smem + (size_t)n_waves * g8_wave_doubles(nb) + wid * kDenseWeights;
     g8_table_init(E, lane, e8);
     // per-node constants of the 8 lanes of a group, read from LDS in the
     // sweeps to keep registers for more wavefronts per SIMD
@@ -188,13 +187,12 @@ __global__ __launch_bounds__(BLOCK, 3) void k_nbody_g8(const NbodyParams p) {
     }
     // dense-output rows, read from LDS at the epochs inside a step
     __shared__ double dcoef[kDenseCoefDoubles];
-    __shared__ __align__(16) double dwts[BLOCK / kWave][kDenseWeights];
     if (p.e_first < p.e_land)
-        for (int i = tid; i < kDenseCoefDoubles; i += BLOCK) dcoef[i] = p.dense_coef[i];
+        for (int i = tid; i < kDenseCoefDoubles; i += (int)blockDim.x) dcoef[i] = p.dense_coef[i];
     __syncthreads();
     const NodeRow& R = rows[gl];
 
-    const long gi = ((long)blockIdx.x * (BLOCK / kWave) + wid) * GroupMap<G>::kBodies + M.grp;
+    const long gi = ((long)blockIdx.x * n_waves + wid) * GroupMap<G>::kBodies + M.grp;
     const bool valid = gi < p.n_obj;
     const int j = valid ? (p.perm ? p.perm[gi] : (int)gi) : 0;
     G8State S;
@@ -230,17 +228,13 @@ __global__ __launch_bounds__(BLOCK, 3) void k_nbody_g8(const NbodyParams p) {
     }
     auto dense_out = [&](double ts, double h, const double dn[3], const G8State& St) {
         const bool ok = St.active && St.status == 0;
-        dense_epochs(dcoef, dwts[wid], xg, gl, lane, ts, h, dn, St.x0, St.v0, St.F0, p.t_out, e_next, p.e_land,
+        dense_epochs(dcoef, wt, xg, gl, lane, ts, h, dn, St.x0, St.v0, St.F0, p.t_out, e_next, p.e_land,
                      [&](int e, double v) { put(e, v, ok); });
     };
 
     for (int w = 0; w < p.n_win; ++w) {
         const Window W = p.win[w];
-        __syncthreads();
-        stage_window(E, W.seg_lo, W.seg_hi, bstride, tid, BLOCK, coefL);
-        __syncthreads();
-        g8_integrate<NB, NGR, DEG1, G, kStartExtrapolate>(p, R, node, gl, M.grp, lane, coefL, bstride, e8, W.seg_lo,
-                                                          W.seg_hi, W.t_b, S, C, dense_out);
+        g8_integrate<NB, NGR, DEG1, G, kStartExtrapolate>(p, R, node, gl, M.grp, lane, e8, W.t_b, S, C, dense_out);
         if (W.out >= 0 && valid && gl < 6) {
             // lane gl of the group writes component gl of the state
             double* dst = p.x_out + ((size_t)W.out * p.n_obj + j) * 6;
@@ -343,18 +337,11 @@ __global__ void k_hpref_init(const double* __restrict__ x0, double* __restrict__
 
 }  // namespace
 
-size_t nbody_g8_lds_bytes(int n_body, int deg1, int max_win_segs, int block) {
-    return ((((size_t)n_body * max_win_segs * 3 * deg1 + 1) & ~(size_t)1) +
-            (size_t)(block / kWave) * g8_wave_doubles(n_body)) * sizeof(double) +
-           sizeof(NodeRow) * kGroup + (kDenseCoefDoubles + block / kWave * kDenseWeights) * sizeof(double);
-}
-
 hipError_t launch_nbody(const NbodyParams& p, int block, int lanes_per_body, hipStream_t s) {
     const size_t lds = ((size_t)p.eph.n_body * p.max_win_segs * 3 * p.eph.deg1 +
                         (size_t)(block / kWave) * kNodes * p.eph.n_body * 6) * sizeof(double);
     if (lanes_per_body == 7 || lanes_per_body == 8) {
-        const size_t lds8 = ((((size_t)p.eph.n_body * p.max_win_segs * 3 * p.eph.deg1 + 1) & ~(size_t)1) +
-                             (size_t)(block / kWave) * g8_wave_doubles(p.eph.n_body)) * sizeof(double);
+        const size_t lds8 = (size_t)(block / kWave) * (g8_wave_doubles(p.eph.n_body) + kDenseWeights) * sizeof(double);
         const long per_wave = lanes_per_body == 7 ? GroupMap<7>::kBodies : GroupMap<8>::kBodies;
         const long waves = ((long)p.n_obj + per_wave - 1) / per_wave;
         const int wpb = block / kWave;
@@ -362,29 +349,19 @@ hipError_t launch_nbody(const NbodyParams& p, int block, int lanes_per_body, hip
         if (grid == 0) return hipSuccess;
         // perturber tables of the common shapes get an unrolled force loop
         const int nb = p.eph.n_body, ngr = p.eph.n_gr, d1 = p.eph.deg1;
-#define KETE_G8(B, G)                                                                                           \
+#define KETE_G8(G)                                                                                              \
     do {                                                                                                        \
         if (nb == 10 && ngr == 3 && d1 == 13)                                                                   \
-            hipLaunchKernelGGL((k_nbody_g8<B, G, 10, 3, 13>), dim3(grid), dim3(B), lds8, s, p);                 \
+            hipLaunchKernelGGL((k_nbody_g8<G, 10, 3, 13>), dim3(grid), dim3(block), lds8, s, p);                \
         else if (nb == 3 && ngr == 2 && d1 == 13)                                                               \
-            hipLaunchKernelGGL((k_nbody_g8<B, G, 3, 2, 13>), dim3(grid), dim3(B), lds8, s, p);                  \
-        else hipLaunchKernelGGL((k_nbody_g8<B, G, 0, 0, 0>), dim3(grid), dim3(B), lds8, s, p);                  \
+            hipLaunchKernelGGL((k_nbody_g8<G, 3, 2, 13>), dim3(grid), dim3(block), lds8, s, p);                 \
+        else if (d1 == 13)                                                                                      \
+            hipLaunchKernelGGL((k_nbody_g8<G, 0, 0, 13>), dim3(grid), dim3(block), lds8, s, p);                 \
+        else hipLaunchKernelGGL((k_nbody_g8<G, 0, 0, 0>), dim3(grid), dim3(block), lds8, s, p);                 \
     } while (0)
-        if (lanes_per_body == 7) {
-            switch (block) {
-                case 64: KETE_G8(64, 7); break;
-                case 128: KETE_G8(128, 7); break;
-                case 256: KETE_G8(256, 7); break;
-                default: return hipErrorInvalidValue;
-            }
-        } else {
-            switch (block) {
-                case 64: KETE_G8(64, 8); break;
-                case 128: KETE_G8(128, 8); break;
-                case 256: KETE_G8(256, 8); break;
-                default: return hipErrorInvalidValue;
-            }
-        }
+        if (block != 64 && block != 128 && block != 256) return hipErrorInvalidValue;
+        if (lanes_per_body == 7) KETE_G8(7);
+        else KETE_G8(8);
 #undef KETE_G8
         return hipGetLastError();
     }

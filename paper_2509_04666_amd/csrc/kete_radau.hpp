@@ -118,17 +118,6 @@ __device__ __forceinline__ void stage_window(const EphemArgs& E, int seg_lo, int
     }
 }
 
-// Stage segments a..b into LDS unless they are already there (one
-// wavefront per block: lanes 0..63 copy).
-__device__ __forceinline__ void ensure_window(const EphemArgs& E, int a, int b, int& lo, int& hi, double* coefL,
-                                              int bstride) {
-    if (a >= lo && b <= hi) return;
-    __syncthreads();
-    stage_window(E, a, b, bstride, threadIdx.x, 64, coefL);
-    __syncthreads();
-    lo = a; hi = b;
-}
-
 // The collocation corrector: fixed-point sweeps over the 7 nodes
 // (Gauss-Seidel: each node sees the increments already updated) until the
 // change of b6 relative to |a| is below 1e-16, stops decreasing after the
@@ -316,6 +305,7 @@ constexpr int kSlot = 8;
 // Doubles per node row: 4 (4 n_body + 1) dwords, so the 8 rows read
 // together by an 8-lane group fall in distinct LDS banks.
 __host__ __device__ inline int g8_row(int n_body) { return n_body * kSlot + 2; }
+__device__ __forceinline__ int g8_row(const EphemArgs& E) { return g8_row(E.n_body); }
 
 // Exchange rows of the grouped corrector, after the wave's node table:
 // per group three rows (x, y, z) of 8 doubles, lane gl writing column gl,
@@ -360,45 +350,92 @@ __device__ __forceinline__ void g8_table_init(const EphemArgs& E, int lane, doub
     }
 }
 
+// Coefficients of one coordinate's segment, read together.  DEG1 = 0 takes
+// the count at run time and pads with zeros to the largest, which leaves the
+// Clenshaw recurrences' values as they are.
+template <int DEG1>
+struct ChainCoef {
+    static constexpr int kN = DEG1 > 0 ? DEG1 : KETE_MAX_DEGREE + 1;
+    double c[kN];
+    __device__ __forceinline__ void load(const double* __restrict__ p, int deg1) {
+#pragma unroll
+        for (int k = 0; k < kN; ++k) c[k] = (DEG1 > 0 || k < deg1) ? p[k] : 0.0;
+    }
+    __device__ __forceinline__ double value(double tau) const {
+        const double t2 = tau + tau;
+        double b2 = c[kN - 1], b1 = fma(t2, b2, c[kN - 2]);
+#pragma unroll
+        for (int k = kN - 3; k >= 1; --k) {
+            const double b0 = fma(t2, b1, c[k] - b2);
+            b2 = b1; b1 = b0;
+        }
+        return fma(tau, b1, c[0] - b2);
+    }
+    __device__ __forceinline__ void value_slope(double tau, double& p, double& dp) const {
+        const double t2 = tau + tau;
+        double b2 = c[kN - 1], b1 = fma(t2, b2, c[kN - 2]);
+        double d2 = 0.0, d1 = 2.0 * b2;
+#pragma unroll
+        for (int k = kN - 3; k >= 1; --k) {
+            const double b0 = fma(t2, b1, c[k] - b2);
+            const double d0 = fma(t2, d1, 2.0 * b1 - d2);
+            b2 = b1; b1 = b0; d2 = d1; d1 = d0;
+        }
+        p = fma(tau, b1, c[0] - b2);
+        dp = fma(tau, d1, b1 - d2);
+    }
+};
+
 // Perturber states at the node times of a step.  Lane k of each 8-lane
 // group takes node (k & 7) + 1 (node 8 is the step end) and finds that
 // node's segment and tau once; the 3 n_body coordinates are spread over
-// the 8 groups (group g takes coordinates g, g + 8, ...).  Coordinates of
-// the slots with the Eq. A.3 term come first and also get the velocity
-// (derivative chain); a pass holding any of them evaluates derivatives in
-// every lane so the wavefront does not diverge.  Node 0 (the step start,
-// needed before the first step or when the caller asks) takes one more
-// pass with coordinate = lane.  The node of a lane here follows lane & 7
-// whatever the lane's body group.
+// the 8 groups (group g takes coordinates g, g + 8, ...), two of a lane's
+// chains in flight.  Coordinates of the slots with the Eq. A.3 term come
+// first and also get the velocity (derivative chain); a pair of passes
+// holding any of them evaluates derivatives in every lane so the wavefront
+// does not diverge.  Node 0 (the step start, needed before the first step or
+// when the caller asks) takes one more pass with coordinate = lane.  The
+// node of a lane here follows lane & 7 whatever the lane's body group.
+//
+// The coefficients come straight from the table (156 KB for ten bodies and a
+// year: it stays in each XCD's L2), a step's chains reading two or three
+// segments of it.  Staged in LDS instead they tied the wavefronts of a block
+// to one window of a few segments: barriers at its ends, where every step
+// also had to land.
 template <int NB, int NGR, int DEG1>
-__device__ __forceinline__ void node_ephemeris8(const double* __restrict__ coefL, int bstride, const EphemArgs& E,
-                                                const RadauConst& rc, int seg_lo, int seg_hi, double t, double h,
+__device__ __forceinline__ void node_ephemeris8(const EphemArgs& E, const RadauConst& rc, double t, double h,
                                                 double t_end, bool node0, int lane, double* __restrict__ e8) {
     const int nb = NB > 0 ? NB : E.n_body;
     const int ngr = NB > 0 ? NGR : E.n_gr;
     const int deg1 = DEG1 > 0 ? DEG1 : E.deg1;
     const int cps = 3 * deg1, nc = 3 * nb, ngc = 3 * ngr;
+    const int bstride = E.n_seg * cps;
     const double sc = 2.0 * E.inv_seg;
     auto chains = [&](int n, double tt, int c0, int cstep, int npass) {
-        const int k = seg_index(tt, E.t_start, E.inv_seg, seg_lo, seg_hi);
+        const int k = seg_index(tt, E.t_start, E.inv_seg, 0, E.n_seg - 1);
         const double tau = 2.0 * (tt - (E.t_start + (double)k * E.seg_days)) * E.inv_seg - 1.0;
-        const double* cb = coefL + (k - seg_lo) * cps;
-        double* row = e8 + n * g8_row(nb);
-        // one chain in flight per lane: the coefficient loads of several
-        // unrolled passes would crowd out the integrator state
+        const double* cb = E.coef + (size_t)k * cps;
+        double* row = e8 + n * g8_row(E);
 #pragma unroll 1
-        for (int j = 0; j < npass; ++j) {
-            const int c = c0 + cstep * j;
-            if (c >= nc) continue;
-            const int sl = c / 3, i = c - 3 * sl;
-            const double* cp = cb + slot_body(E, sl) * bstride + i * deg1;
-            if (cstep * j < ngc) {                 // wave-uniform: the pass holds derivative chains
-                double pv, dv;
-                clenshaw_n<DEG1>(cp, deg1, tau, pv, dv);
-                row[sl * kSlot + i] = pv;
-                if (c < ngc) row[sl * kSlot + 4 + i] = dv * sc;
+        for (int j = 0; j < npass; j += 2) {
+            const int ca = c0 + cstep * j, cc = ca + cstep;
+            const int qa = ca < nc ? ca : nc - 1, qc = cc < nc ? cc : nc - 1;
+            const int sa = qa / 3, ia = qa - 3 * sa, sb = qc / 3, ib = qc - 3 * sb;
+            ChainCoef<DEG1> A, B;
+            A.load(cb + slot_body(E, sa) * bstride + ia * deg1, deg1);
+            B.load(cb + slot_body(E, sb) * bstride + ib * deg1, deg1);
+            if (cstep * j < ngc) {                 // wave-uniform: the pair holds derivative chains
+                double pa, da, pb, db;
+                A.value_slope(tau, pa, da);
+                B.value_slope(tau, pb, db);
+                if (ca < nc) row[sa * kSlot + ia] = pa;
+                if (ca < ngc) row[sa * kSlot + 4 + ia] = da * sc;
+                if (cc < nc) row[sb * kSlot + ib] = pb;
+                if (cc < ngc) row[sb * kSlot + 4 + ib] = db * sc;
             } else {
-                row[sl * kSlot + i] = clenshaw_value_n<DEG1>(cp, deg1, tau);
+                const double pa = A.value(tau), pb = B.value(tau);
+                if (ca < nc) row[sa * kSlot + ia] = pa;
+                if (cc < nc) row[sb * kSlot + ib] = pb;
             }
         }
     };
@@ -756,9 +793,8 @@ constexpr double kPredMaxRatio = 3.0;
 // where the kernel has room).
 enum G8Start { kStartZero = 0, kStartExtrapolate = 1, kStartExtrapolateHeld = 2 };
 
-// Integrate one window [S.t, tb] whose Chebyshev segments seg_lo..seg_hi
-// are staged at coefL, with wave-shared adaptive steps (the 8 bodies of
-// the wavefront take the smallest step any of them asks for).
+// Integrate [S.t, tb] with wave-shared adaptive steps (the bodies of the
+// wavefront take the smallest step any of them asks for).
 struct G8NoVisit {
     template <class... A>
     __device__ __forceinline__ void operator()(A&&...) const {}
@@ -770,8 +806,7 @@ struct G8NoVisit {
 // node 0 (the step start) on every step.
 template <int NB, int NGR, int DEG1, int G, int START = kStartZero, class Params, class Visit = G8NoVisit>
 __device__ __forceinline__ void g8_integrate(const Params& p, const NodeRow& R, int node, int gl, int grp, int lane,
-                                             const double* __restrict__ coefL, int bstride, double* __restrict__ e8,
-                                             int seg_lo, int seg_hi, double tb, G8State& S, G8Count& C,
+                                             double* __restrict__ e8, double tb, G8State& S, G8Count& C,
                                              Visit&& visit = Visit(), bool need_node0 = false,
                                              double t_stop = kInf) {
     const EphemArgs& E = p.eph;
@@ -796,7 +831,7 @@ __device__ __forceinline__ void g8_integrate(const Params& p, const NodeRow& R, 
         // node 0 is evaluated before the first step; with need_node0 it is
         // afterwards the previous step's end row, copied when that step is accepted
         const int n0 = (S.haveF0 && (!need_node0 || S.row0)) ? 1 : 0;
-        node_ephemeris8<NB, NGR, DEG1>(coefL, bstride, E, rc, seg_lo, seg_hi, S.t, h, t_end, n0 == 0, lane, e8);
+        node_ephemeris8<NB, NGR, DEG1>(E, rc, S.t, h, t_end, n0 == 0, lane, e8);
         S.row0 = true;
         C.chain += (kNodes - n0) * E.n_gr * 3;
         C.vchain += (kNodes - n0) * (nb - E.n_gr) * 3;
