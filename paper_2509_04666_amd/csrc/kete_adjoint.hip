@@ -222,20 +222,17 @@ __device__ __forceinline__ void init_lane_state(const AdjParams& p, bool valid, 
     S.haveF0 = false;
 }
 
-template <int NB, int NGR, int DEG1>
+template <int NB, int NGR, int NJ2, int DEG1>
 __global__ __launch_bounds__(64, 3) void k_adjoint_fwd(const AdjParams p) {
     extern __shared__ __align__(16) double smem[];
     const int lane = threadIdx.x;
-    const int gl = lane & (kGroup - 1);
-    const int node = gl < 7 ? gl + 1 : 7;
+    const GroupMap<kGroup> M(lane);
+    const int gl = M.gl;
     const EphemArgs& E = p.eph;
-    double* e8 = smem;
-    g8_table_init(E, lane, e8);
-    NodeRow R;
-    load_node_row(p.rc, node, R);
-    // dense-output rows, read from LDS at the observations inside a step
-    __shared__ double dcoef[kDenseCoefDoubles];
-    for (int i = lane; i < kDenseCoefDoubles; i += 64) dcoef[i] = p.dense_coef[i];
+    __shared__ __align__(16) GroupConst gc;
+    load_group_const(p.group_const, &gc, lane, kWave);
+    const G8Lds T = g8_lds<1>(E, smem, M.grp);
+    g8_table_init<1>(E, lane, smem);
     __syncthreads();
     const long gi = ((long)blockIdx.x * 64 + lane) / kGroup;
     const bool valid = gi < p.n_obj;
@@ -270,7 +267,7 @@ __global__ __launch_bounds__(64, 3) void k_adjoint_fwd(const AdjParams p) {
         bool pend = pending();
         if (__ballot(pend) == 0ull) return;
         // the step's node increments into the group's exchange rows
-        double* xg = g8_xch(e8, E.n_body, lane / kGroup);
+        double* xg = T.xg;
         wave_lds_sync();
         xg[gl] = dn[0];
         xg[8 + gl] = dn[1];
@@ -279,7 +276,7 @@ __global__ __launch_bounds__(64, 3) void k_adjoint_fwd(const AdjParams p) {
         while (__ballot(pend) != 0ull) {
             if (pend) {
                 double X[3], V[3];
-                dense_state_rows(dcoef, xg, St.x0, St.v0, St.F0, h, (tob[kobs] - ts) / h, X, V);
+                dense_state_rows(gc, xg, St.x0, St.v0, St.F0, h, (tob[kobs] - ts) / h, X, V);
                 store_obs(kobs, X, V);
                 ++kobs;
             }
@@ -290,9 +287,8 @@ __global__ __launch_bounds__(64, 3) void k_adjoint_fwd(const AdjParams p) {
     // (windows, if asked for, end on the fixed grid of aligned_end, so a
     // recompute that starts at a checkpoint cuts its steps where this run did)
     while (S.t < p.t_end)
-        g8_integrate<NB, NGR, DEG1, kGroup, kStartExtrapolateHeld>(
-            p, R, node, gl, lane / kGroup, lane, e8,
-            aligned_end(S.t, p.t_end, E.t_start, E.seg_days, E.inv_seg, p.window_segs), S, C, visit);
+        g8_integrate<NB, NGR, NJ2, DEG1, kGroup>(
+            p, gc, T, M, lane, aligned_end(S.t, p.t_end, E.t_start, E.seg_days, E.inv_seg, p.window_segs), S, C, visit);
     // checkpoints no step start reached: the end state
     for (; c_next <= p.n_ckpt; ++c_next)
         if (valid) save_ckpt_g8(p, c_next, j, gl, S, p.t_end);
@@ -382,15 +378,6 @@ __device__ __forceinline__ void load_adj_cols(const RadauConst& rc, int gl, AdjC
     }
 }
 
-// Per-node constants of the 8 lanes of a group (LDS rows, indexed by gl).
-__device__ __forceinline__ void fill_node_rows(const RadauConst& rc, int tid, NodeRow* rows) {
-    if (tid < kGroup) {
-        NodeRow r;
-        load_node_row(rc, tid < 7 ? tid + 1 : 7, r);
-        rows[tid] = r;
-    }
-}
-
 // Backward, first half for checkpoint segment c: recompute the segment from
 // its checkpoint with the forward's grouping and step sequence
 // (one wavefront per block: the checkpoints' times differ between
@@ -400,12 +387,12 @@ __device__ __forceinline__ void fill_node_rows(const RadauConst& rc, int tid, No
 constexpr int kSegOverflow = 1 << 30;
 static_assert(kAdjLanes == kGroup, "adjoint wavefronts hold 8 objects");
 
-template <int NB, int NGR, int DEG1>
+template <int NB, int NGR, int NJ2, int DEG1>
 __global__ __launch_bounds__(64, 2) void k_adj_recompute(const AdjParams p, const int c) {
     extern __shared__ __align__(16) double smem[];
     const int lane = threadIdx.x;
-    const int gl = lane & (kGroup - 1);
-    const int node = gl < 7 ? gl + 1 : 7;
+    const GroupMap<kGroup> M(lane);
+    const int gl = M.gl;
     const int jnode = gl < 7 ? gl + 1 : 0;          // node whose Jacobians this lane keeps
     const EphemArgs& E = p.eph;
     const long wave = blockIdx.x;
@@ -422,12 +409,12 @@ __global__ __launch_bounds__(64, 2) void k_adj_recompute(const AdjParams p, cons
         if (lane == 0) p.seg_ns[wave] = 0;
         return;                                     // the whole block: one wavefront
     }
-    double* e8 = smem;
-    g8_table_init(E, lane, e8);
-    __shared__ NodeRow rows[kGroup];
-    fill_node_rows(p.rc, lane, rows);
+    __shared__ __align__(16) GroupConst gc;
+    load_group_const(p.group_const, &gc, lane, kWave);
+    const G8Lds T = g8_lds<1>(E, smem, M.grp);
+    g8_table_init<1>(E, lane, smem);
     __syncthreads();
-    const NodeRow& R = rows[gl];
+    const NodeRow& R = gc.row[gl];
     bool overflow_steps = false;
     G8State S;
     init_lane_state(p, false, j, S);
@@ -454,7 +441,7 @@ __global__ __launch_bounds__(64, 2) void k_adj_recompute(const AdjParams p, cons
         auto store = [&](double ts, double h, const double dn[3], const G8State& St) {
             if (ns >= p.s_max) { overflow_steps = true; return; }
             double D[7][3];
-            g8_exchange(g8_xch(e8, E.n_body, lane / kGroup), gl, dn, D);
+            g8_exchange(T.xg, gl, dn, D);
             if (valid) {
                 double* sp = p.steps + (size_t)ns * kStepDoubles * N;
                 if (gl == 6) sp[gi] = ts;
@@ -472,7 +459,7 @@ __global__ __launch_bounds__(64, 2) void k_adj_recompute(const AdjParams p, cons
                     V[i] = fma(h, av, St.v0[i]);
                 }
                 double Jx[9], Jv[9];
-                accel_jac8<NB, NGR>(e8 + jnode * g8_row(E.n_body), E, X, V, Jx, Jv);
+                accel_jac8<NB, NGR>(T.e8 + jnode * T.row, E, X, V, Jx, Jv);
                 double* jp = p.jac + (size_t)ns * 8 * kJacDoubles * N;
                 #pragma unroll
                 for (int q = 0; q < 9; ++q) {
@@ -485,9 +472,9 @@ __global__ __launch_bounds__(64, 2) void k_adj_recompute(const AdjParams p, cons
     // the forward's steps (and windows) from the checkpoint on, until the
     // step start where the forward took the next checkpoint
     while (S.t < t_stop)
-        g8_integrate<NB, NGR, DEG1, kGroup, kStartExtrapolateHeld>(
-            p, R, node, gl, lane / kGroup, lane, e8,
-            aligned_end(S.t, p.t_end, E.t_start, E.seg_days, E.inv_seg, p.window_segs), S, Cn, store, true, t_stop);
+        g8_integrate<NB, NGR, NJ2, DEG1, kGroup>(
+            p, gc, T, M, lane, aligned_end(S.t, p.t_end, E.t_start, E.seg_days, E.inv_seg, p.window_segs), S, Cn, store,
+            true, t_stop);
     if (lane == 0 && wave * kGroup < p.n_obj) p.seg_ns[wave] = min(ns, p.s_max) | (overflow_steps ? kSegOverflow : 0);
 }
 
@@ -715,7 +702,7 @@ __global__ __launch_bounds__(64) void k_adj_sweep(const AdjParams p, const int c
 }  // namespace
 
 size_t adjoint_lds_bytes(const AdjParams& p) {
-    return (size_t)g8_wave_doubles(p.eph.n_body) * sizeof(double);
+    return (size_t)g8_wave_doubles(g8_slots(p.eph.n_body, p.eph.n_gr, 1)) * sizeof(double);
 }
 
 
@@ -752,13 +739,6 @@ static hipError_t pooled_event(hipEvent_t* out) {
     return hipSuccess;
 }
 
-// The dense-output rows of the constants into device memory for the forward.
-__global__ void k_adj_dense_coef(const AdjParams p) {
-    const int i = threadIdx.x;
-    if (i < 56) p.dense_coef[i] = p.rc.Ap[i / 8][i % 8];
-    else if (i < kDenseCoefDoubles) p.dense_coef[i] = p.rc.Bp[(i - 56) / 8][(i - 56) % 8];
-}
-
 hipError_t launch_adjoint(const AdjParams& p, int mode, hipStream_t s) {
     const int64_t waves = ((int64_t)p.n_obj + kGroup - 1) / kGroup;
     const int grid = (int)waves;
@@ -766,13 +746,16 @@ hipError_t launch_adjoint(const AdjParams& p, int mode, hipStream_t s) {
     const int64_t n_o = (int64_t)p.n_obj * p.k_obs;
     const unsigned go = (unsigned)((n_o + 255) / 256);
     const size_t lds = adjoint_lds_bytes(p);
-    const int nb = p.eph.n_body, ngr = p.eph.n_gr, d1 = p.eph.deg1;
+    const int shape = group_shape(p.eph);
+    hipError_t e;
     if (mode == KETE_ADJ_FWD) {
-        hipLaunchKernelGGL(k_adj_dense_coef, dim3(1), dim3(128), 0, s, p);
-        if (nb == 10 && ngr == 3 && d1 == 13) hipLaunchKernelGGL((k_adjoint_fwd<10, 3, 13>), dim3(grid), dim3(64), lds, s, p);
-        else if (nb == 3 && ngr == 2 && d1 == 13)
-            hipLaunchKernelGGL((k_adjoint_fwd<3, 2, 13>), dim3(grid), dim3(64), lds, s, p);
-        else hipLaunchKernelGGL((k_adjoint_fwd<0, 0, 0>), dim3(grid), dim3(64), lds, s, p);
+        if ((e = launch_group_const(p.rc, p.group_const, s)) != hipSuccess) return e;
+        switch (shape) {
+            case 2: hipLaunchKernelGGL((k_adjoint_fwd<10, 3, 2, 13>), dim3(grid), dim3(64), lds, s, p); break;
+            case 3: hipLaunchKernelGGL((k_adjoint_fwd<3, 2, 2, 13>), dim3(grid), dim3(64), lds, s, p); break;
+            case 1: hipLaunchKernelGGL((k_adjoint_fwd<0, 0, 0, 13>), dim3(grid), dim3(64), lds, s, p); break;
+            default: hipLaunchKernelGGL((k_adjoint_fwd<0, 0, 0, 0>), dim3(grid), dim3(64), lds, s, p); break;
+        }
         if (n_o > 0) {
             hipLaunchKernelGGL(k_obs_sky, dim3(go), dim3(256), 0, s, p);
             hipLaunchKernelGGL(k_obs_status, dim3((unsigned)((p.n_obj + 255) / 256)), dim3(256), 0, s, p);
@@ -786,7 +769,6 @@ hipError_t launch_adjoint(const AdjParams& p, int mode, hipStream_t s) {
     // sweeps, into one of two step stores: the store of segment c is free
     // once the sweep of segment c + 2 has read it.
     hipStream_t r = nullptr;
-    hipError_t e;
     if ((e = aux_stream(&r)) != hipSuccess) return e;
     const int C = p.n_ckpt;
     hipEvent_t ready[2] = {nullptr, nullptr}, freed[2] = {nullptr, nullptr}, start = nullptr;
@@ -810,11 +792,12 @@ hipError_t launch_adjoint(const AdjParams& p, int mode, hipStream_t s) {
         const int b = c & 1;
         if (c + 2 < C && (e = hipStreamWaitEvent(r, freed[b], 0)) != hipSuccess) return e;
         const AdjParams q = in_store(b);
-        if (nb == 10 && ngr == 3 && d1 == 13)
-            hipLaunchKernelGGL((k_adj_recompute<10, 3, 13>), dim3(grid), dim3(64), lds, r, q, c);
-        else if (nb == 3 && ngr == 2 && d1 == 13)
-            hipLaunchKernelGGL((k_adj_recompute<3, 2, 13>), dim3(grid), dim3(64), lds, r, q, c);
-        else hipLaunchKernelGGL((k_adj_recompute<0, 0, 0>), dim3(grid), dim3(64), lds, r, q, c);
+        switch (shape) {
+            case 2: hipLaunchKernelGGL((k_adj_recompute<10, 3, 2, 13>), dim3(grid), dim3(64), lds, r, q, c); break;
+            case 3: hipLaunchKernelGGL((k_adj_recompute<3, 2, 2, 13>), dim3(grid), dim3(64), lds, r, q, c); break;
+            case 1: hipLaunchKernelGGL((k_adj_recompute<0, 0, 0, 13>), dim3(grid), dim3(64), lds, r, q, c); break;
+            default: hipLaunchKernelGGL((k_adj_recompute<0, 0, 0, 0>), dim3(grid), dim3(64), lds, r, q, c); break;
+        }
         return hipEventRecord(ready[b], r);
     };
     if ((e = recompute(C - 1)) != hipSuccess) return e;

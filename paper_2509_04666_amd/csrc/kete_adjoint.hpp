@@ -44,7 +44,7 @@ struct AdjParams {
     double* adj_state;          // [N][kAdjStateDoubles] carried between backward segments
     int32_t* seg_ns;            // [2][ceil(N / 8)] steps stored per wavefront, per step store
     double* adj_tab;            // [kAdjTabDoubles] constant rows of the reverse sweep
-    double* dense_coef;         // [kDenseCoefDoubles] Ap, Bp of rc (written by the forward launch)
+    double* group_const;        // [kGroupConstDoubles] written by the forward launch
     int32_t s_max;
     int32_t window_segs;        // segments between forced step ends (0: none)
     int32_t max_iter;

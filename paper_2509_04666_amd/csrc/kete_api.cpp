@@ -239,15 +239,8 @@ int ephem_args(const kete_ephem_t* eph, double c_light, EphemArgs& E) {
         if (E.kgr[b] != 0.0) E.has_gr = 1;
     }
     if (!(eph->gm[0] > 0)) return fail(KETE_EINVAL, "gm[0] (Sun) must be positive");
-    int slot = 0;
-    for (int pass = 0; pass < 2; ++pass)
-        for (int b = 0; b < eph->n_body; ++b)
-            if ((E.kgr[b] != 0.0) == (pass == 0)) {
-                E.slot_of |= (unsigned long long)slot << (4 * b);
-                E.body_at |= (unsigned long long)b << (4 * slot);
-                ++slot;
-                if (pass == 0) ++E.n_gr;
-            }
+    bool has_j2[KETE_MAX_BODIES] = {};
+    int n_j2 = 0;
     if (eph->j2) {
         for (int b = 0; b < eph->n_body; ++b) {
             const double* q = eph->j2 + 5 * b;
@@ -255,14 +248,34 @@ int ephem_args(const kete_ephem_t* eph, double c_light, EphemArgs& E) {
             const double pn = std::sqrt(q[2] * q[2] + q[3] * q[3] + q[4] * q[4]);
             if (!std::isfinite(q[0]) || !(q[1] > 0) || !std::isfinite(q[1]) || !(std::fabs(pn - 1.0) < 1e-6))
                 return fail(KETE_EINVAL, "j2[%d]: need finite J2, radius > 0 and a unit pole", b);
-            if (E.n_j2 >= KETE_MAX_J2) return fail(KETE_EINVAL, "more than %d bodies with J2", KETE_MAX_J2);
-            const int i = E.n_j2++;
-            E.j2_body[i] = b;
-            E.j2_slot[i] = body_slot(E, b);
-            E.j2k[i] = 1.5 * q[0] * eph->gm[b] * q[1] * q[1];
-            for (int c = 0; c < 3; ++c) E.j2p[i][c] = q[2 + c] / pn;
+            if (n_j2 >= KETE_MAX_J2) return fail(KETE_EINVAL, "more than %d bodies with J2", KETE_MAX_J2);
+            has_j2[b] = true;
+            ++n_j2;
         }
     }
+    // slots: Eq. A.3 and A.4, Eq. A.3 alone, the others; J2 bodies in the
+    // order of their slots, those without Eq. A.3 last
+    int slot = 0;
+    for (int pass = 0; pass < 3; ++pass)
+        for (int b = 0; b < eph->n_body; ++b) {
+            const bool gr = E.kgr[b] != 0.0;
+            if ((gr ? (has_j2[b] ? 0 : 1) : 2) != pass) continue;
+            E.slot_of |= (unsigned long long)slot << (4 * b);
+            E.body_at |= (unsigned long long)b << (4 * slot);
+            if (gr) ++E.n_gr;
+            if (has_j2[b]) {
+                const double* q = eph->j2 + 5 * b;
+                const double pn = std::sqrt(q[2] * q[2] + q[3] * q[3] + q[4] * q[4]);
+                const int i = E.n_j2++;
+                if (gr) ++E.n_j2g;
+                E.j2_body[i] = b;
+                E.j2_slot[i] = slot;
+                E.j2_slots |= (uint32_t)slot << (4 * i);
+                E.j2k[i] = 1.5 * q[0] * eph->gm[b] * q[1] * q[1];
+                for (int c = 0; c < 3; ++c) E.j2p[i][c] = q[2 + c] / pn;
+            }
+            ++slot;
+        }
     return KETE_OK;
 }
 
@@ -435,7 +448,7 @@ static void auto_integrator_shape(bool grouped, int& block, int& wsegs) {
     if (wsegs <= 0) wsegs = grouped ? 0 : 2;
 }
 
-// The output epochs and the dense-output rows travel in front of the window
+// The output epochs and the grouped kernels' constants travel in front of the window
 // plan (one staged copy).
 // Step-size buckets of the batched jobs' sort: kBucketSub per octave over
 // opts->n_buckets octaves (1 octave: no sort).
@@ -470,7 +483,7 @@ static SortScratch sort_scratch(int32_t* base, int64_t n_obj) {
 }
 
 static size_t epoch_table_bytes(int64_t n_out) {
-    return ((((size_t)n_out + kDenseCoefDoubles) * sizeof(double)) + 31) & ~(size_t)31;
+    return ((((size_t)n_out + kGroupConstDoubles) * sizeof(double)) + 31) & ~(size_t)31;
 }
 
 size_t kete_propagate_workspace_size(int64_t n_obj, int64_t n_out, const kete_opts_t* opts) {
@@ -567,8 +580,8 @@ int kete_propagate_nbody(const kete_ephem_t* eph, const double* x0, double t0, i
     double* h_pref = c.take<double>((size_t)n_obj);
     int32_t* perm = c.take<int32_t>((size_t)n_obj);
     char* plan = c.take<char>(epoch_table_bytes(n_out) + (size_t)max_win * sizeof(Window));
-    double* dcoef = (double*)plan;
-    double* dt_out = dcoef + kDenseCoefDoubles;
+    double* gconst = (double*)plan;
+    double* dt_out = gconst + kGroupConstDoubles;
     Window* dwin = (Window*)(plan + epoch_table_bytes(n_out));
     const SortScratch sorts = sort_scratch(c.take<int32_t>(sort_scratch_ints(n_obj)), n_obj);
 
@@ -576,9 +589,8 @@ int kete_propagate_nbody(const kete_ephem_t* eph, const double* x0, double t0, i
     {
         std::vector<char> host(epoch_table_bytes(n_out) + win.size() * sizeof(Window));
         const RadauConst& rcst = radau_const();
-        std::memcpy(host.data(), &rcst.Ap[0][0], 56 * sizeof(double));
-        std::memcpy(host.data() + 56 * sizeof(double), &rcst.Bp[0][0], 56 * sizeof(double));
-        std::memcpy(host.data() + kDenseCoefDoubles * sizeof(double), t_out, (size_t)n_out * sizeof(double));
+        for (int i = 0; i < kGroupConstDoubles; ++i) reinterpret_cast<double*>(host.data())[i] = group_const_at(rcst, i);
+        std::memcpy(host.data() + kGroupConstDoubles * sizeof(double), t_out, (size_t)n_out * sizeof(double));
         std::memcpy(host.data() + epoch_table_bytes(n_out), win.data(), win.size() * sizeof(Window));
         if ((rc = stage_to_device(plan, host.data(), host.size(), s))) return rc;
     }
@@ -594,7 +606,7 @@ int kete_propagate_nbody(const kete_ephem_t* eph, const double* x0, double t0, i
     P.status = status;
     P.x_out = x_out;
     P.t_out = dt_out;
-    P.dense_coef = dcoef;
+    P.group_const = gconst;
     P.stats = (unsigned long long*)stats;
     P.n_obj = (int32_t)n_obj;
     P.max_iter = opts->max_iter;
@@ -630,6 +642,7 @@ int kete_propagate_nbody(const kete_ephem_t* eph, const double* x0, double t0, i
             P.perm = nullptr;
         }
         P.win = dwin + first;
+        P.t_begin = win[first].t_a;
         P.n_win = last - first + 1;
         P.first_launch = (e0 == 0);
         {
@@ -927,7 +940,7 @@ size_t kete_adjoint_workspace_size(int64_t n_obj, int32_t k_obs, double t0, doub
     c.take<double>((size_t)n_obj * kAdjStateDoubles);                 // carried backward state
     c.take<int32_t>((size_t)2 * ((n_obj + kAdjLanes - 1) / kAdjLanes));     // steps per wavefront, per store
     c.take<double>((size_t)kAdjTabDoubles);                           // reverse-sweep constants
-    c.take<double>((size_t)kDenseCoefDoubles);                        // dense-output rows
+    c.take<double>((size_t)kGroupConstDoubles);                        // constants of the grouped kernels
     return c.off;
 }
 
@@ -969,7 +982,7 @@ int kete_propagate_adjoint(const kete_ephem_t* eph, int32_t mode, const double* 
     double* adj_state = c.take<double>((size_t)n_obj * kAdjStateDoubles);
     int32_t* seg_ns = c.take<int32_t>((size_t)2 * ((n_obj + kAdjLanes - 1) / kAdjLanes));
     double* adj_tab = c.take<double>((size_t)kAdjTabDoubles);
-    double* dense_coef = c.take<double>((size_t)kDenseCoefDoubles);
+    double* group_const = c.take<double>((size_t)kGroupConstDoubles);
 
     hipStream_t s = (hipStream_t)stream;
 
@@ -1002,7 +1015,7 @@ int kete_propagate_adjoint(const kete_ephem_t* eph, int32_t mode, const double* 
     P.adj_state = adj_state;
     P.seg_ns = seg_ns;
     P.adj_tab = adj_tab;
-    P.dense_coef = dense_coef;
+    P.group_const = group_const;
     P.window_segs = window_segs(opts);
     P.max_iter = opts->max_iter;
     P.max_steps = opts->max_steps;
@@ -1146,7 +1159,7 @@ int batch_dims(const kete_ephem_t* eph, const kete_batch_t* bt, int64_t pairs_ca
 struct BatchWs {
     int2* tiles;
     unsigned int* tile_counter;
-    double* dense_coef;
+    double* group_const;
     int32_t* perm;
     FovParams P;
     int32_t *qkey, *cnt, *fcnt, *fstart, *okey, *orank, *osorted, *osub, *ostart, *ocnt, *icnt, *istart;
@@ -1161,7 +1174,7 @@ size_t batch_carve(const BatchDims& d, const kete_batch_t* bt, char* base, Batch
     Carver c{base};
     w.tiles = c.take<int2>((size_t)std::max(d.n_tiles, 1));
     w.tile_counter = c.take<unsigned int>(64);
-    w.dense_coef = c.take<double>(kDenseCoefDoubles);
+    w.group_const = c.take<double>(kGroupConstDoubles);
     w.perm = c.take<int32_t>((size_t)std::max<int64_t>(bt->n_bodies, 1));
     FovParams& P = w.P;
     std::memset(&P, 0, sizeof(P));
@@ -1286,7 +1299,7 @@ int kete_batch_run(const kete_ephem_t* eph, const kete_batch_t* batch, int64_t p
     B.max_steps = opts->max_steps;
     B.zero_start = opts->zero_start != 0;
     B.land_epochs = opts->land_epochs != 0;
-    B.dense_coef = w.dense_coef;
+    B.group_const = w.group_const;
     B.eps = opts->eps;
     B.h_min = opts->h_min;
     B.h_max = opts->h_max;

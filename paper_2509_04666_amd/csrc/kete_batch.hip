@@ -75,7 +75,7 @@ __global__ __launch_bounds__(256) void k_job_bucket(const BatchParams p) {
 // One wavefront per block; it pops tiles of KETE_BATCH_TILE bodies of one
 // job and integrates them as lane groups (one lane per collocation node,
 // see GroupMap) through the job's epochs.
-template <int NB, int NGR, int DEG1>
+template <int NB, int NGR, int NJ2, int DEG1>
 __global__ __launch_bounds__(64, 3) void k_batch_g8(const BatchParams p) {
     constexpr int G = KETE_BATCH_LANES;
     static_assert(GroupMap<G>::kBodies == KETE_BATCH_TILE, "tile = bodies per wavefront");
@@ -83,16 +83,12 @@ __global__ __launch_bounds__(64, 3) void k_batch_g8(const BatchParams p) {
     const int lane = threadIdx.x;
     const GroupMap<G> M(lane);
     const int gl = M.gl;
-    const int node = gl < 7 ? gl + 1 : 7;
     const EphemArgs& E = p.eph;
-    double* e8 = smem;
-    g8_table_init(E, lane, e8);
-    NodeRow R;
-    load_node_row(p.rc, node, R);
-    // dense-output rows and the wavefront's weight slots
-    __shared__ double dcoef[kDenseCoefDoubles];
+    __shared__ __align__(16) GroupConst K;
     __shared__ __align__(16) double dwts[kDenseWeights];
-    for (int i = lane; i < kDenseCoefDoubles; i += 64) dcoef[i] = p.dense_coef[i];
+    load_group_const(p.group_const, &K, lane, kWave);
+    const G8Lds T = g8_lds<GroupMap<G>::kLanes>(E, smem, M.grp);
+    g8_table_init<GroupMap<G>::kLanes>(E, lane, smem);
     __syncthreads();
     for (;;) {
         int tile = 0;
@@ -125,7 +121,6 @@ __global__ __launch_bounds__(64, 3) void k_batch_g8(const BatchParams p) {
         S.haveF0 = false;
         G8Count C;
         const double* ep = p.epochs + job.epoch_off;
-        double* xg = g8_xch(e8, E.n_body, M.grp);
         auto put = [&](int e, double v, bool ok) {       // lane gl writes component gl
             if (valid && gl < 6)
                 p.x_out[job.xout_off + ((int64_t)e * job.n_obj + local) * 6 + gl] = ok ? v : __builtin_nan("");
@@ -147,16 +142,16 @@ __global__ __launch_bounds__(64, 3) void k_batch_g8(const BatchParams p) {
                 while (e_end + 1 < job.n_epoch && (fwd ? ep[e_end + 1] > ep[e_end] : ep[e_end + 1] < ep[e_end]))
                     ++e_end;
             const double target = ep[e_end];
-            int e_next = e;                              // wave-uniform cursor over e .. e_end - 1
+            EpochCursor ec{ep, e, e_end, 0.0};           // wave-uniform cursor over e .. e_end - 1
+            ec.fetch(lane);
             auto dense_out = [&](double ts, double h, const double dn[3], const G8State& St) {
                 const bool ok = St.active && St.status == 0;
-                dense_epochs(dcoef, dwts, xg, gl, lane, ts, h, dn, St.x0, St.v0, St.F0, ep, e_next, e_end,
+                dense_epochs(K, dwts, T.xg, gl, lane, ts, h, dn, St.x0, St.v0, St.F0, ec,
                              [&](int k, double v) { put(k, v, ok); });
             };
             while (S.t != target) {
                 const Window Wn = next_window(S.t, target, E.t_start, E.seg_days, E.inv_seg, E.n_seg, p.window_segs);
-                g8_integrate<NB, NGR, DEG1, G, kStartExtrapolate>(p, R, node, gl, M.grp, lane, e8, Wn.t_b, S, C,
-                                                                  dense_out);
+                g8_integrate<NB, NGR, NJ2, DEG1, G>(p, K, T, M, lane, Wn.t_b, S, C, dense_out);
                 S.t = Wn.t_b;
             }
             put(e_end, state_component(S.x0, S.v0, gl < 6 ? gl : 5), S.active && S.status == 0);
@@ -169,15 +164,21 @@ __global__ __launch_bounds__(64, 3) void k_batch_g8(const BatchParams p) {
 }  // namespace
 
 size_t batch_lds_bytes(const BatchParams& p) {
-    return (size_t)g8_wave_doubles(p.eph.n_body) * sizeof(double);
+    return (size_t)g8_wave_doubles(g8_slots(p.eph.n_body, p.eph.n_gr, GroupMap<KETE_BATCH_LANES>::kLanes)) *
+           sizeof(double);
 }
 
-// The dense-output rows of the constants into device memory (a tiny kernel,
-// so the copy is part of a captured graph too).
-__global__ void k_dense_coef(const BatchParams p) {
+// The grouped kernels' constants into device memory (a tiny kernel, so the
+// copy is part of a captured graph too).
+__global__ void k_group_const(const RadauConst rc, double* __restrict__ out) {
     const int i = threadIdx.x;
-    if (i < 56) p.dense_coef[i] = p.rc.Ap[i / 8][i % 8];
-    else if (i < kDenseCoefDoubles) p.dense_coef[i] = p.rc.Bp[(i - 56) / 8][(i - 56) % 8];
+    if (i < kGroupConstDoubles) out[i] = group_const_at(rc, i);
+}
+
+hipError_t launch_group_const(const RadauConst& rc, double* out, hipStream_t s) {
+    static_assert(kGroupConstDoubles <= 320, "one thread per constant");
+    hipLaunchKernelGGL(k_group_const, dim3(1), dim3(320), 0, s, rc, out);
+    return hipGetLastError();
 }
 
 hipError_t launch_batch(const BatchParams& p, int waves_per_cu, hipStream_t s) {
@@ -185,16 +186,17 @@ hipError_t launch_batch(const BatchParams& p, int waves_per_cu, hipStream_t s) {
     if (hipGetDevice(&dev) == hipSuccess) hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
     hipError_t e;
     if ((e = fill_zero(p.tile_counter, sizeof(unsigned int), s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_dense_coef, dim3(1), dim3(128), 0, s, p);
+    if ((e = launch_group_const(p.rc, p.group_const, s)) != hipSuccess) return e;
     if (p.n_jobs > 0 && p.n_buckets > 1)
         hipLaunchKernelGGL(k_job_bucket, dim3((unsigned)p.n_jobs), dim3(256), 0, s, p);
     const int grid = std::max(1, std::min(ncu * waves_per_cu, p.n_tiles));
     const size_t lds = batch_lds_bytes(p);
-    const int nb = p.eph.n_body, ngr = p.eph.n_gr, d1 = p.eph.deg1;
-    if (nb == 10 && ngr == 3 && d1 == 13) hipLaunchKernelGGL((k_batch_g8<10, 3, 13>), dim3(grid), dim3(64), lds, s, p);
-    else if (nb == 3 && ngr == 2 && d1 == 13)
-        hipLaunchKernelGGL((k_batch_g8<3, 2, 13>), dim3(grid), dim3(64), lds, s, p);
-    else hipLaunchKernelGGL((k_batch_g8<0, 0, 0>), dim3(grid), dim3(64), lds, s, p);
+    switch (group_shape(p.eph)) {
+        case 2: hipLaunchKernelGGL((k_batch_g8<10, 3, 2, 13>), dim3(grid), dim3(64), lds, s, p); break;
+        case 3: hipLaunchKernelGGL((k_batch_g8<3, 2, 2, 13>), dim3(grid), dim3(64), lds, s, p); break;
+        case 1: hipLaunchKernelGGL((k_batch_g8<0, 0, 0, 13>), dim3(grid), dim3(64), lds, s, p); break;
+        default: hipLaunchKernelGGL((k_batch_g8<0, 0, 0, 0>), dim3(grid), dim3(64), lds, s, p); break;
+    }
     return hipGetLastError();
 }
 

@@ -31,7 +31,7 @@ struct BatchParams {
     int32_t max_steps;
     int32_t zero_start;         // corrector starts from zero increments (no extrapolation)
     int32_t land_epochs;        // land on every epoch (else epochs inside a step come off its polynomial)
-    double* dense_coef;         // [kDenseCoefDoubles] Ap, Bp of rc, written by the launch
+    double* group_const;        // [kGroupConstDoubles] written by the launch
     double eps, h_min, h_max, h_init, safety;
 };
 

@@ -20,14 +20,16 @@ struct EphemArgs {
     double gm[KETE_MAX_BODIES];
     double kgr[KETE_MAX_BODIES];   // gm/c^2 for bodies with the Eq. A.3 term, else 0
     // Slot order of the grouped integrator's perturber table: bodies with
-    // the Eq. A.3 term first (n_gr of them), then the others, each group
-    // in body order.  slot_of holds 4 bits per body.
+    // the Eq. A.3 term first (n_gr of them, those that also carry the Eq.
+    // A.4 term before the rest), then the others, each group in body order.  slot_of holds 4 bits per body.
     int32_t n_gr, pad_;
     unsigned long long slot_of;    // slot of body b: 4 bits at 4 b
     unsigned long long body_at;    // body in slot s: 4 bits at 4 s
-    // Bodies with the Eq. A.4 term: body index, grouped-table slot,
-    // k = (3/2) J2 mu R^2 and the unit pole.
-    int32_t n_j2, pad2_;
+    // Bodies with the Eq. A.4 term: body index, grouped-table slot (also
+    // packed, 4 bits each), k = (3/2) J2 mu R^2 and the unit pole.  The
+    // n_j2g that carry the Eq. A.3 term come first and have the first slots.
+    int32_t n_j2, n_j2g;
+    uint32_t j2_slots, pad2_;
     int32_t j2_body[KETE_MAX_J2], j2_slot[KETE_MAX_J2];
     double j2k[KETE_MAX_J2];
     double j2p[KETE_MAX_J2][3];

@@ -32,8 +32,28 @@ struct RadauConst {
     double Lden[7];
     double L1[7];
 };
-// Ap then Bp, as copied next to the output epochs for the dense-output kernels
-constexpr int kDenseCoefDoubles = 2 * 7 * 8;
+// The constants the grouped kernels keep in LDS (GroupConst), as laid out by
+// fill_group_const: Ap, Bp, then per lane gl = 0..7 of a group the row {s,
+// s^2/2, A, B, 2 spare} of its node (gl + 1, and 7 for gl = 7), the nodes,
+// Lden and L1 (8 each), and the step-end weights of D_1..D_7 and F_0 in the
+// position and the velocity.
+constexpr int kGroupConstDoubles = 2 * 56 + 8 * 18 + 5 * 8;
+__host__ __device__ inline double group_const_at(const RadauConst& rc, int i) {
+    if (i < 56) return rc.Ap[i / 8][i % 8];
+    if (i < 112) return rc.Bp[(i - 56) / 8][i % 8];
+    i -= 112;
+    if (i < 144) {
+        const int n = i / 18 < 7 ? i / 18 + 1 : 7, k = i % 18;
+        return k == 0 ? rc.s[n] : k == 1 ? rc.half_s2[n] : k < 9 ? rc.A[n][k - 2] : k < 16 ? rc.B[n][k - 9] : 0.0;
+    }
+    i -= 144;
+    const int k = i % 8;
+    if (i < 8) return rc.s[k];
+    if (i < 16) return k < 7 ? rc.Lden[k] : 0.0;
+    if (i < 24) return k < 7 ? rc.L1[k] : 0.0;
+    if (i < 32) return k < 7 ? rc.A[8][k] : rc.half_s2[8];
+    return k < 7 ? rc.B[8][k] : 1.0;
+}
 
 // One staged ephemeris window of the integration: [t_a, t_b] lies within
 // Chebyshev segments [seg_lo, seg_hi]; out >= 0 marks an output epoch.
@@ -115,7 +135,7 @@ struct NbodyParams {
     unsigned long long* stats;  // [8] or null
     const Window* win;      // windows of this launch
     const double* t_out;    // [E] output epochs (device)
-    const double* dense_coef;   // [2][7][8] the monomial rows Ap, Bp of RadauConst (device)
+    const double* group_const;  // [kGroupConstDoubles] (device)
     int32_t e_first;        // epochs e_first .. e_land - 1 are read off the step polynomials,
     int32_t e_land;         // epoch e_land ends the launch's last window (no dense epochs: e_first = e_land)
     int32_t n_win;
@@ -126,10 +146,23 @@ struct NbodyParams {
     int32_t first_launch;
     int32_t zero_start;     // corrector starts from zero increments (no extrapolation)
     int32_t pad_;
+    double t_begin;         // start of the launch's first window
     double eps, h_min, h_max, h_init, safety;
 };
 
 const RadauConst& radau_const();
+// The grouped kernels' constants (group_const_at) into device memory by a kernel.
+hipError_t launch_group_const(const RadauConst& rc, double* out, hipStream_t s);
+
+// Instantiation of the grouped kernels for a perturber table: 2 and 3 the
+// default model's shape (10 bodies, 3 with Eq. A.3, 2 of them with Eq. A.4)
+// and that of the Sun with two planets, whose force is unrolled; 1 any other
+// count with 13 coefficients, 0 any.
+inline int group_shape(const EphemArgs& E) {
+    if (E.deg1 != 13) return 0;
+    if (E.n_j2 != 2 || E.n_j2g != 2) return 1;
+    return E.n_body == 10 && E.n_gr == 3 ? 2 : E.n_body == 3 && E.n_gr == 2 ? 3 : 1;
+}
 
 // lanes_per_body: 1 (one lane per object) or 8 (an 8-lane group per object).
 hipError_t launch_nbody(const NbodyParams& p, int block, int lanes_per_body, hipStream_t s);

@@ -157,99 +157,85 @@ __global__ __launch_bounds__(BLOCK) void k_nbody(const NbodyParams p) {
     }
 }
 
-// G lanes per object (7 or 8, see GroupMap): a wavefront integrates 9 or
-// 8 objects, each spread over a group whose lanes own one collocation
-// node each.  The objects of a wavefront share the time grid and the
-// perturber table as above; each sweep evaluates the force at all 7 nodes
-// of an object at once.  Output and counters are per object, as in
-// k_nbody.
-template <int G, int NB, int NGR, int DEG1>
+// G lanes per object (see GroupMap): a wavefront integrates 9 objects (or 8,
+// 4, 2, 1), each spread over a group whose lanes own the collocation nodes.
+// The objects of a wavefront share the time grid and the perturber table as
+// above; each sweep evaluates the force at all 7 nodes of an object at once.
+// Output and counters are per object, as in k_nbody.
+template <int G, int NB, int NGR, int NJ2, int DEG1>
 __global__ __launch_bounds__(256, 3) void k_nbody_g8(const NbodyParams p) {
     extern __shared__ __align__(16) double smem[];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
     const int n_waves = blockDim.x / kWave;
     const GroupMap<G> M(lane);
-    const int gl = M.gl;                              // lane within the object's group
-    const int node = gl < 7 ? gl + 1 : 7;
+    constexpr int L = GroupMap<G>::kLanes;
+    const int gl = M.gl;
     const EphemArgs& E = p.eph;
-    const RadauConst& rc = p.rc;
-    const int nb = E.n_body;
-    double* e8 = smem + (size_t)wid * g8_wave_doubles(nb);
-    double* wt = smem + (size_t)n_waves * g8_wave_doubles(nb) + wid * kDenseWeights;
-    g8_table_init(E, lane, e8);
-    // per-node constants of the 8 lanes of a group, read from LDS in the
-    // sweeps to keep registers for more wavefronts per SIMD
-    __shared__ NodeRow rows[kGroup];
-    if (tid < kGroup) {
-        NodeRow r;
-        load_node_row(rc, tid < 7 ? tid + 1 : 7, r);
-        rows[tid] = r;
-    }
-    // dense-output rows, read from LDS at the epochs inside a step
-    __shared__ double dcoef[kDenseCoefDoubles];
-    if (p.e_first < p.e_land)
-        for (int i = tid; i < kDenseCoefDoubles; i += (int)blockDim.x) dcoef[i] = p.dense_coef[i];
-    __syncthreads();
-    const NodeRow& R = rows[gl];
-
+    __shared__ __align__(16) GroupConst K;
     const long gi = ((long)blockIdx.x * n_waves + wid) * GroupMap<G>::kBodies + M.grp;
     const bool valid = gi < p.n_obj;
     const int j = valid ? (p.perm ? p.perm[gi] : (int)gi) : 0;
+    load_group_const(p.group_const, &K, tid, (int)blockDim.x);
+    const int slots = g8_slots(E.n_body, E.n_gr, L);
+    double* base = smem + (size_t)wid * (g8_wave_doubles(slots) + kDenseWeights);
+    double* wt = base + g8_wave_doubles(slots);
+    const G8Lds T = g8_lds<L>(E, base, M.grp);
+    g8_table_init<L>(E, lane, base);
+
     G8State S;
-    S.active = valid && p.status[j] == 0;
     S.status = valid ? p.status[j] : 0;
+    S.active = valid && S.status == 0;
     S.x0[0] = 1.0; S.x0[1] = S.x0[2] = 0.0;
     S.v0[0] = S.v0[1] = S.v0[2] = 0.0;
     S.F0[0] = S.F0[1] = S.F0[2] = 0.0;
     double hin = kInf;
     if (valid) {
 #pragma unroll
-        for (int i = 0; i < 3; ++i) { S.x0[i] = p.state[6 * j + i]; S.v0[i] = p.state[6 * j + 3 + i]; }
+        for (int i = 0; i < 3; ++i) { S.x0[i] = p.state[6 * (size_t)j + i]; S.v0[i] = p.state[6 * (size_t)j + 3 + i]; }
         hin = p.h_pref[j];
     }
-    S.hw = groups_min<G>(S.active ? hin : kInf);
-    if (!(S.hw < kInf)) S.hw = p.h_init;
-    S.hp_new = kInf;
-    S.t = p.win[0].t_a;
-    S.haveF0 = false;
-    G8Count C;
-
     // Epochs e_first .. e_land - 1 come off the collocation polynomial of
     // the accepted step that spans them (the cursor is wave-uniform: the
     // wavefront's objects share every step).
-    double* xg = g8_xch(e8, nb, M.grp);
-    int e_next = p.e_first;
-    auto put = [&](int e, double v, bool ok) {      // lane gl writes component gl
-        if (valid && gl < 6) p.x_out[((size_t)e * p.n_obj + j) * 6 + gl] = ok ? v : __builtin_nan("");
+    EpochCursor ec{p.t_out, p.e_first, p.e_land, 0.0};
+    ec.fetch(lane);
+    S.hw = groups_min<G>(S.active ? hin : kInf);
+    if (!(S.hw < kInf)) S.hw = p.h_init;
+    S.hp_new = kInf;
+    S.t = p.t_begin;
+    S.haveF0 = false;
+    G8Count C;
+    __syncthreads();
+
+    const bool writer = valid && gl < 6 && M.sub == 0;
+    auto put = [&](int e, double v, bool ok) {      // node lane gl writes component gl
+        if (writer) p.x_out[((size_t)e * p.n_obj + j) * 6 + gl] = ok ? v : __builtin_nan("");
     };
-    while (e_next < p.e_land && p.t_out[e_next] == S.t) {       // epochs at the start time
-        put(e_next, state_component(S.x0, S.v0, gl < 6 ? gl : 5), S.active && S.status == 0);
-        ++e_next;
+    while (ec.next < ec.end && uniform(ec.tk) == S.t) {         // epochs at the start time
+        put(ec.next, state_component(S.x0, S.v0, gl < 6 ? gl : 5), S.active && S.status == 0);
+        ++ec.next;
+        ec.fetch(lane);
     }
     auto dense_out = [&](double ts, double h, const double dn[3], const G8State& St) {
         const bool ok = St.active && St.status == 0;
-        dense_epochs(dcoef, wt, xg, gl, lane, ts, h, dn, St.x0, St.v0, St.F0, p.t_out, e_next, p.e_land,
+        dense_epochs(K, wt, T.xg, gl, lane, ts, h, dn, St.x0, St.v0, St.F0, ec,
                      [&](int e, double v) { put(e, v, ok); });
     };
 
     for (int w = 0; w < p.n_win; ++w) {
-        const Window W = p.win[w];
-        g8_integrate<NB, NGR, DEG1, G, kStartExtrapolate>(p, R, node, gl, M.grp, lane, e8, W.t_b, S, C, dense_out);
-        if (W.out >= 0 && valid && gl < 6) {
-            // lane gl of the group writes component gl of the state
-            double* dst = p.x_out + ((size_t)W.out * p.n_obj + j) * 6;
-            const bool ok = S.active && S.status == 0;
-            dst[gl] = ok ? state_component(S.x0, S.v0, gl) : __builtin_nan("");
-        }
+        const double t_b = p.win[w].t_b;
+        const int out = p.win[w].out;
+        g8_integrate<NB, NGR, NJ2, DEG1, G>(p, K, T, M, lane, t_b, S, C, dense_out);
+        if (out >= 0) put(out, state_component(S.x0, S.v0, gl < 6 ? gl : 5), S.active && S.status == 0);
     }
-    if (valid && gl < 6) p.state[6 * j + gl] = state_component(S.x0, S.v0, gl);
-    if (valid && gl == 0) {
+    if (writer) p.state[6 * (size_t)j + gl] = state_component(S.x0, S.v0, gl);
+    if (valid && gl == 0 && M.sub == 0) {
         if (S.hp_new < kInf) p.h_pref[j] = S.hp_new;
         p.status[j] = S.status;
     }
     const unsigned long long c_steps = C.steps, c_iter = C.iter, c_rej = C.rej, c_lsteps = C.lsteps,
                              c_liter = C.liter, c_chain = C.chain, c_vchain = C.vchain, c_lpred = C.lpred;
-    if (p.stats && lane == 0 && __ballot(valid) != 0ull) {
+    if (p.stats && __ballot(valid) != 0ull && lane == 0) {
         atomicAdd(p.stats + 0, c_steps);
         atomicAdd(p.stats + 1, c_iter);
         atomicAdd(p.stats + 2, c_rej);
@@ -337,33 +323,33 @@ __global__ void k_hpref_init(const double* __restrict__ x0, double* __restrict__
 
 }  // namespace
 
+// The grouped kernel with G lanes per object; the usual shapes of the
+// perturber table (bodies, bodies with the Eq. A.3 and A.4 terms) get an
+// unrolled force.
+template <int G>
+static hipError_t launch_groups(const NbodyParams& p, int block, hipStream_t s) {
+    const int wpb = block / kWave;
+    const long waves = ((long)p.n_obj + GroupMap<G>::kBodies - 1) / GroupMap<G>::kBodies;
+    const dim3 grid((unsigned)((waves + wpb - 1) / wpb));
+    if (grid.x == 0) return hipSuccess;
+    const EphemArgs& E = p.eph;
+    const size_t lds = (size_t)wpb * (g8_wave_doubles(g8_slots(E.n_body, E.n_gr, GroupMap<G>::kLanes)) + kDenseWeights) *
+                       sizeof(double);
+    switch (group_shape(E)) {
+        case 2: hipLaunchKernelGGL((k_nbody_g8<G, 10, 3, 2, 13>), grid, dim3(block), lds, s, p); break;
+        case 3: hipLaunchKernelGGL((k_nbody_g8<G, 3, 2, 2, 13>), grid, dim3(block), lds, s, p); break;
+        case 1: hipLaunchKernelGGL((k_nbody_g8<G, 0, 0, 0, 13>), grid, dim3(block), lds, s, p); break;
+        default: hipLaunchKernelGGL((k_nbody_g8<G, 0, 0, 0, 0>), grid, dim3(block), lds, s, p); break;
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_nbody(const NbodyParams& p, int block, int lanes_per_body, hipStream_t s) {
     const size_t lds = ((size_t)p.eph.n_body * p.max_win_segs * 3 * p.eph.deg1 +
                         (size_t)(block / kWave) * kNodes * p.eph.n_body * 6) * sizeof(double);
     if (lanes_per_body == 7 || lanes_per_body == 8) {
-        const size_t lds8 = (size_t)(block / kWave) * (g8_wave_doubles(p.eph.n_body) + kDenseWeights) * sizeof(double);
-        const long per_wave = lanes_per_body == 7 ? GroupMap<7>::kBodies : GroupMap<8>::kBodies;
-        const long waves = ((long)p.n_obj + per_wave - 1) / per_wave;
-        const int wpb = block / kWave;
-        const int grid = (int)((waves + wpb - 1) / wpb);
-        if (grid == 0) return hipSuccess;
-        // perturber tables of the common shapes get an unrolled force loop
-        const int nb = p.eph.n_body, ngr = p.eph.n_gr, d1 = p.eph.deg1;
-#define KETE_G8(G)                                                                                              \
-    do {                                                                                                        \
-        if (nb == 10 && ngr == 3 && d1 == 13)                                                                   \
-            hipLaunchKernelGGL((k_nbody_g8<G, 10, 3, 13>), dim3(grid), dim3(block), lds8, s, p);                \
-        else if (nb == 3 && ngr == 2 && d1 == 13)                                                               \
-            hipLaunchKernelGGL((k_nbody_g8<G, 3, 2, 13>), dim3(grid), dim3(block), lds8, s, p);                 \
-        else if (d1 == 13)                                                                                      \
-            hipLaunchKernelGGL((k_nbody_g8<G, 0, 0, 13>), dim3(grid), dim3(block), lds8, s, p);                 \
-        else hipLaunchKernelGGL((k_nbody_g8<G, 0, 0, 0>), dim3(grid), dim3(block), lds8, s, p);                 \
-    } while (0)
         if (block != 64 && block != 128 && block != 256) return hipErrorInvalidValue;
-        if (lanes_per_body == 7) KETE_G8(7);
-        else KETE_G8(8);
-#undef KETE_G8
-        return hipGetLastError();
+        return lanes_per_body == 7 ? launch_groups<7>(p, block, s) : launch_groups<8>(p, block, s);
     }
     if (lanes_per_body != 1) return hipErrorInvalidValue;
     const int grid = (int)((p.n_obj + block - 1) / block);

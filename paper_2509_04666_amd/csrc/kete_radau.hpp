@@ -16,10 +16,9 @@ constexpr double kInf = 1e300;
 // the componentwise expression in the body's equatorial frame reads
 //   a = -k / |d|^5 [(1 - 5 z^2 / |d|^2) d + 2 z p].
 // id = 1 / |d|.
-__device__ __forceinline__ void j2_add(const EphemArgs& E, int q, const double d[3], double id, double a[3]) {
-    const double* p = E.j2p[q];
+__device__ __forceinline__ void j2_add(double k, const double* p, const double d[3], double id, double a[3]) {
     const double id2 = id * id;
-    const double s = -E.j2k[q] * (id2 * id2 * id);
+    const double s = -k * (id2 * id2 * id);
     const double z = fma(d[0], p[0], fma(d[1], p[1], d[2] * p[2]));
     const double c = s * fma(-5.0 * z * id2, z, 1.0);
     const double e = 2.0 * s * z;
@@ -78,7 +77,7 @@ __device__ __forceinline__ void accel(const double* __restrict__ e, const EphemA
     for (int q = 0; q < E.n_j2; ++q) {
         const double* pb = e + 6 * E.j2_body[q];
         const double d[3] = {X[0] - pb[0], X[1] - pb[1], X[2] - pb[2]};
-        j2_add(E, q, d, rsqrt(fma(d[0], d[0], fma(d[1], d[1], d[2] * d[2]))), F);
+        j2_add(E.j2k[q], E.j2p[q], d, rsqrt(fma(d[0], d[0], fma(d[1], d[1], d[2] * d[2]))), F);
     }
 }
 
@@ -186,60 +185,64 @@ __device__ __forceinline__ int corrector(const RadauConst& rc, const EphemArgs& 
     return it;
 }
 
-// ---------------------------------------------------------------- 8 lanes per body
-// A body can be spread over an 8-lane group: lane k of the group owns
-// collocation node k + 1 (lane 7 repeats node 7), every lane keeps the
-// body's state and all seven increments, and one corrector sweep updates
-// all nodes at once from the previous sweep's increments (a Jacobi sweep
-// of the same fixed-point map, converging to the same collocation
-// solution).
+// ---------------------------------------------------------------- lane groups
+// A body is spread over a lane group: the group's lanes own the collocation
+// nodes 1..7 (one or more lanes per node), every lane keeps the body's state,
+// and one corrector sweep updates all nodes at once from the previous
+// sweep's increments (a Jacobi sweep of the same fixed-point map, converging
+// to the same collocation solution).
 constexpr int kGroup = 8;
 
-// Lanes of a wavefront by body.  With G = 8 a wavefront holds 8 bodies,
-// lanes 8g..8g+7 for body g.  With G = 7 it holds 9: lanes 7g..7g+6 for
-// body g, and lane 63 joins body 8 as its eighth lane.  In both layouts
-// lane gl = 7 of a group repeats node 7, so every node has exactly one
-// owning lane and the code below needs no other distinction.
+// Lanes of a wavefront by body, G lanes per body.  G = 7: 9 bodies, lanes
+// 7g..7g+6 for body g, and lane 63 joins body 8 as its eighth lane.  G = 8:
+// 8 bodies, lanes 8g..8g+7.  G = 14, 28, 56: 4, 2 or 1 bodies with kLanes =
+// 2, 4 or 8 adjacent lanes per node, which share the node's force sum, and
+// lanes 56..63 joining the last body.  gl is the lane's node less one; lanes
+// with gl = 7 repeat node 7, so every node has exactly one owning set of
+// lanes and the code below needs no other distinction.  sub numbers the
+// lanes of a node.
 template <int G>
 struct GroupMap {
-    static_assert(G == 7 || G == 8, "7 or 8 lanes per body");
-    static constexpr int kBodies = G == 8 ? 8 : 9;   // bodies per wavefront
-    int grp, gl;
+    static_assert(G == 7 || G == 8 || G == 14 || G == 28 || G == 56, "lanes per body");
+    static constexpr int kLanes = G == 8 ? 1 : G / 7;
+    static constexpr int kBodies = G == 8 ? 8 : 64 / G;      // bodies per wavefront
+    int grp, gl, sub;
     __device__ __forceinline__ explicit GroupMap(int lane) {
+        sub = 0;
         if constexpr (G == 8) {
             grp = lane >> 3;
             gl = lane & 7;
         } else {
-            grp = lane < 63 ? lane / 7 : 8;
-            gl = lane - 7 * grp;
+            const bool in = lane < kBodies * G;
+            grp = in ? lane / G : kBodies - 1;
+            gl = in ? (lane - grp * G) / kLanes : 7;
+            if constexpr (kLanes > 1) sub = lane & (kLanes - 1);
         }
     }
 };
 constexpr int kMaxGroups = 9;
 
-// Constants of one node, held in registers by the lane that owns it.
+// Constants of one node.
 struct NodeRow {
     double s, hs2, A[7], B[7];
     double pad_[2];       // 144-byte rows: the 8 rows start in distinct LDS banks
 };
 
-// Row n (lane-varying, 1..7) selected from uniform constants without any
-// lane-indexed memory access.
-__device__ __forceinline__ void load_node_row(const RadauConst& rc, int n, NodeRow& r) {
-    r.s = 0.0; r.hs2 = 0.0;
-#pragma unroll
-    for (int m = 0; m < 7; ++m) { r.A[m] = 0.0; r.B[m] = 0.0; }
-#pragma unroll
-    for (int k = 1; k <= 7; ++k) {
-        const bool me = (n == k);
-        r.s = me ? rc.s[k] : r.s;
-        r.hs2 = me ? rc.half_s2[k] : r.hs2;
-#pragma unroll
-        for (int m = 0; m < 7; ++m) {
-            r.A[m] = me ? rc.A[k][m] : r.A[m];
-            r.B[m] = me ? rc.B[k][m] : r.B[m];
-        }
-    }
+// Constants of the grouped kernels, copied to LDS from the device table that
+// fill_group_const describes (GroupConst's doubles in order).
+struct GroupConst {
+    double Ap[7][8], Bp[7][8];      // dense output
+    NodeRow row[kGroup];            // by gl
+    double s[8];                    // nodes 0..7
+    double Lden[8], L1[8];          // extrapolated corrector start
+    double A8[8], B8[8];            // step end: weights of D_1..D_7, then of F_0
+};
+static_assert(sizeof(GroupConst) == kGroupConstDoubles * sizeof(double), "the device table is one GroupConst");
+
+__device__ __forceinline__ void load_group_const(const double* __restrict__ src, GroupConst* dst, int tid,
+                                                 int nthreads) {
+    double* d = &dst->Ap[0][0];
+    for (int i = tid; i < kGroupConstDoubles; i += nthreads) d[i] = src[i];
 }
 
 // Wave-wide reductions of values that are equal within each group, as a
@@ -297,32 +300,103 @@ __device__ __forceinline__ double groups_max(double x) { return groups_reduce<G,
 template <int G = kGroup>
 __device__ __forceinline__ double groups_min(double x) { return groups_reduce<G, false>(x); }
 
-// Perturber table of the grouped integrator: per node and slot 8 doubles
+// Sum over the L adjacent lanes of a node (every lane gets the same bits:
+// each step adds the same two values on both sides).
+template <int L>
+__device__ __forceinline__ void node_sum(double a[3]) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        if constexpr (L > 1) a[c] += dpp_double<0xB1>(a[c]);
+        if constexpr (L > 2) a[c] += dpp_double<0x4E>(a[c]);
+        if constexpr (L > 4) a[c] += dpp_double<0x141>(a[c]);
+    }
+}
+
+// Perturber table of the grouped integrators: per node and slot 8 doubles
 // (x, y, z, GM, vx, vy, vz, GM/c^2).  GM values are written once per
 // launch (g8_table_init); node_ephemeris8 fills positions, and velocities
-// only for the slots that carry the Eq. A.3 term.
+// only for the slots that carry the Eq. A.3 term (zero for the others).
+// Slots past the last body stand for massless ones far away, which add
+// exactly nothing: with one lane per node the bodies without the term are
+// padded to whole fours, else the slots to whole rounds of the lanes.
 constexpr int kSlot = 8;
-// Doubles per node row: 4 (4 n_body + 1) dwords, so the 8 rows read
-// together by an 8-lane group fall in distinct LDS banks.
-__host__ __device__ inline int g8_row(int n_body) { return n_body * kSlot + 2; }
-__device__ __forceinline__ int g8_row(const EphemArgs& E) { return g8_row(E.n_body); }
+__host__ __device__ inline int g8_slots(int n_body, int n_gr, int lanes) {
+    return lanes == 1 ? n_gr + ((n_body - n_gr + 3) & ~3) : (n_body + lanes - 1) / lanes * lanes;
+}
+// Doubles per node row: 4 (4 slots + 1) dwords, so the 8 rows read together
+// by an 8-lane group fall in distinct LDS banks.
+__host__ __device__ inline int g8_row(int slots) { return slots * kSlot + 2; }
 
 // Exchange rows of the grouped corrector, after the wave's node table:
 // per group three rows (x, y, z) of 8 doubles, lane gl writing column gl,
 // padded to 26 doubles so that the 16-byte reads of the groups of a
 // wavefront fall in distinct LDS banks.
 constexpr int kXchGroup = 26;
-// Doubles of LDS per wavefront: node table plus exchange rows.
-__host__ __device__ inline int g8_wave_doubles(int n_body) {
-    return kNodes * g8_row(n_body) + kMaxGroups * kXchGroup;
+// Constants {k, pole} of the bodies with the Eq. A.4 term, after the
+// exchange rows: 8 entries by slot for those that carry the Eq. A.3 term too
+// (they have the first slots; zero for the others), then KETE_MAX_J2 by
+// index for the rest.
+constexpr int kJ2Doubles = 4 * (8 + KETE_MAX_J2);
+// Doubles of LDS per wavefront: node table, exchange rows, J2 constants.
+__host__ __device__ inline int g8_wave_doubles(int slots) {
+    return kNodes * g8_row(slots) + kMaxGroups * kXchGroup + kJ2Doubles;
 }
-__device__ __forceinline__ double* g8_xch(double* e8, int n_body, int grp) {
-    return e8 + kNodes * g8_row(n_body) + grp * kXchGroup;
+
+// One wavefront's LDS areas, and the shape of its table.
+struct G8Lds {
+    double* e8;             // node table
+    double* xg;             // this group's exchange rows
+    const double* j2;       // J2 constants
+    int row;                // doubles per node row
+};
+template <int L>
+__device__ __forceinline__ G8Lds g8_lds(const EphemArgs& E, double* base, int grp) {
+    const int slots = g8_slots(E.n_body, E.n_gr, L);
+    G8Lds s;
+    s.e8 = base;
+    s.row = g8_row(slots);
+    s.xg = base + kNodes * s.row + grp * kXchGroup;
+    s.j2 = base + kNodes * s.row + kMaxGroups * kXchGroup;
+    return s;
+}
+
+// The entries of the table and of the J2 constants that hold for the whole
+// launch; one wavefront.
+template <int L>
+__device__ __forceinline__ void g8_table_init(const EphemArgs& E, int lane, double* __restrict__ base) {
+    const int slots = g8_slots(E.n_body, E.n_gr, L);
+    const int row = g8_row(slots);
+    const int n = lane < kNodes ? lane : 0;      // lanes past the nodes repeat node 0
+    double* r = base + n * row;
+#pragma unroll
+    for (int b = 0; b < KETE_MAX_BODIES; ++b) {
+        if (b >= E.n_body) break;
+        double* q = r + body_slot(E, b) * kSlot;
+        q[3] = E.gm[b];
+        q[4] = q[5] = q[6] = 0.0;
+        q[7] = E.kgr[b];
+    }
+    for (int sl = E.n_body; sl < slots; ++sl) {
+        double* q = r + sl * kSlot;
+        q[0] = 1e6;
+        for (int k = 1; k < kSlot; ++k) q[k] = 0.0;
+    }
+    double* j2 = base + kNodes * row + kMaxGroups * kXchGroup;
+    if (lane < kJ2Doubles) j2[lane] = 0.0;
+    wave_lds_sync();
+#pragma unroll
+    for (int q = 0; q < KETE_MAX_J2; ++q) {
+        if (q >= E.n_j2) break;
+        double* d = j2 + 4 * (q < E.n_j2g ? q : 8 + q);
+        d[0] = E.j2k[q];
+        d[1] = E.j2p[q][0]; d[2] = E.j2p[q][1]; d[3] = E.j2p[q][2];
+    }
+    wave_lds_sync();
 }
 
 // Publish this lane's increment dn (node gl + 1) and read the increments
 // D[m] of nodes m + 1 = 1..7 of the group.  Every lane of the wavefront
-// takes part.
+// takes part (the lanes of a node write the same values).
 __device__ __forceinline__ void g8_exchange(double* __restrict__ xg, int gl, const double dn[3], double D[7][3]) {
     wave_lds_sync();                        // earlier reads of the rows are done
     xg[gl] = dn[0];
@@ -336,16 +410,6 @@ __device__ __forceinline__ void g8_exchange(double* __restrict__ xg, int gl, con
             const double2 v = *reinterpret_cast<const double2*>(xg + 8 * c + 2 * k);
             D[2 * k][c] = v.x;
             if (2 * k + 1 < 7) D[2 * k + 1][c] = v.y;
-        }
-    }
-}
-
-__device__ __forceinline__ void g8_table_init(const EphemArgs& E, int lane, double* __restrict__ e8) {
-    for (int b = 0; b < E.n_body; ++b) {
-        const int sl = body_slot(E, b);
-        for (int n = lane; n < kNodes; n += kWave) {
-            e8[n * g8_row(E.n_body) + sl * kSlot + 3] = E.gm[b];
-            e8[n * g8_row(E.n_body) + sl * kSlot + 7] = E.kgr[b];
         }
     }
 }
@@ -386,25 +450,25 @@ struct ChainCoef {
     }
 };
 
-// Perturber states at the node times of a step.  Lane k of each 8-lane
-// group takes node (k & 7) + 1 (node 8 is the step end) and finds that
-// node's segment and tau once; the 3 n_body coordinates are spread over
-// the 8 groups (group g takes coordinates g, g + 8, ...), two of a lane's
-// chains in flight.  Coordinates of the slots with the Eq. A.3 term come
-// first and also get the velocity (derivative chain); a pair of passes
-// holding any of them evaluates derivatives in every lane so the wavefront
-// does not diverge.  Node 0 (the step start, needed before the first step or
-// when the caller asks) takes one more pass with coordinate = lane.  The
-// node of a lane here follows lane & 7 whatever the lane's body group.
+// Perturber states at the node times of a step.  Lane k of each 8 takes
+// node (k & 7) + 1 (node 8 is the step end) and finds that node's segment
+// and tau once; the 3 n_body coordinates are spread over the 8 eights (eight
+// g takes coordinates g, g + 8, ...), two of a lane's chains in flight.
+// Coordinates of the slots with the Eq. A.3 term come first and also get the
+// velocity (derivative chain); a pair of passes holding any of them
+// evaluates derivatives in every lane so the wavefront does not diverge.
+// Node 0 (the step start, needed before the first step or when the caller
+// asks) takes one more pass with coordinate = lane.  The node of a lane here
+// follows lane & 7 whatever the lane's body group.
 //
 // The coefficients come straight from the table (156 KB for ten bodies and a
 // year: it stays in each XCD's L2), a step's chains reading two or three
 // segments of it.  Staged in LDS instead they tied the wavefronts of a block
 // to one window of a few segments: barriers at its ends, where every step
-// also had to land.
+// also had to land (750,000 bodies for a year: 28.3 ms a launch, 20.9 so).
 template <int NB, int NGR, int DEG1>
-__device__ __forceinline__ void node_ephemeris8(const EphemArgs& E, const RadauConst& rc, double t, double h,
-                                                double t_end, bool node0, int lane, double* __restrict__ e8) {
+__device__ __forceinline__ void node_ephemeris8(const EphemArgs& E, const GroupConst& K, const G8Lds& T, double t,
+                                                double h, double t_end, bool node0, int lane) {
     const int nb = NB > 0 ? NB : E.n_body;
     const int ngr = NB > 0 ? NGR : E.n_gr;
     const int deg1 = DEG1 > 0 ? DEG1 : E.deg1;
@@ -415,7 +479,7 @@ __device__ __forceinline__ void node_ephemeris8(const EphemArgs& E, const RadauC
         const int k = seg_index(tt, E.t_start, E.inv_seg, 0, E.n_seg - 1);
         const double tau = 2.0 * (tt - (E.t_start + (double)k * E.seg_days)) * E.inv_seg - 1.0;
         const double* cb = E.coef + (size_t)k * cps;
-        double* row = e8 + n * g8_row(E);
+        double* row = T.e8 + n * T.row;
 #pragma unroll 1
         for (int j = 0; j < npass; j += 2) {
             const int ca = c0 + cstep * j, cc = ca + cstep;
@@ -440,7 +504,8 @@ __device__ __forceinline__ void node_ephemeris8(const EphemArgs& E, const RadauC
         }
     };
     const int nl = lane & (kGroup - 1);
-    chains(nl + 1, nl == kGroup - 1 ? t_end : t + rc.s[nl + 1] * h, lane / kGroup, kGroup, (nc + kGroup - 1) / kGroup);
+    chains(nl + 1, nl == kGroup - 1 ? t_end : fma(K.row[nl].s, h, t), lane / kGroup, kGroup,
+           (nc + kGroup - 1) / kGroup);
     if (node0) chains(0, t, lane, kWave, 1);
     wave_lds_sync();
 }
@@ -456,95 +521,137 @@ __device__ __forceinline__ double rsqrt_pos(double x) {
     return fma(y0 * e, fma(e, 0.375, 0.5), y0);
 }
 
-// Force of Eqs. A.1 + A.3 + A.4 from the grouped table e8 (one node):
-// slots below NGR carry the Eq. A.3 term, the J2 bodies (found by slot)
-// the Eq. A.4 term.  NB = 0 takes the counts at run time.
-template <int NB, int NGR>
-__device__ __forceinline__ void accel8(const double* __restrict__ e8, const EphemArgs& E, const double X[3],
-                                       const double V[3], double F[3]) {
-    const int nb = NB > 0 ? NB : E.n_body;
-    const int ngr = NB > 0 ? NGR : E.n_gr;
-    double ax = 0.0, ay = 0.0, az = 0.0;
+// Adds to a[] the terms of M slots, pb + m step: Eq. A.1, with GR Eq. A.3
+// (nothing for slots whose GM/c^2 is zero), and for the first MJ of them
+// Eq. A.4 with the constants jc + 4 m jstep (see j2_add; its part along r
+// joins the coefficient of r).  The M slots advance side by side: a slot's
+// chain (offset, inverse distance, coefficient) is some 20 dependent
+// operations, and one after another they left a lone wavefront waiting.
+template <int M, bool GR, int MJ = 0>
+__device__ __forceinline__ void force_terms(const double* __restrict__ pb, int step, const double* __restrict__ jc,
+                                            int jstep, const double X[3], const double V[3], double a[3]) {
+    static_assert(MJ <= M, "J2 slots are among the slots");
+    double r[M][3], gm[M], ir[M], ir3[M], f[M], w[M][3], kg[M];
 #pragma unroll
-    for (int b = 0; b < (NB > 0 ? NGR : KETE_MAX_BODIES); ++b) {
-        if (NB == 0 && b >= ngr) break;
-        const double* pb = e8 + kSlot * b;
-        const double2 pxy = *reinterpret_cast<const double2*>(pb);
-        const double2 pzg = *reinterpret_cast<const double2*>(pb + 2);
-        const double2 vxy = *reinterpret_cast<const double2*>(pb + 4);
-        const double2 vzk = *reinterpret_cast<const double2*>(pb + 6);
-        const double rx = X[0] - pxy.x, ry = X[1] - pxy.y, rz = X[2] - pzg.x;
-        const double r2 = fma(rx, rx, fma(ry, ry, rz * rz));
-        const double ir = rsqrt_pos(r2);
-        const double ir3 = ir * ir * ir;
-        const double gm = pzg.y;
-        const double wx = V[0] - vxy.x, wy = V[1] - vxy.y, wz = V[2] - vzk.x;
-        const double w2 = fma(wx, wx, fma(wy, wy, wz * wz));
-        const double rw = fma(rx, wx, fma(ry, wy, rz * wz));
-        const double g = vzk.y * ir3;
-        const double f = fma(g, 4.0 * gm * ir - w2, -gm * ir3);
-        const double q = 4.0 * g * rw;
-        ax = fma(q, wx, ax); ay = fma(q, wy, ay); az = fma(q, wz, az);
-        ax = fma(f, rx, ax); ay = fma(f, ry, ay); az = fma(f, rz, az);
+    for (int m = 0; m < M; ++m) {
+        const double2 xy = *reinterpret_cast<const double2*>(pb + m * step);
+        const double2 zg = *reinterpret_cast<const double2*>(pb + m * step + 2);
+        r[m][0] = X[0] - xy.x; r[m][1] = X[1] - xy.y; r[m][2] = X[2] - zg.x;
+        gm[m] = zg.y;
+        if constexpr (GR) {
+            const double2 vxy = *reinterpret_cast<const double2*>(pb + m * step + 4);
+            const double2 vzk = *reinterpret_cast<const double2*>(pb + m * step + 6);
+            w[m][0] = V[0] - vxy.x; w[m][1] = V[1] - vxy.y; w[m][2] = V[2] - vzk.x;
+            kg[m] = vzk.y;
+        }
     }
 #pragma unroll
-    for (int b = (NB > 0 ? NGR : 0); b < (NB > 0 ? NB : KETE_MAX_BODIES); ++b) {
-        if (NB == 0 && b >= nb - ngr) break;
-        const double* pb = e8 + kSlot * (NB > 0 ? b : b + ngr);
-        const double2 pxy = *reinterpret_cast<const double2*>(pb);
-        const double2 pzg = *reinterpret_cast<const double2*>(pb + 2);
-        const double rx = X[0] - pxy.x, ry = X[1] - pxy.y, rz = X[2] - pzg.x;
-        const double r2 = fma(rx, rx, fma(ry, ry, rz * rz));
-        const double ir = rsqrt_pos(r2);
-        const double f = -pzg.y * (ir * ir * ir);
-        ax = fma(f, rx, ax); ay = fma(f, ry, ay); az = fma(f, rz, az);
+    for (int m = 0; m < M; ++m) ir[m] = rsqrt_pos(fma(r[m][0], r[m][0], fma(r[m][1], r[m][1], r[m][2] * r[m][2])));
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        ir3[m] = ir[m] * ir[m] * ir[m];
+        f[m] = -gm[m] * ir3[m];
     }
-    F[0] = ax; F[1] = ay; F[2] = az;
-    for (int q = 0; q < E.n_j2; ++q) {
-        const double* pb = e8 + kSlot * E.j2_slot[q];
-        const double d[3] = {X[0] - pb[0], X[1] - pb[1], X[2] - pb[2]};
-        j2_add(E, q, d, rsqrt_pos(fma(d[0], d[0], fma(d[1], d[1], d[2] * d[2]))), F);
+    if constexpr (GR) {
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            const double w2 = fma(w[m][0], w[m][0], fma(w[m][1], w[m][1], w[m][2] * w[m][2]));
+            const double rw = fma(r[m][0], w[m][0], fma(r[m][1], w[m][1], r[m][2] * w[m][2]));
+            const double g = kg[m] * ir3[m];
+            f[m] = fma(g, 4.0 * gm[m] * ir[m] - w2, f[m]);
+            const double q = 4.0 * g * rw;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) a[c] = fma(q, w[m][c], a[c]);
+        }
     }
+#pragma unroll
+    for (int m = 0; m < MJ; ++m) {
+        const double2 kp = *reinterpret_cast<const double2*>(jc + 4 * m * jstep);
+        const double2 pq = *reinterpret_cast<const double2*>(jc + 4 * m * jstep + 2);
+        const double p[3] = {kp.y, pq.x, pq.y};
+        const double ir2 = ir[m] * ir[m];
+        const double s = -kp.x * (ir3[m] * ir2);
+        const double z = fma(r[m][0], p[0], fma(r[m][1], p[1], r[m][2] * p[2]));
+        f[m] = fma(s, fma(-5.0 * z * ir2, z, 1.0), f[m]);
+        const double e = 2.0 * s * z;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) a[c] = fma(e, p[c], a[c]);
+    }
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) a[c] = fma(f[m], r[m][c], a[c]);
 }
 
-// The same force computed by a group together: node lane gl < 7 takes
-// slots gl, gl + 7, ...; the partial sums meet in the group's exchange
-// rows xg and every lane adds them in the same order, so all lanes of the
-// group return the same total.  The whole wavefront takes part.
-__device__ __forceinline__ void accel8_group(const double* __restrict__ e8, const EphemArgs& E, const double X[3],
-                                             const double V[3], int gl, double* __restrict__ xg, double F[3]) {
-    double ax = 0.0, ay = 0.0, az = 0.0;
-    for (int sl = gl; gl < 7 && sl < E.n_body; sl += 7) {
-        const double* pb = e8 + kSlot * sl;
-        const double2 pxy = *reinterpret_cast<const double2*>(pb);
-        const double2 pzg = *reinterpret_cast<const double2*>(pb + 2);
-        const double rx = X[0] - pxy.x, ry = X[1] - pxy.y, rz = X[2] - pzg.x;
-        const double r2 = fma(rx, rx, fma(ry, ry, rz * rz));
-        const double ir = rsqrt_pos(r2);
-        const double ir3 = ir * ir * ir;
-        const double gm = pzg.y;
-        double f = -gm * ir3;
-        if (sl < E.n_gr) {
-            const double2 vxy = *reinterpret_cast<const double2*>(pb + 4);
-            const double2 vzk = *reinterpret_cast<const double2*>(pb + 6);
-            const double wx = V[0] - vxy.x, wy = V[1] - vxy.y, wz = V[2] - vzk.x;
-            const double w2 = fma(wx, wx, fma(wy, wy, wz * wz));
-            const double rw = fma(rx, wx, fma(ry, wy, rz * wz));
-            const double g = vzk.y * ir3;
-            f = fma(g, 4.0 * gm * ir - w2, f);
-            const double q = 4.0 * g * rw;
-            ax = fma(q, wx, ax); ay = fma(q, wy, ay); az = fma(q, wz, az);
+// Eq. A.4 of the J2 bodies outside the first slots (none in the default
+// model), from the table row.
+__device__ __forceinline__ void j2_extra(const EphemArgs& E, const double* __restrict__ row, int q, const double X[3],
+                                         double a[3]) {
+    const double* pb = row + kSlot * E.j2_slot[q];
+    const double d[3] = {X[0] - pb[0], X[1] - pb[1], X[2] - pb[2]};
+    j2_add(E.j2k[q], E.j2p[q], d, rsqrt_pos(fma(d[0], d[0], fma(d[1], d[1], d[2] * d[2]))), a);
+}
+
+// Force of Eqs. A.1 + A.3 + A.4 at one node from its table row: with L = 1
+// lane per node every slot; else lane sub takes slots sub, sub + L, ... (the
+// same kind of round in every lane: slots with the Eq. A.3 term come first,
+// those with the Eq. A.4 term first among them) and the lanes' sums are
+// added.  NB = 0 takes the counts at run time.
+template <int NB, int NGR, int NJ2, int L>
+__device__ __forceinline__ void accel8(const double* __restrict__ row, const G8Lds& T, const EphemArgs& E, int sub,
+                                       const double X[3], const double V[3], double F[3]) {
+    F[0] = F[1] = F[2] = 0.0;
+    const double* pb = row + kSlot * sub;
+    const double* jc = T.j2 + 4 * sub;
+    if constexpr (NB > 0) {
+        constexpr int kRounds = (NB + L - 1) / L, kGr = (NGR + L - 1) / L, kJ = (NJ2 + L - 1) / L;
+        constexpr int kPlain = kRounds - kGr;
+        if constexpr (kGr > 0) force_terms<kGr, true, kJ>(pb, kSlot * L, jc, L, X, V, F);
+        constexpr int kHalf = kPlain > 4 ? (kPlain + 1) / 2 : kPlain;
+        if constexpr (kHalf > 0) force_terms<kHalf, false>(pb + kSlot * L * kGr, kSlot * L, jc, 0, X, V, F);
+        if constexpr (kPlain > kHalf)
+            force_terms<kPlain - kHalf, false>(pb + kSlot * L * (kGr + kHalf), kSlot * L, jc, 0, X, V, F);
+    } else {
+        const int rounds = g8_slots(E.n_body, E.n_gr, L) / L, gr = (E.n_gr + L - 1) / L, nj = (E.n_j2g + L - 1) / L;
+        int k = 0;
+        for (; k < nj; ++k) force_terms<1, true, 1>(pb + kSlot * L * k, 0, jc + 4 * L * k, 0, X, V, F);
+        for (; k + 1 < gr; k += 2) force_terms<2, true>(pb + kSlot * L * k, kSlot * L, jc, 0, X, V, F);
+        for (; k < gr; ++k) force_terms<1, true>(pb + kSlot * L * k, 0, jc, 0, X, V, F);
+        for (; k + 3 < rounds; k += 4) force_terms<4, false>(pb + kSlot * L * k, kSlot * L, jc, 0, X, V, F);
+        for (; k < rounds; ++k) force_terms<1, false>(pb + kSlot * L * k, 0, jc, 0, X, V, F);
+        if (sub == 0)
+            for (int q = E.n_j2g; q < E.n_j2; ++q) j2_extra(E, row, q, X, F);
+    }
+    node_sum<L>(F);
+}
+
+// The same force computed by a group together: its lanes take slots gl L +
+// sub, ... (lanes with gl = 7 none); the partial sums meet in the group's
+// exchange rows and every lane adds them in the same order, so all lanes of
+// the group return the same total.  The whole wavefront takes part.
+template <int L>
+__device__ __forceinline__ void accel8_group(const double* __restrict__ row, const G8Lds& T, const EphemArgs& E,
+                                             const double X[3], const double V[3], int gl, int sub, double F[3]) {
+    double part[3] = {0.0, 0.0, 0.0};
+    const int lane_slot = gl * L + sub;
+    for (int s0 = 0; s0 < E.n_body; s0 += 7 * L) {
+        const int sl = s0 + lane_slot;
+        if (gl < 7 && sl < E.n_body) {
+            if (s0 < E.n_gr) force_terms<1, true>(row + kSlot * sl, 0, T.j2, 0, X, V, part);
+            else force_terms<1, false>(row + kSlot * sl, 0, T.j2, 0, X, V, part);
         }
-        ax = fma(f, rx, ax); ay = fma(f, ry, ay); az = fma(f, rz, az);
     }
-    double part[3] = {ax, ay, az};
-    if (gl < E.n_j2) {                         // node lane q takes J2 body q
-        const double* pb = e8 + kSlot * E.j2_slot[gl];
+    if (lane_slot < E.n_j2 && gl < 7) {        // J2 body q by lane q of the group
+        const bool first = lane_slot < E.n_j2g;
+        const double* pb = row + kSlot * (first ? lane_slot : (int)((E.j2_slots >> (4 * lane_slot)) & 15u));
+        const double* jc = T.j2 + 4 * (first ? lane_slot : 8 + lane_slot);
         const double d[3] = {X[0] - pb[0], X[1] - pb[1], X[2] - pb[2]};
-        j2_add(E, gl, d, rsqrt_pos(fma(d[0], d[0], fma(d[1], d[1], d[2] * d[2]))), part);
+        const double id = rsqrt_pos(fma(d[0], d[0], fma(d[1], d[1], d[2] * d[2])));
+        j2_add(jc[0], jc + 1, d, id, part);
     }
+    node_sum<L>(part);
     double D[7][3];
-    g8_exchange(xg, gl, part, D);
+    g8_exchange(T.xg, gl, part, D);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         double f = D[0][c];
@@ -639,21 +746,16 @@ __device__ __forceinline__ double step_factor(double q) {
 // increments (values Dp at its nodes, 0 at its start) evaluated at the new
 // node's time sig = 1 + q s_n of the old step, less its value at sig = 1.
 // The Lagrange basis of the 8 nodes is formed from prefix and suffix
-// products of (sig - s_k).  With RELOAD the constants are read through an
-// opaque zero offset, so they are loaded here rather than kept in scalar
-// registers across the step loop.
-template <bool RELOAD>
-__device__ __forceinline__ void extrapolate_increment(const RadauConst& rc, double* __restrict__ xg, int gl,
-                                                      const NodeRow& R, const double Dp[3], double q, double dn[3]) {
-    int z = 0;
-    if constexpr (RELOAD) asm volatile("s_mov_b32 %0, 0" : "=s"(z));
+// products of (sig - s_k).
+__device__ __forceinline__ void extrapolate_increment(const GroupConst& K, double* __restrict__ xg, int gl,
+                                                      const double Dp[3], double q, double dn[3]) {
     double D[7][3];
     g8_exchange(xg, gl, Dp, D);
-    const double sig = fma(q, R.s, 1.0);
+    const double sig = fma(q, K.row[gl].s, 1.0);
     double dk[8], pre[8];
     dk[0] = sig;
 #pragma unroll
-    for (int k = 1; k < 8; ++k) dk[k] = sig - rc.s[k + z];
+    for (int k = 1; k < 8; ++k) dk[k] = sig - K.s[k];
     pre[0] = 1.0;
 #pragma unroll
     for (int k = 1; k < 8; ++k) pre[k] = pre[k - 1] * dk[k - 1];
@@ -661,44 +763,47 @@ __device__ __forceinline__ void extrapolate_increment(const RadauConst& rc, doub
     dn[0] = dn[1] = dn[2] = 0.0;
 #pragma unroll
     for (int m = 7; m >= 1; --m) {
-        const double w = fma(pre[m] * suf, rc.Lden[m - 1 + z], -rc.L1[m - 1 + z]);
+        const double w = fma(pre[m] * suf, K.Lden[m - 1], -K.L1[m - 1]);
 #pragma unroll
         for (int c = 0; c < 3; ++c) dn[c] = fma(w, D[m - 1][c], dn[c]);
         suf *= dk[m];
     }
 }
 
-// Corrector for a body spread over an 8-lane group (see above), with the
-// same stopping rule as corrector().  Each lane keeps only its own node's
-// increment dn; the other nodes' increments are read from the group's
-// lanes when the predictor sums and b6 are formed.  With q > 0 the
-// iteration starts from the previous step's increments Dp extrapolated
-// (extrapolate_increment), otherwise from zero.  On return dn holds the
-// converged increment of this lane's node, b6 the highest coefficient and
-// d6 the increment of node 7 (all lanes).
-template <int NB, int NGR, int G, bool RELOAD = true>
-__device__ __forceinline__ int corrector_g8(const RadauConst& rc, const EphemArgs& E, const double* __restrict__ e8,
-                                            double* __restrict__ xg, int gl, const NodeRow& R, int node,
-                                            const double x0[3], const double v0[3],
+// Corrector of the lane groups (see above).  Each lane keeps only its own
+// node's increment dn; the other nodes' increments are read from the group's
+// lanes when the predictor sums and b6 are formed.  With q > 0 the iteration
+// starts from the previous step's increments Dp extrapolated
+// (extrapolate_increment), otherwise from zero.  A body is done when the
+// change of its b6 relative to |a| is below 1e-16, or has stopped decreasing
+// after the third sweep (corrector()'s rule, body by body); the wavefront
+// sweeps until all of its bodies are, which a vote tells without a reduction
+// over the lanes.  On return dn holds the converged increment of this lane's
+// node, b6 the highest coefficient and d6 the increment of node 7 (all
+// lanes).
+template <int NB, int NGR, int NJ2, int L>
+__device__ __forceinline__ int corrector_g8(const RadauConst& rc, const GroupConst& K, const EphemArgs& E,
+                                            const G8Lds& T, int gl, int sub, const double x0[3], const double v0[3],
                                             const double F0[3], double h, bool active, int max_iter, double dn[3],
-                                            double b6[3], double d6[3], const double* Dp = nullptr,
-                                            double q = 0.0) {
+                                            double b6[3], double d6[3], const double Dp[3], double q) {
+    const NodeRow& R = K.row[gl];
     const double hh = h * h, sh = R.s * h;
-    const double* en = e8 + node * g8_row(E.n_body);
+    const double* en = T.e8 + (gl < 7 ? gl + 1 : 7) * T.row;
     const bool started = q > 0.0;           // wave-uniform
-    if (started) extrapolate_increment<RELOAD>(rc, xg, gl, R, Dp, q, dn);
+    if (started) extrapolate_increment(K, T.xg, gl, Dp, q, dn);
     else dn[0] = dn[1] = dn[2] = 0.0;
     b6[0] = b6[1] = b6[2] = 0.0;
     d6[0] = d6[1] = d6[2] = 0.0;
-    double pc = 1e300;
+    double last = 1e300;
+    bool done = !active;
     int it = 0;
     for (;;) {
-        double ax[3], av[3], bb[3];
+        double ax[3], av[3];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) { ax[c] = R.hs2 * F0[c]; av[c] = R.s * F0[c]; bb[c] = 0.0; }
+        for (int c = 0; c < 3; ++c) { ax[c] = R.hs2 * F0[c]; av[c] = R.s * F0[c]; }
         if (it > 0 || started) {
-            double D[7][3];
-            g8_exchange(xg, gl, dn, D);
+            double D[7][3], bb[3] = {0.0, 0.0, 0.0};
+            g8_exchange(T.xg, gl, dn, D);
 #pragma unroll
             for (int m = 0; m < 7; ++m) {
 #pragma unroll
@@ -710,7 +815,6 @@ __device__ __forceinline__ int corrector_g8(const RadauConst& rc, const EphemArg
                     if (m == 6) d6[c] = d;
                 }
             }
-            const double pcl = pc;
             double db = 0.0, fm = 0.0;
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
@@ -718,10 +822,14 @@ __device__ __forceinline__ int corrector_g8(const RadauConst& rc, const EphemArg
                 b6[c] = bb[c];
                 fm = fmax(fm, fabs(d6[c] + F0[c]));
             }
-            // the ratio only steers the stopping rule: the reciprocal estimate suffices
-            const double lpc = (active && fm > 0.0) ? db * __builtin_amdgcn_rcp(fm) : 0.0;
-            pc = groups_max<G>(lpc);
-            if (it > 0 && (pc < 1e-16 || (it > 2 && pcl <= pc) || it >= max_iter)) break;
+            // the ratio only steers the stopping rule: the reciprocal estimate
+            // suffices (a body whose ratio is not a number holds no one up)
+            const double pc = fm > 0.0 ? db * __builtin_amdgcn_rcp(fm) : 0.0;
+            if (it > 0) {
+                done = done || !(pc >= 1e-16) || (it > 2 && last <= pc);
+                if (__ballot(!done) == 0ull || it >= max_iter) break;
+            }
+            last = pc;
         }
         ++it;
         double X[3], V[3];
@@ -734,7 +842,7 @@ __device__ __forceinline__ int corrector_g8(const RadauConst& rc, const EphemArg
             V[0] = v0[0]; V[1] = v0[1]; V[2] = v0[2];
         }
         double F[3];
-        accel8<NB, NGR>(en, E, X, V, F);
+        accel8<NB, NGR, NJ2, L>(en, T, E, sub, X, V, F);
 #pragma unroll
         for (int c = 0; c < 3; ++c) dn[c] = F[c] - F0[c];
     }
@@ -742,24 +850,20 @@ __device__ __forceinline__ int corrector_g8(const RadauConst& rc, const EphemArg
 }
 
 // Step end of a group-integrated body from the converged increments.
-__device__ __forceinline__ void step_end_g8(const RadauConst& rc, double* __restrict__ xg, int gl, const double dn[3],
+__device__ __forceinline__ void step_end_g8(const GroupConst& K, double* __restrict__ xg, int gl, const double dn[3],
                                             double h, double x0[3], double v0[3], const double F0[3]) {
     double ax[3], av[3];
     double D[7][3];
     g8_exchange(xg, gl, dn, D);
-    // opaque zero row offset: the constants are loaded where used instead
-    // of being held in (spilled) scalar registers for the whole kernel
-    int z;
-    asm volatile("s_mov_b32 %0, 0" : "=s"(z));
 #pragma unroll
-    for (int c = 0; c < 3; ++c) { ax[c] = rc.half_s2[8 + z] * F0[c]; av[c] = F0[c]; }
+    for (int c = 0; c < 3; ++c) { ax[c] = K.A8[7] * F0[c]; av[c] = F0[c]; }
 #pragma unroll
     for (int m = 0; m < 7; ++m) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             const double d = D[m][c];
-            ax[c] = fma(rc.A[8 + z][m], d, ax[c]);
-            av[c] = fma(rc.B[8 + z][m], d, av[c]);
+            ax[c] = fma(K.A8[m], d, ax[c]);
+            av[c] = fma(K.B8[m], d, av[c]);
         }
     }
     const double hh = h * h;
@@ -770,7 +874,7 @@ __device__ __forceinline__ void step_end_g8(const RadauConst& rc, double* __rest
     }
 }
 
-// Stepping state of a group-integrated body (replicated in its 8 lanes).
+// Stepping state of a group-integrated body (replicated in its lanes).
 struct G8State {
     double x0[3], v0[3], F0[3];
     double Dp[3] = {0.0, 0.0, 0.0};   // this lane's increment in the last accepted step
@@ -788,31 +892,27 @@ struct G8Count {
 // corrector starts from the extrapolated increments.
 constexpr double kPredMaxRatio = 3.0;
 
-// Corrector start of g8_integrate: always from zero, or extrapolated from
-// the previous step (constants reloaded at each use, or held in registers
-// where the kernel has room).
-enum G8Start { kStartZero = 0, kStartExtrapolate = 1, kStartExtrapolateHeld = 2 };
-
-// Integrate [S.t, tb] with wave-shared adaptive steps (the bodies of the
-// wavefront take the smallest step any of them asks for).
 struct G8NoVisit {
     template <class... A>
     __device__ __forceinline__ void operator()(A&&...) const {}
 };
 
+// Integrate [S.t, tb] with wave-shared adaptive steps (the bodies of the
+// wavefront take the smallest step any of them asks for).  Correctors start
+// from the previous step extrapolated unless p.zero_start.
 // visit(ts, h, dn, S) is called by every lane after each accepted step,
-// before S moves to the step end (dn: this lane's converged increment,
-// e8: the step's perturber table).  With need_node0 the table also holds
-// node 0 (the step start) on every step.
-template <int NB, int NGR, int DEG1, int G, int START = kStartZero, class Params, class Visit = G8NoVisit>
-__device__ __forceinline__ void g8_integrate(const Params& p, const NodeRow& R, int node, int gl, int grp, int lane,
-                                             double* __restrict__ e8, double tb, G8State& S, G8Count& C,
+// before S moves to the step end (dn: this lane's converged increment, T.e8:
+// the step's perturber table).  With need_node0 the table also holds node 0
+// (the step start) on every step.
+template <int NB, int NGR, int NJ2, int DEG1, int G, class Params, class Visit = G8NoVisit>
+__device__ __forceinline__ void g8_integrate(const Params& p, const GroupConst& K, const G8Lds& T,
+                                             const GroupMap<G>& M, int lane, double tb, G8State& S, G8Count& C,
                                              Visit&& visit = Visit(), bool need_node0 = false,
                                              double t_stop = kInf) {
+    constexpr int L = GroupMap<G>::kLanes;
     const EphemArgs& E = p.eph;
     const RadauConst& rc = p.rc;
-    const int nb = E.n_body;
-    double* xg = g8_xch(e8, nb, grp);
+    const int nb = E.n_body, gl = M.gl, sub = M.sub;
     if (__ballot(S.active) == 0ull) { S.t = tb; return; }
     while (S.t != tb) {
         if (S.t >= t_stop) return;          // a recompute ends where the recorded run took its checkpoint
@@ -831,31 +931,30 @@ __device__ __forceinline__ void g8_integrate(const Params& p, const NodeRow& R, 
         // node 0 is evaluated before the first step; with need_node0 it is
         // afterwards the previous step's end row, copied when that step is accepted
         const int n0 = (S.haveF0 && (!need_node0 || S.row0)) ? 1 : 0;
-        node_ephemeris8<NB, NGR, DEG1>(E, rc, S.t, h, t_end, n0 == 0, lane, e8);
+        node_ephemeris8<NB, NGR, DEG1>(E, K, T, S.t, h, t_end, n0 == 0, lane);
         S.row0 = true;
         C.chain += (kNodes - n0) * E.n_gr * 3;
         C.vchain += (kNodes - n0) * (nb - E.n_gr) * 3;
-        if (!S.haveF0) { accel8<NB, NGR>(e8, E, S.x0, S.v0, S.F0); S.haveF0 = true; }
+        if (!S.haveF0) { accel8_group<L>(T.e8, T, E, S.x0, S.v0, gl, sub, S.F0); S.haveF0 = true; }
 
         double q = 0.0;                       // wave-uniform, like h and S.hprev
-        if constexpr (START != kStartZero) {
-            if (!p.zero_start && S.hprev != 0.0) q = h / S.hprev;
-            if (!(q <= kPredMaxRatio)) q = 0.0;
-        }
+        if (!p.zero_start && S.hprev != 0.0) q = h / S.hprev;
+        if (!(q <= kPredMaxRatio)) q = 0.0;
         double dn[3], b6p[3], d6[3];
-        const int it = corrector_g8<NB, NGR, G, START != kStartExtrapolateHeld>(rc, E, e8, xg, gl, R, node, S.x0, S.v0,
-                                                                                S.F0, h, S.active, p.max_iter, dn, b6p,
-                                                                                d6, S.Dp, q);
+        const int it = corrector_g8<NB, NGR, NJ2, L>(rc, K, E, T, gl, sub, S.x0, S.v0, S.F0, h, S.active, p.max_iter,
+                                                     dn, b6p, d6, S.Dp, q);
         C.iter += it;
-        const unsigned long long n_act = __popcll(__ballot(S.active && gl == 0));
+        const unsigned long long n_act = __popcll(__ballot(S.active && gl == 0 && sub == 0));
         C.liter += (unsigned long long)it * n_act;
         if (q > 0.0) C.lpred += n_act;
 
         double fm = 0.0, bm = 0.0;
 #pragma unroll
         for (int c = 0; c < 3; ++c) { fm = fmax(fm, fabs(d6[c] + S.F0[c])); bm = fmax(bm, fabs(b6p[c])); }
-        const double ebl = fm > 0.0 ? bm / fm : 0.0;
-        double hl = (ebl > 0.0 && ebl < kInf) ? fabs(h) * step_factor(p.eps / ebl) : fabs(h) / p.safety;
+        // (the reciprocal estimate suffices: the factor only sets the next step)
+        double hl = (bm > 0.0 && fm > 0.0 && bm < kInf && fm < kInf)
+                        ? fabs(h) * step_factor(p.eps * fm * __builtin_amdgcn_rcp(bm))
+                        : fabs(h) / p.safety;
         if (!S.active) hl = kInf;
         if (S.active && hl < p.h_min) { S.status = KETE_ST_STEP_UNDERFLOW; S.active = false; hl = kInf; }
         const double hn = groups_min<G>(hl);
@@ -866,12 +965,10 @@ __device__ __forceinline__ void g8_integrate(const Params& p, const NodeRow& R, 
             continue;
         }
         visit(S.t, h, dn, S);
-        if constexpr (START != kStartZero) {
 #pragma unroll
-            for (int c = 0; c < 3; ++c) S.Dp[c] = dn[c];
-            S.hprev = h;
-        }
-        step_end_g8(rc, xg, gl, dn, h, S.x0, S.v0, S.F0);
+        for (int c = 0; c < 3; ++c) S.Dp[c] = dn[c];
+        S.hprev = h;
+        step_end_g8(K, T.xg, gl, dn, h, S.x0, S.v0, S.F0);
         S.t = t_end;
         ++C.steps;
         C.lsteps += n_act;
@@ -879,10 +976,10 @@ __device__ __forceinline__ void g8_integrate(const Params& p, const NodeRow& R, 
                           isfinite(S.v0[1]) && isfinite(S.v0[2]))) {
             S.status = KETE_ST_NONFINITE; S.active = false;
         }
-        accel8_group(e8 + 8 * g8_row(nb), E, S.x0, S.v0, gl, xg, S.F0);
+        accel8_group<L>(T.e8 + 8 * T.row, T, E, S.x0, S.v0, gl, sub, S.F0);
         if (need_node0) {
             wave_lds_sync();
-            for (int i = lane; i < g8_row(nb); i += kWave) e8[i] = e8[8 * g8_row(nb) + i];
+            for (int i = lane; i < T.row; i += kWave) T.e8[i] = T.e8[8 * T.row + i];
             wave_lds_sync();
         }
         if (landed) {
@@ -902,10 +999,10 @@ __device__ __forceinline__ double state_component(const double x0[3], const doub
 // Collocation polynomial at fraction sig of the step (sig = 1: step end),
 // from the monomial weights alpha_m(sig) = sum_k Ap[m][k] sig^(k+2) and
 // beta_m(sig) = sum_k Bp[m][k] sig^(k+1) (m = 1..7, k = 0..7), their rows
-// read from a copy in LDS (cw: Ap[7][8] then Bp[7][8]), and the step's node
+// read from a copy in LDS (K), and the step's node
 // increments from the group's exchange rows xg (component c of node m + 1 at
 // xg[8 c + m]), one node at a time; sig may differ between groups.
-__device__ __forceinline__ void dense_state_rows(const double* __restrict__ cw, const double* __restrict__ xg,
+__device__ __forceinline__ void dense_state_rows(const GroupConst& K, const double* __restrict__ xg,
                                                  const double x0[3], const double v0[3], const double F0[3],
                                                  double h, double sig, double X[3], double V[3]) {
     double ax[3], av[3];
@@ -913,8 +1010,8 @@ __device__ __forceinline__ void dense_state_rows(const double* __restrict__ cw, 
     for (int c = 0; c < 3; ++c) { ax[c] = 0.5 * sig * sig * F0[c]; av[c] = sig * F0[c]; }
 #pragma unroll 1
     for (int m = 0; m < 7; ++m) {
-        const double* am = cw + 8 * m;
-        const double* bm = cw + 56 + 8 * m;
+        const double* am = K.Ap[m];
+        const double* bm = K.Bp[m];
         double a = am[7], b = bm[7];
 #pragma unroll
         for (int k = 6; k >= 0; --k) { a = fma(a, sig, am[k]); b = fma(b, sig, bm[k]); }
@@ -935,10 +1032,10 @@ __device__ __forceinline__ void dense_state_rows(const double* __restrict__ cw, 
     }
 }
 
-// Dense output of a step for a wavefront's objects: epochs t_out[e_next ..
-// e_end - 1] that lie inside the step [ts, ts + h] are read off its
-// collocation polynomial and put(e, value) gets component gl (0..5) of each
-// object's state; e_next moves past them.  The step is the same for every
+// Dense output of a step for a wavefront's objects: the cursor's epochs that
+// lie inside the step [ts, ts + h] are read off its collocation polynomial
+// and put(e, value) gets component gl (0..5) of each object's state; the
+// cursor moves past them.  The step is the same for every
 // object, so its weights are too: the 16 lanes of a quarter of the wavefront
 // evaluate one epoch's (slots 0..6 alpha_m(sig) = sum_k Ap[m][k] sig^(k+2)
 // and 7 sig^2 / 2 of the force at the step start; 8..14 beta_m(sig) = sum_k
@@ -950,15 +1047,24 @@ __device__ __forceinline__ void dense_state_rows(const double* __restrict__ cw, 
 // instructions an epoch, a fifth of the integrator's with epochs 3 days apart.)
 constexpr int kDenseRound = 4;              // epochs per round
 constexpr int kDenseWeights = 16 * kDenseRound;
+// The cursor keeps the next four epochs' times in the lanes, read ahead.
+struct EpochCursor {
+    const double* t_out;
+    int next, end;          // wave-uniform
+    double tk;              // t_out[next + lane / 16] (of the last epoch past the end)
+    __device__ __forceinline__ void fetch(int lane) {
+        const int e = next + (lane >> 4);
+        if (next < end) tk = t_out[e < end ? e : end - 1];
+    }
+};
 template <class Put>
-__device__ __forceinline__ void dense_epochs(const double* __restrict__ cw, double* __restrict__ wt,
-                                             double* __restrict__ xg, int gl, int lane, double ts, double h,
-                                             const double dn[3], const double x0[3], const double v0[3],
-                                             const double F0[3], const double* __restrict__ t_out, int& e_next,
-                                             int e_end, Put&& put) {
-    if (e_next >= e_end) return;
+__device__ __forceinline__ void dense_epochs(const GroupConst& K, double* __restrict__ wt, double* __restrict__ xg,
+                                             int gl, int lane, double ts, double h, const double dn[3],
+                                             const double x0[3], const double v0[3], const double F0[3],
+                                             EpochCursor& ec, Put&& put) {
+    if (ec.next >= ec.end) return;
     const double te = ts + h;
-    const double t_first = t_out[e_next];
+    const double t_first = uniform(ec.tk);
     if (!(h > 0.0 ? t_first <= te : t_first >= te)) return;
     wave_lds_sync();                        // earlier reads of the exchange rows are done
     xg[gl] = dn[0];
@@ -980,12 +1086,13 @@ __device__ __forceinline__ void dense_epochs(const double* __restrict__ cw, doub
     D[7] = c == 0 ? F0[0] : c == 1 ? F0[1] : F0[2];
     const double hc = vel ? h : h * h;
     const int m = lane & 15;
-    const double* pm = cw + 8 * (m < 7 ? m : m < 15 ? m - 1 : 13);
+    const double* pm = &K.Ap[0][0] + 8 * (m < 7 ? m : m < 15 ? m - 1 : 13);
     for (;;) {
-        const int el = e_next + (lane >> 4);
-        const double tk = t_out[el < e_end ? el : e_end - 1];
-        const int n = __popcll(__ballot(el < e_end && (h > 0.0 ? tk <= te : tk >= te))) >> 4;
-        const double sig = (tk - ts) / h;
+        const int el = ec.next + (lane >> 4), e0 = ec.next;
+        const int n = __popcll(__ballot(el < ec.end && (h > 0.0 ? ec.tk <= te : ec.tk >= te))) >> 4;
+        const double sig = (ec.tk - ts) / h;
+        ec.next += n;
+        ec.fetch(lane);
         double w = pm[7];
 #pragma unroll
         for (int k = 6; k >= 0; --k) w = fma(w, sig, pm[k]);
@@ -1009,10 +1116,9 @@ __device__ __forceinline__ void dense_epochs(const double* __restrict__ cw, doub
             a = fma(q2.y, D[5], a);
             a = fma(q3.x, D[6], a);
             const double sg = wt[16 * k + 15];
-            put(e_next + k, vel ? fma(hc, a, vc) : fma(hc, a, fma(sg * h, vc, xc)));
+            put(e0 + k, vel ? fma(hc, a, vc) : fma(hc, a, fma(sg * h, vc, xc)));
         }
-        e_next += n;
-        if (n < kDenseRound || e_next >= e_end) break;
+        if (n < kDenseRound || ec.next >= ec.end) break;
     }
 }
 
