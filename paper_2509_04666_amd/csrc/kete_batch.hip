@@ -154,6 +154,8 @@ __global__ __launch_bounds__(64, 3) void k_batch_g8(const BatchParams p) {
                 g8_integrate<NB, NGR, NJ2, DEG1, G>(p, K, T, M, lane, Wn.t_b, S, C, dense_out);
                 S.t = Wn.t_b;
             }
+            // a wavefront whose objects have all failed ends its steps before their epochs
+            while (ec.next < ec.end) put(ec.next++, 0.0, false);
             put(e_end, state_component(S.x0, S.v0, gl < 6 ? gl : 5), S.active && S.status == 0);
             e = e_end + 1;
         }

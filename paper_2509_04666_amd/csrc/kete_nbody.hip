@@ -228,6 +228,8 @@ __global__ __launch_bounds__(256, 3) void k_nbody_g8(const NbodyParams p) {
         g8_integrate<NB, NGR, NJ2, DEG1, G>(p, K, T, M, lane, t_b, S, C, dense_out);
         if (out >= 0) put(out, state_component(S.x0, S.v0, gl < 6 ? gl : 5), S.active && S.status == 0);
     }
+    // a wavefront whose objects have all failed ends its steps before their epochs
+    while (ec.next < ec.end) put(ec.next++, 0.0, false);
     if (writer) p.state[6 * (size_t)j + gl] = state_component(S.x0, S.v0, gl);
     if (valid && gl == 0 && M.sub == 0) {
         if (S.hp_new < kInf) p.h_pref[j] = S.hp_new;

@@ -218,3 +218,24 @@ def test_batched_autotune_and_cache(torch_cuda, batched, tmp_path):
     assert hit2 and ms2 == ms
     for k in ("n_buckets", "persist_waves", "window_segs", "fov_block", "cell_chord"):
         assert getattr(best2, k) == getattr(best, k)
+
+
+def test_batched_failed_jobs_write_every_epoch(torch_cuda):
+    """Jobs whose objects all fail in the first step: NaN at every epoch away
+    from the start epoch, and the status."""
+    torch, api = torch_cuda
+    ephem, jobs = _jobs()
+    opts = api.default_opts(h_min=200.0)
+    runner = api.BatchRunner(api.DeviceEphemeris.from_synth(ephem), jobs, opts)
+    runner.x_out.fill_(0.0)
+    runner.run()
+    torch.cuda.synchronize()
+    x, status = runner.x_out.cpu().numpy(), runner.status.cpu().numpy()
+    for k, (x0, t0, _) in enumerate(jobs):
+        ep = runner.job_epochs[k]
+        n, off = x0.shape[0], runner.jobs_host[k].xout_off
+        xk = x[off:off + 6 * n * ep.size].reshape(ep.size, n, 6)
+        away = ep != t0
+        assert np.all(np.isnan(xk[away])), k
+        if away.any():
+            assert np.all(status[runner.obj_off[k]:runner.obj_off[k + 1]] == 2), k

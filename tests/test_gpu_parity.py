@@ -402,6 +402,26 @@ def test_propagate_status_codes(torch_cuda, orc):
     assert np.all(s3.cpu().numpy() == 2)
 
 
+@pytest.mark.parametrize("n", [1, 8, 9, 200])
+@pytest.mark.parametrize("lanes", [0, 1, 7, 8])
+def test_propagate_all_objects_of_a_wavefront_fail(torch_cuda, n, lanes):
+    """Every epoch after the failure is NaN, also those that the integrator
+    would have passed inside a step, where no object of a wavefront is left."""
+    torch, api = torch_cuda
+    case = synth.survey_case(n_obj=n, n_frames=0)
+    eph = api.DeviceEphemeris.from_synth(case.ephem)
+    epochs = [0.0, 2.0, 5.0, 9.0, 40.0]
+    opts = api.default_opts(lanes_per_body=lanes) if lanes else api.default_opts()
+    x, s = api.propagate(eph, _dev_x(torch, case.x0), 0.0, epochs, opts)
+    assert np.all(s.cpu().numpy() == 0) and np.all(np.isfinite(x.cpu().numpy()))
+    del x, s                        # the next outputs take the same memory
+    opts.h_min = 200.0
+    x, s = api.propagate(eph, _dev_x(torch, case.x0), 0.0, epochs, opts)
+    x = x.cpu().numpy()
+    assert np.all(s.cpu().numpy() == 2)
+    assert np.array_equal(x[0], case.x0) and np.all(np.isnan(x[1:]))
+
+
 # ---------------------------------------------------------------- FoV
 def _pair_set(pf, ps, po):
     return set(zip(np.asarray(pf).tolist(), np.asarray(ps).tolist(), np.asarray(po).tolist()))
