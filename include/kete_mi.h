@@ -107,7 +107,9 @@ typedef struct {
     int32_t fov_block;       /* FoV threads per block: 64/128/256 (128) */
     int32_t adj_seg_steps;   /* adjoint: steps stored per checkpoint segment (32) */
     int32_t persist_waves;   /* batched runs: resident waves per compute unit (8) */
-    int32_t lanes_per_body;  /* integrator lanes per object: 1, 7 (9 per wavefront) or 8 (7) */
+    int32_t lanes_per_body;  /* integrator lanes per object: 1, 8 (8 objects a wavefront), or 7: 9 objects
+                                a wavefront, and for short lists and the objects of most steps
+                                4 or one (7) */
     int32_t zero_start;      /* 1: every corrector starts from zero increments, as in App. A.6;
                                 0: grouped integrators start from the previous step's
                                 collocation polynomial extrapolated (0) */
@@ -212,7 +214,9 @@ size_t kete_propagate_workspace_size(int64_t n_obj, int64_t n_out, const kete_op
  * Integrator: Gauss-Radau collocation with 8 nodes (the method of
  * App. A.6, predictor removed), IAS15 step control.  By default 7 lanes
  * share an object's force sums and the 9 objects of a wavefront share its
- * step size (objects are grouped by a predicted step size); states at
+ * step size (objects are grouped by a predicted step size); in short lists
+ * 14 lanes or all 56 do, and the objects of most steps have a wavefront of
+ * their own; states at
  * epochs inside a step are read off the step's collocation polynomial and
  * only the last epoch of a launch is landed on (opts lanes_per_body,
  * land_epochs).

@@ -198,7 +198,7 @@ __device__ __forceinline__ void save_ckpt_g8(const AdjParams& p, int c, int j, i
     const double v = gl < 6 ? state_component(S.x0, S.v0, gl)
                             : gl == 6 ? S.hw : (S.active ? 0.0 : (double)(S.status ? S.status : 1));
     ck[gl] = v;
-    const double f = gl == 0 ? S.F0[0] : gl == 1 ? S.F0[1] : gl == 2 ? S.F0[2] : (S.haveF0 ? 1.0 : 0.0);
+    const double f = gl < 3 ? vector_component(S.F0, gl) : (S.haveF0 ? 1.0 : 0.0);
     if (gl < 4) ck[8 + gl] = f;
     if (gl < 7) {
 #pragma unroll
@@ -231,8 +231,8 @@ __global__ __launch_bounds__(64, 3) void k_adjoint_fwd(const AdjParams p) {
     const EphemArgs& E = p.eph;
     __shared__ __align__(16) GroupConst gc;
     load_group_const(p.group_const, &gc, lane, kWave);
-    const G8Lds T = g8_lds<1>(E, smem, M.grp);
-    g8_table_init<1>(E, lane, smem);
+    const G8Lds T = g8_lds<kGroup>(E, smem, M.grp);
+    g8_table_init<kGroup>(E, lane, smem);
     __syncthreads();
     const long gi = ((long)blockIdx.x * 64 + lane) / kGroup;
     const bool valid = gi < p.n_obj;
@@ -246,11 +246,34 @@ __global__ __launch_bounds__(64, 3) void k_adjoint_fwd(const AdjParams p) {
     const int K = p.k_obs;
     int kobs = 0;
     const double* tob = p.t_obs + (size_t)j * K;
-    auto store_obs = [&](int k, const double X[3], const double V[3]) {
-        if (gl < 6) p.obs_state[((size_t)j * K + k) * 6 + gl] = state_component(X, V, gl);
+    // The group's lanes hold the times of eight observations, k_buf .. k_buf
+    // + 7, so that a step seldom loads: a load waits for the states stored
+    // before it.
+    int k_buf = 0;
+    double t_buf = 0.0;
+    auto load_times = [&]() {
+        k_buf = kobs;
+        t_buf = valid && kobs + gl < K ? tob[kobs + gl] : kInf;
+    };
+    auto next_time = [&]() { return __shfl(t_buf, kobs - k_buf, kGroup); };        // the whole group calls it
+    auto advance = [&]() {
+        if (++kobs - k_buf == kGroup) load_times();
+    };
+    load_times();
+    auto store_obs = [&](double v) {
+        if (gl < 6) p.obs_state[((size_t)j * K + kobs) * 6 + gl] = v;
     };
     // observations at the start epoch
-    if (valid) while (kobs < K && tob[kobs] <= S.t) { store_obs(kobs, S.x0, S.v0); ++kobs; }
+    for (;;) {
+        const bool at = valid && kobs < K && next_time() <= S.t;
+        if (__ballot(at) == 0ull) break;
+        const double v = state_component(S.x0, S.v0, gl < 6 ? gl : 5);
+        if (at) { store_obs(v); advance(); }
+    }
+    __shared__ __align__(16) double obs_wt[kGroup][16];
+    double* wt = obs_wt[M.grp];
+    const bool vel = gl >= 3;
+    const int comp = vel ? (gl < 6 ? gl - 3 : 2) : gl;
     // Checkpoint c (1 .. C - 1) is the state at the first accepted step
     // start at or after t0 + c ckpt_days (wave-uniform: the wavefront's
     // objects share their steps), so steps are not cut at checkpoints.
@@ -261,27 +284,19 @@ __global__ __launch_bounds__(64, 3) void k_adjoint_fwd(const AdjParams p) {
             ++c_next;
         }
         const double te = ts + h;
-        auto pending = [&]() {
-            return valid && St.active && kobs < K && (h > 0 ? tob[kobs] <= te : tob[kobs] >= te);
-        };
+        double tk = next_time();
+        auto pending = [&]() { return valid && St.active && kobs < K && (h > 0 ? tk <= te : tk >= te); };
         bool pend = pending();
         if (__ballot(pend) == 0ull) return;
-        // the step's node increments into the group's exchange rows
-        double* xg = T.xg;
-        wave_lds_sync();
-        xg[gl] = dn[0];
-        xg[8 + gl] = dn[1];
-        xg[16 + gl] = dn[2];
-        wave_lds_sync();
-        while (__ballot(pend) != 0ull) {
-            if (pend) {
-                double X[3], V[3];
-                dense_state_rows(gc, xg, St.x0, St.v0, St.F0, h, (tob[kobs] - ts) / h, X, V);
-                store_obs(kobs, X, V);
-                ++kobs;
-            }
+        double D[8];
+        dense_increments(T.xg, gl, comp, dn, St.F0, D);
+        const double xc = vector_component(St.x0, comp), vc = vector_component(St.v0, comp);
+        do {
+            const double v = dense_component8(gc, wt, gl, vel, pend ? (tk - ts) / h : 0.0, h, xc, vc, D);
+            if (pend) { store_obs(v); advance(); }
+            tk = next_time();
             pend = pending();
-        }
+        } while (__ballot(pend) != 0ull);
     };
     if (valid) save_ckpt_g8(p, 0, j, gl, S, S.t);
     // (windows, if asked for, end on the fixed grid of aligned_end, so a
@@ -411,8 +426,8 @@ __global__ __launch_bounds__(64, 2) void k_adj_recompute(const AdjParams p, cons
     }
     __shared__ __align__(16) GroupConst gc;
     load_group_const(p.group_const, &gc, lane, kWave);
-    const G8Lds T = g8_lds<1>(E, smem, M.grp);
-    g8_table_init<1>(E, lane, smem);
+    const G8Lds T = g8_lds<kGroup>(E, smem, M.grp);
+    g8_table_init<kGroup>(E, lane, smem);
     __syncthreads();
     const NodeRow& R = gc.row[gl];
     bool overflow_steps = false;
@@ -702,7 +717,7 @@ __global__ __launch_bounds__(64) void k_adj_sweep(const AdjParams p, const int c
 }  // namespace
 
 size_t adjoint_lds_bytes(const AdjParams& p) {
-    return (size_t)g8_wave_doubles(g8_slots(p.eph.n_body, p.eph.n_gr, 1)) * sizeof(double);
+    return (size_t)g8_wave_doubles<kGroup>(p.eph) * sizeof(double);
 }
 
 

@@ -24,7 +24,8 @@ namespace kete {
 hipError_t launch_hpref_init(const double* x0, double* h_pref, uint32_t* keys, int n, double mu, double dt_lo,
                              double dt_hi, int n_class, hipStream_t s);
 hipError_t launch_body_sort(const uint32_t* keys, int n, int n_class, int32_t* perm, int32_t* tmp, int32_t* counts,
-                            hipStream_t s);
+                            const int32_t** n_first, hipStream_t s);
+int solo_waves_for(int n, bool classes);
 hipError_t launch_iota(int32_t* perm, int n, hipStream_t s);
 size_t bucket_scratch_ints(int64_t n_obj, int n_buckets);
 }  // namespace kete
@@ -457,11 +458,11 @@ static int bucket_count(const kete_opts_t* o) {
     return oct > 1 ? oct * kBucketSub : 1;
 }
 
-// Step classes of the body sort (the critical class and kClassSub per
-// octave over opts->n_buckets octaves; 1: no sort).
+// Step classes of the body sort (the solo and the critical class and
+// kClassSub per octave over opts->n_buckets octaves; 1: no sort).
 static int sort_classes(const kete_opts_t* o) {
     const int oct = std::min(std::max(1, o->n_buckets), 32);
-    return oct > 1 ? 1 + kClassSub * oct : 1;
+    return oct > 1 ? 2 + kClassSub * oct : 1;
 }
 
 // Scratch of the body sort: counting-sort counts, then the keys and the
@@ -594,14 +595,10 @@ int kete_propagate_nbody(const kete_ephem_t* eph, const double* x0, double t0, i
         std::memcpy(host.data() + epoch_table_bytes(n_out), win.data(), win.size() * sizeof(Window));
         if ((rc = stage_to_device(plan, host.data(), host.size(), s))) return rc;
     }
-    HIPCHK(hipMemcpyAsync(state, x0, (size_t)n_obj * 6 * sizeof(double), hipMemcpyDeviceToDevice, s));
-    HIPCHK(fill_zero(status, (size_t)n_obj * sizeof(int32_t), s));
-
     NbodyParams P;
     std::memset(&P, 0, sizeof(P));
     P.eph = E;
     P.rc = radau_const();
-    P.state = state;
     P.h_pref = h_pref;
     P.status = status;
     P.x_out = x_out;
@@ -633,16 +630,22 @@ int kete_propagate_nbody(const kete_ephem_t* eph, const double* x0, double t0, i
             dt_lo = std::min(dt_lo, t_out[k] - ta);
             dt_hi = std::max(dt_hi, t_out[k] - ta);
         }
-        HIPCHK(launch_hpref_init(state, h_pref, ncls > 1 ? sorts.keys : nullptr, (int)n_obj, E.gm[0], dt_lo, dt_hi,
+        P.state_in = e0 == 0 ? x0 : state;
+        P.state = e1 + 1 < n_out ? state : nullptr;
+        HIPCHK(launch_hpref_init(P.state_in, h_pref, ncls > 1 ? sorts.keys : nullptr, (int)n_obj, E.gm[0], dt_lo, dt_hi,
                                  ncls, s));
         if (ncls > 1) {
-            HIPCHK(launch_body_sort(sorts.keys, (int)n_obj, ncls, perm, sorts.tmp, sorts.counts, s));
+            HIPCHK(launch_body_sort(sorts.keys, (int)n_obj, ncls, perm, sorts.tmp, sorts.counts, &P.n_solo, s));
             P.perm = perm;
         } else {
             P.perm = nullptr;
+            P.n_solo = nullptr;
         }
+        P.solo_waves = opts->lanes_per_body == 7 ? solo_waves_for((int)n_obj, ncls > 1) : 0;
+        if (P.solo_waves == n_obj || P.solo_waves == 0) P.n_solo = nullptr;
         P.win = dwin + first;
         P.t_begin = win[first].t_a;
+        P.t_only = win[last].t_b;
         P.n_win = last - first + 1;
         P.first_launch = (e0 == 0);
         {
@@ -1040,7 +1043,7 @@ int kete_propagate_adjoint(const kete_ephem_t* eph, int32_t mode, const double* 
         HIPCHK(launch_hpref_init(x0, h_pref, ncls > 1 ? sorts.keys : nullptr, (int)n_obj, E.gm[0], 0.0, t_end - t0,
                                  ncls, s));
         if (ncls > 1) {
-            HIPCHK(launch_body_sort(sorts.keys, (int)n_obj, ncls, perm, sorts.tmp, sorts.counts, s));
+            HIPCHK(launch_body_sort(sorts.keys, (int)n_obj, ncls, perm, sorts.tmp, sorts.counts, nullptr, s));
         } else {
             HIPCHK(launch_iota(perm, (int)n_obj, s));
         }

@@ -76,7 +76,7 @@ __global__ __launch_bounds__(256) void k_job_bucket(const BatchParams p) {
 // job and integrates them as lane groups (one lane per collocation node,
 // see GroupMap) through the job's epochs.
 template <int NB, int NGR, int NJ2, int DEG1>
-__global__ __launch_bounds__(64, 3) void k_batch_g8(const BatchParams p) {
+__global__ __launch_bounds__(64, 2) void k_batch_g8(const BatchParams p) {
     constexpr int G = KETE_BATCH_LANES;
     static_assert(GroupMap<G>::kBodies == KETE_BATCH_TILE, "tile = bodies per wavefront");
     extern __shared__ __align__(16) double smem[];
@@ -87,8 +87,8 @@ __global__ __launch_bounds__(64, 3) void k_batch_g8(const BatchParams p) {
     __shared__ __align__(16) GroupConst K;
     __shared__ __align__(16) double dwts[kDenseWeights];
     load_group_const(p.group_const, &K, lane, kWave);
-    const G8Lds T = g8_lds<GroupMap<G>::kLanes>(E, smem, M.grp);
-    g8_table_init<GroupMap<G>::kLanes>(E, lane, smem);
+    const G8Lds T = g8_lds<G>(E, smem, M.grp);
+    g8_table_init<G>(E, lane, smem);
     __syncthreads();
     for (;;) {
         int tile = 0;
@@ -142,8 +142,7 @@ __global__ __launch_bounds__(64, 3) void k_batch_g8(const BatchParams p) {
                 while (e_end + 1 < job.n_epoch && (fwd ? ep[e_end + 1] > ep[e_end] : ep[e_end + 1] < ep[e_end]))
                     ++e_end;
             const double target = ep[e_end];
-            EpochCursor ec{ep, e, e_end, 0.0};           // wave-uniform cursor over e .. e_end - 1
-            ec.fetch(lane);
+            EpochCursor ec(ep, e, e_end, lane);          // wave-uniform cursor over e .. e_end - 1
             auto dense_out = [&](double ts, double h, const double dn[3], const G8State& St) {
                 const bool ok = St.active && St.status == 0;
                 dense_epochs(K, dwts, T.xg, gl, lane, ts, h, dn, St.x0, St.v0, St.F0, ec,
@@ -166,8 +165,7 @@ __global__ __launch_bounds__(64, 3) void k_batch_g8(const BatchParams p) {
 }  // namespace
 
 size_t batch_lds_bytes(const BatchParams& p) {
-    return (size_t)g8_wave_doubles(g8_slots(p.eph.n_body, p.eph.n_gr, GroupMap<KETE_BATCH_LANES>::kLanes)) *
-           sizeof(double);
+    return (size_t)g8_wave_doubles<KETE_BATCH_LANES>(p.eph) * sizeof(double);
 }
 
 // The grouped kernels' constants into device memory (a tiny kernel, so the

@@ -480,6 +480,14 @@ __device__ __forceinline__ double uniform(double x) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+// Read lane m's value (m uniform) into every lane.
+__device__ __forceinline__ double lane_value(double v, int m) {
+    const long long u = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)(u & 0xffffffffll), m);
+    const int hi = __builtin_amdgcn_readlane((int)(u >> 32), m);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
 // Wave-wide reductions over the 64 lanes (results are wave-uniform).
 __device__ __forceinline__ double wave_max(double x) {
 #pragma unroll

@@ -898,14 +898,6 @@ __device__ __forceinline__ int batch_of_key(const int64_t* __restrict__ koff, in
     return lo;
 }
 
-// Read lane m's value (m uniform) into every lane.
-__device__ __forceinline__ double lane_value(double v, int m) {
-    const long long u = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)(u & 0xffffffffll), m);
-    const int hi = __builtin_amdgcn_readlane((int)(u >> 32), m);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
 // Work items of the join: one per 64 narrow objects of a (batch, cell).
 __global__ void k_item_count(const FovParams p, int32_t* __restrict__ icnt) {
     const int64_t key = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;

@@ -34,10 +34,10 @@ struct RadauConst {
 };
 // The constants the grouped kernels keep in LDS (GroupConst), as laid out by
 // fill_group_const: Ap, Bp, then per lane gl = 0..7 of a group the row {s,
-// s^2/2, A, B, 2 spare} of its node (gl + 1, and 7 for gl = 7), the nodes,
-// Lden and L1 (8 each), and the step-end weights of D_1..D_7 and F_0 in the
-// position and the velocity.
-constexpr int kGroupConstDoubles = 2 * 56 + 8 * 18 + 5 * 8;
+// s^2/2, A, B, 2 spare} of its node (gl + 1, and 7 for gl = 7), the nodes
+// 1..7, Lden and L1 (7 each), and the step-end weights of D_1..D_7 and F_0 in
+// the position and of D_1..D_7 in the velocity.
+constexpr int kGroupConstDoubles = 2 * 56 + 8 * 18 + 3 * 7 + 8 + 7;
 __host__ __device__ inline double group_const_at(const RadauConst& rc, int i) {
     if (i < 56) return rc.Ap[i / 8][i % 8];
     if (i < 112) return rc.Bp[(i - 56) / 8][i % 8];
@@ -47,12 +47,11 @@ __host__ __device__ inline double group_const_at(const RadauConst& rc, int i) {
         return k == 0 ? rc.s[n] : k == 1 ? rc.half_s2[n] : k < 9 ? rc.A[n][k - 2] : k < 16 ? rc.B[n][k - 9] : 0.0;
     }
     i -= 144;
-    const int k = i % 8;
-    if (i < 8) return rc.s[k];
-    if (i < 16) return k < 7 ? rc.Lden[k] : 0.0;
-    if (i < 24) return k < 7 ? rc.L1[k] : 0.0;
-    if (i < 32) return k < 7 ? rc.A[8][k] : rc.half_s2[8];
-    return k < 7 ? rc.B[8][k] : 1.0;
+    if (i < 7) return rc.s[i + 1];
+    if (i < 14) return rc.Lden[i - 7];
+    if (i < 21) return rc.L1[i - 14];
+    if (i < 28) return rc.A[8][i - 21];
+    return i == 28 ? rc.half_s2[8] : rc.B[8][i - 29];
 }
 
 // One staged ephemeris window of the integration: [t_a, t_b] lies within
@@ -127,7 +126,8 @@ __host__ __device__ inline double aligned_end(double t, double target, double t_
 struct NbodyParams {
     EphemArgs eph;
     RadauConst rc;
-    double* state;          // [N][6] working state
+    const double* state_in; // [N][6] states at the launch's start
+    double* state;          // [N][6] working state, null when nothing follows the launch
     double* h_pref;         // [N] preferred step (days, > 0)
     const int32_t* perm;    // [N] object order (bucketed) or null
     int32_t* status;        // [N]
@@ -143,10 +143,14 @@ struct NbodyParams {
     int32_t max_iter;
     int32_t max_steps;
     int32_t max_win_segs;   // LDS capacity in segments (one lane per object)
-    int32_t first_launch;
+    int32_t first_launch;   // no status to read yet
     int32_t zero_start;     // corrector starts from zero increments (no extrapolation)
     int32_t pad_;
+    int32_t solo_waves;     // wavefronts of one object each, ahead of the others (G8 kernels)
+    int32_t wave_doubles;   // LDS of a wavefront in doubles (set by the launch)
+    const int32_t* n_solo;  // device: objects that get one, or null (all of solo_waves do)
     double t_begin;         // start of the launch's first window
+    double t_only;          // end of its window when n_win is 1
     double eps, h_min, h_max, h_init, safety;
 };
 
@@ -176,14 +180,19 @@ constexpr int kMaxBuckets = 256;
 // Sort keys of the bodies of one integrator launch (k_hpref_init): the high
 // 16 bits hold the step class, the low 16 the time class; bodies are
 // ordered by class, then by time (two stable counting-sort passes).
-//   step class 0: "critical" bodies, whose predicted step count over the
+//   step class 0: bodies for a wavefront of their own (see solo_waves_for),
+//     with more than kSoloSteps predicted steps shorter than kSoloMaxStep
+//     days, the most steps first (16 classes an octave): the bodies of fast
+//     orbits, not the slow ones of a long span;
+//   step class 1: "critical" bodies, whose predicted step count over the
 //     launch exceeds kCritSteps: they set the launch's longest wavefronts,
-//     so they come first, ordered by the time of their smallest distance
+//     so they come next, ordered by the time of their smallest distance
 //     alone (kCritTimeBins classes), which lines up their perihelion
 //     passages inside a wavefront;
-//   step class 1 + k: the others, kClassSub classes per octave of the
+//   step class 2 + k: the others, kClassSub classes per octave of the
 //     predicted step above h_ref, then kTimeBins classes of that time.
 constexpr double kCritSteps = 100.0;
+constexpr double kSoloSteps = 150.0, kSoloMaxStep = 5.0;
 constexpr int kClassSub = 2;
 constexpr int kTimeBins = 64;
 constexpr int kCritTimeBins = 256;

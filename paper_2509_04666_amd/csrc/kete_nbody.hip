@@ -21,6 +21,8 @@ hipError_t launch_bucket(const BucketParams& p, hipStream_t s);
 
 namespace {
 
+constexpr int kSoloLanes = 56;
+
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_nbody(const NbodyParams p) {
     extern __shared__ double smem[];
@@ -36,14 +38,17 @@ __global__ __launch_bounds__(BLOCK) void k_nbody(const NbodyParams p) {
     const long gi = (long)blockIdx.x * BLOCK + tid;
     const bool valid = gi < p.n_obj;
     const int j = valid ? (p.perm ? p.perm[gi] : (int)gi) : 0;
-    bool active = valid && p.status[j] == 0;
-    int my_status = valid ? p.status[j] : 0;
+    int my_status = valid && !p.first_launch ? p.status[j] : 0;
+    bool active = valid && my_status == 0;
 
     double x0[3] = {1.0, 0.0, 0.0}, v0[3] = {0.0, 0.0, 0.0};
     double hin = kInf;
     if (valid) {
 #pragma unroll
-        for (int i = 0; i < 3; ++i) { x0[i] = p.state[6 * j + i]; v0[i] = p.state[6 * j + 3 + i]; }
+        for (int i = 0; i < 3; ++i) {
+            x0[i] = p.state_in[6 * (size_t)j + i];
+            v0[i] = p.state_in[6 * (size_t)j + 3 + i];
+        }
         hin = p.h_pref[j];
     }
     double hw = wave_min(active ? hin : kInf);
@@ -143,8 +148,9 @@ __global__ __launch_bounds__(BLOCK) void k_nbody(const NbodyParams p) {
     }
     if (valid) {
 #pragma unroll
-        for (int i = 0; i < 3; ++i) { p.state[6 * j + i] = x0[i]; p.state[6 * j + 3 + i] = v0[i]; }
-        if (hp_new < kInf) p.h_pref[j] = hp_new;
+        for (int i = 0; i < 3; ++i)
+            if (p.state) { p.state[6 * (size_t)j + i] = x0[i]; p.state[6 * (size_t)j + 3 + i] = v0[i]; }
+        if (p.state && hp_new < kInf) p.h_pref[j] = hp_new;
         p.status[j] = my_status;
     }
     if (p.stats && lane == 0 && __ballot(valid) != 0ull) {
@@ -157,33 +163,28 @@ __global__ __launch_bounds__(BLOCK) void k_nbody(const NbodyParams p) {
     }
 }
 
-// G lanes per object (see GroupMap): a wavefront integrates 9 objects (or 8,
-// 4, 2, 1), each spread over a group whose lanes own the collocation nodes.
-// The objects of a wavefront share the time grid and the perturber table as
-// above; each sweep evaluates the force at all 7 nodes of an object at once.
-// Output and counters are per object, as in k_nbody.
+// One wavefront of the grouped kernel, G lanes per object (see GroupMap): 9
+// objects (or 8, 4, 1) from place `first` of the order on, each spread over a
+// group whose lanes own the collocation nodes.  The objects of a wavefront
+// share the time grid and the perturber table as above; each sweep evaluates
+// the force at all 7 nodes of an object at once.  Output and counters are
+// per object, as in k_nbody.  wt: the wavefront's dense-output weights, base:
+// its other LDS.
 template <int G, int NB, int NGR, int NJ2, int DEG1>
-__global__ __launch_bounds__(256, 3) void k_nbody_g8(const NbodyParams p) {
-    extern __shared__ __align__(16) double smem[];
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
-    const int n_waves = blockDim.x / kWave;
+__device__ __forceinline__ void nbody_wave(const NbodyParams& p, const GroupConst& K, long first, double* wt,
+                                           double* base) {
+    const int lane = threadIdx.x & (kWave - 1);
     const GroupMap<G> M(lane);
-    constexpr int L = GroupMap<G>::kLanes;
     const int gl = M.gl;
     const EphemArgs& E = p.eph;
-    __shared__ __align__(16) GroupConst K;
-    const long gi = ((long)blockIdx.x * n_waves + wid) * GroupMap<G>::kBodies + M.grp;
+    const long gi = first + M.grp;
     const bool valid = gi < p.n_obj;
     const int j = valid ? (p.perm ? p.perm[gi] : (int)gi) : 0;
-    load_group_const(p.group_const, &K, tid, (int)blockDim.x);
-    const int slots = g8_slots(E.n_body, E.n_gr, L);
-    double* base = smem + (size_t)wid * (g8_wave_doubles(slots) + kDenseWeights);
-    double* wt = base + g8_wave_doubles(slots);
-    const G8Lds T = g8_lds<L>(E, base, M.grp);
-    g8_table_init<L>(E, lane, base);
+    const G8Lds T = g8_lds<G>(E, base, M.grp);
+    g8_table_init<G>(E, lane, base);
 
     G8State S;
-    S.status = valid ? p.status[j] : 0;
+    S.status = valid && !p.first_launch ? p.status[j] : 0;
     S.active = valid && S.status == 0;
     S.x0[0] = 1.0; S.x0[1] = S.x0[2] = 0.0;
     S.v0[0] = S.v0[1] = S.v0[2] = 0.0;
@@ -191,30 +192,30 @@ __global__ __launch_bounds__(256, 3) void k_nbody_g8(const NbodyParams p) {
     double hin = kInf;
     if (valid) {
 #pragma unroll
-        for (int i = 0; i < 3; ++i) { S.x0[i] = p.state[6 * (size_t)j + i]; S.v0[i] = p.state[6 * (size_t)j + 3 + i]; }
+        for (int i = 0; i < 3; ++i) {
+            S.x0[i] = p.state_in[6 * (size_t)j + i];
+            S.v0[i] = p.state_in[6 * (size_t)j + 3 + i];
+        }
         hin = p.h_pref[j];
     }
     // Epochs e_first .. e_land - 1 come off the collocation polynomial of
     // the accepted step that spans them (the cursor is wave-uniform: the
     // wavefront's objects share every step).
-    EpochCursor ec{p.t_out, p.e_first, p.e_land, 0.0};
-    ec.fetch(lane);
+    EpochCursor ec(p.t_out, p.e_first, p.e_land, lane);
     S.hw = groups_min<G>(S.active ? hin : kInf);
     if (!(S.hw < kInf)) S.hw = p.h_init;
     S.hp_new = kInf;
     S.t = p.t_begin;
     S.haveF0 = false;
     G8Count C;
-    __syncthreads();
 
     const bool writer = valid && gl < 6 && M.sub == 0;
     auto put = [&](int e, double v, bool ok) {      // node lane gl writes component gl
         if (writer) p.x_out[((size_t)e * p.n_obj + j) * 6 + gl] = ok ? v : __builtin_nan("");
     };
-    while (ec.next < ec.end && uniform(ec.tk) == S.t) {         // epochs at the start time
+    while (ec.next < ec.end && ec.time() == S.t) {              // epochs at the start time
         put(ec.next, state_component(S.x0, S.v0, gl < 6 ? gl : 5), S.active && S.status == 0);
-        ++ec.next;
-        ec.fetch(lane);
+        ec.advance(1, lane);
     }
     auto dense_out = [&](double ts, double h, const double dn[3], const G8State& St) {
         const bool ok = St.active && St.status == 0;
@@ -223,16 +224,17 @@ __global__ __launch_bounds__(256, 3) void k_nbody_g8(const NbodyParams p) {
     };
 
     for (int w = 0; w < p.n_win; ++w) {
-        const double t_b = p.win[w].t_b;
-        const int out = p.win[w].out;
+        // the only window of a launch comes with the arguments
+        const double t_b = p.n_win == 1 ? p.t_only : p.win[w].t_b;
+        const int out = p.n_win == 1 ? p.e_land : p.win[w].out;
         g8_integrate<NB, NGR, NJ2, DEG1, G>(p, K, T, M, lane, t_b, S, C, dense_out);
         if (out >= 0) put(out, state_component(S.x0, S.v0, gl < 6 ? gl : 5), S.active && S.status == 0);
     }
     // a wavefront whose objects have all failed ends its steps before their epochs
     while (ec.next < ec.end) put(ec.next++, 0.0, false);
-    if (writer) p.state[6 * (size_t)j + gl] = state_component(S.x0, S.v0, gl);
+    if (writer && p.state) p.state[6 * (size_t)j + gl] = state_component(S.x0, S.v0, gl);
     if (valid && gl == 0 && M.sub == 0) {
-        if (S.hp_new < kInf) p.h_pref[j] = S.hp_new;
+        if (p.state && S.hp_new < kInf) p.h_pref[j] = S.hp_new;
         p.status[j] = S.status;
     }
     const unsigned long long c_steps = C.steps, c_iter = C.iter, c_rej = C.rej, c_lsteps = C.lsteps,
@@ -246,6 +248,38 @@ __global__ __launch_bounds__(256, 3) void k_nbody_g8(const NbodyParams p) {
         atomicAdd(p.stats + 5, c_chain);
         atomicAdd(p.stats + 6, c_vchain);
         atomicAdd(p.stats + 7, c_lpred);
+    }
+}
+
+// The launch's wavefronts: the first p.solo_waves take one object each, 56
+// lanes of it, the rest G lanes per object.  With p.n_solo (device) only as
+// many of the first as it says have an object, and the others begin behind
+// those; without, every one does.
+//   A lone object takes its own steps (the shared step of nine objects on
+// fast orbits, each at another place of its own, is near the shortest any of
+// them ever needs) and its sweep is short, the force of a node summed by
+// eight lanes.  It uses the chip less well than nine objects a wavefront, so
+// it is for launches with fewer objects than keep the chip busy, and for the
+// objects whose wavefronts would end the launch (see solo_waves_for).
+template <int G, int NB, int NGR, int NJ2, int DEG1>
+__global__ __launch_bounds__(256, 2) void k_nbody_g8(const NbodyParams p) {
+    extern __shared__ __align__(16) double smem[];
+    __shared__ __align__(16) GroupConst K;
+    const int wid = threadIdx.x / kWave, n_waves = blockDim.x / kWave;
+    load_group_const(p.group_const, &K, threadIdx.x, (int)blockDim.x);
+    __syncthreads();
+    const long wave = (long)blockIdx.x * n_waves + wid;
+    double* wt = smem + (size_t)wid * p.wave_doubles;
+    if constexpr (G != 8) {
+        const int solo = p.n_solo ? min(*p.n_solo, p.solo_waves) : p.solo_waves;
+        if (wave < p.solo_waves) {
+            if (wave < solo) nbody_wave<kSoloLanes, NB, NGR, NJ2, DEG1>(p, K, wave, wt, wt + kDenseWeights);
+            return;
+        }
+        const long first = solo + (wave - p.solo_waves) * GroupMap<G>::kBodies;
+        if (first < p.n_obj) nbody_wave<G, NB, NGR, NJ2, DEG1>(p, K, first, wt, wt + kDenseWeights);
+    } else {
+        nbody_wave<G, NB, NGR, NJ2, DEG1>(p, K, wave * GroupMap<G>::kBodies, wt, wt + kDenseWeights);
     }
 }
 
@@ -312,12 +346,16 @@ __global__ void k_hpref_init(const double* __restrict__ x0, double* __restrict__
     const double span = dt_hi - dt_lo;
     const double frac = span > 0.0 ? fmin(fmax((tm - dt_lo) / span, 0.0), 1.0) : 0.0;
     uint32_t hi, lo;
-    if (h > 0.0 && span / h > kCritSteps) {
+    const double steps = h > 0.0 ? span / h : 0.0;
+    if (steps > kSoloSteps && h < kSoloMaxStep) {
         hi = 0;
+        lo = (uint32_t)fmin(fmax(kCritTimeBins - 1.0 - 16.0 * log2(steps / kSoloSteps), 0.0), kCritTimeBins - 1.0);
+    } else if (steps > kCritSteps) {
+        hi = 1;
         lo = (uint32_t)fmin(frac * kCritTimeBins, kCritTimeBins - 1.0);
     } else {
-        const double c = (h > 0.0 && h < kInf) ? floor(kClassSub * log2(h / h_ref)) : (double)(n_class - 2);
-        hi = 1u + (uint32_t)fmin(fmax(c, 0.0), (double)(n_class - 2));
+        const double c = (h > 0.0 && h < kInf) ? floor(kClassSub * log2(h / h_ref)) : (double)(n_class - 3);
+        hi = 2u + (uint32_t)fmin(fmax(c, 0.0), (double)(n_class - 3));
         lo = (uint32_t)fmin(frac * kTimeBins, kTimeBins - 1.0);
     }
     keys[j] = hi << 16 | lo;
@@ -325,18 +363,40 @@ __global__ void k_hpref_init(const double* __restrict__ x0, double* __restrict__
 
 }  // namespace
 
+// Wavefronts of one object each, for a launch of n objects of which the
+// device may name the heaviest (`classes`: they are sorted by predicted step).
+// Up to kSoloAll objects, two wavefronts a SIMD, all of them.  Up to
+// kSoloSomeObj, fewer than eight rounds of wavefronts on the chip, the
+// heaviest kSoloSome: with nine a wavefront the fast orbits took 3.3 ms of a
+// 100,000-object year whose other wavefronts were done in 2.4 ms (2.8 ms with
+// their own).  In a longer launch their wavefronts end among the others:
+// 750,000 objects take 17.1 ms either way.
+constexpr int kSoloAll = 2048, kSoloSome = 1024, kSoloSomeObj = 220000;
+// Two lanes per node (4 objects a wavefront) up to here: at most two
+// wavefronts a SIMD, whose sweeps are half as long.
+//   (20,011 objects carried back five years, the heaviest 1,024 of them
+// alone: 14.9 -> 7.5 ms; 63 objects over a month: 55 -> 43 us.)
+constexpr int kPairLanesObj = 8192;
+int solo_waves_for(int n, bool classes) {
+    if (n <= kSoloAll) return n;
+    return classes && n <= kSoloSomeObj ? kSoloSome : 0;
+}
+
 // The grouped kernel with G lanes per object; the usual shapes of the
 // perturber table (bodies, bodies with the Eq. A.3 and A.4 terms) get an
 // unrolled force.
 template <int G>
-static hipError_t launch_groups(const NbodyParams& p, int block, hipStream_t s) {
+static hipError_t launch_groups(NbodyParams p, int block, hipStream_t s) {
     const int wpb = block / kWave;
-    const long waves = ((long)p.n_obj + GroupMap<G>::kBodies - 1) / GroupMap<G>::kBodies;
+    const EphemArgs& E = p.eph;
+    // with n_solo the objects not taken alone may be all of them
+    const long rest = p.n_solo ? p.n_obj : std::max(0, p.n_obj - p.solo_waves);
+    const long waves = p.solo_waves + (rest + GroupMap<G>::kBodies - 1) / GroupMap<G>::kBodies;
     const dim3 grid((unsigned)((waves + wpb - 1) / wpb));
     if (grid.x == 0) return hipSuccess;
-    const EphemArgs& E = p.eph;
-    const size_t lds = (size_t)wpb * (g8_wave_doubles(g8_slots(E.n_body, E.n_gr, GroupMap<G>::kLanes)) + kDenseWeights) *
-                       sizeof(double);
+    p.wave_doubles = kDenseWeights + (p.solo_waves ? std::max(g8_wave_doubles<G>(E), g8_wave_doubles<kSoloLanes>(E))
+                                                   : g8_wave_doubles<G>(E));
+    const size_t lds = (size_t)wpb * p.wave_doubles * sizeof(double);
     switch (group_shape(E)) {
         case 2: hipLaunchKernelGGL((k_nbody_g8<G, 10, 3, 2, 13>), grid, dim3(block), lds, s, p); break;
         case 3: hipLaunchKernelGGL((k_nbody_g8<G, 3, 2, 2, 13>), grid, dim3(block), lds, s, p); break;
@@ -351,7 +411,9 @@ hipError_t launch_nbody(const NbodyParams& p, int block, int lanes_per_body, hip
                         (size_t)(block / kWave) * kNodes * p.eph.n_body * 6) * sizeof(double);
     if (lanes_per_body == 7 || lanes_per_body == 8) {
         if (block != 64 && block != 128 && block != 256) return hipErrorInvalidValue;
-        return lanes_per_body == 7 ? launch_groups<7>(p, block, s) : launch_groups<8>(p, block, s);
+        if (lanes_per_body == 8) return launch_groups<8>(p, block, s);
+        return p.n_obj - p.solo_waves <= kPairLanesObj ? launch_groups<14>(p, block, s)
+                                                       : launch_groups<7>(p, block, s);
     }
     if (lanes_per_body != 1) return hipErrorInvalidValue;
     const int grid = (int)((p.n_obj + block - 1) / block);
@@ -374,9 +436,10 @@ hipError_t launch_hpref_init(const double* x0, double* h_pref, uint32_t* keys, i
 }
 
 // Bodies ordered by their keys: the time class first, then (stably) the
-// step class, into perm; tmp [n] holds the first pass's order.
+// step class, into perm; tmp [n] holds the first pass's order.  *n_first
+// becomes the device address of the number of bodies in step class 0.
 hipError_t launch_body_sort(const uint32_t* keys, int n, int n_class, int32_t* perm, int32_t* tmp, int32_t* counts,
-                            hipStream_t s) {
+                            const int32_t** n_first, hipStream_t s) {
     BucketParams B;
     B.keys = keys;
     B.counts = counts;
@@ -392,6 +455,9 @@ hipError_t launch_body_sort(const uint32_t* keys, int n, int n_class, int32_t* p
     B.perm = perm;
     B.n_buckets = n_class;
     B.shift = 16;
+    // the class-major offsets of the second pass: class 1 starts where class 0 ends
+    const int nblk = (n + 255) / 256;
+    if (n_first) *n_first = counts + (size_t)n_class * nblk + nblk;
     return launch_bucket(B, s);
 }
 

@@ -220,7 +220,6 @@ struct GroupMap {
         }
     }
 };
-constexpr int kMaxGroups = 9;
 
 // Constants of one node.
 struct NodeRow {
@@ -233,9 +232,9 @@ struct NodeRow {
 struct GroupConst {
     double Ap[7][8], Bp[7][8];      // dense output
     NodeRow row[kGroup];            // by gl
-    double s[8];                    // nodes 0..7
-    double Lden[8], L1[8];          // extrapolated corrector start
-    double A8[8], B8[8];            // step end: weights of D_1..D_7, then of F_0
+    double s[7];                    // nodes 1..7
+    double Lden[7], L1[7];          // extrapolated corrector start
+    double A8[8], B8[7];            // step end: weights of D_1..D_7 (A8[7]: of F_0)
 };
 static_assert(sizeof(GroupConst) == kGroupConstDoubles * sizeof(double), "the device table is one GroupConst");
 
@@ -337,9 +336,14 @@ constexpr int kXchGroup = 26;
 // (they have the first slots; zero for the others), then KETE_MAX_J2 by
 // index for the rest.
 constexpr int kJ2Doubles = 4 * (8 + KETE_MAX_J2);
-// Doubles of LDS per wavefront: node table, exchange rows, J2 constants.
-__host__ __device__ inline int g8_wave_doubles(int slots) {
-    return kNodes * g8_row(slots) + kMaxGroups * kXchGroup + kJ2Doubles;
+// Doubles of LDS per wavefront: node table, exchange rows of its bodies, J2
+// constants.
+__host__ __device__ inline int g8_wave_doubles(int slots, int bodies) {
+    return kNodes * g8_row(slots) + bodies * kXchGroup + kJ2Doubles;
+}
+template <int G>
+inline int g8_wave_doubles(const EphemArgs& E) {
+    return g8_wave_doubles(g8_slots(E.n_body, E.n_gr, GroupMap<G>::kLanes), GroupMap<G>::kBodies);
 }
 
 // One wavefront's LDS areas, and the shape of its table.
@@ -349,22 +353,22 @@ struct G8Lds {
     const double* j2;       // J2 constants
     int row;                // doubles per node row
 };
-template <int L>
+template <int G>
 __device__ __forceinline__ G8Lds g8_lds(const EphemArgs& E, double* base, int grp) {
-    const int slots = g8_slots(E.n_body, E.n_gr, L);
+    const int slots = g8_slots(E.n_body, E.n_gr, GroupMap<G>::kLanes);
     G8Lds s;
     s.e8 = base;
     s.row = g8_row(slots);
     s.xg = base + kNodes * s.row + grp * kXchGroup;
-    s.j2 = base + kNodes * s.row + kMaxGroups * kXchGroup;
+    s.j2 = base + kNodes * s.row + GroupMap<G>::kBodies * kXchGroup;
     return s;
 }
 
 // The entries of the table and of the J2 constants that hold for the whole
 // launch; one wavefront.
-template <int L>
+template <int G>
 __device__ __forceinline__ void g8_table_init(const EphemArgs& E, int lane, double* __restrict__ base) {
-    const int slots = g8_slots(E.n_body, E.n_gr, L);
+    const int slots = g8_slots(E.n_body, E.n_gr, GroupMap<G>::kLanes);
     const int row = g8_row(slots);
     const int n = lane < kNodes ? lane : 0;      // lanes past the nodes repeat node 0
     double* r = base + n * row;
@@ -381,7 +385,7 @@ __device__ __forceinline__ void g8_table_init(const EphemArgs& E, int lane, doub
         q[0] = 1e6;
         for (int k = 1; k < kSlot; ++k) q[k] = 0.0;
     }
-    double* j2 = base + kNodes * row + kMaxGroups * kXchGroup;
+    double* j2 = base + kNodes * row + GroupMap<G>::kBodies * kXchGroup;
     if (lane < kJ2Doubles) j2[lane] = 0.0;
     wave_lds_sync();
 #pragma unroll
@@ -480,14 +484,17 @@ __device__ __forceinline__ void node_ephemeris8(const EphemArgs& E, const GroupC
         const double tau = 2.0 * (tt - (E.t_start + (double)k * E.seg_days)) * E.inv_seg - 1.0;
         const double* cb = E.coef + (size_t)k * cps;
         double* row = T.e8 + n * T.row;
+        auto at = [&](int c) {                     // coefficients of coordinate c
+            const int qc = c < nc ? c : nc - 1, sl = qc / 3;
+            return cb + slot_body(E, sl) * bstride + (qc - 3 * sl) * deg1;
+        };
 #pragma unroll 1
         for (int j = 0; j < npass; j += 2) {
             const int ca = c0 + cstep * j, cc = ca + cstep;
-            const int qa = ca < nc ? ca : nc - 1, qc = cc < nc ? cc : nc - 1;
-            const int sa = qa / 3, ia = qa - 3 * sa, sb = qc / 3, ib = qc - 3 * sb;
+            const int sa = ca / 3, ia = ca - 3 * sa, sb = cc / 3, ib = cc - 3 * sb;
             ChainCoef<DEG1> A, B;
-            A.load(cb + slot_body(E, sa) * bstride + ia * deg1, deg1);
-            B.load(cb + slot_body(E, sb) * bstride + ib * deg1, deg1);
+            A.load(at(ca), deg1);
+            B.load(at(cc), deg1);
             if (cstep * j < ngc) {                 // wave-uniform: the pair holds derivative chains
                 double pa, da, pb, db;
                 A.value_slope(tau, pa, da);
@@ -606,7 +613,11 @@ __device__ __forceinline__ void accel8(const double* __restrict__ row, const G8L
     if constexpr (NB > 0) {
         constexpr int kRounds = (NB + L - 1) / L, kGr = (NGR + L - 1) / L, kJ = (NJ2 + L - 1) / L;
         constexpr int kPlain = kRounds - kGr;
-        if constexpr (kGr > 0) force_terms<kGr, true, kJ>(pb, kSlot * L, jc, L, X, V, F);
+        // at most two slots with the Eq. A.3 term side by side, and four without
+        constexpr int kGrA = kGr > 2 ? 2 : kGr, kJa = kJ > kGrA ? kGrA : kJ;
+        if constexpr (kGrA > 0) force_terms<kGrA, true, kJa>(pb, kSlot * L, jc, L, X, V, F);
+        if constexpr (kGr > kGrA)
+            force_terms<kGr - kGrA, true, kJ - kJa>(pb + kSlot * L * kGrA, kSlot * L, jc + 4 * L * kGrA, L, X, V, F);
         constexpr int kHalf = kPlain > 4 ? (kPlain + 1) / 2 : kPlain;
         if constexpr (kHalf > 0) force_terms<kHalf, false>(pb + kSlot * L * kGr, kSlot * L, jc, 0, X, V, F);
         if constexpr (kPlain > kHalf)
@@ -755,7 +766,7 @@ __device__ __forceinline__ void extrapolate_increment(const GroupConst& K, doubl
     double dk[8], pre[8];
     dk[0] = sig;
 #pragma unroll
-    for (int k = 1; k < 8; ++k) dk[k] = sig - K.s[k];
+    for (int k = 1; k < 8; ++k) dk[k] = sig - K.s[k - 1];
     pre[0] = 1.0;
 #pragma unroll
     for (int k = 1; k < 8; ++k) pre[k] = pre[k - 1] * dk[k - 1];
@@ -793,7 +804,6 @@ __device__ __forceinline__ int corrector_g8(const RadauConst& rc, const GroupCon
     if (started) extrapolate_increment(K, T.xg, gl, Dp, q, dn);
     else dn[0] = dn[1] = dn[2] = 0.0;
     b6[0] = b6[1] = b6[2] = 0.0;
-    d6[0] = d6[1] = d6[2] = 0.0;
     double last = 1e300;
     bool done = !active;
     int it = 0;
@@ -812,7 +822,6 @@ __device__ __forceinline__ int corrector_g8(const RadauConst& rc, const GroupCon
                     ax[c] = fma(R.A[m], d, ax[c]);
                     av[c] = fma(R.B[m], d, av[c]);
                     bb[c] = fma(rc.E6[m], d, bb[c]);
-                    if (m == 6) d6[c] = d;
                 }
             }
             double db = 0.0, fm = 0.0;
@@ -820,7 +829,7 @@ __device__ __forceinline__ int corrector_g8(const RadauConst& rc, const GroupCon
             for (int c = 0; c < 3; ++c) {
                 db = fmax(db, fabs(bb[c] - b6[c]));
                 b6[c] = bb[c];
-                fm = fmax(fm, fabs(d6[c] + F0[c]));
+                fm = fmax(fm, fabs(D[6][c] + F0[c]));
             }
             // the ratio only steers the stopping rule: the reciprocal estimate
             // suffices (a body whose ratio is not a number holds no one up)
@@ -846,6 +855,8 @@ __device__ __forceinline__ int corrector_g8(const RadauConst& rc, const GroupCon
 #pragma unroll
         for (int c = 0; c < 3; ++c) dn[c] = F[c] - F0[c];
     }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) d6[c] = T.xg[8 * c + 6];       // as published last
     return it;
 }
 
@@ -922,12 +933,14 @@ __device__ __forceinline__ void g8_integrate(const Params& p, const GroupConst& 
         double h = dir * hmag;
         bool landed = false;
         if (fabs(h) >= fabs(tb - S.t)) { h = tb - S.t; landed = true; }
+        // (times and steps are the same in every lane: kept in scalar registers)
+        h = uniform(h);
         if ((long)C.steps >= p.max_steps) {
             if (S.active) { S.status = KETE_ST_MAX_STEPS; S.active = false; }
             S.t = tb;
             return;
         }
-        const double t_end = landed ? tb : S.t + h;
+        const double t_end = uniform(landed ? tb : S.t + h);
         // node 0 is evaluated before the first step; with need_node0 it is
         // afterwards the previous step's end row, copied when that step is accepted
         const int n0 = (S.haveF0 && (!need_node0 || S.row0)) ? 1 : 0;
@@ -940,6 +953,7 @@ __device__ __forceinline__ void g8_integrate(const Params& p, const GroupConst& 
         double q = 0.0;                       // wave-uniform, like h and S.hprev
         if (!p.zero_start && S.hprev != 0.0) q = h / S.hprev;
         if (!(q <= kPredMaxRatio)) q = 0.0;
+        q = uniform(q);
         double dn[3], b6p[3], d6[3];
         const int it = corrector_g8<NB, NGR, NJ2, L>(rc, K, E, T, gl, sub, S.x0, S.v0, S.F0, h, S.active, p.max_iter,
                                                      dn, b6p, d6, S.Dp, q);
@@ -983,53 +997,85 @@ __device__ __forceinline__ void g8_integrate(const Params& p, const GroupConst& 
             wave_lds_sync();
         }
         if (landed) {
-            S.hw = fmin(S.hw, hn);
+            S.hw = uniform(fmin(S.hw, hn));
         } else {
-            S.hw = fmin(hn, fabs(h) / p.safety);
+            S.hw = uniform(fmin(hn, fabs(h) / p.safety));
             S.hp_new = fmin(S.hp_new, fmin(hl, fabs(h) / p.safety));
         }
     }
 }
 
-// Component gl (0..5) of a state.
+// Component c (0..2) of a vector and gl (0..5) of a state.  The components
+// are made opaque first: selects between plain array elements are merged
+// into one load at a selected address, which keeps the whole array in
+// scratch memory, read again by every sweep (a third of the integrator's
+// time).
+__device__ __forceinline__ double vector_component(const double x[3], int c) {
+    double a = x[0], b = x[1], d = x[2];
+    asm("" : "+v"(a));
+    asm("" : "+v"(b));
+    asm("" : "+v"(d));
+    return c == 0 ? a : c == 1 ? b : d;
+}
 __device__ __forceinline__ double state_component(const double x0[3], const double v0[3], int gl) {
-    return gl == 0 ? x0[0] : gl == 1 ? x0[1] : gl == 2 ? x0[2] : gl == 3 ? v0[0] : gl == 4 ? v0[1] : v0[2];
+    const double a = vector_component(x0, gl), b = vector_component(v0, gl - 3);
+    return gl < 3 ? a : b;
 }
 
-// Collocation polynomial at fraction sig of the step (sig = 1: step end),
-// from the monomial weights alpha_m(sig) = sum_k Ap[m][k] sig^(k+2) and
-// beta_m(sig) = sum_k Bp[m][k] sig^(k+1) (m = 1..7, k = 0..7), their rows
-// read from a copy in LDS (K), and the step's node
-// increments from the group's exchange rows xg (component c of node m + 1 at
-// xg[8 c + m]), one node at a time; sig may differ between groups.
-__device__ __forceinline__ void dense_state_rows(const GroupConst& K, const double* __restrict__ xg,
-                                                 const double x0[3], const double v0[3], const double F0[3],
-                                                 double h, double sig, double X[3], double V[3]) {
-    double ax[3], av[3];
+// The node increments of component c of a step, and F_0's, as the dense
+// output reads them: from the group's exchange rows, where each lane
+// publishes its node's increment dn first.  The whole wavefront calls it.
+__device__ __forceinline__ void dense_increments(double* __restrict__ xg, int gl, int c, const double dn[3],
+                                                 const double F0[3], double D[8]) {
+    wave_lds_sync();                        // earlier reads of the exchange rows are done
+    xg[gl] = dn[0];
+    xg[8 + gl] = dn[1];
+    xg[16 + gl] = dn[2];
+    wave_lds_sync();
 #pragma unroll
-    for (int c = 0; c < 3; ++c) { ax[c] = 0.5 * sig * sig * F0[c]; av[c] = sig * F0[c]; }
-#pragma unroll 1
-    for (int m = 0; m < 7; ++m) {
-        const double* am = K.Ap[m];
-        const double* bm = K.Bp[m];
-        double a = am[7], b = bm[7];
-#pragma unroll
-        for (int k = 6; k >= 0; --k) { a = fma(a, sig, am[k]); b = fma(b, sig, bm[k]); }
-        a *= sig * sig;
-        b *= sig;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const double d = xg[8 * c + m];
-            ax[c] = fma(a, d, ax[c]);
-            av[c] = fma(b, d, av[c]);
-        }
+    for (int k = 0; k < 4; ++k) {
+        const double2 d = *reinterpret_cast<const double2*>(xg + 8 * c + 2 * k);
+        D[2 * k] = d.x;
+        D[2 * k + 1] = d.y;
     }
-    const double hh = h * h;
+    D[7] = vector_component(F0, c);
+}
+
+// sum_m w[m] D[m] + w[7] F_0 from eight weights in LDS.
+__device__ __forceinline__ double dense_sum(const double* __restrict__ w, const double D[8]) {
+    const double2* q = reinterpret_cast<const double2*>(w);
+    const double2 q0 = q[0], q1 = q[1], q2 = q[2], q3 = q[3];
+    double a = q3.y * D[7];
+    a = fma(q0.x, D[0], a);
+    a = fma(q0.y, D[1], a);
+    a = fma(q1.x, D[2], a);
+    a = fma(q1.y, D[3], a);
+    a = fma(q2.x, D[4], a);
+    a = fma(q2.y, D[5], a);
+    return fma(q3.x, D[6], a);
+}
+
+// This lane's component of the collocation polynomial at fraction sig of the
+// step, which differs between the 8-lane groups: lane gl of a group evaluates
+// the weights alpha and beta of node gl + 1 (lane 7 those of F_0) into the
+// group's 16 slots wt, and each lane forms the component it stands for
+// (velocity if vel) from them and D (dense_increments).  The whole wavefront
+// calls it.
+__device__ __forceinline__ double dense_component8(const GroupConst& K, double* __restrict__ wt, int gl, bool vel,
+                                                   double sig, double h, double xc, double vc, const double D[8]) {
+    const double* am = K.Ap[gl < 7 ? gl : 6];
+    const double* bm = K.Bp[gl < 7 ? gl : 6];
+    double a = am[7], b = bm[7];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        X[c] = fma(hh, ax[c], fma(sig * h, v0[c], x0[c]));
-        V[c] = fma(h, av[c], v0[c]);
-    }
+    for (int k = 6; k >= 0; --k) { a = fma(a, sig, am[k]); b = fma(b, sig, bm[k]); }
+    a *= sig * sig;
+    b *= sig;
+    wave_lds_sync();                        // earlier reads of wt are done
+    wt[gl] = gl < 7 ? a : 0.5 * sig * sig;
+    wt[8 + gl] = gl < 7 ? b : sig;
+    wave_lds_sync();
+    const double s = dense_sum(wt + (vel ? 8 : 0), D);
+    return vel ? fma(h, s, vc) : fma(h * h, s, fma(sig * h, vc, xc));
 }
 
 // Dense output of a step for a wavefront's objects: the cursor's epochs that
@@ -1047,14 +1093,27 @@ __device__ __forceinline__ void dense_state_rows(const GroupConst& K, const doub
 // instructions an epoch, a fifth of the integrator's with epochs 3 days apart.)
 constexpr int kDenseRound = 4;              // epochs per round
 constexpr int kDenseWeights = 16 * kDenseRound;
-// The cursor keeps the next four epochs' times in the lanes, read ahead.
+// The cursor keeps 64 epochs' times in the lanes, so that a step seldom
+// loads: a load waits for the states stored before it.
 struct EpochCursor {
     const double* t_out;
     int next, end;          // wave-uniform
-    double tk;              // t_out[next + lane / 16] (of the last epoch past the end)
-    __device__ __forceinline__ void fetch(int lane) {
-        const int e = next + (lane >> 4);
-        if (next < end) tk = t_out[e < end ? e : end - 1];
+    int base = 0;           // lane l holds t_out[base + l] (the last epoch past the end)
+    double buf = 0.0;
+    __device__ __forceinline__ EpochCursor(const double* t, int first, int last, int lane)
+        : t_out(t), next(first), end(last) { load(lane); }
+    __device__ __forceinline__ void load(int lane) {
+        base = next;
+        const int e = next + lane;
+        if (next < end) buf = t_out[e < end ? e : end - 1];
+    }
+    __device__ __forceinline__ double time() const {           // of epoch `next`
+        return lane_value(buf, __builtin_amdgcn_readfirstlane(next - base));
+    }
+    __device__ __forceinline__ double time_ahead(int k) const { return __shfl(buf, next - base + k, kWave); }
+    __device__ __forceinline__ void advance(int n, int lane) {
+        next += n;
+        if (next - base > kWave - 4) load(lane);
     }
 };
 template <class Put>
@@ -1064,35 +1123,24 @@ __device__ __forceinline__ void dense_epochs(const GroupConst& K, double* __rest
                                              EpochCursor& ec, Put&& put) {
     if (ec.next >= ec.end) return;
     const double te = ts + h;
-    const double t_first = uniform(ec.tk);
+    const double t_first = ec.time();
     if (!(h > 0.0 ? t_first <= te : t_first >= te)) return;
-    wave_lds_sync();                        // earlier reads of the exchange rows are done
-    xg[gl] = dn[0];
-    xg[8 + gl] = dn[1];
-    xg[16 + gl] = dn[2];
-    wave_lds_sync();
     // this lane's component: coordinate c of the position or velocity
     const bool vel = gl >= 3;
     const int c = vel ? (gl < 6 ? gl - 3 : 2) : gl;
     double D[8];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const double2 d = *reinterpret_cast<const double2*>(xg + 8 * c + 2 * k);
-        D[2 * k] = d.x;
-        D[2 * k + 1] = d.y;
-    }
-    const double xc = c == 0 ? x0[0] : c == 1 ? x0[1] : x0[2];
-    const double vc = c == 0 ? v0[0] : c == 1 ? v0[1] : v0[2];
-    D[7] = c == 0 ? F0[0] : c == 1 ? F0[1] : F0[2];
+    dense_increments(xg, gl, c, dn, F0, D);
+    const double xc = vector_component(x0, c);
+    const double vc = vector_component(v0, c);
     const double hc = vel ? h : h * h;
     const int m = lane & 15;
     const double* pm = &K.Ap[0][0] + 8 * (m < 7 ? m : m < 15 ? m - 1 : 13);
     for (;;) {
         const int el = ec.next + (lane >> 4), e0 = ec.next;
-        const int n = __popcll(__ballot(el < ec.end && (h > 0.0 ? ec.tk <= te : ec.tk >= te))) >> 4;
-        const double sig = (ec.tk - ts) / h;
-        ec.next += n;
-        ec.fetch(lane);
+        const double tk = ec.time_ahead(lane >> 4);
+        const int n = __popcll(__ballot(el < ec.end && (h > 0.0 ? tk <= te : tk >= te))) >> 4;
+        const double sig = (tk - ts) / h;
+        ec.advance(n, lane);
         double w = pm[7];
 #pragma unroll
         for (int k = 6; k >= 0; --k) w = fma(w, sig, pm[k]);
@@ -1105,16 +1153,7 @@ __device__ __forceinline__ void dense_epochs(const GroupConst& K, double* __rest
 #pragma unroll
         for (int k = 0; k < kDenseRound; ++k) {
             if (k >= n) break;
-            const double2* q = reinterpret_cast<const double2*>(wt + 16 * k + (vel ? 8 : 0));
-            const double2 q0 = q[0], q1 = q[1], q2 = q[2], q3 = q[3];
-            double a = q3.y * D[7];
-            a = fma(q0.x, D[0], a);
-            a = fma(q0.y, D[1], a);
-            a = fma(q1.x, D[2], a);
-            a = fma(q1.y, D[3], a);
-            a = fma(q2.x, D[4], a);
-            a = fma(q2.y, D[5], a);
-            a = fma(q3.x, D[6], a);
+            const double a = dense_sum(wt + 16 * k + (vel ? 8 : 0), D);
             const double sg = wt[16 * k + 15];
             put(e0 + k, vel ? fma(hc, a, vc) : fma(hc, a, fma(sg * h, vc, xc)));
         }

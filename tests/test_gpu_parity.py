@@ -402,6 +402,56 @@ def test_propagate_status_codes(torch_cuda, orc):
     assert np.all(s3.cpu().numpy() == 2)
 
 
+@pytest.mark.parametrize("n,span", [(1, 220.0), (2048, 220.0), (2049, 220.0), (8193, 220.0), (9217, 220.0),
+                                    (220000, 20.0)])
+def test_lone_paired_and_grouped_objects(torch_cuda, n, span):
+    """The list sizes at which objects move between wavefronts of their own,
+    two lanes per node and nine a wavefront, against the 8-lane groups: with
+    fast orbits of many steps among them, more epochs inside a step and in
+    all than a wavefront's lanes hold, and none of the last launch's state."""
+    torch, api = torch_cuda
+    case = synth.survey_case(n_obj=n, n_frames=0, neo_frac=0.3)
+    eph = api.DeviceEphemeris.from_synth(case.ephem)
+    x0 = _dev_x(torch, case.x0)
+    t_out = np.concatenate([np.linspace(0.0, 12.0, 70 if n < 100000 else 3), [span]])
+    for back in (False, True):
+        t0, t = (span, span - t_out) if back else (0.0, t_out)
+        x, s = api.propagate(eph, x0, t0, t)
+        y, r = api.propagate(eph, x0, t0, t, api.default_opts(lanes_per_body=8))
+        assert torch.equal(s, r) and int(s.abs().max()) == 0
+        d = (x - y).abs().max().item()
+        _say(f"n {n} back {back}: max |dx| vs 8-lane groups {d:.3e}")
+        assert d < 1e-10
+
+
+@pytest.mark.parametrize("n", [40, 3000, 9300])
+@pytest.mark.parametrize("table", ["degree 9", "J2 without Eq. A.3", "four bodies", "no J2", "no Eq. A.3"])
+def test_propagate_other_tables(torch_cuda, table, n):
+    """Perturber tables that the unrolled force does not cover, in each of
+    the wavefront layouts, against the one-lane integrator."""
+    torch, api = torch_cuda
+    case = synth.survey_case(n_obj=n, n_frames=0, neo_frac=0.2)
+    e = case.ephem
+    flags, j2 = e.flags.copy(), e.j2.copy()
+    bodies = list(range(e.n_body))
+    if table == "J2 without Eq. A.3": flags[np.nonzero(j2[:, 0])[0][-1]] = 0
+    if table == "four bodies": bodies = bodies[:4]
+    if table == "no J2": j2[:] = 0.0
+    if table == "no Eq. A.3": flags[:] = 0
+    coef = e.coef[bodies][..., :10] if table == "degree 9" else e.coef[bodies]
+    e = dataclasses.replace(e, coef=np.ascontiguousarray(coef), gm=e.gm[bodies], flags=flags[bodies],
+                            names=[e.names[b] for b in bodies], j2=np.ascontiguousarray(j2[bodies]))
+    eph = api.DeviceEphemeris.from_synth(e)
+    x0 = _dev_x(torch, case.x0)
+    t_out = [1.0, 30.0, 60.0]
+    x, s = api.propagate(eph, x0, 0.0, t_out)
+    y, r = api.propagate(eph, x0, 0.0, t_out, api.default_opts(lanes_per_body=1))
+    assert torch.equal(s, r) and int(s.abs().max()) == 0
+    d = (x - y).abs().max().item()
+    _say(f"{table}, n {n}: max |dx| vs one lane per object {d:.3e}")
+    assert d < 1e-11
+
+
 @pytest.mark.parametrize("n", [1, 8, 9, 200])
 @pytest.mark.parametrize("lanes", [0, 1, 7, 8])
 def test_propagate_all_objects_of_a_wavefront_fail(torch_cuda, n, lanes):
