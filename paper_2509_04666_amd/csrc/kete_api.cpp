@@ -871,13 +871,17 @@ int kete_fov_check(const kete_ephem_t* eph, const double* x_epoch, int32_t* stat
         HIPCHK(fill_zero(counters, kFovCounters * sizeof(unsigned long long), s));
         HIPCHK(fill_zero(P.fail, (size_t)n_obj * sizeof(int32_t), s));
         HIPCHK(fov_single_job_layout(b_poff, b_obj0, b_xoff, b_G, b_koff, n_batch, n_obj, G, s));
+        P.direct = fov_is_direct((double)n_obj * (double)F, P.n_pairs_total);
         HIPCHK(fov_prepare(P, qkey, cnt, cnt, scan_scratch, s));
         P.n_wide = counters + 6;
-        HIPCHK(fov_sort_objects(P, okey, orank, ocnt, ostart, osorted, osub, oscan, s));
-        P.obj_sorted = osorted;
-        P.obj_start = ostart;
-        P.obj_count = ocnt;
-        {
+        if (P.direct) {
+            TimedScope tj(kTimeFovJoin, s);
+            HIPCHK(fov_direct(P, qkey, s));
+        } else {
+            HIPCHK(fov_sort_objects(P, okey, orank, ocnt, ostart, osorted, osub, oscan, s));
+            P.obj_sorted = osorted;
+            P.obj_start = ostart;
+            P.obj_count = ocnt;
             TimedScope tj(kTimeFovJoin, s);
             HIPCHK(fov_candidates(P, icnt, istart, items, (unsigned int*)(counters + kFovCursorBase), oscan, wscan, s));
         }
@@ -1063,6 +1067,7 @@ namespace {
 struct BatchDims {
     int64_t F = 0, B = 0, NP = 0, nkeys = 0, cand_cap = 0, pairs_cap = 0, max_batch_obj = 0;
     int32_t n_tiles = 0, n_sub = 1;
+    double obj_frames = 0.0;                    // sum over batches of objects x frames
     std::vector<int2> tiles;
     std::vector<int64_t> b_poff, b_xoff, b_koff;
     std::vector<int32_t> b_obj0, b_G;
@@ -1129,6 +1134,7 @@ int batch_dims(const kete_ephem_t* eph, const kete_batch_t* bt, int64_t pairs_ca
             d.b_obj0[b] = (int32_t)J[j].obj_off;
             d.b_G[b] = G;
         }
+        d.obj_frames += (double)J[j].n_obj * (double)nf;
         np += J[j].n_obj;
         nk += (int64_t)G * G * G + 1;
         d.max_batch_obj = std::max<int64_t>(d.max_batch_obj, J[j].n_obj);
@@ -1357,12 +1363,16 @@ int kete_batch_run(const kete_ephem_t* eph, const kete_batch_t* batch, int64_t p
     HIPCHK(fill_zero(w.counters, kFovCounters * sizeof(unsigned long long), s));
     HIPCHK(fill_zero(P.fail, (size_t)std::max<int64_t>(batch->n_bodies, 1) * sizeof(int32_t), s));
     if (dc.B > 0 && dc.F > 0 && dc.NP > 0) {
+        P.direct = fov_is_direct(dc.obj_frames, dc.NP);
         HIPCHK(fov_prepare(P, w.qkey, w.cnt, w.cnt, w.scan_scratch, s));
-        HIPCHK(fov_sort_objects(P, w.okey, w.orank, w.ocnt, w.ostart, w.osorted, w.osub, w.oscan, s));
-        P.obj_sorted = w.osorted;
-        P.obj_start = w.ostart;
-        P.obj_count = w.ocnt;
-        {
+        if (P.direct) {
+            TimedScope tj(kTimeFovJoin, s);
+            HIPCHK(fov_direct(P, w.qkey, s));
+        } else {
+            HIPCHK(fov_sort_objects(P, w.okey, w.orank, w.ocnt, w.ostart, w.osorted, w.osub, w.oscan, s));
+            P.obj_sorted = w.osorted;
+            P.obj_start = w.ostart;
+            P.obj_count = w.ocnt;
             TimedScope tj(kTimeFovJoin, s);
             HIPCHK(fov_candidates(P, w.icnt, w.istart, w.items, (unsigned int*)(w.counters + kFovCursorBase), w.oscan,
                                   w.wscan, s));

@@ -596,6 +596,50 @@ def test_fov_survey_geometry(torch_cuda, orc):
         assert abs(_edge_of(orc, case.ephem, xe, order, off, t_ref, fr, (f, s, loc[j]))) < MAS, (f, s, j)
 
 
+@pytest.mark.parametrize("n_obj", [1, 63, 64, 65, 3000])
+@pytest.mark.parametrize("n_sub", [1, 16, 64, 120])
+def test_fov_few_frames_a_batch(torch_cuda, n_sub, n_obj):
+    """Batches of few frames, which are joined without a sky grid, give the
+    pairs that the sorted join finds: the same frames three times over are
+    enough of them for that one.  No frames, one, and more than a wavefront's
+    share to a batch; among the objects a failed one, one without a state,
+    one at the observer and one too fast for a bound."""
+    torch, api = torch_cuda
+    sizes = [1, 0, 5, 64, 65, 130]
+    case = synth.footprint_case(n_obj=3000, n_frames=sum(sizes), span=12.0)
+    fr = case.frames
+    if n_sub == 1: fr = dataclasses.replace(fr, normals=np.ascontiguousarray(fr.normals[:, :1]))
+    if n_sub in (16, 120): fr = _random_layout_frames(np.random.default_rng(83), fr, n_sub=n_sub)
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    order = np.argsort(fr.t, kind="stable").astype(np.int32)
+    ts = fr.t[order]
+    t_ref = np.array([0.5 * (ts[a] + ts[b - 1]) if b > a else 0.5 * (ts[a - 1] + ts[a])
+                      for a, b in zip(off[:-1], off[1:])])
+    eph = api.DeviceEphemeris.from_synth(case.ephem)
+    x, st = api.propagate(eph, _dev_x(torch, case.x0[:n_obj]), 0.0, t_ref)
+    if n_obj > 60:
+        st[3] = 1
+        x[5, 7] = float("nan")
+        x[4, 9, :3] = torch.as_tensor(fr.obs[order[off[4]]], device="cuda")
+        x[3, 11, 3:] = 100.0
+    b1 = api.Batches.from_host(order, off, t_ref)
+    F, R = fr.t.size, 3
+    # copy c of frame f is frame c F + f, in the same batch
+    order3 = np.concatenate([(order[a:b, None] + F * np.arange(R)).ravel() for a, b in zip(off[:-1], off[1:])])
+    b3 = api.Batches.from_host(order3.astype(np.int32), R * off, t_ref)
+    fr3 = dataclasses.replace(fr, t=np.tile(fr.t, R), obs=np.tile(fr.obs, (R, 1)),
+                              normals=np.tile(fr.normals, (R, 1, 1, 1)))
+    s1, s3 = st.clone(), st.clone()
+    pf, ps, po, c1 = api.fov_check(eph, x, b1, api.DeviceFrames.from_synth(fr), s1, return_stats=True)
+    qf, qs, qo, c3 = api.fov_check(eph, x, b3, api.DeviceFrames.from_synth(fr3), s3, return_stats=True)
+    _say(f"n_obj {n_obj}, n_sub {n_sub}: {pf.numel()} pairs, stats {c1.tolist()} against {c3.tolist()}")
+    assert torch.equal(s1, s3)
+    assert n_obj < 3000 or pf.numel() > 0
+    # both lists are sorted by (frame, sub-frame, object): the copies follow each other
+    assert torch.equal(qf, torch.cat([pf + c * F for c in range(R)]).to(qf.dtype))
+    assert torch.equal(qs, ps.repeat(R)) and torch.equal(qo, po.repeat(R))
+
+
 def test_fov_capacity_and_empty(torch_cuda, orc):
     torch, api = torch_cuda
     from paper_2509_04666_amd import _lib
