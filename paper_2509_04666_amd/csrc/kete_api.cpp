@@ -22,7 +22,7 @@
 
 namespace kete {
 hipError_t launch_hpref_init(const double* x0, double* h_pref, uint32_t* keys, int n, double mu, double dt_lo,
-                             double dt_hi, int n_class, hipStream_t s);
+                             double dt_hi, int n_class, int n_epochs, hipStream_t s);
 hipError_t launch_body_sort(const uint32_t* keys, int n, int n_class, int32_t* perm, int32_t* tmp, int32_t* counts,
                             const int32_t** n_first, hipStream_t s);
 int solo_waves_for(int n, bool classes);
@@ -632,17 +632,19 @@ int kete_propagate_nbody(const kete_ephem_t* eph, const double* x0, double t0, i
         }
         P.state_in = e0 == 0 ? x0 : state;
         P.state = e1 + 1 < n_out ? state : nullptr;
-        HIPCHK(launch_hpref_init(P.state_in, h_pref, ncls > 1 ? sorts.keys : nullptr, (int)n_obj, E.gm[0], dt_lo, dt_hi,
-                                 ncls, s));
-        if (ncls > 1) {
+        P.solo_waves = opts->lanes_per_body == 7 ? solo_waves_for((int)n_obj, ncls > 1) : 0;
+        // wavefronts of one object, all of them on the chip at once, need no order
+        const bool sorted = ncls > 1 && P.solo_waves < n_obj;
+        HIPCHK(launch_hpref_init(P.state_in, h_pref, sorted ? sorts.keys : nullptr, (int)n_obj, E.gm[0], dt_lo, dt_hi,
+                                 ncls, (int)(e1 - e0), s));
+        if (sorted) {
             HIPCHK(launch_body_sort(sorts.keys, (int)n_obj, ncls, perm, sorts.tmp, sorts.counts, &P.n_solo, s));
             P.perm = perm;
         } else {
             P.perm = nullptr;
             P.n_solo = nullptr;
         }
-        P.solo_waves = opts->lanes_per_body == 7 ? solo_waves_for((int)n_obj, ncls > 1) : 0;
-        if (P.solo_waves == n_obj || P.solo_waves == 0) P.n_solo = nullptr;
+        if (P.solo_waves == 0) P.n_solo = nullptr;
         P.win = dwin + first;
         P.t_begin = win[first].t_a;
         P.t_only = win[last].t_b;
@@ -1045,7 +1047,7 @@ int kete_propagate_adjoint(const kete_ephem_t* eph, int32_t mode, const double* 
     if (mode == KETE_ADJ_FWD) {
         HIPCHK(fill_zero(status, (size_t)n_obj * sizeof(int32_t), s));
         HIPCHK(launch_hpref_init(x0, h_pref, ncls > 1 ? sorts.keys : nullptr, (int)n_obj, E.gm[0], 0.0, t_end - t0,
-                                 ncls, s));
+                                 ncls, 0, s));
         if (ncls > 1) {
             HIPCHK(launch_body_sort(sorts.keys, (int)n_obj, ncls, perm, sorts.tmp, sorts.counts, nullptr, s));
         } else {

@@ -336,7 +336,8 @@ __global__ void k_iota(int32_t* __restrict__ perm, int n) {
 // heliocentric: the Sun is within 0.01 au of the barycentre, which only
 // blurs the ordering).
 __global__ void k_hpref_init(const double* __restrict__ x0, double* __restrict__ h_pref, uint32_t* __restrict__ keys,
-                             int n, double mu, double dt_lo, double dt_hi, int n_class, double h_ref) {
+                             int n, double mu, double dt_lo, double dt_hi, int n_class, double h_ref,
+                             int keep_order) {
     const long j = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= n) return;
     double tm = 0.0;
@@ -354,9 +355,15 @@ __global__ void k_hpref_init(const double* __restrict__ x0, double* __restrict__
         hi = 1;
         lo = (uint32_t)fmin(frac * kCritTimeBins, kCritTimeBins - 1.0);
     } else {
-        const double c = (h > 0.0 && h < kInf) ? floor(kClassSub * log2(h / h_ref)) : (double)(n_class - 3);
+        // With keep_order the bodies that cross the span in one step stay in
+        // the order of their index, so that their states at the epochs inside
+        // it are written next to each other (the 1,368 epochs of a day for
+        // 100,000 bodies: 7.8 -> 2.8 ms).
+        const bool one = keep_order && h >= span;
+        const double hs = one ? span : h;
+        const double c = (hs > 0.0 && hs < kInf) ? floor(kClassSub * log2(hs / h_ref)) : (double)(n_class - 3);
         hi = 2u + (uint32_t)fmin(fmax(c, 0.0), (double)(n_class - 3));
-        lo = (uint32_t)fmin(frac * kTimeBins, kTimeBins - 1.0);
+        lo = one ? 0u : (uint32_t)fmin(frac * kTimeBins, kTimeBins - 1.0);
     }
     keys[j] = hi << 16 | lo;
 }
@@ -427,11 +434,15 @@ hipError_t launch_nbody(const NbodyParams& p, int block, int lanes_per_body, hip
     return hipGetLastError();
 }
 
+// Epochs from which bodies of one step keep their order: an epoch of 100,000
+// of them costs 3.6 us less to write in order, and their wavefronts 3 us more
+// where near orbits, whose corrector takes more sweeps, are not kept apart.
+constexpr int kOrderEpochs = 4;
 hipError_t launch_hpref_init(const double* x0, double* h_pref, uint32_t* keys, int n, double mu, double dt_lo,
-                             double dt_hi, int n_class, hipStream_t s) {
+                             double dt_hi, int n_class, int n_epochs, hipStream_t s) {
     if (n == 0) return hipSuccess;
     hipLaunchKernelGGL(k_hpref_init, dim3((n + 255) / 256), dim3(256), 0, s, x0, h_pref, keys, n, mu, dt_lo, dt_hi,
-                       n_class, 1.0 / 64.0);
+                       n_class, 1.0 / 64.0, n_epochs >= kOrderEpochs);
     return hipGetLastError();
 }
 

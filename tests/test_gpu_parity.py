@@ -424,6 +424,22 @@ def test_lone_paired_and_grouped_objects(torch_cuda, n, span):
         assert d < 1e-10
 
 
+@pytest.mark.parametrize("n,n_out", [(2049, 5), (9300, 3), (9300, 4), (9300, 70)])
+def test_many_epochs_of_a_day(torch_cuda, n, n_out):
+    """Objects that cross the span in one step keep their order when their
+    epochs are many; the states are those of the unsorted run."""
+    torch, api = torch_cuda
+    case = synth.survey_case(n_obj=n, n_frames=0, neo_frac=0.3)
+    eph = api.DeviceEphemeris.from_synth(case.ephem)
+    x0 = _dev_x(torch, case.x0)
+    for end in (1.0, -1.0, 4.0):
+        t_out = np.linspace(0.0, end, n_out + 1)[1:]
+        x, s = api.propagate(eph, x0, 0.0, t_out)
+        y, r = api.propagate(eph, x0, 0.0, t_out, api.default_opts(n_buckets=1))
+        assert torch.equal(s, r) and int(s.abs().max()) == 0
+        assert (x - y).abs().max().item() < 1e-12
+
+
 @pytest.mark.parametrize("n", [40, 3000, 9300])
 @pytest.mark.parametrize("table", ["degree 9", "J2 without Eq. A.3", "four bodies", "no J2", "no Eq. A.3"])
 def test_propagate_other_tables(torch_cuda, table, n):
