@@ -1172,6 +1172,10 @@ struct BatchWs {
     unsigned int* tile_counter;
     double* group_const;
     int32_t* perm;
+    uint32_t* keys;
+    double* job_ext;
+    int32_t *job_solo, *solo_hist, *tile_order;
+    int2* solo;
     FovParams P;
     int32_t *qkey, *cnt, *fcnt, *fstart, *okey, *orank, *osorted, *osub, *ostart, *ocnt, *icnt, *istart;
     ulonglong2* items;
@@ -1187,6 +1191,12 @@ size_t batch_carve(const BatchDims& d, const kete_batch_t* bt, char* base, Batch
     w.tile_counter = c.take<unsigned int>(64);
     w.group_const = c.take<double>(kGroupConstDoubles);
     w.perm = c.take<int32_t>((size_t)std::max<int64_t>(bt->n_bodies, 1));
+    w.keys = c.take<uint32_t>((size_t)std::max<int64_t>(bt->n_bodies, 1));
+    w.job_ext = c.take<double>((size_t)2 * std::max(bt->n_jobs, 1));
+    w.job_solo = c.take<int32_t>((size_t)std::max(bt->n_jobs, 1));
+    w.solo = c.take<int2>((size_t)kBatchSolo);
+    w.solo_hist = c.take<int32_t>((size_t)2 * (kSoloBins + 1) + 2 * kTileBins);
+    w.tile_order = c.take<int32_t>((size_t)std::max(d.n_tiles, 1));
     FovParams& P = w.P;
     std::memset(&P, 0, sizeof(P));
     P.fcap = c.take<double>((size_t)d.F * 8);
@@ -1304,6 +1314,14 @@ int kete_batch_run(const kete_ephem_t* eph, const kete_batch_t* batch, int64_t p
     B.x_out = x_out;
     B.status = status;
     B.perm = w.perm;
+    B.keys = w.keys;
+    B.job_ext = w.job_ext;
+    B.job_solo = w.job_solo;
+    B.solo = w.solo;
+    B.all_solo = batch->n_bodies <= kSoloAll && dc.n_tiles <= kSoloAll;
+    B.solo_hist = w.solo_hist;
+    B.tile_hist = w.solo_hist + 2 * (kSoloBins + 1);
+    B.tile_order = w.tile_order;
     B.n_buckets = bucket_count(opts);
     B.window_segs = window_segs(opts);
     B.max_iter = opts->max_iter;

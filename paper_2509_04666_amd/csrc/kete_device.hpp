@@ -489,6 +489,16 @@ __device__ __forceinline__ double lane_value(double v, int m) {
 }
 
 // Wave-wide reductions over the 64 lanes (results are wave-uniform).
+// True in the wavefront's first lane, in a form the optimizer cannot carry
+// from one pass of a loop to the next: knowing that a lane is not the first,
+// the compiler sent the other lanes of a loop that begins with
+//   if (lane == 0) at = atomicAdd(...);  at = readfirstlane(at);
+// back to the readfirstlane by themselves, and they took entry 0 for ever.
+__device__ __forceinline__ bool first_lane(int lane) {
+    asm volatile("" : "+v"(lane));
+    return lane == 0;
+}
+
 __device__ __forceinline__ double wave_max(double x) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) x = fmax(x, __shfl_xor(x, off, kWave));

@@ -959,7 +959,7 @@ __device__ __forceinline__ bool take_slice(unsigned int* __restrict__ cursors, i
         const int lo = (int)((int64_t)n * x / kXcds), hi = (int)((int64_t)n * (x + 1) / kXcds);
         unsigned int* c = cursors + kCursorStride * x;
         int at = 0;
-        if ((threadIdx.x & 63) == 0) {
+        if (first_lane(threadIdx.x & 63)) {
             at = hi - lo;
             const bool look = tried > 0 || at < (int)(gridDim.x * (blockDim.x / kWave)) / kXcds;
             if (at > 0 && (!look || (int)__hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < at))

@@ -193,6 +193,10 @@ constexpr int kMaxBuckets = 256;
 //     predicted step above h_ref, then kTimeBins classes of that time.
 constexpr double kCritSteps = 100.0;
 constexpr double kSoloSteps = 150.0, kSoloMaxStep = 5.0;
+// lanes of an object that has a wavefront of its own, and the list length up
+// to which every object has one: two wavefronts a SIMD
+constexpr int kSoloAll = 2048;
+constexpr int kSoloLanes = 56;
 constexpr int kClassSub = 2;
 constexpr int kTimeBins = 64;
 constexpr int kCritTimeBins = 256;

@@ -21,7 +21,6 @@ hipError_t launch_bucket(const BucketParams& p, hipStream_t s);
 
 namespace {
 
-constexpr int kSoloLanes = 56;
 
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_nbody(const NbodyParams p) {
@@ -378,7 +377,7 @@ __global__ void k_hpref_init(const double* __restrict__ x0, double* __restrict__
 // 100,000-object year whose other wavefronts were done in 2.4 ms (2.8 ms with
 // their own).  In a longer launch their wavefronts end among the others:
 // 750,000 objects take 17.1 ms either way.
-constexpr int kSoloAll = 2048, kSoloSome = 1024, kSoloSomeObj = 220000;
+constexpr int kSoloSome = 1024, kSoloSomeObj = 220000;
 // Two lanes per node (4 objects a wavefront) up to here: at most two
 // wavefronts a SIMD, whose sweeps are half as long.
 //   (20,011 objects carried back five years, the heaviest 1,024 of them

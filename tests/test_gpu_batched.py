@@ -239,3 +239,35 @@ def test_batched_failed_jobs_write_every_epoch(torch_cuda):
         assert np.all(np.isnan(xk[away])), k
         if away.any():
             assert np.all(status[runner.obj_off[k]:runner.obj_off[k + 1]] == 2), k
+
+
+@pytest.mark.parametrize("sizes", [(1, 8, 9, 10, 0, 130), (1, 2500, 700, 3)])
+def test_batched_lone_bodies(torch_cuda, sizes):
+    """Jobs of fast orbits over 400 days: bodies of many steps take a
+    wavefront of their own, the first ones of the whole batch when they are
+    more than it has room for, and the others follow in tiles.  Every state
+    is the one of the job run by itself in 8-lane groups."""
+    torch, api = torch_cuda
+    model = synth.PlanetModel.make()
+    ephem = synth.make_ephemeris(model, -8.0, 52)
+    rng = np.random.default_rng(72)
+    jobs = []
+    for n in sizes:
+        el = np.concatenate([synth.neo_elements(rng, n - n // 4), synth.main_belt_elements(rng, n // 4)])
+        fr = synth.frames_targeted(rng, model, synth.main_belt_elements(rng, 20), 0.0, 390.0, 12)
+        jobs.append((synth.bodies_from_elements(model, el, 0.0) if n else np.zeros((0, 6)), 0.0, fr))
+    eph = api.DeviceEphemeris.from_synth(ephem)
+    runner = api.BatchRunner(eph, jobs)
+    runner.x_out.fill_(float("nan"))
+    runner.run()
+    torch.cuda.synchronize()
+    x = runner.x_out
+    for k, (x0, t0, _) in enumerate(jobs):
+        n, ep, off = x0.shape[0], runner.job_epochs[k], runner.jobs_host[k].xout_off
+        if n == 0: continue
+        y, st = api.propagate(eph, _dev(torch, x0), t0, ep, api.default_opts(lanes_per_body=8))
+        assert int(st.abs().max()) == 0
+        assert int(runner.status[runner.obj_off[k]:runner.obj_off[k + 1]].abs().max()) == 0
+        d = (x[off:off + 6 * n * ep.size].reshape(ep.size, n, 6) - y).abs().max().item()
+        _say(f"job of {n}: max |dx| vs its own run {d:.3e}")
+        assert d < 4e-10, k
