@@ -7,12 +7,13 @@
 // polynomial, hopped with light time to the emission point (Sect. 2) and
 // turned into RA/Dec.
 //
-// Backward: the discrete adjoint of that forward map.  Checkpoint
-// segments are processed last to first: the segment's steps are
-// recomputed from its checkpoint (same step sequence, bit for bit) while each step's start, size and force Jacobians at its 8 nodes
-// are stored; the steps are then swept in reverse, solving the linear
-// stage equations of the step's transpose by fixed-point iteration.  The
-// recompute of the next segment runs on a second stream during a sweep.  The light-time hop's
+// Backward: the discrete adjoint of that forward map, swept over the steps
+// last to first, a wavefront at a time.  A step's start and node increments
+// were recorded by the forward (or, past its room for them, are recomputed
+// checkpoint segment by segment, the same steps bit for bit); the force
+// Jacobians at its 8 nodes follow from them, and the linear stage equations
+// of the step's transpose are solved by fixed-point iteration, all in
+// registers.  The light-time hop's
 // Jacobian comes from one forward-mode (six-direction dual number)
 // evaluation of the universal-variable solution at its converged anomaly
 // plus the implicit light-time term.
@@ -20,8 +21,6 @@
 
 #include "kete_adjoint.hpp"
 #include "kete_radau.hpp"
-
-#include <mutex>
 
 namespace kete {
 namespace {
@@ -192,8 +191,9 @@ __device__ void hop_vjp(const AdjParams& p, const SunGlobal& sun, double t_obs, 
 // that a recompute repeats the forward's steps exactly (extrapolated
 // corrector starts included).  Lanes 0..7 of the group write the first
 // eight values, lanes 0..3 the force, lanes 0..6 their node's increment
-// and lane 7 the step and the time.
-__device__ __forceinline__ void save_ckpt_g8(const AdjParams& p, int c, int j, int gl, const G8State& S, double t) {
+// and lane 7 the step, the time and the number of steps before it.
+__device__ __forceinline__ void save_ckpt_g8(const AdjParams& p, int c, int j, int gl, const G8State& S, double t,
+                                             int n_steps) {
     double* ck = p.ckpt + ((size_t)c * p.n_obj + j) * kCkptDoubles;
     const double v = gl < 6 ? state_component(S.x0, S.v0, gl)
                             : gl == 6 ? S.hw : (S.active ? 0.0 : (double)(S.status ? S.status : 1));
@@ -206,6 +206,7 @@ __device__ __forceinline__ void save_ckpt_g8(const AdjParams& p, int c, int j, i
     } else {
         ck[33] = S.hprev;
         ck[34] = t;
+        ck[35] = (double)n_steps;
     }
 }
 
@@ -222,24 +223,61 @@ __device__ __forceinline__ void init_lane_state(const AdjParams& p, bool valid, 
     S.haveF0 = false;
 }
 
-template <int NB, int NGR, int NJ2, int DEG1>
-__global__ __launch_bounds__(64, 3) void k_adjoint_fwd(const AdjParams p) {
-    extern __shared__ __align__(16) double smem[];
+// One step of this lane's object into its slot of the record at rec (see
+// kStepRec).
+__device__ __forceinline__ void write_step(double* __restrict__ rec, int gl, double ts, double h, const double dn[3],
+                                           const G8State& S) {
+    const double q = gl < 6 ? state_component(S.x0, S.v0, gl) : ts;
+    double2* w = reinterpret_cast<double2*>(rec + 4 * gl);
+    w[0] = gl < 7 ? make_double2(dn[0], dn[1]) : make_double2(S.F0[0], S.F0[1]);
+    w[1] = gl < 7 ? make_double2(dn[2], q) : make_double2(S.F0[2], h);
+}
+
+// Lane of node lane i of this lane's group (and of the same place among the
+// lanes of a node), for the two layouts of the adjoint kernels: eight lanes
+// an object, or one object with eight lanes a node.
+template <int G>
+__device__ __forceinline__ int node_lane(int lane, int i) {
+    static_assert(G == 8 || G == 56, "layouts of the adjoint");
+    return G == 8 ? (lane & ~7) + i : 8 * i + (lane & 7);
+}
+
+// The objects of one wavefront, the records of its steps and their layout.
+struct AdjWave {
+    long first;             // its first object in the order, or -1: none
+    bool lone;              // one object
+    double* rec;
+};
+__device__ __forceinline__ AdjWave adj_wave(const AdjParams& p) {
+    const long wave = blockIdx.x;
+    const long solo = p.n_solo ? min(*p.n_solo, p.solo_waves) : p.solo_waves;
+    const size_t per = (size_t)(p.rec_fwd + p.s_max) * kStepRec;
+    AdjWave w;
+    w.lone = wave < p.solo_waves;
+    const long g = wave - p.solo_waves;
+    w.first = w.lone ? (wave < solo ? wave : -1) : solo + g * kAdjBodies;
+    if (w.first >= p.n_obj) w.first = -1;
+    w.rec = p.rec + per * (w.lone ? (size_t)wave : (size_t)p.solo_waves + (size_t)g * kAdjBodies);
+    return w;
+}
+
+template <int G, int NB, int NGR, int NJ2, int DEG1>
+__device__ __forceinline__ void adj_fwd_wave(const AdjParams& p, const AdjWave& w, const GroupConst& gc, double* wt_all,
+                                             double* smem) {
     const int lane = threadIdx.x;
-    const GroupMap<kGroup> M(lane);
+    constexpr int kBodies = GroupMap<G>::kBodies;
+    const GroupMap<G> M(lane);
     const int gl = M.gl;
     const EphemArgs& E = p.eph;
-    __shared__ __align__(16) GroupConst gc;
-    load_group_const(p.group_const, &gc, lane, kWave);
-    const G8Lds T = g8_lds<kGroup>(E, smem, M.grp);
-    g8_table_init<kGroup>(E, lane, smem);
-    __syncthreads();
-    const long gi = ((long)blockIdx.x * 64 + lane) / kGroup;
-    const bool valid = gi < p.n_obj;
-    const int j = valid ? p.perm[gi] : 0;
+    const G8Lds T = g8_lds<G>(E, smem, M.grp);
+    g8_table_init<G>(E, lane, smem);
+    const long gi = w.first + M.grp;
+    const bool valid = gi < p.n_obj, writer = valid && M.sub == 0;
+    const int j = valid ? (p.perm ? p.perm[gi] : (int)gi) : 0;
+    double* rec = w.rec + M.grp * kStepRec;
     G8State S;
     init_lane_state(p, valid, j, S);
-    S.hw = groups_min(valid ? p.h_pref[j] : kInf);
+    S.hw = groups_min<G>(valid ? p.h_pref[j] : kInf);
     if (!(S.hw < kInf)) S.hw = p.h_init;
     S.t = p.t0;
     G8Count C;
@@ -255,13 +293,13 @@ __global__ __launch_bounds__(64, 3) void k_adjoint_fwd(const AdjParams p) {
         k_buf = kobs;
         t_buf = valid && kobs + gl < K ? tob[kobs + gl] : kInf;
     };
-    auto next_time = [&]() { return __shfl(t_buf, kobs - k_buf, kGroup); };        // the whole group calls it
+    auto next_time = [&]() { return __shfl(t_buf, node_lane<G>(lane, kobs - k_buf), kWave); };        // the whole group calls it
     auto advance = [&]() {
         if (++kobs - k_buf == kGroup) load_times();
     };
     load_times();
     auto store_obs = [&](double v) {
-        if (gl < 6) p.obs_state[((size_t)j * K + kobs) * 6 + gl] = v;
+        if (gl < 6 && M.sub == 0) p.obs_state[((size_t)j * K + kobs) * 6 + gl] = v;
     };
     // observations at the start epoch
     for (;;) {
@@ -270,19 +308,20 @@ __global__ __launch_bounds__(64, 3) void k_adjoint_fwd(const AdjParams p) {
         const double v = state_component(S.x0, S.v0, gl < 6 ? gl : 5);
         if (at) { store_obs(v); advance(); }
     }
-    __shared__ __align__(16) double obs_wt[kGroup][16];
-    double* wt = obs_wt[M.grp];
+    double* wt = wt_all + 16 * M.grp;
     const bool vel = gl >= 3;
     const int comp = vel ? (gl < 6 ? gl - 3 : 2) : gl;
     // Checkpoint c (1 .. C - 1) is the state at the first accepted step
     // start at or after t0 + c ckpt_days (wave-uniform: the wavefront's
     // objects share their steps), so steps are not cut at checkpoints.
-    int c_next = 1;
+    int c_next = 1, n_steps = 0;
     auto visit = [&](double ts, double h, const double dn[3], const G8State& St) {
         while (c_next < p.n_ckpt && ts >= p.t0 + c_next * p.ckpt_days) {
-            if (valid) save_ckpt_g8(p, c_next, j, gl, St, ts);
+            if (writer) save_ckpt_g8(p, c_next, j, gl, St, ts, n_steps);
             ++c_next;
         }
+        if (writer && n_steps < p.rec_fwd) write_step(rec + (size_t)n_steps * kBodies * kStepRec, gl, ts, h, dn, St);
+        ++n_steps;
         const double te = ts + h;
         double tk = next_time();
         auto pending = [&]() { return valid && St.active && kobs < K && (h > 0 ? tk <= te : tk >= te); };
@@ -298,16 +337,31 @@ __global__ __launch_bounds__(64, 3) void k_adjoint_fwd(const AdjParams p) {
             pend = pending();
         } while (__ballot(pend) != 0ull);
     };
-    if (valid) save_ckpt_g8(p, 0, j, gl, S, S.t);
+    if (writer) save_ckpt_g8(p, 0, j, gl, S, S.t, 0);
     // (windows, if asked for, end on the fixed grid of aligned_end, so a
     // recompute that starts at a checkpoint cuts its steps where this run did)
     while (S.t < p.t_end)
-        g8_integrate<NB, NGR, NJ2, DEG1, kGroup>(
+        g8_integrate<NB, NGR, NJ2, DEG1, G>(
             p, gc, T, M, lane, aligned_end(S.t, p.t_end, E.t_start, E.seg_days, E.inv_seg, p.window_segs), S, C, visit);
     // checkpoints no step start reached: the end state
     for (; c_next <= p.n_ckpt; ++c_next)
-        if (valid) save_ckpt_g8(p, c_next, j, gl, S, p.t_end);
-    if (valid && gl == 0) p.status[j] = S.status;
+        if (writer) save_ckpt_g8(p, c_next, j, gl, S, p.t_end, n_steps);
+    if (writer && gl == 0) p.status[j] = S.status;
+}
+
+// The forward's wavefronts (see adj_wave): objects of many steps alone, as in
+// the propagation kernel, in one launch with the others.
+template <int NB, int NGR, int NJ2, int DEG1>
+__global__ __launch_bounds__(64, 2) void k_adjoint_fwd(const AdjParams p) {
+    extern __shared__ __align__(16) double smem[];
+    __shared__ __align__(16) GroupConst gc;
+    __shared__ __align__(16) double wt[kAdjBodies * 16];
+    const AdjWave w = adj_wave(p);
+    if (w.first < 0) return;                    // the whole block: one wavefront
+    load_group_const(p.group_const, &gc, threadIdx.x, kWave);
+    __syncthreads();
+    if (w.lone) adj_fwd_wave<kSoloLanes, NB, NGR, NJ2, DEG1>(p, w, gc, wt, smem);
+    else adj_fwd_wave<kGroup, NB, NGR, NJ2, DEG1>(p, w, gc, wt, smem);
 }
 
 // Sky position of every observation from its stored state (forward), one
@@ -393,113 +447,18 @@ __device__ __forceinline__ void load_adj_cols(const RadauConst& rc, int gl, AdjC
     }
 }
 
-// Backward, first half for checkpoint segment c: recompute the segment from
-// its checkpoint with the forward's grouping and step sequence
-// (one wavefront per block: the checkpoints' times differ between
-// wavefronts), storing each step's start and size and this lane's node
-// Jacobians (lane 7: node 0).  The step count (plus kSegOverflow when the
-// step store was too small) goes to seg_ns[wave].
-constexpr int kSegOverflow = 1 << 30;
-static_assert(kAdjLanes == kGroup, "adjoint wavefronts hold 8 objects");
-
-template <int NB, int NGR, int NJ2, int DEG1>
-__global__ __launch_bounds__(64, 2) void k_adj_recompute(const AdjParams p, const int c) {
-    extern __shared__ __align__(16) double smem[];
-    const int lane = threadIdx.x;
-    const GroupMap<kGroup> M(lane);
-    const int gl = M.gl;
-    const int jnode = gl < 7 ? gl + 1 : 0;          // node whose Jacobians this lane keeps
-    const EphemArgs& E = p.eph;
-    const long wave = blockIdx.x;
-    const long gi_raw = wave * kGroup + lane / kGroup;
-    const bool valid = gi_raw < p.n_obj;
-    const size_t gi = valid ? (size_t)gi_raw : 0;   // scratch slot (invalid groups read slot 0, never write)
-    const int j = valid ? p.perm[gi] : 0;
-    const size_t N = p.n_obj;
-    // this checkpoint's time and the next one's (the same for every object
-    // of the wavefront); a segment with no step start stores nothing
-    const double t_c = groups_max(valid ? p.ckpt[((size_t)c * N + j) * kCkptDoubles + 34] : -kInf);
-    const double t_stop = groups_max(valid ? p.ckpt[((size_t)(c + 1) * N + j) * kCkptDoubles + 34] : -kInf);
-    if (!(t_c < t_stop)) {
-        if (lane == 0) p.seg_ns[wave] = 0;
-        return;                                     // the whole block: one wavefront
-    }
-    __shared__ __align__(16) GroupConst gc;
-    load_group_const(p.group_const, &gc, lane, kWave);
-    const G8Lds T = g8_lds<kGroup>(E, smem, M.grp);
-    g8_table_init<kGroup>(E, lane, smem);
-    __syncthreads();
-    const NodeRow& R = gc.row[gl];
-    bool overflow_steps = false;
-    G8State S;
-    init_lane_state(p, false, j, S);
-    double hw = 0.0, hprev = -kInf;
-    bool have_f0 = false;
-    if (valid) {
-        const double* ck = p.ckpt + ((size_t)c * N + j) * kCkptDoubles;
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            S.x0[i] = ck[i]; S.v0[i] = ck[3 + i]; S.F0[i] = ck[8 + i];
-            S.Dp[i] = gl < 7 ? ck[12 + 3 * gl + i] : 0.0;
-        }
-        hw = ck[6];
-        S.active = ck[7] == 0.0;
-        have_f0 = ck[11] != 0.0;
-        hprev = ck[33];
-    }
-    S.hw = groups_max(valid ? hw : 0.0);        // the same value in every valid group
-    S.hprev = groups_max(hprev);                // likewise (invalid groups give -inf)
-    S.haveF0 = __ballot(have_f0) != 0ull;       // as in the forward at this checkpoint
-    S.t = t_c;
-    G8Count Cn;
-    int ns = 0;
-        auto store = [&](double ts, double h, const double dn[3], const G8State& St) {
-            if (ns >= p.s_max) { overflow_steps = true; return; }
-            double D[7][3];
-            g8_exchange(T.xg, gl, dn, D);
-            if (valid) {
-                double* sp = p.steps + (size_t)ns * kStepDoubles * N;
-                if (gl == 6) sp[gi] = ts;
-                if (gl == 7) sp[N + gi] = h;
-                // state at this lane's Jacobian node
-                double X[3], V[3];
-                const double hh = h * h;
-                #pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    if (jnode == 0) { X[i] = St.x0[i]; V[i] = St.v0[i]; continue; }
-                    double ax = R.hs2 * St.F0[i], av = R.s * St.F0[i];
-                    #pragma unroll
-                    for (int m = 0; m < 7; ++m) { ax = fma(R.A[m], D[m][i], ax); av = fma(R.B[m], D[m][i], av); }
-                    X[i] = fma(hh, ax, fma(R.s * h, St.v0[i], St.x0[i]));
-                    V[i] = fma(h, av, St.v0[i]);
-                }
-                double Jx[9], Jv[9];
-                accel_jac8<NB, NGR>(T.e8 + jnode * T.row, E, X, V, Jx, Jv);
-                double* jp = p.jac + (size_t)ns * 8 * kJacDoubles * N;
-                #pragma unroll
-                for (int q = 0; q < 9; ++q) {
-                    jp[((size_t)q * N + gi) * 8 + jnode] = Jx[q];
-                    jp[((size_t)(9 + q) * N + gi) * 8 + jnode] = Jv[q];
-                }
-            }
-            ++ns;
-        };
-    // the forward's steps (and windows) from the checkpoint on, until the
-    // step start where the forward took the next checkpoint
-    while (S.t < t_stop)
-        g8_integrate<NB, NGR, NJ2, DEG1, kGroup>(
-            p, gc, T, M, lane, aligned_end(S.t, p.t_end, E.t_start, E.seg_days, E.inv_seg, p.window_segs), S, Cn, store,
-            true, t_stop);
-    if (lane == 0 && wave * kGroup < p.n_obj) p.seg_ns[wave] = min(ns, p.s_max) | (overflow_steps ? kSegOverflow : 0);
-}
-
 // Constant rows of the reverse sweep, for the 8 lanes of a group: the
 // stage columns (AdjCols) and the dense-output rows alpha(sig) =
 // sum_k dr[k] sig^(k+2) + dr[16] sig^2, beta(sig) = sum_k dr[8+k] sig^(k+1)
 // + dr[17] sig of stage m = lane + 1 (lanes 0..6), and minus the sum over
-// the stages for lane 7.  One block of 64 threads.
-__global__ void k_adj_tables(const AdjParams p) {
+// the stages for lane 7.  The first block writes the
+// grouped kernels' constants, the second these.
+__global__ __launch_bounds__(320) void k_adj_consts(const AdjParams p) {
     const int lane = threadIdx.x;
+    if (blockIdx.x == 0) {
+        if (lane < kGroupConstDoubles) p.group_const[lane] = group_const_at(p.rc, lane);
+        return;
+    }
     if (lane >= kGroup) return;
     const RadauConst& rc = p.rc;
     AdjCols q;
@@ -522,64 +481,86 @@ __global__ void k_adj_tables(const AdjParams p) {
     dr[17] = lane < 7 ? 0.0 : 1.0;
 }
 
-// Backward, second half for checkpoint segment c: the reverse sweep over
-// the stored steps, one 8-lane group per object (lane m - 1 holds the
-// stage cotangent mu_m, lane 7 the step-start term), carrying the state
-// cotangent (lx, lv), the next observation and the overflow flag from
-// segment c + 1 in adj_state; segment 0 adds the observations at the start
-// epoch and writes the gradient.
-__global__ __launch_bounds__(64) void k_adj_sweep(const AdjParams p, const int c) {
+// Backward: one wavefront goes through its objects' steps last to first.
+// Lane m - 1 of an object (see GroupMap; with one object the eight lanes of a
+// node do the same) holds the stage cotangent mu_m, lane 7 the step-start
+// term; each forms the force Jacobians at its node (lane 7: the step start)
+// from the step's record.
+//   A wavefront waits on its own chain: the perturbers at the nodes, the
+// Jacobians, and some eight passes of the stage equations of a step (two
+// exchanges through LDS each).  With each checkpoint segment recomputed by
+// one kernel into memory and swept by another, forward and backward of
+// 100,000 objects x 20 observations over 60 d took 3.9 ms and of 20,000 2.6;
+// from the forward's records 3.3 and 2.2; with the objects of most steps
+// alone 2.5 and 1.5.
+template <int G, int NB, int NGR, int NJ2, int DEG1>
+__device__ __forceinline__ void adj_back_wave(const AdjParams& p, const AdjWave& w, const GroupConst& gc,
+                                              const AdjCols* cols, const double (*drow)[18], double* srec_all,
+                                              double* xw_all, double* smem) {
     const int lane = threadIdx.x;
-    const int gl = lane & (kGroup - 1);
-    const int jnode = gl < 7 ? gl + 1 : 0;
+    constexpr int kBodies = GroupMap<G>::kBodies;
+    const GroupMap<G> M(lane);
+    const int gl = M.gl;
+    const int jnode = gl < 7 ? gl + 1 : 0;          // node whose Jacobians this lane holds
+    const EphemArgs& E = p.eph;
     const RadauConst& rc = p.rc;
-    // exchange slots of the reverse sweep: [group][node lane][6] (W, U)
-    __shared__ double xw_all[kWave * 6];
-    double* xw = xw_all + (lane / kGroup) * kGroup * 6;
-    __shared__ AdjCols cols[kGroup];
-    __shared__ double drow[kGroup][18];      // own dense-output row (see below)
-    {
-        // the constant rows, computed once per call by k_adj_tables
-        const double* src = p.adj_tab;
-        double* dst = &cols[0].cA[0];
-        for (int i = lane; i < kAdjTabDoubles; i += kWave)
-            (i < kGroup * kAdjColDoubles ? dst[i] : drow[0][i - kGroup * kAdjColDoubles]) = src[i];
-    }
-    __syncthreads();
+    double* srec = srec_all + M.grp * kStepRec;
+    double* xw = xw_all + M.grp * kGroup * 6;       // exchange slots: [node lane][6] (W, U)
+    const G8Lds T = g8_lds<G>(E, smem, M.grp);
+    g8_table_init<G>(E, lane, smem);
+    const NodeRow& R = gc.row[gl];
     const AdjCols& Q = cols[gl];
     const double* dr = drow[gl];
-    const long wave = blockIdx.x;
-    const long gi_raw = wave * kGroup + lane / kGroup;
-    const bool valid = gi_raw < p.n_obj;
-    const size_t gi = valid ? (size_t)gi_raw : 0;
-    const int j = valid ? p.perm[gi] : 0;
     const size_t N = p.n_obj;
+    const long gi = w.first + M.grp;
+    const bool valid = gi < p.n_obj, writer = valid && M.sub == 0;
+    const int j = valid ? (p.perm ? p.perm[gi] : (int)gi) : 0;
+    const int j_first = p.perm ? p.perm[w.first] : (int)w.first;
     const int K = p.k_obs;
     const double* tob = p.t_obs + (size_t)j * K;
     const bool ok_final = valid && p.status[j] == 0;
+    // one step of every object of the wavefront, and this lane's slot of it
+    constexpr size_t kStep = (size_t)kBodies * kStepRec;
+    const int slot = M.grp * kStepRec + 4 * gl;
     double lx[3] = {0.0, 0.0, 0.0}, lv[3] = {0.0, 0.0, 0.0};
     int kb = K - 1;
     bool overflow_steps = false;
-    double* as = p.adj_state + (size_t)j * kAdjStateDoubles;
-    if (c < p.n_ckpt - 1 && valid) {
-#pragma unroll
-        for (int i = 0; i < 3; ++i) { lx[i] = as[i]; lv[i] = as[3 + i]; }
-        kb = (int)as[6];
-        overflow_steps = as[7] != 0.0;
-    }
-    const int sn = p.seg_ns[wave];
-    const int ns = sn & (kSegOverflow - 1);
-    overflow_steps = overflow_steps || (sn & kSegOverflow) != 0;
-    for (int st = ns - 1; st >= 0; --st) {
-        const double* sp = p.steps + (size_t)st * kStepDoubles * N;
-        const double ts = sp[gi];
-        const double h = valid ? sp[N + gi] : 1.0;
+
+    // The reverse of one step, its record in srec.
+    auto step_back = [&]() {
+        // (the same in every object)
+        const double ts = uniform(srec_all[4 * 6 + 3]), h = uniform(srec_all[4 * 7 + 3]);
         const double hh = h * h;
+        double D[7][3], x0[3], v0[3], F0[3];
+#pragma unroll
+        for (int m = 0; m < 7; ++m) {
+            const double2 a = *reinterpret_cast<const double2*>(srec + 4 * m);
+            const double2 b = *reinterpret_cast<const double2*>(srec + 4 * m + 2);
+            D[m][0] = a.x; D[m][1] = a.y; D[m][2] = b.x;
+            if (m < 3) x0[m] = b.y;
+            else if (m < 6) v0[m - 3] = b.y;
+        }
+        F0[0] = srec[28]; F0[1] = srec[29]; F0[2] = srec[30];
+        node_ephemeris8<NB, NGR, DEG1>(E, gc, T, ts, h, ts + h, true, lane);
+        double Jx[9], Jv[9];
+        {
+            // state at this lane's Jacobian node
+            double X[3], V[3];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                double ax = R.hs2 * F0[i], av = R.s * F0[i];
+#pragma unroll
+                for (int m = 0; m < 7; ++m) { ax = fma(R.A[m], D[m][i], ax); av = fma(R.B[m], D[m][i], av); }
+                X[i] = jnode == 0 ? x0[i] : fma(hh, ax, fma(R.s * h, v0[i], x0[i]));
+                V[i] = jnode == 0 ? v0[i] : fma(h, av, v0[i]);
+            }
+            accel_jac8<NB, NGR>(T.e8 + jnode * T.row, E, X, V, Jx, Jv);
+        }
         // output cotangents: the step end and the observations inside
-        double G[3], gx0[3], gv0[3];
-        #pragma unroll
+        double G0[3], gx0[3], gv0[3];
+#pragma unroll
         for (int i = 0; i < 3; ++i) {
-            G[i] = hh * Q.gA * lx[i] + h * Q.gB * lv[i];
+            G0[i] = hh * Q.gA * lx[i] + h * Q.gB * lv[i];
             gx0[i] = lx[i];
             gv0[i] = h * lx[i] + lv[i];
         }
@@ -592,13 +573,13 @@ __global__ __launch_bounds__(64) void k_adj_sweep(const AdjParams p, const int c
                 const double lX[3] = {og[0], og[1], og[2]}, lV[3] = {og[3], og[4], og[5]};
                 // this lane's dense-output weights at sig
                 double a = dr[7], b = dr[15];
-                #pragma unroll
+#pragma unroll
                 for (int k = 6; k >= 0; --k) { a = fma(a, sig, dr[k]); b = fma(b, sig, dr[8 + k]); }
                 a = (a + dr[16]) * sig * sig;
                 b = (b + dr[17]) * sig;
-                #pragma unroll
+#pragma unroll
                 for (int i = 0; i < 3; ++i) {
-                    G[i] += hh * a * lX[i] + h * b * lV[i];
+                    G0[i] += hh * a * lX[i] + h * b * lV[i];
                     gx0[i] += lX[i];
                     gv0[i] += sig * h * lX[i] + lV[i];
                 }
@@ -606,17 +587,9 @@ __global__ __launch_bounds__(64) void k_adj_sweep(const AdjParams p, const int c
             }
             pend = pending();
         }
-        // this lane's Jacobians
-        const double* jp = p.jac + (size_t)st * 8 * kJacDoubles * N;
-        double Jx[9], Jv[9];
-        #pragma unroll
-        for (int q = 0; q < 9; ++q) {
-            Jx[q] = valid ? jp[((size_t)q * N + gi) * 8 + jnode] : 0.0;
-            Jv[q] = valid ? jp[((size_t)(9 + q) * N + gi) * 8 + jnode] : 0.0;
-        }
         // stage cotangents: mu_m = G_m + sum_n [h^2 A_m(s_n) Jx_n^T mu_n + h B_m(s_n) Jv_n^T mu_n],
         // lane m - 1 holding mu_m; lane 7 accumulates the step-start term m0
-        double mu[3] = {G[0], G[1], G[2]};
+        double mu[3] = {G0[0], G0[1], G0[2]};
         double wsum[3], usum[3], m0[3] = {0.0, 0.0, 0.0};
         double pc = 1e300, pcl;
         int it = 0;
@@ -625,10 +598,10 @@ __global__ __launch_bounds__(64) void k_adj_sweep(const AdjParams p, const int c
             ++it;
             double W[3] = {0.0, 0.0, 0.0}, U[3] = {0.0, 0.0, 0.0};
             if (gl < 7) {
-                #pragma unroll
+#pragma unroll
                 for (int c2 = 0; c2 < 3; ++c2) {
                     double a = 0.0, b = 0.0;
-                    #pragma unroll
+#pragma unroll
                     for (int r = 0; r < 3; ++r) { a = fma(Jx[3 * r + c2], mu[r], a); b = fma(Jv[3 * r + c2], mu[r], b); }
                     W[c2] = a; U[c2] = b;
                 }
@@ -637,17 +610,17 @@ __global__ __launch_bounds__(64) void k_adj_sweep(const AdjParams p, const int c
             *reinterpret_cast<double2*>(xw + 6 * gl + 2) = make_double2(W[2], U[0]);
             *reinterpret_cast<double2*>(xw + 6 * gl + 4) = make_double2(U[1], U[2]);
             wave_lds_sync();
-            double nm[3] = {G[0], G[1], G[2]};
-            #pragma unroll
+            double nm[3] = {G0[0], G0[1], G0[2]};
+#pragma unroll
             for (int i = 0; i < 3; ++i) { wsum[i] = 0.0; usum[i] = 0.0; }
-            #pragma unroll
+#pragma unroll
             for (int n = 1; n <= 7; ++n) {
                 const double* x = xw + 6 * (n - 1);
                 const double2 w01 = *reinterpret_cast<const double2*>(x);
                 const double2 w2u0 = *reinterpret_cast<const double2*>(x + 2);
                 const double2 u12 = *reinterpret_cast<const double2*>(x + 4);
                 const double wn[3] = {w01.x, w01.y, w2u0.x}, un[3] = {w2u0.y, u12.x, u12.y};
-                #pragma unroll
+#pragma unroll
                 for (int i = 0; i < 3; ++i) {
                     nm[i] += hh * Q.cA[n - 1] * wn[i] + h * Q.cB[n - 1] * un[i];
                     wsum[i] += wn[i];
@@ -657,120 +630,176 @@ __global__ __launch_bounds__(64) void k_adj_sweep(const AdjParams p, const int c
             wave_lds_sync();
             double dm = 0.0, mm = 0.0;
             if (gl < 7) {
-                #pragma unroll
+#pragma unroll
                 for (int i = 0; i < 3; ++i) {
                     dm = fmax(dm, fabs(nm[i] - mu[i]));
                     mm = fmax(mm, fabs(nm[i]));
                     mu[i] = nm[i];
                 }
             } else {
-                #pragma unroll
+#pragma unroll
                 for (int i = 0; i < 3; ++i) m0[i] = nm[i];
             }
+            constexpr int kNodeStep = G == 8 ? 1 : 8;
 #pragma unroll
             for (int off = 1; off < kGroup; off <<= 1) {
-                dm = fmax(dm, __shfl_xor(dm, off, kWave));
-                mm = fmax(mm, __shfl_xor(mm, off, kWave));
+                dm = fmax(dm, __shfl_xor(dm, off * kNodeStep, kWave));
+                mm = fmax(mm, __shfl_xor(mm, off * kNodeStep, kWave));
             }
             // the ratio only steers the stopping rule: the reciprocal estimate suffices
-            pc = groups_max((ok_final && mm > 0.0) ? dm * __builtin_amdgcn_rcp(mm) : 0.0);
+            pc = groups_max<G>((ok_final && mm > 0.0) ? dm * __builtin_amdgcn_rcp(mm) : 0.0);
         } while (!(pc < 1e-16) && !(it > 2 && pcl <= pc) && it < 2 * p.max_iter);
         // step-start Jacobians (lane 7) applied to m0, shared with the group
-        double a0[3], b0[3];
-        #pragma unroll
+#pragma unroll
         for (int i = 0; i < 3; ++i) {
             double a = 0.0, b = 0.0;
-            #pragma unroll
+#pragma unroll
             for (int r = 0; r < 3; ++r) { a = fma(Jx[3 * r + i], m0[r], a); b = fma(Jv[3 * r + i], m0[r], b); }
-            a0[i] = __shfl(a, 7, kGroup);
-            b0[i] = __shfl(b, 7, kGroup);
+            lx[i] = gx0[i] + wsum[i] + __shfl(a, node_lane<G>(lane, 7), kWave);
+            lv[i] = gv0[i] + usum[i] + __shfl(b, node_lane<G>(lane, 7), kWave);
         }
-        #pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            lx[i] = gx0[i] + wsum[i] + a0[i];
-            lv[i] = gv0[i] + usum[i] + b0[i];
+    };
+    // steps [a, b) of the records at `rec`, last first; the next one is read during a step
+    auto sweep = [&](const double* rec, int a, int b) {
+        const double* r = rec + slot;
+        double2 q0 = make_double2(0.0, 0.0), q1 = q0;
+        auto read = [&](int st) {
+            if (!valid || st < a) return;
+            const double2* s = reinterpret_cast<const double2*>(r + (size_t)st * kStep);
+            q0 = s[0];
+            q1 = s[1];
+        };
+        read(b - 1);
+        for (int st = b - 1; st >= a; --st) {
+            wave_lds_sync();                        // the previous record is read
+            if (M.sub == 0) {
+                *reinterpret_cast<double2*>(srec + 4 * gl) = q0;
+                *reinterpret_cast<double2*>(srec + 4 * gl + 2) = q1;
+            }
+            wave_lds_sync();
+            read(st - 1);
+            step_back();
         }
-    }
-    if (c > 0) {
+    };
+    auto ckpt = [&](int c, int obj) { return p.ckpt + ((size_t)c * N + obj) * kCkptDoubles; };
+
+    for (int c = p.n_ckpt - 1; c >= 0; --c) {
+        // the segment's steps, and the times of its checkpoint and the next
+        // (the same for every object of the wavefront)
+        const double *cf = ckpt(c, j_first), *cn = ckpt(c + 1, j_first);
+        const int a = (int)uniform(cf[35]), b = (int)uniform(cn[35]);
+        if (b <= a) continue;
+        const int ns = min(b - a, p.s_max);
+        overflow_steps = overflow_steps || b - a > p.s_max;
+        if (b <= p.rec_fwd) {
+            sweep(w.rec, b - ns, b);
+            continue;
+        }
+        // The forward's steps (and windows) again from the checkpoint on,
+        // until the step start where it took the next one.
+        const double t_c = uniform(cf[34]), t_stop = uniform(cn[34]);
+        G8State S;
+        init_lane_state(p, false, j, S);
+        double hw = 0.0, hprev = -kInf;
+        bool have_f0 = false;
         if (valid) {
-            const double v = gl < 6 ? state_component(lx, lv, gl) : gl == 6 ? (double)kb : (overflow_steps ? 1.0 : 0.0);
-            as[gl] = v;
+            const double* ck = ckpt(c, j);
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                S.x0[i] = ck[i]; S.v0[i] = ck[3 + i]; S.F0[i] = ck[8 + i];
+                S.Dp[i] = gl < 7 ? ck[12 + 3 * gl + i] : 0.0;
+            }
+            hw = ck[6];
+            S.active = ck[7] == 0.0;
+            have_f0 = ck[11] != 0.0;
+            hprev = ck[33];
         }
-        return;
+        S.hw = groups_max<G>(valid ? hw : 0.0);     // the same value in every valid group
+        S.hprev = groups_max<G>(hprev);             // likewise (invalid groups give -inf)
+        S.haveF0 = __ballot(have_f0) != 0ull;       // as in the forward at this checkpoint
+        S.t = t_c;
+        G8Count Cn;
+        int n = 0;
+        double* seg = w.rec + (size_t)p.rec_fwd * kStep;
+        auto store = [&](double ts, double h, const double dn[3], const G8State& St) {
+            if (writer && n < ns) write_step(seg + (size_t)n * kStep + M.grp * kStepRec, gl, ts, h, dn, St);
+            ++n;
+        };
+        while (S.t < t_stop)
+            g8_integrate<NB, NGR, NJ2, DEG1, G>(
+                p, gc, T, M, lane, aligned_end(S.t, p.t_end, E.t_start, E.seg_days, E.inv_seg, p.window_segs), S, Cn,
+                store, true, t_stop);
+        sweep(seg, 0, min(n, ns));
     }
     // observations at the start epoch
     if (ok_final) {
         while (kb >= 0) {
             const double* og = p.obs_grad + ((size_t)j * K + kb) * 6;
-            #pragma unroll
+#pragma unroll
             for (int i = 0; i < 3; ++i) { lx[i] += og[i]; lv[i] += og[3 + i]; }
             --kb;
         }
     }
-    if (valid) {
+    if (writer) {
         const bool good = ok_final && !overflow_steps;
-        if (gl < 6) p.grad[6 * j + gl] = good ? state_component(lx, lv, gl) : 0.0;
-        if (gl == 0 && overflow_steps && p.status[j] == 0) p.status[j] = KETE_ST_MAX_STEPS;
+        if (gl < 6) p.grad[6 * (size_t)j + gl] = good ? state_component(lx, lv, gl) : 0.0;
+        if (gl == 0 && overflow_steps && ok_final) p.status[j] = KETE_ST_MAX_STEPS;
     }
+}
+
+template <int NB, int NGR, int NJ2, int DEG1>
+__global__ __launch_bounds__(64, 2) void k_adj_back(const AdjParams p) {
+    extern __shared__ __align__(16) double smem[];
+    __shared__ __align__(16) GroupConst gc;
+    __shared__ __align__(16) double srec[kAdjBodies * kStepRec], xw[kAdjBodies * kGroup * 6];
+    __shared__ AdjCols cols[kGroup];
+    __shared__ double drow[kGroup][18];             // dense-output rows
+    const int lane = threadIdx.x;
+    const AdjWave w = adj_wave(p);
+    if (w.first < 0) return;                        // the whole block: one wavefront
+    double* dst = &cols[0].cA[0];
+    for (int i = lane; i < kAdjTabDoubles; i += kWave)
+        (i < kGroup * kAdjColDoubles ? dst[i] : drow[0][i - kGroup * kAdjColDoubles]) = p.adj_tab[i];
+    load_group_const(p.group_const, &gc, lane, kWave);
+    __syncthreads();
+    if (w.lone) adj_back_wave<kSoloLanes, NB, NGR, NJ2, DEG1>(p, w, gc, cols, drow, srec, xw, smem);
+    else adj_back_wave<kGroup, NB, NGR, NJ2, DEG1>(p, w, gc, cols, drow, srec, xw, smem);
 }
 
 }  // namespace
 
-size_t adjoint_lds_bytes(const AdjParams& p) {
-    return (size_t)g8_wave_doubles<kGroup>(p.eph) * sizeof(double);
-}
-
-
-// A second stream per device for the backward recomputes: created once, at
-// the default priority, not synchronizing with the null stream.
-static hipError_t aux_stream(hipStream_t* out) {
-    static std::mutex m;
-    static hipStream_t st[64] = {};
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-    std::lock_guard<std::mutex> g(m);
-    if (!st[dev] && (e = hipStreamCreateWithFlags(&st[dev], hipStreamNonBlocking)) != hipSuccess) return e;
-    *out = st[dev];
-    return hipSuccess;
-}
-
-// The backward's five ordering events, created once per host thread and
-// recorded again by every call (a wait uses the record made before it).
-struct AdjEvents {
-    hipEvent_t ev[5] = {};
-    int next = 0;
-};
-static thread_local AdjEvents g_adj_events;
-static hipError_t pooled_event(hipEvent_t* out) {
-    AdjEvents& a = g_adj_events;
-    const int i = a.next++ % 5;
-    if (!a.ev[i]) {
-        const hipError_t e = hipEventCreateWithFlags(&a.ev[i], hipEventDisableTiming);
-        if (e != hipSuccess) return e;
+static hipError_t launch_adjoint_waves(const AdjParams& p, int mode, hipStream_t s) {
+    const dim3 grid((unsigned)adj_waves(p.n_obj, p.solo_waves));
+    const size_t lds = (size_t)std::max(g8_wave_doubles<kGroup>(p.eph), g8_wave_doubles<kSoloLanes>(p.eph)) *
+                       sizeof(double);
+    const int shape = group_shape(p.eph);
+    if (mode == KETE_ADJ_FWD) {
+        switch (shape) {
+            case 2: hipLaunchKernelGGL((k_adjoint_fwd<10, 3, 2, 13>), grid, dim3(64), lds, s, p); break;
+            case 3: hipLaunchKernelGGL((k_adjoint_fwd<3, 2, 2, 13>), grid, dim3(64), lds, s, p); break;
+            case 1: hipLaunchKernelGGL((k_adjoint_fwd<0, 0, 0, 13>), grid, dim3(64), lds, s, p); break;
+            default: hipLaunchKernelGGL((k_adjoint_fwd<0, 0, 0, 0>), grid, dim3(64), lds, s, p); break;
+        }
+    } else {
+        switch (shape) {
+            case 2: hipLaunchKernelGGL((k_adj_back<10, 3, 2, 13>), grid, dim3(64), lds, s, p); break;
+            case 3: hipLaunchKernelGGL((k_adj_back<3, 2, 2, 13>), grid, dim3(64), lds, s, p); break;
+            case 1: hipLaunchKernelGGL((k_adj_back<0, 0, 0, 13>), grid, dim3(64), lds, s, p); break;
+            default: hipLaunchKernelGGL((k_adj_back<0, 0, 0, 0>), grid, dim3(64), lds, s, p); break;
+        }
     }
-    *out = a.ev[i];
-    return hipSuccess;
+    return hipGetLastError();
 }
 
 hipError_t launch_adjoint(const AdjParams& p, int mode, hipStream_t s) {
-    const int64_t waves = ((int64_t)p.n_obj + kGroup - 1) / kGroup;
-    const int grid = (int)waves;
-    if (grid == 0) return hipSuccess;
+    if (p.n_obj <= 0) return hipSuccess;
     const int64_t n_o = (int64_t)p.n_obj * p.k_obs;
     const unsigned go = (unsigned)((n_o + 255) / 256);
-    const size_t lds = adjoint_lds_bytes(p);
-    const int shape = group_shape(p.eph);
     hipError_t e;
     if (mode == KETE_ADJ_FWD) {
-        if ((e = launch_group_const(p.rc, p.group_const, s)) != hipSuccess) return e;
-        switch (shape) {
-            case 2: hipLaunchKernelGGL((k_adjoint_fwd<10, 3, 2, 13>), dim3(grid), dim3(64), lds, s, p); break;
-            case 3: hipLaunchKernelGGL((k_adjoint_fwd<3, 2, 2, 13>), dim3(grid), dim3(64), lds, s, p); break;
-            case 1: hipLaunchKernelGGL((k_adjoint_fwd<0, 0, 0, 13>), dim3(grid), dim3(64), lds, s, p); break;
-            default: hipLaunchKernelGGL((k_adjoint_fwd<0, 0, 0, 0>), dim3(grid), dim3(64), lds, s, p); break;
-        }
+        static_assert(kGroupConstDoubles <= 320, "one thread per constant");
+        hipLaunchKernelGGL(k_adj_consts, dim3(2), dim3(320), 0, s, p);
+        if ((e = launch_adjoint_waves(p, mode, s)) != hipSuccess) return e;
         if (n_o > 0) {
             hipLaunchKernelGGL(k_obs_sky, dim3(go), dim3(256), 0, s, p);
             hipLaunchKernelGGL(k_obs_status, dim3((unsigned)((p.n_obj + 255) / 256)), dim3(256), 0, s, p);
@@ -778,53 +807,7 @@ hipError_t launch_adjoint(const AdjParams& p, int mode, hipStream_t s) {
         return hipGetLastError();
     }
     if (n_o > 0) hipLaunchKernelGGL(k_obs_vjp, dim3(go), dim3(256), 0, s, p);
-    hipLaunchKernelGGL(k_adj_tables, dim3(1), dim3(64), 0, s, p);
-    // The sweeps run on s, last segment first.  The recompute of segment c
-    // needs only its checkpoint, so it runs on a second stream ahead of the
-    // sweeps, into one of two step stores: the store of segment c is free
-    // once the sweep of segment c + 2 has read it.
-    hipStream_t r = nullptr;
-    if ((e = aux_stream(&r)) != hipSuccess) return e;
-    const int C = p.n_ckpt;
-    hipEvent_t ready[2] = {nullptr, nullptr}, freed[2] = {nullptr, nullptr}, start = nullptr;
-    g_adj_events.next = 0;
-    if ((e = pooled_event(&start)) != hipSuccess) return e;
-    for (int b = 0; b < 2; ++b) {
-        if ((e = pooled_event(&ready[b])) != hipSuccess || (e = pooled_event(&freed[b])) != hipSuccess) return e;
-    }
-    // the recomputes start after everything already queued on s (the forward's checkpoints)
-    if ((e = hipEventRecord(start, s)) != hipSuccess || (e = hipStreamWaitEvent(r, start, 0)) != hipSuccess) return e;
-    const size_t store = (size_t)p.s_max * kStepRecDoubles * p.n_obj;
-    const size_t ns_len = (size_t)((p.n_obj + kAdjLanes - 1) / kAdjLanes);
-    auto in_store = [&](int b) {
-        AdjParams q = p;
-        q.steps = p.steps + b * store;
-        q.jac = q.steps + (size_t)p.s_max * kStepDoubles * p.n_obj;
-        q.seg_ns = p.seg_ns + b * ns_len;
-        return q;
-    };
-    auto recompute = [&](int c) -> hipError_t {
-        const int b = c & 1;
-        if (c + 2 < C && (e = hipStreamWaitEvent(r, freed[b], 0)) != hipSuccess) return e;
-        const AdjParams q = in_store(b);
-        switch (shape) {
-            case 2: hipLaunchKernelGGL((k_adj_recompute<10, 3, 2, 13>), dim3(grid), dim3(64), lds, r, q, c); break;
-            case 3: hipLaunchKernelGGL((k_adj_recompute<3, 2, 2, 13>), dim3(grid), dim3(64), lds, r, q, c); break;
-            case 1: hipLaunchKernelGGL((k_adj_recompute<0, 0, 0, 13>), dim3(grid), dim3(64), lds, r, q, c); break;
-            default: hipLaunchKernelGGL((k_adj_recompute<0, 0, 0, 0>), dim3(grid), dim3(64), lds, r, q, c); break;
-        }
-        return hipEventRecord(ready[b], r);
-    };
-    if ((e = recompute(C - 1)) != hipSuccess) return e;
-    for (int c = C - 1; c >= 0; --c) {
-        const int b = c & 1;
-        if ((e = hipStreamWaitEvent(s, ready[b], 0)) != hipSuccess) return e;
-        // the next recompute is queued before this sweep, into the other store
-        if (c > 0 && (e = recompute(c - 1)) != hipSuccess) return e;
-        hipLaunchKernelGGL(k_adj_sweep, dim3(grid), dim3(64), 0, s, in_store(b), c);
-        if ((e = hipEventRecord(freed[b], s)) != hipSuccess) return e;
-    }
-    return hipGetLastError();
+    return launch_adjoint_waves(p, mode, s);
 }
 
 

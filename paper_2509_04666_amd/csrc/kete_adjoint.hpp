@@ -6,21 +6,25 @@
 
 namespace kete {
 
-// x[3], v[3], wave step, failed flag, force F0[3], F0 valid, the last accepted step's increments
-// at nodes 1..7 [7][3], that step (0: none), the checkpoint's time, 1 spare
+// Checkpoint: x[3], v[3], wave step, failed flag, force F0[3], F0 valid, the last accepted step's increments
+// at nodes 1..7 [7][3], that step (0: none), the checkpoint's time, steps accepted before it
 constexpr int kCkptDoubles = 36;
-constexpr int kAdjStateDoubles = 8; // lx[3], lv[3], next observation, overflow flag
-constexpr int kAdjLanes = 8;         // lanes per object in the adjoint kernels (8 objects per wavefront)
 constexpr int kAdjTabDoubles = 8 * (16 + 18);   // constant rows of the reverse sweep
-constexpr int kStepDoubles = 2;      // per stored step and object: start time, step size
-constexpr int kJacDoubles = 18;      // per stored step, node and object: Jx (9), Jv (9)
-constexpr int kStepRecDoubles = kStepDoubles + 8 * kJacDoubles;   // step store per step and object
+// One accepted step of one object, eight slots of four doubles: slot m < 7
+// the increment at node m + 1 and the m-th of x[3], v[3] and the step's
+// start time, slot 7 the force at the start and the step size.
+constexpr int kStepRec = 32;
+// Room for step records: kRecSteps per object and step of a checkpoint
+// segment (opts adj_seg_steps).  The steps of one segment, at most that
+// number, have their place at the end of a wavefront's; the rest hold the
+// forward's steps from the start on.
+constexpr int kRecSteps = 9;
 
 struct AdjParams {
     EphemArgs eph;
     RadauConst rc;
     const double* x0;           // [N][6]
-    const int32_t* perm;        // [N] object order (bucketed)
+    const int32_t* perm;        // [N] object order (bucketed), or null
     double t0;
     int32_t n_obj;
     int32_t k_obs;
@@ -39,11 +43,13 @@ struct AdjParams {
     double* obs_state;          // [N][K][6] states at the observation times (forward)
     double* obs_grad;           // [N][K][6] dL/d(state) at the observation times (backward)
     double* obs_hop;            // [N][K][2] light time and final universal anomaly (forward)
-    double* steps;              // [s_max][kStepDoubles][N] (store 0; store 1 follows the Jacobians)
-    double* jac;                // [s_max][kJacDoubles][N][8 nodes]: one object's nodes side by side
-    double* adj_state;          // [N][kAdjStateDoubles] carried between backward segments
-    int32_t* seg_ns;            // [2][ceil(N / 8)] steps stored per wavefront, per step store
-    double* adj_tab;            // [kAdjTabDoubles] constant rows of the reverse sweep
+    int32_t solo_waves;         // wavefronts of one object, before those of kAdjBodies
+    int32_t pad_solo;
+    const int32_t* n_solo;      // device: objects that may have one of their own, or null: all of the first solo_waves
+    double* rec;                // [wavefronts][rec_fwd + s_max][objects of one][kStepRec]
+    int32_t rec_fwd;            // steps of a wavefront that the forward records
+    int32_t pad2_;
+    double* adj_tab;            // [kAdjTabDoubles] constant rows of the reverse sweep, written by the forward launch
     double* group_const;        // [kGroupConstDoubles] written by the forward launch
     int32_t s_max;
     int32_t window_segs;        // segments between forced step ends (0: none)
@@ -56,7 +62,16 @@ struct AdjParams {
     int32_t zero_start;         // correctors start from zero increments (no extrapolation)
 };
 
-size_t adjoint_lds_bytes(const AdjParams& p);
+// Wavefronts of the adjoint kernels: the first solo_waves have room for one
+// object each, the others for kAdjBodies.
+constexpr int kAdjBodies = 8;
+inline int64_t adj_waves(int64_t n_obj, int solo_waves) {
+    return solo_waves + (solo_waves < n_obj ? (n_obj + kAdjBodies - 1) / kAdjBodies : 0);
+}
+inline size_t adj_rec_doubles(int64_t n_obj, int solo_waves, int s_max) {
+    const int64_t places = solo_waves + (adj_waves(n_obj, solo_waves) - solo_waves) * kAdjBodies;
+    return (size_t)places * kStepRec * (size_t)(kRecSteps * s_max);
+}
 hipError_t launch_adjoint(const AdjParams& p, int mode, hipStream_t s);
 
 }  // namespace kete

@@ -22,11 +22,11 @@
 
 namespace kete {
 hipError_t launch_hpref_init(const double* x0, double* h_pref, uint32_t* keys, int n, double mu, double dt_lo,
-                             double dt_hi, int n_class, int n_epochs, hipStream_t s);
+                             double dt_hi, int n_class, int n_epochs, double solo_steps, hipStream_t s);
 hipError_t launch_body_sort(const uint32_t* keys, int n, int n_class, int32_t* perm, int32_t* tmp, int32_t* counts,
-                            const int32_t** n_first, hipStream_t s);
+                            hipStream_t s);
+const int32_t* body_sort_first(const int32_t* counts, int n, int n_class);
 int solo_waves_for(int n, bool classes);
-hipError_t launch_iota(int32_t* perm, int n, hipStream_t s);
 size_t bucket_scratch_ints(int64_t n_obj, int n_buckets);
 }  // namespace kete
 
@@ -636,9 +636,10 @@ int kete_propagate_nbody(const kete_ephem_t* eph, const double* x0, double t0, i
         // wavefronts of one object, all of them on the chip at once, need no order
         const bool sorted = ncls > 1 && P.solo_waves < n_obj;
         HIPCHK(launch_hpref_init(P.state_in, h_pref, sorted ? sorts.keys : nullptr, (int)n_obj, E.gm[0], dt_lo, dt_hi,
-                                 ncls, (int)(e1 - e0), s));
+                                 ncls, (int)(e1 - e0), kSoloSteps, s));
         if (sorted) {
-            HIPCHK(launch_body_sort(sorts.keys, (int)n_obj, ncls, perm, sorts.tmp, sorts.counts, &P.n_solo, s));
+            HIPCHK(launch_body_sort(sorts.keys, (int)n_obj, ncls, perm, sorts.tmp, sorts.counts, s));
+            P.n_solo = body_sort_first(sorts.counts, (int)n_obj, ncls);
             P.perm = perm;
         } else {
             P.perm = nullptr;
@@ -941,13 +942,11 @@ size_t kete_adjoint_workspace_size(int64_t n_obj, int32_t k_obs, double t0, doub
     c.take<int32_t>((size_t)n_obj);                                   // perm
     c.take<double>((size_t)n_obj);                                    // h_pref
     c.take<double>((size_t)(C + 1) * n_obj * kCkptDoubles);
-    c.take<double>((size_t)2 * adj_steps(opts) * kStepRecDoubles * n_obj);   // two step stores
+    c.take<double>(adj_rec_doubles(n_obj, solo_waves_for((int)n_obj, sort_classes(opts) > 1), adj_steps(opts)));
     c.take<double>((size_t)n_obj * std::max(0, k_obs) * 6);    // observation states
     c.take<double>((size_t)n_obj * std::max(0, k_obs) * 6);    // observation cotangents
     c.take<double>((size_t)n_obj * std::max(0, k_obs) * 2);    // light times and anomalies
     c.take<int32_t>(sort_scratch_ints(n_obj));
-    c.take<double>((size_t)n_obj * kAdjStateDoubles);                 // carried backward state
-    c.take<int32_t>((size_t)2 * ((n_obj + kAdjLanes - 1) / kAdjLanes));     // steps per wavefront, per store
     c.take<double>((size_t)kAdjTabDoubles);                           // reverse-sweep constants
     c.take<double>((size_t)kGroupConstDoubles);                        // constants of the grouped kernels
     return c.off;
@@ -976,6 +975,8 @@ int kete_propagate_adjoint(const kete_ephem_t* eph, int32_t mode, const double* 
     if (!(opts->eps > 0) || !(opts->h_init > 0) || !(opts->h_min > 0) || opts->max_iter < 1 || opts->max_steps < 1)
         return fail(KETE_EINVAL, "eps, h_init, h_min, max_iter and max_steps must be positive");
     const int ncls = sort_classes(opts);
+    const int solo_waves = solo_waves_for((int)n_obj, ncls > 1);
+    const bool sorted = ncls > 1 && solo_waves < n_obj;        // all alone: no order needed
     if (!workspace) return fail(KETE_EWORKSPACE, "workspace is null");
     const size_t need = kete_adjoint_workspace_size(n_obj, k_obs, t0, t_end, ckpt_days, opts);
     if (ws_bytes < need) return fail(KETE_EWORKSPACE, "workspace %zu bytes < %zu required", ws_bytes, need);
@@ -983,13 +984,11 @@ int kete_propagate_adjoint(const kete_ephem_t* eph, int32_t mode, const double* 
     int32_t* perm = c.take<int32_t>((size_t)n_obj);
     double* h_pref = c.take<double>((size_t)n_obj);
     double* ckpt = c.take<double>((size_t)(C + 1) * n_obj * kCkptDoubles);
-    double* scratch = c.take<double>((size_t)2 * adj_steps(opts) * kStepRecDoubles * n_obj);
+    double* rec = c.take<double>(adj_rec_doubles(n_obj, solo_waves, adj_steps(opts)));
     double* obs_state = c.take<double>((size_t)n_obj * k_obs * 6);
     double* obs_grad = c.take<double>((size_t)n_obj * k_obs * 6);
     double* obs_hop = c.take<double>((size_t)n_obj * k_obs * 2);
     const SortScratch sorts = sort_scratch(c.take<int32_t>(sort_scratch_ints(n_obj)), n_obj);
-    double* adj_state = c.take<double>((size_t)n_obj * kAdjStateDoubles);
-    int32_t* seg_ns = c.take<int32_t>((size_t)2 * ((n_obj + kAdjLanes - 1) / kAdjLanes));
     double* adj_tab = c.take<double>((size_t)kAdjTabDoubles);
     double* group_const = c.take<double>((size_t)kGroupConstDoubles);
 
@@ -1000,7 +999,7 @@ int kete_propagate_adjoint(const kete_ephem_t* eph, int32_t mode, const double* 
     P.eph = E;
     P.rc = radau_const();
     P.x0 = x0;
-    P.perm = perm;
+    P.perm = sorted ? perm : nullptr;
     P.t0 = t0;
     P.n_obj = (int32_t)n_obj;
     P.k_obs = k_obs;
@@ -1018,11 +1017,11 @@ int kete_propagate_adjoint(const kete_ephem_t* eph, int32_t mode, const double* 
     P.obs_state = obs_state;
     P.obs_grad = obs_grad;
     P.obs_hop = obs_hop;
-    P.steps = scratch;
-    P.jac = scratch + (size_t)adj_steps(opts) * kStepDoubles * n_obj;
+    P.rec = rec;
+    P.solo_waves = solo_waves;
+    P.n_solo = sorted && solo_waves > 0 ? body_sort_first(sorts.counts, (int)n_obj, ncls) : nullptr;
     P.s_max = adj_steps(opts);
-    P.adj_state = adj_state;
-    P.seg_ns = seg_ns;
+    P.rec_fwd = (kRecSteps - 1) * P.s_max;
     P.adj_tab = adj_tab;
     P.group_const = group_const;
     P.window_segs = window_segs(opts);
@@ -1045,14 +1044,9 @@ int kete_propagate_adjoint(const kete_ephem_t* eph, int32_t mode, const double* 
     P.sin_eps = std::sin(obliq);
 
     if (mode == KETE_ADJ_FWD) {
-        HIPCHK(fill_zero(status, (size_t)n_obj * sizeof(int32_t), s));
-        HIPCHK(launch_hpref_init(x0, h_pref, ncls > 1 ? sorts.keys : nullptr, (int)n_obj, E.gm[0], 0.0, t_end - t0,
-                                 ncls, 0, s));
-        if (ncls > 1) {
-            HIPCHK(launch_body_sort(sorts.keys, (int)n_obj, ncls, perm, sorts.tmp, sorts.counts, nullptr, s));
-        } else {
-            HIPCHK(launch_iota(perm, (int)n_obj, s));
-        }
+        HIPCHK(launch_hpref_init(x0, h_pref, sorted ? sorts.keys : nullptr, (int)n_obj, E.gm[0], 0.0, t_end - t0, ncls,
+                                 0, kAdjSoloSteps, s));
+        if (sorted) HIPCHK(launch_body_sort(sorts.keys, (int)n_obj, ncls, perm, sorts.tmp, sorts.counts, s));
     }
     {
         TimedScope ts(kTimeAdjoint, s);

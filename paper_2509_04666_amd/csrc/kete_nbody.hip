@@ -325,18 +325,13 @@ __global__ __launch_bounds__(256) void k_bucket_scatter(const BucketParams p, co
     }
 }
 
-__global__ void k_iota(int32_t* __restrict__ perm, int n) {
-    const long j = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j < n) perm[j] = (int32_t)j;
-}
-
 // Predicted step and sort key (see BucketParams) of every body over the
 // launch's time span [dt_lo, dt_hi] from its start state (taken as
 // heliocentric: the Sun is within 0.01 au of the barycentre, which only
 // blurs the ordering).
 __global__ void k_hpref_init(const double* __restrict__ x0, double* __restrict__ h_pref, uint32_t* __restrict__ keys,
                              int n, double mu, double dt_lo, double dt_hi, int n_class, double h_ref,
-                             int keep_order) {
+                             int keep_order, double solo_steps) {
     const long j = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= n) return;
     double tm = 0.0;
@@ -347,9 +342,9 @@ __global__ void k_hpref_init(const double* __restrict__ x0, double* __restrict__
     const double frac = span > 0.0 ? fmin(fmax((tm - dt_lo) / span, 0.0), 1.0) : 0.0;
     uint32_t hi, lo;
     const double steps = h > 0.0 ? span / h : 0.0;
-    if (steps > kSoloSteps && h < kSoloMaxStep) {
+    if (steps > solo_steps && h < kSoloMaxStep) {
         hi = 0;
-        lo = (uint32_t)fmin(fmax(kCritTimeBins - 1.0 - 16.0 * log2(steps / kSoloSteps), 0.0), kCritTimeBins - 1.0);
+        lo = (uint32_t)fmin(fmax(kCritTimeBins - 1.0 - 16.0 * log2(steps / solo_steps), 0.0), kCritTimeBins - 1.0);
     } else if (steps > kCritSteps) {
         hi = 1;
         lo = (uint32_t)fmin(frac * kCritTimeBins, kCritTimeBins - 1.0);
@@ -438,18 +433,23 @@ hipError_t launch_nbody(const NbodyParams& p, int block, int lanes_per_body, hip
 // where near orbits, whose corrector takes more sweeps, are not kept apart.
 constexpr int kOrderEpochs = 4;
 hipError_t launch_hpref_init(const double* x0, double* h_pref, uint32_t* keys, int n, double mu, double dt_lo,
-                             double dt_hi, int n_class, int n_epochs, hipStream_t s) {
+                             double dt_hi, int n_class, int n_epochs, double solo_steps, hipStream_t s) {
     if (n == 0) return hipSuccess;
     hipLaunchKernelGGL(k_hpref_init, dim3((n + 255) / 256), dim3(256), 0, s, x0, h_pref, keys, n, mu, dt_lo, dt_hi,
-                       n_class, 1.0 / 64.0, n_epochs >= kOrderEpochs);
+                       n_class, 1.0 / 64.0, n_epochs >= kOrderEpochs, solo_steps);
     return hipGetLastError();
 }
 
 // Bodies ordered by their keys: the time class first, then (stably) the
-// step class, into perm; tmp [n] holds the first pass's order.  *n_first
-// becomes the device address of the number of bodies in step class 0.
+// step class, into perm; tmp [n] holds the first pass's order.  Afterwards
+// body_sort_first gives the device address of the number of bodies in step
+// class 0: the class-major offsets of the second pass, where class 1 starts.
+const int32_t* body_sort_first(const int32_t* counts, int n, int n_class) {
+    const int nblk = (n + 255) / 256;
+    return counts + (size_t)n_class * nblk + nblk;
+}
 hipError_t launch_body_sort(const uint32_t* keys, int n, int n_class, int32_t* perm, int32_t* tmp, int32_t* counts,
-                            const int32_t** n_first, hipStream_t s) {
+                            hipStream_t s) {
     BucketParams B;
     B.keys = keys;
     B.counts = counts;
@@ -465,16 +465,7 @@ hipError_t launch_body_sort(const uint32_t* keys, int n, int n_class, int32_t* p
     B.perm = perm;
     B.n_buckets = n_class;
     B.shift = 16;
-    // the class-major offsets of the second pass: class 1 starts where class 0 ends
-    const int nblk = (n + 255) / 256;
-    if (n_first) *n_first = counts + (size_t)n_class * nblk + nblk;
     return launch_bucket(B, s);
-}
-
-hipError_t launch_iota(int32_t* perm, int n, hipStream_t s) {
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_iota, dim3((n + 255) / 256), dim3(256), 0, s, perm, n);
-    return hipGetLastError();
 }
 
 hipError_t launch_bucket(const BucketParams& p, hipStream_t s) {

@@ -176,3 +176,30 @@ def test_adjoint_failed_objects_get_zero_gradient(torch_cuda):
     grad = ctx.backward(xt, torch.ones_like(sky))
     assert torch.all(grad[3] == 0)
     assert torch.all(torch.isfinite(grad[torch.arange(70, device="cuda") != 3]))
+
+
+@pytest.mark.parametrize("n", [1, 9, 2048, 2049, 5000])
+def test_adjoint_recorded_and_recomputed_steps(torch_cuda, n):
+    """Objects alone, eight to a wavefront and both in one list: the backward
+    from the forward's step records, and with room for so few of them that
+    fast orbits' later steps are computed again from the checkpoints; a
+    checkpoint segment of more steps than the option allows fails."""
+    torch, api = torch_cuda
+    g = synth.gradient_case(n_obj=n, k_obs=9, arc=100.0, neo_frac=0.2)
+    x0 = _t(torch, g.x0)
+    grads = []
+    for ckpt, steps, again in ((5.0, 256, 1), (0.5, 4, 2)):
+        eph, ctx = _setup(torch, api, g, ckpt, adj_seg_steps=steps)
+        sky = ctx.forward(x0)
+        for _ in range(again):              # a second backward finds what the first one found
+            grads.append(ctx.backward(x0, torch.ones_like(sky) * 1e-3))
+        assert int((ctx.status != 0).sum()) == 0
+    assert torch.equal(grads[1], grads[2])
+    rel = ((grads[1] - grads[0]).norm(dim=1) / grads[0].norm(dim=1)).max().item()
+    _say(f"{n} objects, records vs recomputed: max rel {rel:.3e}")
+    assert rel < 1e-9
+    eph, ctx = _setup(torch, api, g, 100.0, adj_seg_steps=1)
+    sky = ctx.forward(x0)
+    assert int((ctx.status != 0).sum()) == 0
+    grad = ctx.backward(x0, torch.ones_like(sky))
+    assert torch.all(ctx.status == 3) and torch.all(grad == 0)
