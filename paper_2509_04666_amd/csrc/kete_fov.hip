@@ -1687,18 +1687,22 @@ __device__ __forceinline__ void sort_cell(int s0, int s1, int64_t xo, int32_t* _
     }
 }
 
+// A block takes `per` keys at a time, few where there are few: with 256 the
+// 8,001 cells of one batch kept 32 blocks busy, one cell after another
+// (200,000 objects: 140 us, now 22).
 __global__ __launch_bounds__(256) void k_obj_cell_sort(const FovParams p, const int32_t* __restrict__ start,
-                                                      int32_t* __restrict__ sorted, const int32_t* __restrict__ osub) {
+                                                      int32_t* __restrict__ sorted, const int32_t* __restrict__ osub,
+                                                      int per) {
     __shared__ int32_t sj[kCellSortCap], sk[kCellSortCap];
     __shared__ int cnt[kSubKeys];
     __shared__ int wsum[4];
     __shared__ unsigned long long s_need[4];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    // the block's threads look at 256 keys at once; the keys with more
+    // the block's threads look at `per` <= 256 keys at once; the keys with more
     // than two items' worth of objects are then sorted one after another
-    for (int64_t k0 = (int64_t)blockIdx.x * 256; k0 < p.n_keys; k0 += (int64_t)gridDim.x * 256) {
+    for (int64_t k0 = (int64_t)blockIdx.x * per; k0 < p.n_keys; k0 += (int64_t)gridDim.x * per) {
         const int64_t kt = k0 + tid;
-        const bool need = kt < p.n_keys && start[kt + 1] - start[kt] > 2 * kWave;
+        const bool need = tid < per && kt < p.n_keys && start[kt + 1] - start[kt] > 2 * kWave;
         const unsigned long long m = __ballot(need);
         if (lane == 0) s_need[wv] = m;
         __syncthreads();
@@ -1988,7 +1992,7 @@ __device__ __forceinline__ void unpack_pair(unsigned k, int64_t f, int ob, int i
 }
 
 // Ordering inside each frame's segment of the pair keys (keys are unique),
-// by segment size: up to kSortSmall by one thread (insertion sort), up to
+// by segment size: up to kSortSmall by half a wavefront (ranks), up to
 // kSortWave by one wavefront in LDS (radix sort), up to kSortLds by a
 // block in LDS (radix sort), larger ones by a block with bottom-up merge
 // passes through global memory (merge-path partitions), ping-ponging with
@@ -1997,20 +2001,35 @@ constexpr int kSortSmall = 32;
 constexpr int kSortWave = 1024;
 constexpr int kSortLds = 8192;
 
-__global__ void k_pair_sort_small(unsigned* __restrict__ keys, const int32_t* __restrict__ fstart,
-                                  int64_t n_frames, int ob, int32_t* __restrict__ pf, int32_t* __restrict__ ps,
-                                  int32_t* __restrict__ po) {
-    const int64_t f = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (f >= n_frames) return;
-    const int a = fstart[f], e = fstart[f + 1];
-    if (e - a > kSortSmall) return;
-    for (int i = a + 1; i < e; ++i) {
-        const unsigned k = keys[i];
-        int j = i - 1;
-        while (j >= a && keys[j] > k) { keys[j + 1] = keys[j]; --j; }
-        keys[j + 1] = k;
+// Each lane of half a wavefront holds a key of its frame and counts the
+// smaller ones, read four at a time from LDS; that is its key's place.  (One
+// thread a frame, by insertion in global memory, took 79 us for 20,003 frames
+// of a dozen keys, the chain of the longest; this takes 5.)
+__global__ __launch_bounds__(256) void k_pair_sort_small(const unsigned* __restrict__ keys,
+                                                         const int32_t* __restrict__ fstart, int64_t n_frames, int ob,
+                                                         int32_t* __restrict__ pf, int32_t* __restrict__ ps,
+                                                         int32_t* __restrict__ po) {
+    __shared__ __align__(16) unsigned sh[256];
+    static_assert(kSortSmall == 32, "a half-wavefront's lanes");
+    const int l = threadIdx.x & (kSortSmall - 1);
+    unsigned* A = sh + (threadIdx.x & ~(kSortSmall - 1));
+    const int64_t f = ((int64_t)blockIdx.x * 256 + threadIdx.x) / kSortSmall;
+    int a = 0, n = 0;
+    if (f < n_frames) {
+        a = fstart[f];
+        n = fstart[f + 1] - a;
     }
-    for (int i = a; i < e; ++i) unpack_pair(keys[i], f, ob, i, pf, ps, po);
+    if (n > kSortSmall) n = 0;
+    const unsigned k = l < n ? keys[a + l] : ~0u;
+    A[l] = k;
+    wave_lds_sync();
+    int rank = 0;
+#pragma unroll
+    for (int q = 0; q < kSortSmall / 4; ++q) {
+        const uint4 v = *reinterpret_cast<const uint4*>(A + 4 * q);
+        rank += (v.x < k) + (v.y < k) + (v.z < k) + (v.w < k);
+    }
+    if (l < n) unpack_pair(k, f, ob, a + rank, pf, ps, po);
 }
 
 // Stable LSD radix sort of one frame's keys by one wavefront in LDS.  The
@@ -2355,8 +2374,10 @@ hipError_t fov_sort_objects(const FovParams& p, int32_t* okey, int32_t* orank, i
     static_assert(kKeyBlock == 256, "the scatter uses the key pass's chunks");
     hipLaunchKernelGGL(k_obj_scatter, dim3(gk), dim3(256), 0, s, p, (const int32_t*)okey, (const int32_t*)orank,
                        (const int32_t*)start, sorted);
-    hipLaunchKernelGGL(k_obj_cell_sort, dim3((unsigned)std::min<int64_t>(nkeys, (int64_t)cu_count() * 8)), dim3(256),
-                       0, s, p, (const int32_t*)start, sorted, (const int32_t*)osub);
+    const int64_t sort_blocks = std::min<int64_t>(nkeys, (int64_t)cu_count() * 8);
+    const int per = (int)std::max<int64_t>(1, std::min<int64_t>(256, nkeys / sort_blocks));
+    hipLaunchKernelGGL(k_obj_cell_sort, dim3((unsigned)sort_blocks), dim3(256), 0, s, p, (const int32_t*)start, sorted,
+                       (const int32_t*)osub, per);
     return hipGetLastError();
 }
 
@@ -2464,8 +2485,8 @@ hipError_t fov_sort(unsigned long long* keys, int64_t n, int64_t n_frames, int64
                                   (const int32_t*)fstart, fcnt, ob, seg);
     if (n_frames > 0) {
         const unsigned gb = (unsigned)std::min<int64_t>(n_frames, (int64_t)cu_count() * 16);
-        hipLaunchKernelGGL(k_pair_sort_small, dim3((unsigned)((n_frames + 255) / 256)), dim3(256), 0, s, seg,
-                           (const int32_t*)fstart, n_frames, ob, pf, ps, po);
+        hipLaunchKernelGGL(k_pair_sort_small, dim3((unsigned)((n_frames * kSortSmall + 255) / 256)), dim3(256), 0, s,
+                           (const unsigned*)seg, (const int32_t*)fstart, n_frames, ob, pf, ps, po);
         hipLaunchKernelGGL((k_pair_sort_radix<kSortWave, 4>), dim3(gb), dim3(256), 0, s, (const unsigned*)seg,
                            (const int32_t*)fstart, n_frames, kSortSmall, ob, bits, rb, pf, ps, po);
         hipLaunchKernelGGL((k_pair_sort_radix_block<4096>), dim3(gb), dim3(64 * kSortWaves), 0, s,

@@ -656,6 +656,27 @@ def test_fov_few_frames_a_batch(torch_cuda, n_sub, n_obj):
     assert torch.equal(qs, ps.repeat(R)) and torch.equal(qo, po.repeat(R))
 
 
+@pytest.mark.parametrize("copies", [1, 31, 32, 33, 1023, 1025, 4097, 8193])
+def test_fov_pairs_of_a_frame_sorted(torch_cuda, copies):
+    """Copies of one object, as many pairs in each frame that holds it: the
+    sizes at which the sort of a frame's pairs changes hands."""
+    torch, api = torch_cuda
+    case = synth.footprint_case(n_obj=1500, n_frames=300, span=3.0)
+    eph = api.DeviceEphemeris.from_synth(case.ephem)
+    fr = api.DeviceFrames.from_synth(case.frames)
+    order, off, t_ref = api.make_batches(case.frames.t, 3.0)
+    x, _ = api.propagate(eph, _dev_x(torch, case.x0), 0.0, t_ref)
+    b = api.Batches.from_host(order, off, t_ref)
+    pf, ps, po = api.fov_check(eph, x, b, fr)
+    j = int(torch.bincount(po.long()).argmax())           # the object of most pairs
+    one = torch.nonzero(po == j)[:, 0]
+    f1, s1 = pf[one], ps[one]
+    qf, qs, qo = api.fov_check(eph, x[:, j:j + 1].expand(-1, copies, -1).contiguous(), b, fr)
+    assert torch.equal(qf, f1.repeat_interleave(copies))
+    assert torch.equal(qs, s1.repeat_interleave(copies))
+    assert torch.equal(qo, torch.arange(copies, device="cuda", dtype=qo.dtype).repeat(one.numel()))
+
+
 def test_fov_capacity_and_empty(torch_cuda, orc):
     torch, api = torch_cuda
     from paper_2509_04666_amd import _lib
