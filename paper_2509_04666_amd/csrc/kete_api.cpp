@@ -675,6 +675,22 @@ constexpr int kFovWideCursorBase = kFovCursorBase + kJoinCursorWords / 2;
 constexpr int kFovStatBase = kFovWideCursorBase + kJoinCursorWords / 2;
 constexpr int kFovCounters = kFovStatBase + kStatSlots * kStatStride;
 
+static FovClear fov_clear_list(const FovParams& P, unsigned long long* counters, int64_t n_obj, int32_t* cnt,
+                               int32_t* ocnt) {
+    FovClear c;
+    std::memset(&c, 0, sizeof(c));
+    c.p[0] = (unsigned int*)counters;
+    c.words[0] = 2 * (size_t)kFovCounters;
+    c.p[1] = (unsigned int*)P.fail;
+    c.words[1] = (size_t)n_obj;
+    if (!P.direct) {
+        c.p[2] = (unsigned int*)cnt;
+        c.p[3] = (unsigned int*)ocnt;
+        c.words[2] = c.words[3] = (size_t)P.n_keys + 1;
+    }
+    return c;
+}
+
 // Drops the pairs of objects whose hop failed (n_fail > 0): survivors of
 // keys[0..np) go to `out`, and their count is read back (one more
 // synchronization, taken only when a hop failed).
@@ -871,11 +887,18 @@ int kete_fov_check(const kete_ephem_t* eph, const double* x_epoch, int32_t* stat
     hipStream_t s = (hipStream_t)stream;
     {
         TimedScope ts(kTimeFov, s);
-        HIPCHK(fill_zero(counters, kFovCounters * sizeof(unsigned long long), s));
-        HIPCHK(fill_zero(P.fail, (size_t)n_obj * sizeof(int32_t), s));
-        HIPCHK(fov_single_job_layout(b_poff, b_obj0, b_xoff, b_G, b_koff, n_batch, n_obj, G, s));
         P.direct = fov_is_direct((double)n_obj * (double)F, P.n_pairs_total);
-        HIPCHK(fov_prepare(P, qkey, cnt, cnt, scan_scratch, s));
+        FovClear clear = fov_clear_list(P, counters, n_obj, cnt, ocnt);
+        clear.b_poff = b_poff;
+        clear.b_obj0 = b_obj0;
+        clear.b_xoff = b_xoff;
+        clear.b_G = b_G;
+        clear.b_koff = b_koff;
+        clear.n_batch = n_batch;
+        clear.n_obj = n_obj;
+        clear.G = G;
+        HIPCHK(fov_clear(clear, s));
+        HIPCHK(fov_prepare(P, qkey, cnt, scan_scratch, s));
         P.n_wide = counters + 6;
         if (P.direct) {
             TimedScope tj(kTimeFovJoin, s);
@@ -1374,11 +1397,10 @@ int kete_batch_run(const kete_ephem_t* eph, const kete_batch_t* batch, int64_t p
     P.max_cells = 1024;
     P.sin_overflow = 0.5;
     TimedScope ts(kTimeFov, s);
-    HIPCHK(fill_zero(w.counters, kFovCounters * sizeof(unsigned long long), s));
-    HIPCHK(fill_zero(P.fail, (size_t)std::max<int64_t>(batch->n_bodies, 1) * sizeof(int32_t), s));
+    P.direct = fov_is_direct(dc.obj_frames, dc.NP);
+    HIPCHK(fov_clear(fov_clear_list(P, w.counters, std::max<int64_t>(batch->n_bodies, 1), w.cnt, w.ocnt), s));
     if (dc.B > 0 && dc.F > 0 && dc.NP > 0) {
-        P.direct = fov_is_direct(dc.obj_frames, dc.NP);
-        HIPCHK(fov_prepare(P, w.qkey, w.cnt, w.cnt, w.scan_scratch, s));
+        HIPCHK(fov_prepare(P, w.qkey, w.cnt, w.scan_scratch, s));
         if (P.direct) {
             TimedScope tj(kTimeFovJoin, s);
             HIPCHK(fov_direct(P, w.qkey, s));

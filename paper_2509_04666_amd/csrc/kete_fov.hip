@@ -438,11 +438,12 @@ __global__ void k_frame_rank(const FovParams p, int32_t* __restrict__ qbatch) {
     frame_to_rank(p, f, q);
 }
 
-__global__ void k_frame_scatter(const FovParams p, const int32_t* __restrict__ qkey, int32_t* __restrict__ cursor) {
+// left: the cells' counts, each taken down to zero.
+__global__ void k_frame_scatter(const FovParams p, const int32_t* __restrict__ qkey, int32_t* __restrict__ left) {
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= p.n_frames) return;
     const int key = qkey[q];
-    const int pos = p.cell_start[key] + atomicAdd(cursor + key, 1);
+    const int pos = p.cell_start[key] + atomicSub(left + key, 1) - 1;
     frame_to_rank(p, p.frame_order[q], pos);
 }
 
@@ -1946,10 +1947,10 @@ __device__ __forceinline__ unsigned radix_key(unsigned long long k, int ob) {
 
 // Each run takes its place in the block's share of its frame's segment
 // from the LDS table, and each frame of the block takes that share with
-// one atomic on the frame's cursor.
+// one atomic on the frame's count (left), which ends at zero.
 __global__ __launch_bounds__(256) void k_pair_scatter(const unsigned long long* __restrict__ keys, int64_t n,
                                                       const int32_t* __restrict__ fstart,
-                                                      int32_t* __restrict__ fcur, int ob, unsigned* __restrict__ out) {
+                                                      int32_t* __restrict__ left, int ob, unsigned* __restrict__ out) {
     __shared__ int hkey[kRunSlots], hcnt[kRunSlots];
     for (int q = threadIdx.x; q < kRunSlots; q += 256) { hkey[q] = -1; hcnt[q] = 0; }
     __syncthreads();
@@ -1973,7 +1974,7 @@ __global__ __launch_bounds__(256) void k_pair_scatter(const unsigned long long* 
     __syncthreads();
     // hcnt becomes the block's base in each frame's segment
     for (int q = threadIdx.x; q < kRunSlots; q += 256)
-        if (hkey[q] >= 0) hcnt[q] = fstart[hkey[q]] + atomicAdd(fcur + hkey[q], hcnt[q]);
+        if (hkey[q] >= 0) hcnt[q] = fstart[hkey[q]] + atomicSub(left + hkey[q], hcnt[q]) - hcnt[q];
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < kRunChunks; ++c) {
@@ -2271,19 +2272,29 @@ __global__ __launch_bounds__(256) void k_pair_sort_large(unsigned* __restrict__ 
 }
 
 // ---------------------------------------------------------------- layout
-__global__ void k_single_job_layout(int64_t* b_poff, int32_t* b_obj0, int64_t* b_xoff, int32_t* b_G, int64_t* b_koff,
-                                    int64_t n_batch, int64_t n_obj, int G) {
-    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (b > n_batch) return;
-    b_poff[b] = b * n_obj;
-    b_koff[b] = b * ((int64_t)G * G * G + 1);
-    if (b < n_batch) { b_obj0[b] = 0; b_xoff[b] = 6 * b * n_obj; b_G[b] = G; }
-}
-
 // Zero fill as a kernel (graph-capturable without memset nodes).
 __global__ void k_fill_zero(unsigned int* __restrict__ p, size_t n_words) {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_words; i += (size_t)gridDim.x * blockDim.x)
         p[i] = 0u;
+}
+
+// Several arrays in one launch (each costs 4.7 us), and the layout of a single
+// job's batches unless G is 0.
+__global__ void k_fov_clear(const FovClear c) {
+    const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x, step = (size_t)gridDim.x * blockDim.x;
+#pragma unroll
+    for (int k = 0; k < FovClear::kArrays; ++k)
+        for (size_t i = i0; i < c.words[k]; i += step) c.p[k][i] = 0u;
+    if (c.G > 0)
+        for (size_t b = i0; b <= (size_t)c.n_batch; b += step) {
+            c.b_poff[b] = (int64_t)b * c.n_obj;
+            c.b_koff[b] = (int64_t)b * ((int64_t)c.G * c.G * c.G + 1);
+            if (b < (size_t)c.n_batch) {
+                c.b_obj0[b] = 0;
+                c.b_xoff[b] = 6 * (int64_t)b * c.n_obj;
+                c.b_G[b] = c.G;
+            }
+        }
 }
 
 // ---------------------------------------------------------------- checks
@@ -2322,7 +2333,7 @@ __global__ void k_ephem_eval(EphemArgs E, const double* __restrict__ t, int64_t 
 
 }  // namespace
 
-hipError_t fov_prepare(const FovParams& p, int32_t* qkey, int32_t* cnt, int32_t* cursor, void* scan_scratch,
+hipError_t fov_prepare(const FovParams& p, int32_t* qkey, int32_t* cnt, void* scan_scratch,
                        hipStream_t s) {
     const int64_t n_keys = p.n_keys;
     const int64_t F = p.n_frames;
@@ -2338,11 +2349,9 @@ hipError_t fov_prepare(const FovParams& p, int32_t* qkey, int32_t* cnt, int32_t*
     if (p.direct) {
         if (F > 0) hipLaunchKernelGGL(k_frame_rank, dim3(gF), dim3(256), 0, s, p, qkey);
     } else {
-        if ((e = fill_zero(cnt, (size_t)(n_keys + 1) * sizeof(int32_t), s)) != hipSuccess) return e;
         if (F > 0) hipLaunchKernelGGL(k_frame_keys, dim3(gF), dim3(256), 0, s, p, qkey, cnt);
         if ((e = exclusive_scan_i32(cnt, (int32_t*)p.cell_start, n_keys, scan_scratch, s)) != hipSuccess) return e;
-        if ((e = fill_zero(cursor, (size_t)n_keys * sizeof(int32_t), s)) != hipSuccess) return e;
-        if (F > 0) hipLaunchKernelGGL(k_frame_scatter, dim3(gF), dim3(256), 0, s, p, (const int32_t*)qkey, cursor);
+        if (F > 0) hipLaunchKernelGGL(k_frame_scatter, dim3(gF), dim3(256), 0, s, p, (const int32_t*)qkey, cnt);
     }
     // the locator pass writes the cell-ordered frame copies itself
     if (F > 0 && !p.loc) hipLaunchKernelGGL(k_frame_gather, dim3(gw), dim3(256), 0, s, p);
@@ -2364,7 +2373,6 @@ hipError_t fov_sort_objects(const FovParams& p, int32_t* okey, int32_t* orank, i
     const int64_t nkeys = p.n_keys;
     if (n == 0) return hipSuccess;
     hipError_t e;
-    if ((e = fill_zero(cnt, (size_t)(nkeys + 1) * sizeof(int32_t), s)) != hipSuccess) return e;
     // one block per (batch, chunk of kKeyBlock objects)
     const int64_t chunks = (p.max_batch_obj + kKeyBlock - 1) / kKeyBlock;
     if (p.n_batch <= 0 || chunks <= 0) return hipSuccess;
@@ -2381,10 +2389,12 @@ hipError_t fov_sort_objects(const FovParams& p, int32_t* okey, int32_t* orank, i
     return hipGetLastError();
 }
 
-hipError_t fov_single_job_layout(int64_t* b_poff, int32_t* b_obj0, int64_t* b_xoff, int32_t* b_G, int64_t* b_koff,
-                                 int64_t n_batch, int64_t n_obj, int G, hipStream_t s) {
-    hipLaunchKernelGGL(k_single_job_layout, dim3((unsigned)((n_batch + 1 + 255) / 256)), dim3(256), 0, s, b_poff,
-                       b_obj0, b_xoff, b_G, b_koff, n_batch, n_obj, G);
+hipError_t fov_clear(const FovClear& c, hipStream_t s) {
+    size_t most = c.G > 0 ? (size_t)c.n_batch + 1 : 0;
+    for (int k = 0; k < FovClear::kArrays; ++k) most = std::max(most, c.words[k]);
+    if (most == 0) return hipSuccess;
+    const unsigned g = (unsigned)std::min<size_t>((most + 255) / 256, 65536);
+    hipLaunchKernelGGL(k_fov_clear, dim3(g), dim3(256), 0, s, c);
     return hipGetLastError();
 }
 
@@ -2407,7 +2417,6 @@ hipError_t fov_candidates(FovParams& p, int32_t* icnt, int32_t* istart, ulonglon
     hipLaunchKernelGGL(k_item_count, dim3(gk), dim3(256), 0, s, p, icnt);
     if ((e = exclusive_scan_i32(icnt, istart, p.n_keys, scan_scratch, s)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_item_scatter, dim3(gk), dim3(256), 0, s, p, (const int32_t*)icnt);
-    if ((e = fill_zero(item_next, kJoinCursorWords * sizeof(unsigned int), s)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_fov_cells, dim3((unsigned)(cu_count() * kJoinWaves)), dim3(256), 0, s, p);
     // the wide list, with the join's item counts as scratch (free now)
     hipLaunchKernelGGL(k_wide_count, dim3((unsigned)((p.n_batch + 255) / 256)), dim3(256), 0, s, p, icnt);
@@ -2419,7 +2428,6 @@ hipError_t fov_candidates(FovParams& p, int32_t* icnt, int32_t* istart, ulonglon
     const unsigned gw = (unsigned)((p.n_pairs_total + 255) / 256);
     hipLaunchKernelGGL(k_wide_parts, dim3(gw), dim3(256), 0, s, p);
     if ((e = exclusive_scan_i32(p.wide_parts, p.wide_off, p.n_pairs_total, wide_scan_scratch, s)) != hipSuccess) return e;
-    if ((e = fill_zero(p.wide_next, kJoinCursorWords * sizeof(unsigned int), s)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_fov_wide, dim3((unsigned)(cu_count() * kJoinWaves)), dim3(256), 0, s, p);
     return hipGetLastError();
 }
@@ -2480,7 +2488,6 @@ hipError_t fov_sort(unsigned long long* keys, int64_t n, int64_t n_frames, int64
     const unsigned run_blocks = (unsigned)((n + kRunKeysPerBlock - 1) / kRunKeysPerBlock);
     if (n > 0) hipLaunchKernelGGL(k_pair_hist, dim3(run_blocks), dim3(256), 0, s, keys, n, fcnt);
     if ((e = exclusive_scan_i32(fcnt, fstart, n_frames, scan_scratch, s)) != hipSuccess) return e;
-    if ((e = fill_zero(fcnt, (size_t)n_frames * sizeof(int32_t), s)) != hipSuccess) return e;
     if (n > 0) hipLaunchKernelGGL(k_pair_scatter, dim3(run_blocks), dim3(256), 0, s, keys, n,
                                   (const int32_t*)fstart, fcnt, ob, seg);
     if (n_frames > 0) {

@@ -131,7 +131,7 @@ inline bool fov_is_direct(double obj_frames, int64_t n_pairs_total) {
 
 // Frame caps, batch records and the frames in the order the joins read:
 // sky cells, or batches for the direct join (qkey: each rank's batch).
-hipError_t fov_prepare(const FovParams& p, int32_t* qkey, int32_t* cnt, int32_t* cursor, void* scan_scratch,
+hipError_t fov_prepare(const FovParams& p, int32_t* qkey, int32_t* cnt, void* scan_scratch,
                        hipStream_t s);
 // Objects of every batch into sky-cell order (sorted, with start/cnt per
 // key), each cell's objects ordered by their sub-cell key (osub, scratch of
@@ -178,8 +178,20 @@ hipError_t fov_sort(unsigned long long* keys, int64_t n, int64_t n_frames, int64
 hipError_t launch_directions(const FovParams& p, const double* x_ref, double t_ref, const double* t_obs,
                              const double* obs, int64_t n_q, double* d, double* tau, hipStream_t s);
 hipError_t launch_ephem_eval(const EphemArgs& E, const double* t, int64_t n_q, double* out, hipStream_t s);
-hipError_t fov_single_job_layout(int64_t* b_poff, int32_t* b_obj0, int64_t* b_xoff, int32_t* b_G, int64_t* b_koff,
-                                 int64_t n_batch, int64_t n_obj, int G, hipStream_t s);
+// What a FoV call clears before its first kernel: the counters, the failed
+// objects' flags, and for the sorted join the cells' counts of frames (cnt of
+// fov_prepare) and of objects (cnt of fov_sort_objects).  Without host tables
+// (G > 0) the batches of a single job are laid out by the same launch.
+struct FovClear {
+    static constexpr int kArrays = 4;
+    unsigned int* p[kArrays];
+    size_t words[kArrays];
+    int64_t *b_poff, *b_xoff, *b_koff;
+    int32_t *b_obj0, *b_G;
+    int64_t n_batch, n_obj;
+    int32_t G;
+};
+hipError_t fov_clear(const FovClear& c, hipStream_t s);
 hipError_t fill_zero(void* p, size_t bytes, hipStream_t s);
 
 }  // namespace kete

@@ -677,6 +677,28 @@ def test_fov_pairs_of_a_frame_sorted(torch_cuda, copies):
     assert torch.equal(qo, torch.arange(copies, device="cuda", dtype=qo.dtype).repeat(one.numel()))
 
 
+@pytest.mark.parametrize("n_frames", [8191, 8192, 8193, (1 << 20) + 1])
+def test_fov_frame_counts(torch_cuda, n_frames):
+    """Numbers of frames at which the prefix sums over them change hands:
+    copies of 300 frames, each with its original's pairs."""
+    torch, api = torch_cuda
+    case = synth.footprint_case(n_obj=5000, n_frames=300, span=3.0)
+    fr = dataclasses.replace(case.frames, normals=np.ascontiguousarray(case.frames.normals[:, 20:21]))
+    eph = api.DeviceEphemeris.from_synth(case.ephem)
+    x, _ = api.propagate(eph, _dev_x(torch, case.x0), 0.0, [1.5])
+    one = lambda n: api.Batches.from_host(np.arange(n, dtype=np.int32), np.array([0, n], np.int32), np.array([1.5]))
+    pf, ps, po = api.fov_check(eph, x, one(300), api.DeviceFrames.from_synth(fr))
+    assert pf.numel() > 0
+    k = np.arange(n_frames) % 300
+    many = dataclasses.replace(fr, t=fr.t[k], obs=fr.obs[k], normals=fr.normals[k])
+    qf, qs, qo = api.fov_check(eph, x, one(n_frames), api.DeviceFrames.from_synth(many))
+    c = torch.arange((n_frames + 299) // 300, device="cuda")[:, None] * 300
+    f = (c + pf[None, :].long()).ravel()
+    keep = f < n_frames
+    assert torch.equal(qf.long(), f[keep])
+    assert torch.equal(qo, po.repeat(c.shape[0])[keep]) and int(qs.abs().max()) == 0
+
+
 def test_fov_capacity_and_empty(torch_cuda, orc):
     torch, api = torch_cuda
     from paper_2509_04666_amd import _lib
