@@ -877,6 +877,8 @@ int kete_fov_check(const kete_ephem_t* eph, const double* x_epoch, int32_t* stat
     P.mu = E.gm[0];
     P.smu = std::sqrt(E.gm[0]);
     P.c_light = cl;
+    P.inv_mu = 1.0 / P.mu;
+    P.inv_c = 1.0 / cl;
     P.lt_tol = opts->lt_tol > 0 ? opts->lt_tol : 1e-15;
     P.lt_iter = opts->lt_iter > 0 ? opts->lt_iter : 10;
     if (opts->kepler_iter < 0) return fail(KETE_EINVAL, "kepler_iter must be >= 0");
@@ -1390,6 +1392,8 @@ int kete_batch_run(const kete_ephem_t* eph, const kete_batch_t* batch, int64_t p
     P.mu = E.gm[0];
     P.smu = std::sqrt(E.gm[0]);
     P.c_light = cl;
+    P.inv_mu = 1.0 / P.mu;
+    P.inv_c = 1.0 / cl;
     P.lt_tol = opts->lt_tol > 0 ? opts->lt_tol : 1e-15;
     P.lt_iter = opts->lt_iter > 0 ? opts->lt_iter : 10;
     if (opts->kepler_iter < 0) return fail(KETE_EINVAL, "kepler_iter must be >= 0");

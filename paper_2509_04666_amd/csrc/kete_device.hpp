@@ -489,6 +489,28 @@ __device__ __forceinline__ double lane_value(double v, int m) {
 }
 
 // Wave-wide reductions over the 64 lanes (results are wave-uniform).
+// 1/sqrt(x) for a positive normal x: the hardware estimate y0 times the
+// series (1 - e)^(-1/2) = 1 + e/2 + 3e^2/8 + O(e^3), e = 1 - x y0^2.  The
+// truncation leaves a relative error of about 5e^3/16, below an ulp when
+// the estimate is good to 2^-19.  No special-value handling: a zero or
+// non-finite x gives a non-finite result, reported as a failed body.
+__device__ __forceinline__ double rsqrt_pos(double x) {
+    const double y0 = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y0, y0, 1.0);
+    return fma(y0 * e, fma(e, 0.375, 0.5), y0);
+}
+
+// sqrt(x) from it, 0 for x = 0, and 1/x for a normal x (two Newton steps on
+// the estimate): within a few ulp, without the special cases that make the
+// compiler's own two to three times as long.  A negative, infinite or NaN x
+// gives NaN in both.
+__device__ __forceinline__ double sqrt_pos(double x) { return x == 0.0 ? 0.0 : x * rsqrt_pos(x); }
+__device__ __forceinline__ double rcp_norm(double x) {
+    double y = __builtin_amdgcn_rcp(x);
+    y = fma(fma(-x, y, 1.0), y, y);
+    return fma(fma(-x, y, 1.0), y, y);
+}
+
 // True in the wavefront's first lane, in a form the optimizer cannot carry
 // from one pass of a loop to the next: knowing that a lane is not the first,
 // the compiler sent the other lanes of a loop that begins with

@@ -537,45 +537,49 @@ __device__ __forceinline__ bool object_bounds(const FovParams& p, int b, int64_t
     const double Dobs = bt[9], Delta = bt[10], cosRm = bt[11], sinRm = bt[12], Vsun = bt[13];
     double r0[3], v0[3];
     for (int c = 0; c < 3; ++c) { r0[c] = o.x[c] - bt[c]; v0[c] = o.v[c] - bt[3 + c]; }
-    const double r0n = sqrt(dot3(r0, r0));
+    // (Square roots and quotients within a few ulp suffice: every bound below
+    // is widened by 1e-12 or more.  A NaN ends as `overflow`.)
+    const double r2 = dot3(r0, r0), ir0 = rsqrt_pos(r2), r0n = r2 * ir0;
     const double v2 = dot3(v0, v0);
     double hv[3];
     cross3(r0, v0, hv);
-    const double hn = sqrt(dot3(hv, hv));
+    const double h2 = dot3(hv, hv);
     const double rv = dot3(r0, v0);
     double ev[3];
-    for (int c = 0; c < 3; ++c) ev[c] = ((v2 - mu / r0n) * r0[c] - rv * v0[c]) / mu;
-    const double ecc = sqrt(dot3(ev, ev));
-    const double vp = (hn > 0.0) ? mu * (1.0 + ecc) / hn * (1.0 + 1e-12) : 1e300;
-    const double q = (hn > 0.0) ? hn * hn / (mu * (1.0 + ecc)) * (1.0 - 1e-12) : 0.0;
+    const double w = fma(-mu, ir0, v2);
+    for (int c = 0; c < 3; ++c) ev[c] = (w * r0[c] - rv * v0[c]) * p.inv_mu;
+    const double e1 = 1.0 + sqrt_pos(dot3(ev, ev));
+    const double vp = (h2 > 0.0) ? mu * e1 * rsqrt_pos(h2) * (1.0 + 1e-12) : 1e300;
+    const double q = (h2 > 0.0) ? h2 * p.inv_mu * rcp_norm(e1) * (1.0 - 1e-12) : 0.0;
     const double V = vp + Vsun;
     double dref[3];
     for (int c = 0; c < 3; ++c) dref[c] = o.x[c] - bt[6 + c];
-    const double dn = sqrt(dot3(dref, dref));
-    for (int c = 0; c < 3; ++c) o.dh[c] = dref[c] / dn;
+    const double d2 = dot3(dref, dref), idn = rsqrt_pos(d2), dn = d2 * idn;
+    for (int c = 0; c < 3; ++c) o.dh[c] = dref[c] * idn;
     const bool bounded = (V < 0.5 * cl) && (dn > 0.0);
     o.taumax = 0.0; o.sth = 1.0; o.cth = 0.0;
     o.overflow = !bounded;
     if (bounded) {
-        o.taumax = (dn + Dobs + V * Delta) / (cl - V) * (1.0 + 1e-12);
+        o.taumax = (dn + Dobs + V * Delta) * rcp_norm(cl - V) * (1.0 + 1e-12);
         const double delta = V * (Delta + o.taumax) + Dobs + 1e-12;
-        o.sth = delta / dn;
+        o.sth = delta * idn;
         if (!(o.sth < p.sin_overflow)) o.overflow = true;
-        else o.cth = sqrt(1.0 - o.sth * o.sth);
+        else o.cth = sqrt_pos(1.0 - o.sth * o.sth);
     }
     // the linear test also uses the Sun's acceleration bound, which covers
     // light times up to kMaxLightDays
     o.lin_ok = bounded && o.taumax <= kMaxLightDays;
     const double rmin = fmax(q, r0n - vp * (Delta + o.taumax));
-    o.a2b = (rmin > 0.0) ? mu / (rmin * rmin) : 1e300;
-    o.vbn = sqrt(dot3(o.v, o.v));
+    const double irm = rcp_norm(rmin);
+    o.a2b = (rmin > 0.0) ? mu * irm * irm : 1e300;
+    o.vbn = sqrt_pos(dot3(o.v, o.v));
     o.ncell = 0;
     if (!o.overflow) {
         const double cosRT = cosRm * o.cth - sinRm * o.sth;      // cos(Rmax + theta)
         if (!(cosRT > 0.0)) {
             o.overflow = true;
         } else if constexpr (kBox) {
-            const double chord = sqrt(2.0 - 2.0 * cosRT) + 1e-9;
+            const double chord = sqrt_pos(2.0 - 2.0 * cosRT) + 1e-9;
             o.ncell = 1;
             for (int c = 0; c < 3; ++c) {
                 o.lo[c] = cell_coord(o.dh[c] - chord, p.b_G[b]);
@@ -631,15 +635,15 @@ __device__ __forceinline__ double lin_predict(const ObjBounds& o, const double o
 // light-time term |v| tau_max, which dominates eps0 for most bodies, is
 // scaled down by |v| / c.  Returns the bound, doubled as lin_predict's.
 __device__ __forceinline__ double lin_predict_lt(const ObjBounds& o, const double ob[4], double tr, double Asun,
-                                                 double c_light, double ul[3]) {
+                                                 double inv_c, double ul[3]) {
     const double dt = ob[0] - tr;
     double u0[3];
     for (int c = 0; c < 3; ++c) u0[c] = o.x[c] + o.v[c] * dt - ob[1 + c];
-    const double tau0 = sqrt(dot3(u0, u0)) / c_light;
+    const double tau0 = sqrt_pos(dot3(u0, u0)) * inv_c;
     for (int c = 0; c < 3; ++c) ul[c] = u0[c] - o.v[c] * tau0;
     const double ad = fabs(dt) + o.taumax;
     const double acc = 0.5 * (o.a2b + Asun) * ad * ad;
-    return 2.0 * (acc + o.vbn * (o.vbn * o.taumax + acc) / c_light + 1e-12);
+    return 2.0 * (acc + o.vbn * (o.vbn * o.taumax + acc) * inv_c + 1e-12);
 }
 
 // Can a line of sight within e2 of ul reach the frame's cap (centre cp,
@@ -710,9 +714,9 @@ __device__ __forceinline__ void sub_candidates(int S, bool have_loc, const LocHe
     if (!(uc > 0.0)) return;
     // (the product with 1 / uc and the bound 1 / (1 - q) <= 1 + 2q for
     // q <= 1/2 replace two divisions; both errors are far inside the margin)
-    const double iuc = 1.0 / uc;
+    const double iuc = rcp_norm(uc);
     const double X = dot3(u, h.e1) * iuc, Y = dot3(u, h.e2) * iuc;
-    const double ru = sqrt(X * X + Y * Y);
+    const double ru = sqrt_pos(X * X + Y * Y);
     if (!(ru * t < 0.5)) return;
     const double T = (ru + t) * (1.0 + 2.0 * ru * t);
     const double mg = t * (1.0 + T * T) * (1.0 + 1e-9) + 1e-12 * (1.0 + ru);
@@ -787,7 +791,7 @@ __device__ void classify_emit(const FovParams& p, bool has, const ObjBounds& o, 
         all = !o.lin_ok;
         if (o.lin_ok) {
             const double ob[4] = {ob01.x, ob01.y, ob23.x, ob23.y};
-            e2 = lin_predict_lt(o, ob, tr, Asun, p.c_light, ul);
+            e2 = lin_predict_lt(o, ob, tr, Asun, p.inv_c, ul);
             const double u2 = dot3(ul, ul);
             if (!(e2 * e2 < u2)) {
                 all = true;
@@ -796,7 +800,7 @@ __device__ void classify_emit(const FovParams& p, bool has, const ObjBounds& o, 
                 const ulonglong2* M = p.loc ? reinterpret_cast<const ulonglong2*>(
                                                   p.loc + (size_t)kLocStride * (unsigned)r + kLocHead)
                                             : nullptr;
-                sub_candidates(p.n_sub, p.loc != nullptr, h, M, ul, e2 / sqrt(u2 - e2 * e2), m);
+                sub_candidates(p.n_sub, p.loc != nullptr, h, M, ul, e2 * rsqrt_pos(u2 - e2 * e2), m);
                 m0 = m[0];
                 m1 = m[1];
             }

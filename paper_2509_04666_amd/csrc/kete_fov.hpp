@@ -100,6 +100,7 @@ struct FovParams {
     int32_t wide_max_parts;     // parts per object at most (their total must stay below 2^31)
     int32_t pad2;
     double mu, smu, c_light, lt_tol;
+    double inv_mu, inv_c;       // 1 / mu, 1 / c_light
     int32_t lt_iter;
     int32_t max_cells;
     double sin_overflow;

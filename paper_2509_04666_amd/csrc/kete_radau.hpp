@@ -517,17 +517,6 @@ __device__ __forceinline__ void node_ephemeris8(const EphemArgs& E, const GroupC
     wave_lds_sync();
 }
 
-// 1/sqrt(x) for a positive normal x: the hardware estimate y0 times the
-// series (1 - e)^(-1/2) = 1 + e/2 + 3e^2/8 + O(e^3), e = 1 - x y0^2.  The
-// truncation leaves a relative error of about 5e^3/16, below an ulp when
-// the estimate is good to 2^-19.  No special-value handling: a zero or
-// non-finite x gives a non-finite result, reported as a failed body.
-__device__ __forceinline__ double rsqrt_pos(double x) {
-    const double y0 = __builtin_amdgcn_rsq(x);
-    const double e = fma(-x * y0, y0, 1.0);
-    return fma(y0 * e, fma(e, 0.375, 0.5), y0);
-}
-
 // Adds to a[] the terms of M slots, pb + m step: Eq. A.1, with GR Eq. A.3
 // (nothing for slots whose GM/c^2 is zero), and for the first MJ of them
 // Eq. A.4 with the constants jc + 4 m jstep (see j2_add; its part along r
