@@ -511,6 +511,13 @@ __device__ __forceinline__ double rcp_norm(double x) {
     return fma(fma(-x, y, 1.0), y, y);
 }
 
+// A 64-bit value of one lane (wave-uniform index).
+__device__ __forceinline__ unsigned long long lane_value64(unsigned long long x, int l) {
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)x, l);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(x >> 32), l);
+    return (unsigned long long)hi << 32 | lo;
+}
+
 // True in the wavefront's first lane, in a form the optimizer cannot carry
 // from one pass of a loop to the next: knowing that a lane is not the first,
 // the compiler sent the other lanes of a loop that begins with

@@ -522,13 +522,11 @@ struct ObjBounds {
 //    moves by at most asin of that over |d_ref|;
 //  - between the batch epoch and the emission time the heliocentric
 //    acceleration is at most mu / r_min^2 with r_min >= perihelion.
-// Returns false for failed or non-finite objects.  With kBox the cap's box on
+// state_bounds starts from the state in o; both return false for failed or
+// non-finite objects.  With kBox the cap's box on
 // the batch's sky grid is formed too, for the joins that go by its cells.
-template <bool kBox = true>
-__device__ __forceinline__ bool object_bounds(const FovParams& p, int b, int64_t j, ObjBounds& o) {
-    if (p.status && p.status[p.b_obj0[b] + j] != 0) return false;
-    const double* st = p.x_epoch + p.b_xoff[b] + 6 * j;
-    for (int c = 0; c < 3; ++c) { o.x[c] = st[c]; o.v[c] = st[3 + c]; }
+template <bool kBox>
+__device__ __forceinline__ bool state_bounds(const FovParams& p, int b, ObjBounds& o) {
     if (!(isfinite(o.x[0]) && isfinite(o.x[1]) && isfinite(o.x[2]) && isfinite(o.v[0]) && isfinite(o.v[1]) &&
           isfinite(o.v[2])))
         return false;
@@ -590,6 +588,13 @@ __device__ __forceinline__ bool object_bounds(const FovParams& p, int b, int64_t
         }
     }
     return true;
+}
+
+__device__ __forceinline__ bool object_bounds(const FovParams& p, int b, int64_t j, ObjBounds& o) {
+    if (p.status && p.status[p.b_obj0[b] + j] != 0) return false;
+    const double* st = p.x_epoch + p.b_xoff[b] + 6 * j;
+    for (int c = 0; c < 3; ++c) { o.x[c] = st[c]; o.v[c] = st[3 + c]; }
+    return state_bounds<true>(p, b, o);
 }
 
 constexpr int kNarrowCells = 27;
@@ -1233,8 +1238,9 @@ __global__ __launch_bounds__(256, kJoinWaves) void k_fov_cells(const FovParams p
 // them the lanes form their object's bounds and take the per-cell join's
 // tests frame by frame, and the pairs that pass, a few per thousand, the
 // sub-frame tests.  An object's state is read once per item and batch, in
-// order; the bounds' FP64 work sets the time: 100,000 objects x 1,368 batches
-// of a frame take 3.6 ms, 1.8 TB/s (13 ms by way of the sorted join).
+// order and a batch ahead; the bounds' FP64 work and those reads set the time:
+// 100,000 objects x 1,368 batches of a frame take 2.4 ms, 2.8 TB/s (13 ms by
+// way of the sorted join, 3.2 without reading ahead).
 __global__ __launch_bounds__(256, kJoinWaves) void k_fov_direct(const FovParams p, const int32_t* __restrict__ qbatch,
                                                                 int per, int64_t n_rank_items, int64_t n_obj_items) {
     const int lane = threadIdx.x & 63, wv = (threadIdx.x >> 6) & 3;
@@ -1272,7 +1278,23 @@ __global__ __launch_bounds__(256, kJoinWaves) void k_fov_direct(const FovParams 
             const int off = p.batch_off[bl];
             const int r0 = max(off, q0), r1 = min(p.batch_off[bl + 1], q1);
             const int64_t n_obj_l = p.b_poff[bl + 1] - p.b_poff[bl];
+            const int64_t xoff_l = p.b_xoff[bl];
+            const int obj0_l = p.b_obj0[bl];
             unsigned long long todo = __ballot(bb + lane <= b_last && r1 > r0 && n_obj_l > j0);
+            // an object's state for the next batch is read during a batch
+            double nx[6];
+            int n_status = 0;
+            auto read = [&](int s) {
+                const int64_t j = j0 + lane;
+                if (j >= (int64_t)lane_value64((unsigned long long)n_obj_l, s)) return;
+                const double* st = p.x_epoch + (int64_t)lane_value64((unsigned long long)xoff_l, s) + 6 * j;
+#pragma unroll
+                for (int c = 0; c < 6; ++c) nx[c] = st[c];
+                if (p.status) n_status = p.status[__builtin_amdgcn_readlane(obj0_l, s) + j];
+            };
+#pragma unroll
+            for (int c = 0; c < 6; ++c) nx[c] = 0.0;
+            if (todo) read(__ffsll((long long)todo) - 1);
             for (; todo != 0ull; todo &= todo - 1ull) {
                 const int src = __ffsll((long long)todo) - 1;
                 const int b = bb + src;
@@ -1280,12 +1302,14 @@ __global__ __launch_bounds__(256, kJoinWaves) void k_fov_direct(const FovParams 
                 const int64_t j = j0 + lane;
                 ObjBounds o;
 #pragma unroll
-                for (int c = 0; c < 3; ++c) { o.x[c] = 0.0; o.v[c] = 0.0; }
+                for (int c = 0; c < 3; ++c) { o.x[c] = nx[c]; o.v[c] = nx[3 + c]; }
+                const bool failed = n_status != 0;
+                if (todo & (todo - 1ull)) read(__ffsll((long long)(todo & (todo - 1ull))) - 1);
                 o.taumax = o.vbn = o.a2b = 0.0;
                 o.lin_ok = false;
                 o.overflow = false;
-                const bool has = j < p.b_poff[b + 1] - p.b_poff[b];
-                const bool live = has && object_bounds<false>(p, b, j, o);
+                const bool has = j < (int64_t)lane_value64((unsigned long long)n_obj_l, src);
+                const bool live = has && !failed && state_bounds<false>(p, b, o);
                 if (__ballot(live) == 0ull) continue;
                 // (an object's frames of a batch may lie in several items)
                 if (f0 == __builtin_amdgcn_readlane(off, src)) n_over += __popcll(__ballot(live && o.overflow));
@@ -1293,7 +1317,7 @@ __global__ __launch_bounds__(256, kJoinWaves) void k_fov_direct(const FovParams 
                 const double Asun = p.btab[kBatchStride * b + 14];
                 // global object index; bit 63 set: no linear test
                 const unsigned long long gtag =
-                    (unsigned long long)(p.b_obj0[b] + j) | (o.lin_ok ? 0ull : (1ull << 63));
+                    (unsigned long long)(__builtin_amdgcn_readlane(obj0_l, src) + j) | (o.lin_ok ? 0ull : (1ull << 63));
                 int nq = 0;                   // queued (object, frame) pairs, wave-uniform
                 auto drain = [&](int n) {     // sub-frame tests of the first n, one per lane
                     const bool queued = lane < n;
@@ -1562,7 +1586,6 @@ __global__ __launch_bounds__(256, kJoinWaves) void k_fov_wide(const FovParams p)
 // global atomic per distinct key of the block, so objects sharing a cell
 // do not queue on its global counter one by one.
 constexpr int kKeyBlock = 256;
-constexpr int kKeySlots = 2 * kKeyBlock;     // at most half full: probing always ends
 // Sub-cell key of a narrow object: the Morton code of its direction's
 // position on a kSubL^3 grid inside its sky cell, with the objects whose
 // motion cap is wider than kFastCapSin after all the others, so that runs
@@ -1584,52 +1607,67 @@ __device__ __forceinline__ int sub_cell_key(const ObjBounds& o, int G) {
     return m | (o.sth > kFastCapSin ? kSubL * kSubL * kSubL : 0);
 }
 
+// kPer objects a thread: of 2,048 objects at a time fewer land in cells of
+// their own, and the atomics, 19 of them a nanosecond, are what the kernel
+// waits for (750,000 objects x 122 batches: 3.7 ms with one, 1.6 with eight).
+template <int kPer>
 __global__ __launch_bounds__(kKeyBlock) void k_obj_keys(const FovParams p, int32_t* __restrict__ okey,
                                                         int32_t* __restrict__ orank, int32_t* __restrict__ cnt,
                                                         int32_t* __restrict__ osub) {
-    __shared__ int32_t hkey[kKeySlots], hcnt[kKeySlots], hbase[kKeySlots];
+    constexpr int kSlots = 2 * kPer * kKeyBlock;        // at most half full: probing always ends
+    constexpr int kSlotBits = kPer == 1 ? 9 : 12;
+    static_assert(kSlots == 1 << kSlotBits, "a hash of kSlotBits bits");
+    __shared__ int32_t hkey[kSlots], hcnt[kSlots];      // hcnt: the block's count, then its base
     const int tid = threadIdx.x;
-    for (int k = tid; k < kKeySlots; k += kKeyBlock) { hkey[k] = -1; hcnt[k] = 0; }
+    for (int k = tid; k < kSlots; k += kKeyBlock) { hkey[k] = -1; hcnt[k] = 0; }
     __syncthreads();
     // block k takes chunk k / n_batch of batch k % n_batch: the blocks in
     // flight at any time spread over every batch, so that the per-cell
     // counters they update (disjoint between batches) are not all hit at
     // once
     const int b = (int)(blockIdx.x % (unsigned)p.n_batch);
-    const int64_t j = (int64_t)(blockIdx.x / (unsigned)p.n_batch) * kKeyBlock + tid;
-    const int64_t i = p.b_poff[b] + j;
-    const bool valid = i < p.b_poff[b + 1];
-    int slot = 0, lrank = 0;
-    if (valid) {
-        ObjBounds o;
-        const int G = p.b_G[b], G3 = G * G * G;
-        int key, sk;
-        const bool live = object_bounds(p, b, j, o);
-        if (live && is_narrow(o, G)) {
-            key = (int)(p.b_koff[b] + cell_of(o.dh, G));
-            sk = sub_cell_key(o, G);
-        } else {
-            // the batch's wide slot: wide objects ordered by a coarse sky
-            // key (the Morton code of the direction on a kSubL^3 grid of the
-            // whole sphere's cube), objects out of the join last
-            key = (int)(p.b_koff[b] + G3);
-            sk = live ? sub_cell_key(o, 1) : kSubKeys - 1;
+    const int64_t j0 = (int64_t)(blockIdx.x / (unsigned)p.n_batch) * (kPer * kKeyBlock) + tid;
+    const int64_t i0 = p.b_poff[b], i1 = p.b_poff[b + 1];
+    const int G = p.b_G[b], G3 = G * G * G;
+    int slots[kPer], ranks[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int64_t j = j0 + q * kKeyBlock, i = i0 + j;
+        slots[q] = -1;
+        ranks[q] = 0;
+        if (i < i1) {
+            ObjBounds o;
+            int key, sk;
+            const bool live = object_bounds(p, b, j, o);
+            if (live && is_narrow(o, G)) {
+                key = (int)(p.b_koff[b] + cell_of(o.dh, G));
+                sk = sub_cell_key(o, G);
+            } else {
+                // the batch's wide slot: wide objects ordered by a coarse sky
+                // key (the Morton code of the direction on a kSubL^3 grid of the
+                // whole sphere's cube), objects out of the join last
+                key = (int)(p.b_koff[b] + G3);
+                sk = live ? sub_cell_key(o, 1) : kSubKeys - 1;
+            }
+            okey[i] = key;
+            osub[i] = sk;
+            int slot = (int)(((unsigned)key * 2654435761u) >> (32 - kSlotBits));
+            for (;;) {
+                const int prev = atomicCAS(&hkey[slot], -1, key);
+                if (prev == -1 || prev == key) break;
+                slot = (slot + 1) & (kSlots - 1);
+            }
+            slots[q] = slot;
+            ranks[q] = atomicAdd(&hcnt[slot], 1);
         }
-        okey[i] = key;
-        osub[i] = sk;
-        slot = (int)(((unsigned)key * 2654435761u) >> 23) & (kKeySlots - 1);
-        for (;;) {
-            const int prev = atomicCAS(&hkey[slot], -1, key);
-            if (prev == -1 || prev == key) break;
-            slot = (slot + 1) & (kKeySlots - 1);
-        }
-        lrank = atomicAdd(&hcnt[slot], 1);
     }
     __syncthreads();
-    for (int k = tid; k < kKeySlots; k += kKeyBlock)
-        if (hkey[k] >= 0) hbase[k] = atomicAdd(cnt + hkey[k], hcnt[k]);
+    for (int k = tid; k < kSlots; k += kKeyBlock)
+        if (hkey[k] >= 0) hcnt[k] = atomicAdd(cnt + hkey[k], hcnt[k]);
     __syncthreads();
-    if (valid) orank[i] = hbase[slot] + lrank;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q)
+        if (slots[q] >= 0) orank[i0 + j0 + q * kKeyBlock] = hcnt[slots[q]] + ranks[q];
 }
 
 // Objects into their cell's slots, at the rank the key pass drew (the order
@@ -2381,7 +2419,14 @@ hipError_t fov_sort_objects(const FovParams& p, int32_t* okey, int32_t* orank, i
     const int64_t chunks = (p.max_batch_obj + kKeyBlock - 1) / kKeyBlock;
     if (p.n_batch <= 0 || chunks <= 0) return hipSuccess;
     const unsigned gk = (unsigned)(p.n_batch * chunks);
-    hipLaunchKernelGGL(k_obj_keys, dim3(gk), dim3(kKeyBlock), 0, s, p, okey, orank, cnt, osub);
+    // eight objects a thread where that leaves eight blocks a compute unit
+    if (n >= (int64_t)cu_count() * 8 * 8 * kKeyBlock) {
+        const int64_t big = (p.max_batch_obj + 8 * kKeyBlock - 1) / (8 * kKeyBlock);
+        hipLaunchKernelGGL(k_obj_keys<8>, dim3((unsigned)(p.n_batch * big)), dim3(kKeyBlock), 0, s, p, okey, orank, cnt,
+                           osub);
+    } else {
+        hipLaunchKernelGGL(k_obj_keys<1>, dim3(gk), dim3(kKeyBlock), 0, s, p, okey, orank, cnt, osub);
+    }
     if ((e = exclusive_scan_i32(cnt, start, nkeys, scan_scratch, s)) != hipSuccess) return e;
     static_assert(kKeyBlock == 256, "the scatter uses the key pass's chunks");
     hipLaunchKernelGGL(k_obj_scatter, dim3(gk), dim3(256), 0, s, p, (const int32_t*)okey, (const int32_t*)orank,
