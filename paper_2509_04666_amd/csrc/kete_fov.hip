@@ -274,9 +274,18 @@ __global__ __launch_bounds__(256) void k_frame_locator(const FovParams p) {
             if (lane < 3) v = c[lane];
             else if (lane < 6) v = e1[lane - 3];
             else if (lane < 9) v = e2[lane - 6];
-            else if (usable)
-                v = lane == 9 ? x0 : lane == 10 ? y0 : lane == 11 ? idx : lane == 12 ? idy : lane == 13 ? 1.0
-                  : lane == 14 ? x0 + kLocL / idx : y0 + kLocL / idy;
+            else if (lane == 14) v = p.ft[f];
+            else if (lane >= 15 && lane < 18) {
+                const double* o = p.fobs + 3 * (size_t)f;
+                v = dot3(o, lane == 15 ? c : lane == 16 ? e1 : e2);
+            } else if (usable) {
+                const double e = fmax(fmax(fabs(x0), fabs(x1)), fmax(fabs(y0), fabs(y1)));
+                v = lane == 9 ? x0 : lane == 10 ? y0 : lane == 11 ? x1 : lane == 12 ? y1
+                  : lane == 13 ? sqrt(1.0 + e * e) * (1.0 + 1e-9) : lane == 18 ? 1.0
+                  : lane == 19 ? idx : lane == 20 ? idy : 0.0;
+            } else if (lane == 13) {
+                v = 1e300;
+            }
             L[lane] = v;
         }
     }
@@ -666,7 +675,7 @@ __device__ __forceinline__ bool lin_cap_hit(const double* __restrict__ cp, const
     return a >= 0.0 && a * a >= cp[3] * cp[3] * (u2 - e2 * e2);
 }
 
-// Locator header of one frame (see kLocStride), read with eight 16-byte
+// Locator header of one frame (see kLocStride), read with nine 16-byte
 // loads issued together rather than one dependent read after another.
 struct LocHead {
     double c[3], e1[3], e2[3];
@@ -674,13 +683,13 @@ struct LocHead {
 };
 __device__ __forceinline__ LocHead loc_head(const double* __restrict__ L) {
     const double2* q = reinterpret_cast<const double2*>(L);
-    const double2 a = q[0], b = q[1], c = q[2], d = q[3], e = q[4], f = q[5], g = q[6], k = q[7];
+    const double2 a = q[0], b = q[1], c = q[2], d = q[3], e = q[4], f = q[5], g = q[6], k = q[9], l = q[10];
     LocHead h;
     h.c[0] = a.x; h.c[1] = a.y; h.c[2] = b.x;
     h.e1[0] = b.y; h.e1[1] = c.x; h.e1[2] = c.y;
     h.e2[0] = d.x; h.e2[1] = d.y; h.e2[2] = e.x;
-    h.x0 = e.y; h.y0 = f.x; h.idx = f.y; h.idy = g.x; h.usable = g.y;
-    h.x1 = k.x; h.y1 = k.y;
+    h.x0 = e.y; h.y0 = f.x; h.x1 = f.y; h.y1 = g.x;
+    h.usable = k.x; h.idx = k.y; h.idy = l.x;
     return h;
 }
 
@@ -1026,6 +1035,7 @@ struct __align__(16) FrameRec {
 };
 
 constexpr int kLinQueue = 2 * kWave;
+constexpr int kLocChunk = 32;          // frame records staged at once where frames have locators
 
 // Persistent join: every wavefront pops work items until none is left.
 // An item is up to 64 narrow objects of one (batch, cell), one per lane;
@@ -1040,6 +1050,7 @@ constexpr int kLinQueue = 2 * kWave;
 // one XCD start on their own slice of the list, so that neighbouring cells
 // share that XCD's L2, and help the other slices when theirs runs out.
 constexpr int kJoinWaves = 3;        // resident waves per SIMD of the join kernels (168 VGPRs, a few spilled)
+template <bool kLoc>
 __global__ __launch_bounds__(256, kJoinWaves) void k_fov_cells(const FovParams p) {
     const int lane = threadIdx.x & 63, wv = (threadIdx.x >> 6) & 3;
     unsigned long long n_cand = 0, n_exact = 0, n_visit = 0;
@@ -1047,12 +1058,16 @@ __global__ __launch_bounds__(256, kJoinWaves) void k_fov_cells(const FovParams p
     const int n_items = p.item_start[p.n_keys];
     __shared__ unsigned long long bufs[4][kBufEntries], pbufs[4][kPairBufEntries];
     __shared__ unsigned long long queue_all[4][kLinQueue];
-    __shared__ FrameRec fcap_all[4][kWave];
+    __shared__ FrameRec fcap_all[kLoc ? 1 : 4][kLoc ? 1 : kWave];
+    __shared__ __align__(16) double lrec_all[kLoc ? 4 : 1][kLoc ? kLocChunk * kLocJoin : 1];
+    __shared__ int kept_all[kLoc ? 4 : 1][kLoc ? 2 * kWave : 1];
     __shared__ unsigned long long s_stat[4][4];
     unsigned long long* buf = bufs[wv];
     unsigned long long* pbuf = pbufs[wv];
     int npbuf = 0;
-    FrameRec* fcap = fcap_all[wv];
+    FrameRec* fcap = fcap_all[kLoc ? 0 : wv];
+    double* lrec = lrec_all[kLoc ? wv : 0];
+    int* kept = kept_all[kLoc ? wv : 0];
     unsigned long long* queue = queue_all[wv];
     const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     int nbuf = 0;
@@ -1158,11 +1173,76 @@ __global__ __launch_bounds__(256, kJoinWaves) void k_fov_cells(const FovParams p
             lo.lin_ok = (g >> 63) == 0ull;
             classify_emit(p, queued, lo, r, tr, Asun, g & ~(1ull << 63), buf, nbuf, pbuf, npbuf, n_exact);
         };
-        for (int g0 = 0; g0 < total; g0 += kWave) {
+        auto offer = [&](bool hit, unsigned rq) {
+            const unsigned long long mask = __ballot(hit);
+            if (mask == 0ull) return;
+            if (hit) ++n_cand;
+            if (hit) queue[nq + __popcll(mask & lt)] = ((unsigned long long)rq << 8) | (unsigned long long)lane;
+            nq += __popcll(mask);
+            if (nq >= kWave) {
+                wave_lds_sync();
+                drain(kWave);
+                // move the overflow to the front (fewer than 64 entries)
+                const unsigned long long rest = lane < nq - kWave ? queue[kWave + lane] : 0ull;
+                wave_lds_sync();
+                if (lane < nq - kWave) queue[lane] = rest;
+                nq -= kWave;
+                wave_lds_sync();
+            }
+        };
+        // The linear prediction's bound as k0 + k1 (|dt| + taumax)^2; lanes
+        // without a linear test are few and take the locator-box test.
+        const double k0 = 2.0 * (o.vbn * o.taumax + 1e-12), k1 = o.a2b + Asun;
+        const bool lin = live && o.lin_ok;
+        const bool any_wide = __ballot(live && !o.lin_ok) != 0ull;
+        int nk = 0;                           // frames kept and not yet visited, wave-uniform
+        // Visits the first n <= kLocChunk kept frames (kLoc).  An object on x
+        // + v dt, within e2 of it, can lie in the frame's box only if it is
+        // above each of the box's edge planes less e2 times the plane's norm
+        // (1e-11 more covers rounding at up to 1,000 au).
+        auto visit_kept = [&](int n) {
+            wave_lds_sync();                  // the list is written, the previous records are read
+            constexpr int kWords = kLocJoin / 2;
+            for (int i = lane; i < n * kWords; i += kWave) {
+                const int m = i / kWords, w = i - m * kWords;
+                reinterpret_cast<double2*>(lrec)[i] =
+                    reinterpret_cast<const double2*>(p.loc + (size_t)kLocStride * (unsigned)kept[m])[w];
+            }
+            wave_lds_sync();
+            n_visit += (unsigned long long)n;
+            for (int m = 0; m < n; ++m) {
+                const double2* q = reinterpret_cast<const double2*>(lrec + kLocJoin * m);
+                const double2 q0 = q[0], q1 = q[1], q2 = q[2], q3 = q[3], q4 = q[4], q5 = q[5], q6 = q[6], q7 = q[7],
+                              q8 = q[8];
+                const unsigned rq = (unsigned)kept[m];
+                const double dt = q7.x - tr, ad = fabs(dt) + o.taumax;
+                const double u[3] = {fma(o.v[0], dt, o.x[0]), fma(o.v[1], dt, o.x[1]), fma(o.v[2], dt, o.x[2])};
+                const double a = fma(u[0], q0.x, fma(u[1], q0.y, fma(u[2], q1.x, -q7.y)));
+                const double b1 = fma(u[0], q1.y, fma(u[1], q2.x, fma(u[2], q2.y, -q8.x)));
+                const double b2 = fma(u[0], q3.x, fma(u[1], q3.y, fma(u[2], q4.x, -q8.y)));
+                const double E = fma(fma(k1 * ad, ad, k0), q6.y, 1e-11);
+                bool hit = lin && fma(-q4.y, a, b1) >= -E && fma(q5.y, a, -b1) >= -E && fma(-q5.x, a, b2) >= -E &&
+                           fma(q6.x, a, -b2) >= -E;
+                if (any_wide && live && !o.lin_ok) hit = loc_box_hit(p, o, (int)rq);
+                offer(hit, rq);
+            }
+            // the frames behind them move up
+            const int rest = lane < nk - n ? kept[n + lane] : 0, rest2 = lane + kWave < nk - n ? kept[n + kWave + lane] : 0;
+            wave_lds_sync();
+            if (lane < nk - n) kept[lane] = rest;
+            if (lane + kWave < nk - n) kept[kWave + lane] = rest2;
+            nk -= n;
+        };
+        // (the last pass, past the end, only visits what is left)
+        for (int g0 = 0; g0 < total + (kLoc ? kWave : 0); g0 += kWave) {
             // lane l holds frame record g0 + l of the neighbourhood list
             const int g = g0 + lane;
             int nc = 0;
-            for (int t = 1; t < 27; ++t) nc = (__shfl(excl, t, kWave) <= g) ? t : nc;
+#pragma unroll
+            for (int step = 16; step > 0; step >>= 1) {      // the last cell that starts at or before g
+                const int t = nc + step, at = __shfl(excl, t, kWave);
+                nc = t < 27 && at <= g ? t : nc;
+            }
             const int rk = __shfl(my_a0, nc, kWave) + (g - __shfl(excl, nc, kWave));
             // the chunk's frame records that can meet the item's cap go to
             // LDS, packed, and are read back as broadcasts
@@ -1177,47 +1257,32 @@ __global__ __launch_bounds__(256, kJoinWaves) void k_fov_cells(const FovParams p
                 // cos(R_item + R_f); frames of 90 degrees or more are kept
                 keep = !item_cap || !(c23.y > 0.0) ||
                        !(c01.x * ic[0] + c01.y * ic[1] + c23.x * ic[2] < icr * c23.y - isr * sr - 1e-12);
-                if (keep) {
+                if (!kLoc && keep) {
                     const double2* ob = reinterpret_cast<const double2*>(p.cell_obs + 4 * (int64_t)rk);
                     const double2 o01 = ob[0], o23 = ob[1];
                     rec = {{c01.x, c01.y, c23.x}, c23.y, sr, (double)rk, o01.x, {o01.y, o23.x, o23.y}};
                 }
             }
             const unsigned long long kmask = __ballot(keep);
-            wave_lds_sync();                  // the previous chunk's records are read
-            if (keep) fcap[__popcll(kmask & lt)] = rec;
-            wave_lds_sync();
-            const int n = __popcll(kmask);
-            n_visit += (unsigned long long)n;
-            for (int m = 0; m < n; ++m) {
-                const FrameRec cm = fcap[m];
-                const double cpm[5] = {cm.c[0], cm.c[1], cm.c[2], cm.cosr, cm.sinr};
-                const unsigned long long rq = (unsigned long long)(unsigned int)(int)cm.rank;
-                bool hit = live && frame_cap_hit(o, cpm);
-                if (hit) {
-                    if (o.lin_ok) {
-                        const double ob[4] = {cm.t, cm.o[0], cm.o[1], cm.o[2]};
-                        double ul[3];
-                        const double e2 = lin_predict(o, ob, tr, Asun, ul);
-                        hit = lin_cap_hit(cpm, ul, e2);
-                    } else {
-                        hit = loc_box_hit(p, o, (int)rq);
-                    }
-                }
-                const unsigned long long mask = __ballot(hit);
-                if (mask == 0ull) continue;
-                if (hit) ++n_cand;
-                if (hit) queue[nq + __popcll(mask & lt)] = (rq << 8) | (unsigned long long)lane;
-                nq += __popcll(mask);
-                if (nq >= kWave) {
-                    wave_lds_sync();
-                    drain(kWave);
-                    // move the overflow to the front (fewer than 64 entries)
-                    const unsigned long long rest = lane < nq - kWave ? queue[kWave + lane] : 0ull;
-                    wave_lds_sync();
-                    if (lane < nq - kWave) queue[lane] = rest;
-                    nq -= kWave;
-                    wave_lds_sync();
+            if constexpr (kLoc) {
+                if (keep) kept[nk + __popcll(kmask & lt)] = rk;
+                nk += __popcll(kmask);
+                while (nk >= kLocChunk || (g0 >= total && nk > 0)) visit_kept(min(nk, kLocChunk));
+            } else {
+                wave_lds_sync();                  // the previous chunk's records are read
+                if (keep) fcap[__popcll(kmask & lt)] = rec;
+                wave_lds_sync();
+                const int n = __popcll(kmask);
+                n_visit += (unsigned long long)n;
+                for (int m = 0; m < n; ++m) {
+                    const FrameRec cm = fcap[m];
+                    const double cpm[5] = {cm.c[0], cm.c[1], cm.c[2], cm.cosr, cm.sinr};
+                    const double dt = cm.t - tr, ad = fabs(dt) + o.taumax;
+                    const double ul[3] = {fma(o.v[0], dt, o.x[0]) - cm.o[0], fma(o.v[1], dt, o.x[1]) - cm.o[1],
+                                          fma(o.v[2], dt, o.x[2]) - cm.o[2]};
+                    bool hit = lin && lin_cap_hit(cpm, ul, fma(k1 * ad, ad, k0));
+                    if (any_wide && live && !o.lin_ok) hit = frame_cap_hit(o, cpm);
+                    offer(hit, (unsigned)(int)cm.rank);
                 }
             }
         }
@@ -2466,7 +2531,9 @@ hipError_t fov_candidates(FovParams& p, int32_t* icnt, int32_t* istart, ulonglon
     hipLaunchKernelGGL(k_item_count, dim3(gk), dim3(256), 0, s, p, icnt);
     if ((e = exclusive_scan_i32(icnt, istart, p.n_keys, scan_scratch, s)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_item_scatter, dim3(gk), dim3(256), 0, s, p, (const int32_t*)icnt);
-    hipLaunchKernelGGL(k_fov_cells, dim3((unsigned)(cu_count() * kJoinWaves)), dim3(256), 0, s, p);
+    const dim3 join_grid((unsigned)(cu_count() * kJoinWaves));
+    if (p.loc) hipLaunchKernelGGL(k_fov_cells<true>, join_grid, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL(k_fov_cells<false>, join_grid, dim3(256), 0, s, p);
     // the wide list, with the join's item counts as scratch (free now)
     hipLaunchKernelGGL(k_wide_count, dim3((unsigned)((p.n_batch + 255) / 256)), dim3(256), 0, s, p, icnt);
     if ((e = exclusive_scan_i32(icnt, istart, p.n_batch, scan_scratch, s)) != hipSuccess) return e;

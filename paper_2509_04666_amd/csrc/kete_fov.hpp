@@ -13,11 +13,16 @@ constexpr double kMaxLightDays = 1.0;   // light time covered by the staged wind
 // the frame's cap centre and a kLocL x kLocL grid over the gnomonic
 // bounding box of its sub-frames, each cell with a bit mask (two 64-bit
 // words) of the sub-frames whose gnomonic box overlaps it.  Record:
-//   [0..2] centre c, [3..5] e1, [6..8] e2, [9] X0, [10] Y0, [11] 1/dX,
-//   [12] 1/dY, [13] 1 when usable (every vertex in the hemisphere around
-//   c), [14] X1 = X0 + kLocL dX, [15] Y1, then kLocL^2 x 2 mask words.
+//   [0..2] centre c, [3..5] e1, [6..8] e2, the box [9] X0, [10] Y0,
+//   [11] X1 = X0 + kLocL dX, [12] Y1, [13] the largest norm of the box's edge
+//   planes' normals e1 - X c, e2 - Y c (1e300 when not usable), [14] the
+//   frame's time, [15..17] its observer along c, e1, e2, [18] 1 when usable
+//   (every vertex in the hemisphere around c), [19] 1/dX, [20] 1/dY, then
+//   kLocL^2 x 2 mask words.  The first kLocJoin are what the per-cell join
+//   stages.
 constexpr int kLocL = 8;
-constexpr int kLocHead = 16;
+constexpr int kLocHead = 24;
+constexpr int kLocJoin = 18;
 constexpr int kLocStride = kLocHead + 2 * kLocL * kLocL;     // doubles per frame
 
 // Exact-test candidates and pairs share one 64-bit key: frame << 32 |
