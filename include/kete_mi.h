@@ -105,7 +105,7 @@ typedef struct {
                                 integrators and the adjoint, 2 with one lane per body) */
     int32_t lt_iter;         /* light-time updates at most (10) */
     int32_t fov_block;       /* FoV threads per block: 64/128/256 (128) */
-    int32_t adj_seg_steps;   /* adjoint: steps stored per checkpoint segment (32) */
+    int32_t adj_seg_steps;   /* adjoint: steps per checkpoint segment at most (32) */
     int32_t persist_waves;   /* batched runs: resident waves per compute unit (8) */
     int32_t lanes_per_body;  /* integrator lanes per object: 1, 8 (8 objects a wavefront), or 7: 9 objects
                                 a wavefront, and for short lists and the objects of most steps
@@ -377,13 +377,12 @@ size_t kete_adjoint_workspace_size(int64_t n_obj, int32_t k_obs, double t0, doub
  *   mode KETE_ADJ_FWD: writes sky_out [N][K][2] and status [N], and stores
  *     in the workspace a checkpoint per ckpt_days (checkpoint c: the state
  *     at the first integration step starting at or after t0 + c ckpt_days,
- *     so the steps are not cut at checkpoints) and each observation's
- *     light time;
+ *     so the steps are not cut at checkpoints), the integration steps as
+ *     far as there is room for them, and each observation's light time;
  *   mode KETE_ADJ_BWD: given dL_dsky [N][K][2] (device) for the same
  *     inputs, options and workspace, writes grad_x0 [N][6] = dL/dx0: the
- *     discrete adjoint of the forward computation, recomputing each
- *     checkpoint segment (on a second, library-owned stream, ordered by
- *     events; the call's stream sees the whole result).  Objects with a
+ *     discrete adjoint of the forward computation, from its recorded steps
+ *     and, past those, by recomputing checkpoint segments.  Objects with a
  *     non-zero status get a zero gradient.
  * All arrays are device memory; t0, t_end and ckpt_days are host values.
  * Errors: KETE_EINVAL, KETE_ERANGE, KETE_EWORKSPACE, KETE_EDEVICE. */
