@@ -530,7 +530,6 @@ __device__ __forceinline__ double lane_value(double v, int m) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// Wave-wide reductions over the 64 lanes (results are wave-uniform).
 // A 64-bit value of one lane (wave-uniform index).
 __device__ __forceinline__ unsigned long long lane_value64(unsigned long long x, int l) {
     const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)x, l);
@@ -548,6 +547,7 @@ __device__ __forceinline__ bool first_lane(int lane) {
     return lane == 0;
 }
 
+// Wave-wide reductions over the 64 lanes (results are wave-uniform).
 __device__ __forceinline__ double wave_max(double x) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) x = fmax(x, __shfl_xor(x, off, kWave));
