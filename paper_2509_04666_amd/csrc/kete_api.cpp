@@ -967,7 +967,8 @@ size_t kete_adjoint_workspace_size(int64_t n_obj, int32_t k_obs, double t0, doub
     c.take<int32_t>((size_t)n_obj);                                   // perm
     c.take<double>((size_t)n_obj);                                    // h_pref
     c.take<double>((size_t)(C + 1) * n_obj * kCkptDoubles);
-    c.take<double>(adj_rec_doubles(n_obj, solo_waves_for((int)n_obj, sort_classes(opts) > 1), adj_steps(opts)));
+    c.take<double>(adj_rec_doubles(n_obj, solo_waves_for((int)std::min<int64_t>(n_obj, INT32_MAX), sort_classes(opts) > 1),
+                                   adj_steps(opts)));
     c.take<double>((size_t)n_obj * std::max(0, k_obs) * 6);    // observation states
     c.take<double>((size_t)n_obj * std::max(0, k_obs) * 6);    // observation cotangents
     c.take<double>((size_t)n_obj * std::max(0, k_obs) * 2);    // light times and anomalies
