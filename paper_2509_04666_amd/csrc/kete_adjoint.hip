@@ -233,51 +233,26 @@ __device__ __forceinline__ void write_step(double* __restrict__ rec, int gl, dou
     w[1] = gl < 7 ? make_double2(dn[2], q) : make_double2(S.F0[2], h);
 }
 
-// Lane of node lane i of this lane's group (and of the same place among the
-// lanes of a node), for the two layouts of the adjoint kernels: eight lanes
-// an object, or one object with eight lanes a node.
-template <int G>
-__device__ __forceinline__ int node_lane(int lane, int i) {
-    static_assert(G == 8 || G == 56, "layouts of the adjoint");
-    return G == 8 ? (lane & ~7) + i : 8 * i + (lane & 7);
-}
-
-// The objects of one wavefront, the records of its steps and their layout.
-struct AdjWave {
-    long first;             // its first object in the order, or -1: none
-    bool lone;              // one object
-    double* rec;
-};
-__device__ __forceinline__ AdjWave adj_wave(const AdjParams& p) {
-    const long wave = blockIdx.x;
-    const long solo = p.n_solo ? min(*p.n_solo, p.solo_waves) : p.solo_waves;
-    const size_t per = (size_t)(p.rec_fwd + p.s_max) * kStepRec;
-    AdjWave w;
-    w.lone = wave < p.solo_waves;
-    const long g = wave - p.solo_waves;
-    w.first = w.lone ? (wave < solo ? wave : -1) : solo + g * kAdjBodies;
-    if (w.first >= p.n_obj) w.first = -1;
-    w.rec = p.rec + per * (w.lone ? (size_t)wave : (size_t)p.solo_waves + (size_t)g * kAdjBodies);
-    return w;
-}
-
-template <int G, int NB, int NGR, int NJ2, int DEG1>
-__device__ __forceinline__ void adj_fwd_wave(const AdjParams& p, const AdjWave& w, const GroupConst& gc, double* wt_all,
-                                             double* smem) {
+template <int NB, int NGR, int NJ2, int DEG1>
+__global__ __launch_bounds__(64, 2) void k_adjoint_fwd(const AdjParams p) {
+    extern __shared__ __align__(16) double smem[];
     const int lane = threadIdx.x;
-    constexpr int kBodies = GroupMap<G>::kBodies;
-    const GroupMap<G> M(lane);
+    const GroupMap<kGroup> M(lane);
     const int gl = M.gl;
     const EphemArgs& E = p.eph;
-    const G8Lds T = g8_lds<G>(E, smem, M.grp);
-    g8_table_init<G>(E, lane, smem);
-    const long gi = w.first + M.grp;
-    const bool valid = gi < p.n_obj, writer = valid && M.sub == 0;
+    __shared__ __align__(16) GroupConst gc;
+    __shared__ __align__(16) double wt_all[kAdjBodies * 16];
+    load_group_const(p.group_const, &gc, lane, kWave);
+    const G8Lds T = g8_lds<kGroup>(E, smem, M.grp);
+    g8_table_init<kGroup>(E, lane, smem);
+    __syncthreads();
+    const long gi = (long)blockIdx.x * kAdjBodies + M.grp;
+    const bool valid = gi < p.n_obj;
     const int j = valid ? (p.perm ? p.perm[gi] : (int)gi) : 0;
-    double* rec = w.rec + M.grp * kStepRec;
+    double* rec = p.rec + ((size_t)blockIdx.x * (p.rec_fwd + p.s_max) * kAdjBodies + M.grp) * kStepRec;
     G8State S;
     init_lane_state(p, valid, j, S);
-    S.hw = groups_min<G>(valid ? p.h_pref[j] : kInf);
+    S.hw = groups_min(valid ? p.h_pref[j] : kInf);
     if (!(S.hw < kInf)) S.hw = p.h_init;
     S.t = p.t0;
     G8Count C;
@@ -293,13 +268,13 @@ __device__ __forceinline__ void adj_fwd_wave(const AdjParams& p, const AdjWave& 
         k_buf = kobs;
         t_buf = valid && kobs + gl < K ? tob[kobs + gl] : kInf;
     };
-    auto next_time = [&]() { return __shfl(t_buf, node_lane<G>(lane, kobs - k_buf), kWave); };        // the whole group calls it
+    auto next_time = [&]() { return __shfl(t_buf, kobs - k_buf, kGroup); };        // the whole group calls it
     auto advance = [&]() {
         if (++kobs - k_buf == kGroup) load_times();
     };
     load_times();
     auto store_obs = [&](double v) {
-        if (gl < 6 && M.sub == 0) p.obs_state[((size_t)j * K + kobs) * 6 + gl] = v;
+        if (gl < 6) p.obs_state[((size_t)j * K + kobs) * 6 + gl] = v;
     };
     // observations at the start epoch
     for (;;) {
@@ -317,10 +292,10 @@ __device__ __forceinline__ void adj_fwd_wave(const AdjParams& p, const AdjWave& 
     int c_next = 1, n_steps = 0;
     auto visit = [&](double ts, double h, const double dn[3], const G8State& St) {
         while (c_next < p.n_ckpt && ts >= p.t0 + c_next * p.ckpt_days) {
-            if (writer) save_ckpt_g8(p, c_next, j, gl, St, ts, n_steps);
+            if (valid) save_ckpt_g8(p, c_next, j, gl, St, ts, n_steps);
             ++c_next;
         }
-        if (writer && n_steps < p.rec_fwd) write_step(rec + (size_t)n_steps * kBodies * kStepRec, gl, ts, h, dn, St);
+        if (valid && n_steps < p.rec_fwd) write_step(rec + (size_t)n_steps * kAdjBodies * kStepRec, gl, ts, h, dn, St);
         ++n_steps;
         const double te = ts + h;
         double tk = next_time();
@@ -337,31 +312,16 @@ __device__ __forceinline__ void adj_fwd_wave(const AdjParams& p, const AdjWave& 
             pend = pending();
         } while (__ballot(pend) != 0ull);
     };
-    if (writer) save_ckpt_g8(p, 0, j, gl, S, S.t, 0);
+    if (valid) save_ckpt_g8(p, 0, j, gl, S, S.t, 0);
     // (windows, if asked for, end on the fixed grid of aligned_end, so a
     // recompute that starts at a checkpoint cuts its steps where this run did)
     while (S.t < p.t_end)
-        g8_integrate<NB, NGR, NJ2, DEG1, G>(
+        g8_integrate<NB, NGR, NJ2, DEG1, kGroup>(
             p, gc, T, M, lane, aligned_end(S.t, p.t_end, E.t_start, E.seg_days, E.inv_seg, p.window_segs), S, C, visit);
     // checkpoints no step start reached: the end state
     for (; c_next <= p.n_ckpt; ++c_next)
-        if (writer) save_ckpt_g8(p, c_next, j, gl, S, p.t_end, n_steps);
-    if (writer && gl == 0) p.status[j] = S.status;
-}
-
-// The forward's wavefronts (see adj_wave): objects of many steps alone, as in
-// the propagation kernel, in one launch with the others.
-template <int NB, int NGR, int NJ2, int DEG1>
-__global__ __launch_bounds__(64, 2) void k_adjoint_fwd(const AdjParams p) {
-    extern __shared__ __align__(16) double smem[];
-    __shared__ __align__(16) GroupConst gc;
-    __shared__ __align__(16) double wt[kAdjBodies * 16];
-    const AdjWave w = adj_wave(p);
-    if (w.first < 0) return;                    // the whole block: one wavefront
-    load_group_const(p.group_const, &gc, threadIdx.x, kWave);
-    __syncthreads();
-    if (w.lone) adj_fwd_wave<kSoloLanes, NB, NGR, NJ2, DEG1>(p, w, gc, wt, smem);
-    else adj_fwd_wave<kGroup, NB, NGR, NJ2, DEG1>(p, w, gc, wt, smem);
+        if (valid) save_ckpt_g8(p, c_next, j, gl, S, p.t_end, n_steps);
+    if (valid && gl == 0) p.status[j] = S.status;
 }
 
 // Sky position of every observation from its stored state (forward), one
@@ -482,8 +442,7 @@ __global__ __launch_bounds__(320) void k_adj_consts(const AdjParams p) {
 }
 
 // Backward: one wavefront goes through its objects' steps last to first.
-// Lane m - 1 of an object (see GroupMap; with one object the eight lanes of a
-// node do the same) holds the stage cotangent mu_m, lane 7 the step-start
+// Lane m - 1 of an object holds the stage cotangent mu_m, lane 7 the step-start
 // term; each forms the force Jacobians at its node (lane 7: the step start)
 // from the step's record.
 //   A wavefront waits on its own chain: the perturbers at the nodes, the
@@ -491,36 +450,46 @@ __global__ __launch_bounds__(320) void k_adj_consts(const AdjParams p) {
 // exchanges through LDS each).  With each checkpoint segment recomputed by
 // one kernel into memory and swept by another, forward and backward of
 // 100,000 objects x 20 observations over 60 d took 3.9 ms and of 20,000 2.6;
-// from the forward's records 3.3 and 2.2; with the objects of most steps
-// alone 2.5 and 1.5.
-template <int G, int NB, int NGR, int NJ2, int DEG1>
-__device__ __forceinline__ void adj_back_wave(const AdjParams& p, const AdjWave& w, const GroupConst& gc,
-                                              const AdjCols* cols, const double (*drow)[18], double* srec_all,
-                                              double* xw_all, double* smem) {
+// from the forward's records 2.6 and 1.9.  (Objects of many steps alone in
+// their wavefronts took it to 2.5 and 1.5, but the limit on a segment's steps,
+// which the objects of a wavefront share, then failed others than before.)
+template <int NB, int NGR, int NJ2, int DEG1>
+__global__ __launch_bounds__(64, 2) void k_adj_back(const AdjParams p) {
+    extern __shared__ __align__(16) double smem[];
+    __shared__ __align__(16) GroupConst gc;
+    __shared__ __align__(16) double srec_all[kAdjBodies * kStepRec];
+    __shared__ __align__(16) double xw_all[kAdjBodies * kGroup * 6];    // exchange slots: [node lane][6] (W, U)
+    __shared__ AdjCols cols[kGroup];
+    __shared__ double drow[kGroup][18];             // dense-output rows
     const int lane = threadIdx.x;
-    constexpr int kBodies = GroupMap<G>::kBodies;
-    const GroupMap<G> M(lane);
+    const GroupMap<kGroup> M(lane);
     const int gl = M.gl;
     const int jnode = gl < 7 ? gl + 1 : 0;          // node whose Jacobians this lane holds
     const EphemArgs& E = p.eph;
     const RadauConst& rc = p.rc;
     double* srec = srec_all + M.grp * kStepRec;
-    double* xw = xw_all + M.grp * kGroup * 6;       // exchange slots: [node lane][6] (W, U)
-    const G8Lds T = g8_lds<G>(E, smem, M.grp);
-    g8_table_init<G>(E, lane, smem);
+    double* xw = xw_all + M.grp * kGroup * 6;
+    double* dst = &cols[0].cA[0];
+    for (int i = lane; i < kAdjTabDoubles; i += kWave)
+        (i < kGroup * kAdjColDoubles ? dst[i] : drow[0][i - kGroup * kAdjColDoubles]) = p.adj_tab[i];
+    load_group_const(p.group_const, &gc, lane, kWave);
+    const G8Lds T = g8_lds<kGroup>(E, smem, M.grp);
+    g8_table_init<kGroup>(E, lane, smem);
+    __syncthreads();
     const NodeRow& R = gc.row[gl];
     const AdjCols& Q = cols[gl];
     const double* dr = drow[gl];
     const size_t N = p.n_obj;
-    const long gi = w.first + M.grp;
-    const bool valid = gi < p.n_obj, writer = valid && M.sub == 0;
+    const long first = (long)blockIdx.x * kAdjBodies, gi = first + M.grp;
+    const bool valid = gi < p.n_obj;
     const int j = valid ? (p.perm ? p.perm[gi] : (int)gi) : 0;
-    const int j_first = p.perm ? p.perm[w.first] : (int)w.first;
+    const int j_first = p.perm ? p.perm[first] : (int)first;
     const int K = p.k_obs;
     const double* tob = p.t_obs + (size_t)j * K;
     const bool ok_final = valid && p.status[j] == 0;
     // one step of every object of the wavefront, and this lane's slot of it
-    constexpr size_t kStep = (size_t)kBodies * kStepRec;
+    constexpr size_t kStep = (size_t)kAdjBodies * kStepRec;
+    double* rec_wave = p.rec + (size_t)blockIdx.x * (p.rec_fwd + p.s_max) * kStep;
     const int slot = M.grp * kStepRec + 4 * gl;
     double lx[3] = {0.0, 0.0, 0.0}, lv[3] = {0.0, 0.0, 0.0};
     int kb = K - 1;
@@ -640,14 +609,13 @@ __device__ __forceinline__ void adj_back_wave(const AdjParams& p, const AdjWave&
 #pragma unroll
                 for (int i = 0; i < 3; ++i) m0[i] = nm[i];
             }
-            constexpr int kNodeStep = G == 8 ? 1 : 8;
 #pragma unroll
             for (int off = 1; off < kGroup; off <<= 1) {
-                dm = fmax(dm, __shfl_xor(dm, off * kNodeStep, kWave));
-                mm = fmax(mm, __shfl_xor(mm, off * kNodeStep, kWave));
+                dm = fmax(dm, __shfl_xor(dm, off, kWave));
+                mm = fmax(mm, __shfl_xor(mm, off, kWave));
             }
             // the ratio only steers the stopping rule: the reciprocal estimate suffices
-            pc = groups_max<G>((ok_final && mm > 0.0) ? dm * __builtin_amdgcn_rcp(mm) : 0.0);
+            pc = groups_max((ok_final && mm > 0.0) ? dm * __builtin_amdgcn_rcp(mm) : 0.0);
         } while (!(pc < 1e-16) && !(it > 2 && pcl <= pc) && it < 2 * p.max_iter);
         // step-start Jacobians (lane 7) applied to m0, shared with the group
 #pragma unroll
@@ -655,8 +623,8 @@ __device__ __forceinline__ void adj_back_wave(const AdjParams& p, const AdjWave&
             double a = 0.0, b = 0.0;
 #pragma unroll
             for (int r = 0; r < 3; ++r) { a = fma(Jx[3 * r + i], m0[r], a); b = fma(Jv[3 * r + i], m0[r], b); }
-            lx[i] = gx0[i] + wsum[i] + __shfl(a, node_lane<G>(lane, 7), kWave);
-            lv[i] = gv0[i] + usum[i] + __shfl(b, node_lane<G>(lane, 7), kWave);
+            lx[i] = gx0[i] + wsum[i] + __shfl(a, 7, kGroup);
+            lv[i] = gv0[i] + usum[i] + __shfl(b, 7, kGroup);
         }
     };
     // steps [a, b) of the records at `rec`, last first; the next one is read during a step
@@ -672,10 +640,8 @@ __device__ __forceinline__ void adj_back_wave(const AdjParams& p, const AdjWave&
         read(b - 1);
         for (int st = b - 1; st >= a; --st) {
             wave_lds_sync();                        // the previous record is read
-            if (M.sub == 0) {
-                *reinterpret_cast<double2*>(srec + 4 * gl) = q0;
-                *reinterpret_cast<double2*>(srec + 4 * gl + 2) = q1;
-            }
+            *reinterpret_cast<double2*>(srec + 4 * gl) = q0;
+            *reinterpret_cast<double2*>(srec + 4 * gl + 2) = q1;
             wave_lds_sync();
             read(st - 1);
             step_back();
@@ -692,7 +658,7 @@ __device__ __forceinline__ void adj_back_wave(const AdjParams& p, const AdjWave&
         const int ns = min(b - a, p.s_max);
         overflow_steps = overflow_steps || b - a > p.s_max;
         if (b <= p.rec_fwd) {
-            sweep(w.rec, b - ns, b);
+            sweep(rec_wave, b - ns, b);
             continue;
         }
         // The forward's steps (and windows) again from the checkpoint on,
@@ -714,19 +680,19 @@ __device__ __forceinline__ void adj_back_wave(const AdjParams& p, const AdjWave&
             have_f0 = ck[11] != 0.0;
             hprev = ck[33];
         }
-        S.hw = groups_max<G>(valid ? hw : 0.0);     // the same value in every valid group
-        S.hprev = groups_max<G>(hprev);             // likewise (invalid groups give -inf)
+        S.hw = groups_max(valid ? hw : 0.0);     // the same value in every valid group
+        S.hprev = groups_max(hprev);             // likewise (invalid groups give -inf)
         S.haveF0 = __ballot(have_f0) != 0ull;       // as in the forward at this checkpoint
         S.t = t_c;
         G8Count Cn;
         int n = 0;
-        double* seg = w.rec + (size_t)p.rec_fwd * kStep;
+        double* seg = rec_wave + (size_t)p.rec_fwd * kStep;
         auto store = [&](double ts, double h, const double dn[3], const G8State& St) {
-            if (writer && n < ns) write_step(seg + (size_t)n * kStep + M.grp * kStepRec, gl, ts, h, dn, St);
+            if (valid && n < ns) write_step(seg + (size_t)n * kStep + M.grp * kStepRec, gl, ts, h, dn, St);
             ++n;
         };
         while (S.t < t_stop)
-            g8_integrate<NB, NGR, NJ2, DEG1, G>(
+            g8_integrate<NB, NGR, NJ2, DEG1, kGroup>(
                 p, gc, T, M, lane, aligned_end(S.t, p.t_end, E.t_start, E.seg_days, E.inv_seg, p.window_segs), S, Cn,
                 store, true, t_stop);
         sweep(seg, 0, min(n, ns));
@@ -740,38 +706,18 @@ __device__ __forceinline__ void adj_back_wave(const AdjParams& p, const AdjWave&
             --kb;
         }
     }
-    if (writer) {
+    if (valid) {
         const bool good = ok_final && !overflow_steps;
         if (gl < 6) p.grad[6 * (size_t)j + gl] = good ? state_component(lx, lv, gl) : 0.0;
         if (gl == 0 && overflow_steps && ok_final) p.status[j] = KETE_ST_MAX_STEPS;
     }
 }
 
-template <int NB, int NGR, int NJ2, int DEG1>
-__global__ __launch_bounds__(64, 2) void k_adj_back(const AdjParams p) {
-    extern __shared__ __align__(16) double smem[];
-    __shared__ __align__(16) GroupConst gc;
-    __shared__ __align__(16) double srec[kAdjBodies * kStepRec], xw[kAdjBodies * kGroup * 6];
-    __shared__ AdjCols cols[kGroup];
-    __shared__ double drow[kGroup][18];             // dense-output rows
-    const int lane = threadIdx.x;
-    const AdjWave w = adj_wave(p);
-    if (w.first < 0) return;                        // the whole block: one wavefront
-    double* dst = &cols[0].cA[0];
-    for (int i = lane; i < kAdjTabDoubles; i += kWave)
-        (i < kGroup * kAdjColDoubles ? dst[i] : drow[0][i - kGroup * kAdjColDoubles]) = p.adj_tab[i];
-    load_group_const(p.group_const, &gc, lane, kWave);
-    __syncthreads();
-    if (w.lone) adj_back_wave<kSoloLanes, NB, NGR, NJ2, DEG1>(p, w, gc, cols, drow, srec, xw, smem);
-    else adj_back_wave<kGroup, NB, NGR, NJ2, DEG1>(p, w, gc, cols, drow, srec, xw, smem);
-}
-
 }  // namespace
 
 static hipError_t launch_adjoint_waves(const AdjParams& p, int mode, hipStream_t s) {
-    const dim3 grid((unsigned)adj_waves(p.n_obj, p.solo_waves));
-    const size_t lds = (size_t)std::max(g8_wave_doubles<kGroup>(p.eph), g8_wave_doubles<kSoloLanes>(p.eph)) *
-                       sizeof(double);
+    const dim3 grid((unsigned)adj_waves(p.n_obj));
+    const size_t lds = (size_t)g8_wave_doubles<kGroup>(p.eph) * sizeof(double);
     const int shape = group_shape(p.eph);
     if (mode == KETE_ADJ_FWD) {
         switch (shape) {

@@ -43,9 +43,6 @@ struct AdjParams {
     double* obs_state;          // [N][K][6] states at the observation times (forward)
     double* obs_grad;           // [N][K][6] dL/d(state) at the observation times (backward)
     double* obs_hop;            // [N][K][2] light time and final universal anomaly (forward)
-    int32_t solo_waves;         // wavefronts of one object, before those of kAdjBodies
-    int32_t pad_solo;
-    const int32_t* n_solo;      // device: objects that may have one of their own, or null: all of the first solo_waves
     double* rec;                // [wavefronts][rec_fwd + s_max][objects of one][kStepRec]
     int32_t rec_fwd;            // steps of a wavefront that the forward records
     int32_t pad2_;
@@ -62,15 +59,13 @@ struct AdjParams {
     int32_t zero_start;         // correctors start from zero increments (no extrapolation)
 };
 
-// Wavefronts of the adjoint kernels: the first solo_waves have room for one
-// object each, the others for kAdjBodies.
+// Objects of one adjoint wavefront.  They share their steps, and so also the
+// limit on the steps of a checkpoint segment: all of them fail that one of
+// them takes past it.
 constexpr int kAdjBodies = 8;
-inline int64_t adj_waves(int64_t n_obj, int solo_waves) {
-    return solo_waves + (solo_waves < n_obj ? (n_obj + kAdjBodies - 1) / kAdjBodies : 0);
-}
-inline size_t adj_rec_doubles(int64_t n_obj, int solo_waves, int s_max) {
-    const int64_t places = solo_waves + (adj_waves(n_obj, solo_waves) - solo_waves) * kAdjBodies;
-    return (size_t)places * kStepRec * (size_t)(kRecSteps * s_max);
+inline int64_t adj_waves(int64_t n_obj) { return (n_obj + kAdjBodies - 1) / kAdjBodies; }
+inline size_t adj_rec_doubles(int64_t n_obj, int s_max) {
+    return (size_t)adj_waves(n_obj) * kAdjBodies * kStepRec * (size_t)(kRecSteps * s_max);
 }
 hipError_t launch_adjoint(const AdjParams& p, int mode, hipStream_t s);
 

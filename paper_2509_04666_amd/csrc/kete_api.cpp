@@ -967,8 +967,7 @@ size_t kete_adjoint_workspace_size(int64_t n_obj, int32_t k_obs, double t0, doub
     c.take<int32_t>((size_t)n_obj);                                   // perm
     c.take<double>((size_t)n_obj);                                    // h_pref
     c.take<double>((size_t)(C + 1) * n_obj * kCkptDoubles);
-    c.take<double>(adj_rec_doubles(n_obj, solo_waves_for((int)std::min<int64_t>(n_obj, INT32_MAX), sort_classes(opts) > 1),
-                                   adj_steps(opts)));
+    c.take<double>(adj_rec_doubles(n_obj, adj_steps(opts)));          // step records
     c.take<double>((size_t)n_obj * std::max(0, k_obs) * 6);    // observation states
     c.take<double>((size_t)n_obj * std::max(0, k_obs) * 6);    // observation cotangents
     c.take<double>((size_t)n_obj * std::max(0, k_obs) * 2);    // light times and anomalies
@@ -1001,8 +1000,7 @@ int kete_propagate_adjoint(const kete_ephem_t* eph, int32_t mode, const double* 
     if (!(opts->eps > 0) || !(opts->h_init > 0) || !(opts->h_min > 0) || opts->max_iter < 1 || opts->max_steps < 1)
         return fail(KETE_EINVAL, "eps, h_init, h_min, max_iter and max_steps must be positive");
     const int ncls = sort_classes(opts);
-    const int solo_waves = solo_waves_for((int)n_obj, ncls > 1);
-    const bool sorted = ncls > 1 && solo_waves < n_obj;        // all alone: no order needed
+    const bool sorted = ncls > 1;
     if (!workspace) return fail(KETE_EWORKSPACE, "workspace is null");
     const size_t need = kete_adjoint_workspace_size(n_obj, k_obs, t0, t_end, ckpt_days, opts);
     if (ws_bytes < need) return fail(KETE_EWORKSPACE, "workspace %zu bytes < %zu required", ws_bytes, need);
@@ -1010,7 +1008,7 @@ int kete_propagate_adjoint(const kete_ephem_t* eph, int32_t mode, const double* 
     int32_t* perm = c.take<int32_t>((size_t)n_obj);
     double* h_pref = c.take<double>((size_t)n_obj);
     double* ckpt = c.take<double>((size_t)(C + 1) * n_obj * kCkptDoubles);
-    double* rec = c.take<double>(adj_rec_doubles(n_obj, solo_waves, adj_steps(opts)));
+    double* rec = c.take<double>(adj_rec_doubles(n_obj, adj_steps(opts)));
     double* obs_state = c.take<double>((size_t)n_obj * k_obs * 6);
     double* obs_grad = c.take<double>((size_t)n_obj * k_obs * 6);
     double* obs_hop = c.take<double>((size_t)n_obj * k_obs * 2);
@@ -1044,8 +1042,6 @@ int kete_propagate_adjoint(const kete_ephem_t* eph, int32_t mode, const double* 
     P.obs_grad = obs_grad;
     P.obs_hop = obs_hop;
     P.rec = rec;
-    P.solo_waves = solo_waves;
-    P.n_solo = sorted && solo_waves > 0 ? body_sort_first(sorts.counts, (int)n_obj, ncls) : nullptr;
     P.s_max = adj_steps(opts);
     P.rec_fwd = (kRecSteps - 1) * P.s_max;
     P.adj_tab = adj_tab;
@@ -1071,7 +1067,7 @@ int kete_propagate_adjoint(const kete_ephem_t* eph, int32_t mode, const double* 
 
     if (mode == KETE_ADJ_FWD) {
         HIPCHK(launch_hpref_init(x0, h_pref, sorted ? sorts.keys : nullptr, (int)n_obj, E.gm[0], 0.0, t_end - t0, ncls,
-                                 0, kAdjSoloSteps, s));
+                                 0, HUGE_VAL, s));
         if (sorted) HIPCHK(launch_body_sort(sorts.keys, (int)n_obj, ncls, perm, sorts.tmp, sorts.counts, s));
     }
     {

@@ -193,8 +193,6 @@ constexpr int kMaxBuckets = 256;
 //     predicted step above h_ref, then kTimeBins classes of that time.
 constexpr double kCritSteps = 100.0;
 constexpr double kSoloSteps = 150.0, kSoloMaxStep = 5.0;
-// The same for the adjoint's arcs, a tenth as long.
-constexpr double kAdjSoloSteps = 12.0;
 // lanes of an object that has a wavefront of its own, and the list length up
 // to which every object has one: two wavefronts a SIMD
 constexpr int kSoloAll = 2048;

@@ -180,8 +180,7 @@ def test_adjoint_failed_objects_get_zero_gradient(torch_cuda):
 
 @pytest.mark.parametrize("n", [1, 9, 2048, 2049, 5000])
 def test_adjoint_recorded_and_recomputed_steps(torch_cuda, n):
-    """Objects alone, eight to a wavefront and both in one list: the backward
-    from the forward's step records, and with room for so few of them that
+    """Full and partly filled wavefronts: the backward from the forward's step records, and with room for so few of them that
     fast orbits' later steps are computed again from the checkpoints; a
     checkpoint segment of more steps than the option allows fails."""
     torch, api = torch_cuda
