@@ -290,14 +290,14 @@ __global__ __launch_bounds__(64, 2) void k_adjoint_fwd(const AdjParams p) {
     // start at or after t0 + c ckpt_days (wave-uniform: the wavefront's
     // objects share their steps), so steps are not cut at checkpoints.
     int c_next = 1, n_steps = 0;
-    auto visit = [&](double ts, double h, const double dn[3], const G8State& St) {
+    // (te is the time the step lands on: ts + h may round below the last observation)
+    auto visit = [&](double ts, double te, double h, const double dn[3], const G8State& St) {
         while (c_next < p.n_ckpt && ts >= p.t0 + c_next * p.ckpt_days) {
             if (valid) save_ckpt_g8(p, c_next, j, gl, St, ts, n_steps);
             ++c_next;
         }
         if (valid && n_steps < p.rec_fwd) write_step(rec + (size_t)n_steps * kAdjBodies * kStepRec, gl, ts, h, dn, St);
         ++n_steps;
-        const double te = ts + h;
         double tk = next_time();
         auto pending = [&]() { return valid && St.active && kobs < K && (h > 0 ? tk <= te : tk >= te); };
         bool pend = pending();
@@ -687,7 +687,7 @@ __global__ __launch_bounds__(64, 2) void k_adj_back(const AdjParams p) {
         G8Count Cn;
         int n = 0;
         double* seg = rec_wave + (size_t)p.rec_fwd * kStep;
-        auto store = [&](double ts, double h, const double dn[3], const G8State& St) {
+        auto store = [&](double ts, double, double h, const double dn[3], const G8State& St) {
             if (valid && n < ns) write_step(seg + (size_t)n * kStep + M.grp * kStepRec, gl, ts, h, dn, St);
             ++n;
         };

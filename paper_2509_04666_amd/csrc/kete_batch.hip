@@ -248,9 +248,9 @@ __device__ __forceinline__ void batch_wave(const BatchParams& p, const GroupCons
                     ++e_end;
             const double target = ep[e_end];
             EpochCursor ec(ep, e, e_end, lane);          // wave-uniform cursor over e .. e_end - 1
-            auto dense_out = [&](double ts, double h, const double dn[3], const G8State& St) {
+            auto dense_out = [&](double ts, double te, double h, const double dn[3], const G8State& St) {
                 const bool ok = St.active && St.status == 0;
-                dense_epochs(K, dwts, T.xg, gl, lane, ts, h, dn, St.x0, St.v0, St.F0, ec,
+                dense_epochs(K, dwts, T.xg, gl, lane, ts, te, h, dn, St.x0, St.v0, St.F0, ec,
                              [&](int k, double v) { put(k, v, ok); });
             };
             while (S.t != target) {

@@ -216,9 +216,9 @@ __device__ __forceinline__ void nbody_wave(const NbodyParams& p, const GroupCons
         put(ec.next, state_component(S.x0, S.v0, gl < 6 ? gl : 5), S.active && S.status == 0);
         ec.advance(1, lane);
     }
-    auto dense_out = [&](double ts, double h, const double dn[3], const G8State& St) {
+    auto dense_out = [&](double ts, double te, double h, const double dn[3], const G8State& St) {
         const bool ok = St.active && St.status == 0;
-        dense_epochs(K, wt, T.xg, gl, lane, ts, h, dn, St.x0, St.v0, St.F0, ec,
+        dense_epochs(K, wt, T.xg, gl, lane, ts, te, h, dn, St.x0, St.v0, St.F0, ec,
                      [&](int e, double v) { put(e, v, ok); });
     };
 

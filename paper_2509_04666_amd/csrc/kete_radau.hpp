@@ -900,8 +900,8 @@ struct G8NoVisit {
 // Integrate [S.t, tb] with wave-shared adaptive steps (the bodies of the
 // wavefront take the smallest step any of them asks for).  Correctors start
 // from the previous step extrapolated unless p.zero_start.
-// visit(ts, h, dn, S) is called by every lane after each accepted step,
-// before S moves to the step end (dn: this lane's converged increment, T.e8:
+// visit(ts, te, h, dn, S) is called by every lane after each accepted step,
+// before S moves to the step end te (dn: this lane's converged increment, T.e8:
 // the step's perturber table).  With need_node0 the table also holds node 0
 // (the step start) on every step.
 template <int NB, int NGR, int NJ2, int DEG1, int G, class Params, class Visit = G8NoVisit>
@@ -967,7 +967,7 @@ __device__ __forceinline__ void g8_integrate(const Params& p, const GroupConst& 
             ++C.rej;
             continue;
         }
-        visit(S.t, h, dn, S);
+        visit(S.t, t_end, h, dn, S);
 #pragma unroll
         for (int c = 0; c < 3; ++c) S.Dp[c] = dn[c];
         S.hprev = h;
@@ -1068,7 +1068,8 @@ __device__ __forceinline__ double dense_component8(const GroupConst& K, double* 
 }
 
 // Dense output of a step for a wavefront's objects: the cursor's epochs that
-// lie inside the step [ts, ts + h] are read off its collocation polynomial
+// lie inside the step [ts, te] are read off its collocation polynomial
+// (te, not ts + h, which rounds below a landing time)
 // and put(e, value) gets component gl (0..5) of each object's state; the
 // cursor moves past them.  The step is the same for every
 // object, so its weights are too: the 16 lanes of a quarter of the wavefront
@@ -1107,11 +1108,10 @@ struct EpochCursor {
 };
 template <class Put>
 __device__ __forceinline__ void dense_epochs(const GroupConst& K, double* __restrict__ wt, double* __restrict__ xg,
-                                             int gl, int lane, double ts, double h, const double dn[3],
+                                             int gl, int lane, double ts, double te, double h, const double dn[3],
                                              const double x0[3], const double v0[3], const double F0[3],
                                              EpochCursor& ec, Put&& put) {
     if (ec.next >= ec.end) return;
-    const double te = ts + h;
     const double t_first = ec.time();
     if (!(h > 0.0 ? t_first <= te : t_first >= te)) return;
     // this lane's component: coordinate c of the position or velocity

@@ -202,3 +202,30 @@ def test_adjoint_recorded_and_recomputed_steps(torch_cuda, n):
     assert int((ctx.status != 0).sum()) == 0
     grad = ctx.backward(x0, torch.ones_like(sky))
     assert torch.all(ctx.status == 3) and torch.all(grad == 0)
+
+
+def test_adjoint_observation_at_the_end_epoch(torch_cuda):
+    """An observation at t_end belongs to the step that lands there, also
+    where start + (t_end - start) rounds below t_end (a step across t = 0).
+    The workspace starts as NaN, so a state that is not stored shows."""
+    import dataclasses
+    torch, api = torch_cuda
+    g = synth.gradient_case(n_obj=9, k_obs=3, arc=8.0)
+    eph = api.DeviceEphemeris.from_synth(g.ephem)
+    x0 = _t(torch, g.x0)
+    rng = np.random.default_rng(91)
+    below = 0
+    for _ in range(40):
+        t0, t_end = rng.uniform(-7.5, -1.0), rng.uniform(0.1, 5.0)
+        below += t0 + (t_end - t0) < t_end
+        t_obs = np.tile([0.5 * t0, 0.25 * t_end, t_end], (9, 1))
+        skies = []
+        for end in (t_end, t_end + 2.0):
+            ctx = api.AdjointContext(eph, t0, end, _t(torch, t_obs), _t(torch, g.obs_pos), 5.0)
+            ctx.workspace.fill_(255)
+            skies.append(ctx.forward(x0))
+            grad = ctx.backward(x0, torch.ones_like(skies[-1]))
+            assert int(ctx.status.abs().max()) == 0
+            assert torch.isfinite(skies[-1]).all() and torch.isfinite(grad).all(), (t0, t_end)
+        assert (skies[0] - skies[1]).abs().max().item() < 1e-10
+    assert below > 0

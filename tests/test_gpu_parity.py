@@ -488,6 +488,28 @@ def test_propagate_all_objects_of_a_wavefront_fail(torch_cuda, n, lanes):
     assert np.array_equal(x[0], case.x0) and np.all(np.isnan(x[1:]))
 
 
+@pytest.mark.parametrize("n", [9, 3000])
+def test_epochs_close_to_the_last_one(torch_cuda, n):
+    """Epochs a few ulps before the one that a launch lands on, which is
+    reached by a step across t = 0: start + (end - start) may round below
+    them, and their states are those of the end all the same."""
+    torch, api = torch_cuda
+    case = synth.survey_case(n_obj=n, n_frames=0)
+    eph = api.DeviceEphemeris.from_synth(case.ephem)
+    x0 = _dev_x(torch, case.x0)
+    rng = np.random.default_rng(92)
+    below = 0
+    for _ in range(20):
+        t0, end = rng.uniform(-7.5, -1.0), rng.uniform(0.1, 3.0)
+        t_out = end - np.spacing(end) * np.arange(40, -1, -1)
+        below += t0 + (end - t0) < t_out[-2]
+        for lanes in (7, 8):
+            x, s = api.propagate(eph, x0, t0, t_out, api.default_opts(lanes_per_body=lanes))
+            assert int(s.abs().max()) == 0
+            assert (x - x[-1]).abs().max().item() < 1e-13, (t0, end, lanes)
+    assert below > 0
+
+
 # ---------------------------------------------------------------- FoV
 def _pair_set(pf, ps, po):
     return set(zip(np.asarray(pf).tolist(), np.asarray(ps).tolist(), np.asarray(po).tolist()))
