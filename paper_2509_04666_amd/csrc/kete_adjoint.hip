@@ -146,7 +146,8 @@ __device__ __forceinline__ void hop_known(const AdjParams& p, const SunGlobal& s
     double S[3], Sd[3], r[3], v[3], Se[3], Sde[3];
     sun.eval(t_obs, S, Sd);
     for (int i = 0; i < 3; ++i) { r0[i] = xs[i] - S[i]; v0[i] = vs[i] - Sd[i]; }
-    kepler_uv(p.eph.gm[0], p.smu, r0, v0, -tau, chi, r, v, p.kepler_iter);
+    bool quick;
+    kepler_uv(p.eph.gm[0], p.smu, r0, v0, -tau, chi, r, v, p.kepler_iter, quick);
     sun.eval(t_obs - tau, Se, Sde);
     for (int i = 0; i < 3; ++i) {
         d[i] = Se[i] + r[i] - o[i];

@@ -746,6 +746,100 @@ def test_fov_capacity_and_empty(torch_cuda, orc):
     assert pf.numel() == 0
 
 
+def _kepler_updates(mu, x, dt, n):
+    """Relative sizes [n, ...] of the first n updates of the documented
+    universal-variable solve (Laguerre-Conway of order 5 from sqrt(mu) dt / r0)
+    of states x [N, 6] over dt [Q, 1], in double precision, and where the
+    rounding of F moves the last of them by less than the rule's 4 ulps (8 u, u
+    = 2^-53): the terms of F round by some 3 u of their size while the series
+    of c1..c3 are summed as they are (|z| <= 0.1), so where the sum of their
+    sizes is at most 8/3 of |F' chi|."""
+    smu = math.sqrt(mu)
+    r0 = np.linalg.norm(x[:, :3], axis=1)
+    s0 = np.sum(x[:, :3] * x[:, 3:], axis=1) / smu
+    alpha = 2.0 / r0 - np.sum(x[:, 3:] ** 2, axis=1) / mu
+    chi = smu * dt / r0
+    out = []
+    for _ in range(n):
+        z = alpha * chi * chi
+        sz = np.sqrt(np.abs(z)) + 1e-300
+        with np.errstate(over="ignore", invalid="ignore"):
+            c0 = np.where(z > 0, np.cos(sz), np.cosh(sz))
+            c1 = np.where(z > 0, np.sin(sz), np.sinh(sz)) / sz
+            small = np.abs(z) < 1e-3
+            c2 = np.where(small, 0.5 - z / 24 + z * z / 720, (1.0 - c0) / np.where(small, 1.0, z))
+            c3 = np.where(small, 1.0 / 6 - z / 120 + z * z / 5040, (1.0 - c1) / np.where(small, 1.0, z))
+            terms = [r0 * chi * c1, s0 * chi ** 2 * c2, chi ** 3 * c3, -smu * dt]
+            F = sum(terms)
+            Fp = r0 * c0 + s0 * chi * c1 + chi ** 2 * c2
+            Fpp = s0 * c0 + (1.0 - alpha * r0) * chi * c1
+            exact = sum(np.abs(t) for t in terms) <= 8.0 / 3.0 * np.abs(Fp * chi)
+            exact &= np.abs(z) <= 0.1
+            den = Fp + np.copysign(np.sqrt(np.abs(16.0 * Fp * Fp - 20.0 * F * Fpp)), Fp)
+            dx = 5.0 * F / den
+            chi = chi - dx
+            out.append(np.abs(dx / chi))
+    return np.array(out), exact
+
+
+def _one_hop_each(torch, api, cap):
+    """States about a fixed Sun (ellipses up to e = 0.99 and hyperbolae, any
+    place of the orbit), hop lengths from 15 minutes to 100 years, and the
+    directions with kepler_iter = cap from an observer at the Sun, light being
+    so fast that each direction is one hop."""
+    rng = np.random.default_rng(93)
+    n = 2000
+    e = np.where(np.arange(n) < 1600, rng.uniform(0.0, 0.99, n), rng.uniform(1.02, 3.0, n))
+    q = 0.05 * 60.0 ** rng.uniform(size=n)
+    nu = np.where(e < 1, rng.uniform(-3.1, 3.1, n), rng.uniform(-1.2, 1.2, n))
+    r, h = q * (1 + e) / (1 + e * np.cos(nu)), np.sqrt(synth.GM_SUN / (q * (1 + e)))
+    zero = np.zeros(n)
+    x = np.stack([r * np.cos(nu), r * np.sin(nu), zero, -h * np.sin(nu), h * (e + np.cos(nu)), zero], axis=1)
+    dt = 10.0 ** rng.uniform(-2.0, np.log10(36500.0), 64)
+    eph = api.DeviceEphemeris.from_synth(synth.sun_only_ephemeris(0.0, 4570))
+    d, _ = api.lighttime_directions(eph, _dev_x(torch, x), 0.0, _dev_x(torch, dt), _dev_x(torch, np.zeros((64, 3))),
+                                    api.default_opts(kepler_iter=cap, c_light=1e20))
+    return x, dt[:, None], d.cpu().numpy()
+
+
+@pytest.mark.parametrize("cap", [1, 2, 3, 4, 6])
+def test_kepler_cap_counts_the_documented_updates(torch_cuda, cap):
+    """A hop under a small cap fails exactly where the documented solve has
+    not met its rule (an update within 4 ulps, or below 1e-12 and no longer
+    shrinking) by that update, where rounding leaves no doubt."""
+    torch, api = torch_cuda
+    x, dt, d = _one_hop_each(torch, api, cap)
+    failed = np.isnan(d).any(axis=2)
+    u, exact = _kepler_updates(synth.GM_SUN, x, dt, cap)
+    assert np.isfinite(u).all(axis=0).mean() > 0.95          # (the rest overflow)
+    with np.errstate(invalid="ignore"):
+        surely_fails = (u > 1e-11).all(axis=0)
+        surely_ends = (u < 2e-17).any(axis=0) & exact
+    _say(f"cap {cap}: {failed.sum()} of {failed.size} fail; sure {surely_fails.sum()} + {surely_ends.sum()}")
+    assert failed[surely_fails].all()
+    # (the terms' roundings seldom add up to more: 1 of 32,849 on the CPU)
+    assert surely_ends.sum() == 0 or failed[surely_ends].mean() < 1e-3
+
+
+def test_kepler_short_hops_agree_with_the_general_solve(torch_cuda):
+    """The default cap, where short hops take their quicker solve, against a
+    cap one lower, where every hop goes by the general one: nothing fails that
+    the general solve solves, no hop of a few days fails at all, and the
+    directions are the same."""
+    torch, api = torch_cuda
+    x, dt, d = _one_hop_each(torch, api, 60)
+    _, _, g = _one_hop_each(torch, api, 59)
+    bad, bad_g = np.isnan(d).any(axis=2), np.isnan(g).any(axis=2)
+    short = dt * math.sqrt(synth.GM_SUN) < 0.05 * np.linalg.norm(x[:, :3], axis=1) ** 1.5
+    both = ~bad & ~bad_g
+    rel = np.linalg.norm(d - g, axis=2)[both] / np.linalg.norm(g, axis=2)[both]
+    _say(f"default cap {bad.sum()} of {bad.size} fail, one lower {bad_g.sum()}; short {short.mean():.2f}; "
+         f"max rel {rel.max():.2e}")
+    assert short.mean() > 0.2 and not bad[short].any() and not bad_g[short].any()
+    assert not (bad & ~bad_g).any()
+    assert rel.max() < 1e-14
+
+
 def test_kepler_cap_forced_from_the_host(torch_cuda, orc):
     """Host-forced non-convergence (kepler_iter = 1): every object whose
     hop the membership test needs (pairs the linear-motion bound leaves
