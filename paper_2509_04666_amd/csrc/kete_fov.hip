@@ -1338,10 +1338,11 @@ __global__ __launch_bounds__(256, kJoinWaves) void k_fov_direct(const FovParams 
         wave_lds_sync();
         for (int bb = b_first; bb <= b_last; bb += kWave) {
             // lane l looks at batch bb + l: its ranks of the item, and
-            // whether it has objects of the item
+            // whether it has objects of the item (ranks outside every batch
+            // are the first's or the last's, as batch_of_rank has them)
             const int bl = min(bb + lane, b_last);
-            const int off = p.batch_off[bl];
-            const int r0 = max(off, q0), r1 = min(p.batch_off[bl + 1], q1);
+            const int off = bl == 0 ? 0 : p.batch_off[bl];
+            const int r0 = max(off, q0), r1 = bl == p.n_batch - 1 ? q1 : min(p.batch_off[bl + 1], q1);
             const int64_t n_obj_l = p.b_poff[bl + 1] - p.b_poff[bl];
             const int64_t xoff_l = p.b_xoff[bl];
             const int obj0_l = p.b_obj0[bl];

@@ -678,6 +678,38 @@ def test_fov_few_frames_a_batch(torch_cuda, n_sub, n_obj):
     assert torch.equal(qs, ps.repeat(R)) and torch.equal(qo, po.repeat(R))
 
 
+@pytest.mark.parametrize("n_sub", [1, 64])
+def test_fov_frames_outside_every_batch(torch_cuda, n_sub):
+    """Ranks before the first batch's and behind the last one's are tested
+    with those batches, whichever join a call's numbers choose (here the same
+    frames once and three times over).  They hold copies of frames of those
+    batches, whose bounds so cover them."""
+    torch, api = torch_cuda
+    case = synth.footprint_case(n_obj=3000, n_frames=90, span=5.0)
+    fr = case.frames
+    if n_sub == 1: fr = dataclasses.replace(fr, normals=np.ascontiguousarray(fr.normals[:, :1]))
+    order = np.argsort(fr.t, kind="stable")
+    order = np.concatenate([order[[10, 20, 30]], order, order[[50, 55, 60, 65, 70, 75, 87]]])
+    fr = dataclasses.replace(fr, t=fr.t[order], obs=fr.obs[order], normals=fr.normals[order])
+    t_ref = np.array([fr.t[3:43].mean(), fr.t[43:93].mean()])
+    eph = api.DeviceEphemeris.from_synth(case.ephem)
+    x, _ = api.propagate(eph, _dev_x(torch, case.x0), 0.0, t_ref)
+    for copies in (1, 3):
+        some = dataclasses.replace(fr, t=fr.t.repeat(copies), obs=fr.obs.repeat(copies, axis=0),
+                                   normals=fr.normals.repeat(copies, axis=0))
+        frames = api.DeviceFrames.from_synth(some)
+        pairs = []
+        for off in ([0, 43, 100], [3, 43, 93]):
+            b = api.Batches.from_host(np.arange(100 * copies, dtype=np.int32),
+                                      np.array(off, np.int32) * copies, t_ref)
+            pairs.append(api.fov_check(eph, x, b, frames))
+        _say(f"n_sub {n_sub}, {copies} of each: {pairs[0][0].numel()} pairs, "
+             f"{int((pairs[0][0] < 3 * copies).sum() + (pairs[0][0] >= 93 * copies).sum())} of them outside")
+        assert int((pairs[0][0] < 3 * copies).sum()) > 0 and int((pairs[0][0] >= 93 * copies).sum()) > 0
+        for a, c in zip(*pairs):
+            assert torch.equal(a, c)
+
+
 @pytest.mark.parametrize("copies", [1, 31, 32, 33, 1023, 1025, 4097, 8193])
 def test_fov_pairs_of_a_frame_sorted(torch_cuda, copies):
     """Copies of one object, as many pairs in each frame that holds it: the
