@@ -2117,7 +2117,9 @@ constexpr int kSortLds = 8192;
 // Each lane of half a wavefront holds a key of its frame and counts the
 // smaller ones, read four at a time from LDS; that is its key's place.  (One
 // thread a frame, by insertion in global memory, took 79 us for 20,003 frames
-// of a dozen keys, the chain of the longest; this takes 5.)
+// of a dozen keys, the chain of the longest; this takes 5.)  The grid strides
+// over the frames: a thread for each of a frame's lanes passes the 2^32 threads
+// of a launch at 2^27 frames.
 __global__ __launch_bounds__(256) void k_pair_sort_small(const unsigned* __restrict__ keys,
                                                          const int32_t* __restrict__ fstart, int64_t n_frames, int ob,
                                                          int32_t* __restrict__ pf, int32_t* __restrict__ ps,
@@ -2126,23 +2128,27 @@ __global__ __launch_bounds__(256) void k_pair_sort_small(const unsigned* __restr
     static_assert(kSortSmall == 32, "a half-wavefront's lanes");
     const int l = threadIdx.x & (kSortSmall - 1);
     unsigned* A = sh + (threadIdx.x & ~(kSortSmall - 1));
-    const int64_t f = ((int64_t)blockIdx.x * 256 + threadIdx.x) / kSortSmall;
-    int a = 0, n = 0;
-    if (f < n_frames) {
-        a = fstart[f];
-        n = fstart[f + 1] - a;
-    }
-    if (n > kSortSmall) n = 0;
-    const unsigned k = l < n ? keys[a + l] : ~0u;
-    A[l] = k;
-    wave_lds_sync();
-    int rank = 0;
+    constexpr int kFrames = 256 / kSortSmall;           // per block and pass
+    for (int64_t f0 = (int64_t)blockIdx.x * kFrames; f0 < n_frames; f0 += (int64_t)gridDim.x * kFrames) {
+        const int64_t f = f0 + threadIdx.x / kSortSmall;
+        int a = 0, n = 0;
+        if (f < n_frames) {
+            a = fstart[f];
+            n = fstart[f + 1] - a;
+        }
+        if (n > kSortSmall) n = 0;
+        const unsigned k = l < n ? keys[a + l] : ~0u;
+        wave_lds_sync();                    // the previous frame's keys are read
+        A[l] = k;
+        wave_lds_sync();
+        int rank = 0;
 #pragma unroll
-    for (int q = 0; q < kSortSmall / 4; ++q) {
-        const uint4 v = *reinterpret_cast<const uint4*>(A + 4 * q);
-        rank += (v.x < k) + (v.y < k) + (v.z < k) + (v.w < k);
+        for (int q = 0; q < kSortSmall / 4; ++q) {
+            const uint4 v = *reinterpret_cast<const uint4*>(A + 4 * q);
+            rank += (v.x < k) + (v.y < k) + (v.z < k) + (v.w < k);
+        }
+        if (l < n) unpack_pair(k, f, ob, a + rank, pf, ps, po);
     }
-    if (l < n) unpack_pair(k, f, ob, a + rank, pf, ps, po);
 }
 
 // Stable LSD radix sort of one frame's keys by one wavefront in LDS.  The
@@ -2613,8 +2619,9 @@ hipError_t fov_sort(unsigned long long* keys, int64_t n, int64_t n_frames, int64
                                   (const int32_t*)fstart, fcnt, ob, seg);
     if (n_frames > 0) {
         const unsigned gb = (unsigned)std::min<int64_t>(n_frames, (int64_t)cu_count() * 16);
-        hipLaunchKernelGGL(k_pair_sort_small, dim3((unsigned)((n_frames * kSortSmall + 255) / 256)), dim3(256), 0, s,
-                           (const unsigned*)seg, (const int32_t*)fstart, n_frames, ob, pf, ps, po);
+        const unsigned gs = (unsigned)std::min<int64_t>((n_frames * kSortSmall + 255) / 256, (int64_t)cu_count() * 256);
+        hipLaunchKernelGGL(k_pair_sort_small, dim3(gs), dim3(256), 0, s, (const unsigned*)seg, (const int32_t*)fstart,
+                           n_frames, ob, pf, ps, po);
         hipLaunchKernelGGL((k_pair_sort_radix<kSortWave, 4>), dim3(gb), dim3(256), 0, s, (const unsigned*)seg,
                            (const int32_t*)fstart, n_frames, kSortSmall, ob, bits, rb, pf, ps, po);
         hipLaunchKernelGGL((k_pair_sort_radix_block<4096>), dim3(gb), dim3(64 * kSortWaves), 0, s,

@@ -753,6 +753,45 @@ def test_fov_frame_counts(torch_cuda, n_frames):
     assert torch.equal(qo, po.repeat(c.shape[0])[keep]) and int(qs.abs().max()) == 0
 
 
+@pytest.mark.parametrize("n_frames", [1 << 27])
+def test_fov_very_many_frames(torch_cuda, n_frames):
+    """As many frames as pass the threads of one launch with 32 a frame (some
+    700 bytes a frame, inputs and workspace): all away from the one body but
+    a handful that hold it."""
+    torch, api = torch_cuda
+    if torch.cuda.mem_get_info()[0] < 760 * n_frames:
+        pytest.skip("not enough free device memory")
+    case = synth.footprint_case(n_obj=1, n_frames=0, span=3.0)
+    eph = api.DeviceEphemeris.from_synth(case.ephem)
+    x, _ = api.propagate(eph, _dev_x(torch, case.x0), 0.0, [1.5])
+    obs = np.array([1.0, 0.1, 0.0])
+    d, _ = api.lighttime_directions(eph, x[0], 1.5, _dev_x(torch, [1.5]), _dev_x(torch, obs[None]))
+    c = d[0, 0].cpu().numpy()
+    c /= np.linalg.norm(c)
+    rng = np.random.default_rng(94)
+    away = rng.normal(size=(1024, 3))
+    away /= np.linalg.norm(away, axis=1)[:, None]
+    away = np.where((away @ c > 0)[:, None], -away, away) - c
+    away /= np.linalg.norm(away, axis=1)[:, None]
+    half = np.full(1025, 0.01)
+    centre = np.concatenate([away, c[None]])
+    norm = _dev_x(torch, synth.rect_normals(centre, *synth.tangent_basis(centre), half, half))
+    normals = torch.empty((n_frames, 1, 4, 3), dtype=torch.float64, device="cuda")
+    whole = n_frames // 1024 * 1024
+    normals[:whole].view(-1, 1024, 4, 3).copy_(norm[:1024].expand(whole // 1024, 1024, 4, 3))
+    normals[whole:, 0] = norm[:n_frames - whole]
+    hold = [0, 77, n_frames // 2, n_frames - 2, n_frames - 1]
+    normals[hold, 0] = norm[1024]
+    t = torch.full((n_frames,), 1.5, dtype=torch.float64, device="cuda")
+    frames = api.DeviceFrames(t, _dev_x(torch, obs).expand(n_frames, 3).contiguous(), normals)
+    b = api.Batches(torch.arange(n_frames, dtype=torch.int32, device="cuda"),
+                    torch.tensor([0, n_frames], dtype=torch.int32, device="cuda"), _dev_x(torch, [1.5]), np.array([1.5]))
+    pf, ps, po = api.fov_check(eph, x, b, frames, pairs_cap=1000)
+    assert pf.tolist() == hold and not ps.any() and not po.any()
+    del normals, frames, t, b
+    torch.cuda.empty_cache()
+
+
 def test_fov_capacity_and_empty(torch_cuda, orc):
     torch, api = torch_cuda
     from paper_2509_04666_amd import _lib
