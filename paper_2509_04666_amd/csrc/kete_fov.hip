@@ -338,7 +338,7 @@ __global__ __launch_bounds__(256) void k_batch_prep(const FovParams p) {
     double s[3] = {0.0, 0.0, 0.0};
     for (int q = q0 + tid; q < q1; q += 256) {
         const int f = p.frame_order[q];
-        for (int c = 0; c < 3; ++c) s[c] += p.fobs[3 * f + c];
+        for (int c = 0; c < 3; ++c) s[c] += p.fobs[3 * (size_t)f + c];
     }
     for (int c = 0; c < 3; ++c) red[c * 256 + tid] = s[c];
     __syncthreads();
@@ -352,10 +352,11 @@ __global__ __launch_bounds__(256) void k_batch_prep(const FovParams p) {
     double dmax = 0.0, tmax = 0.0, cmin = 1.0;
     for (int q = q0 + tid; q < q1; q += 256) {
         const int f = p.frame_order[q];
-        double dd[3] = {p.fobs[3 * f] - ob[0], p.fobs[3 * f + 1] - ob[1], p.fobs[3 * f + 2] - ob[2]};
+        const double* o = p.fobs + 3 * (size_t)f;
+        double dd[3] = {o[0] - ob[0], o[1] - ob[1], o[2] - ob[2]};
         dmax = fmax(dmax, sqrt(dot3(dd, dd)));
         tmax = fmax(tmax, fabs(p.ft[f] - tr));
-        cmin = fmin(cmin, p.fcap[8 * f + 3]);
+        cmin = fmin(cmin, p.fcap[8 * (size_t)f + 3]);
     }
     red[tid] = dmax; red[256 + tid] = tmax; red[512 + tid] = -cmin;
     __syncthreads();
@@ -364,7 +365,7 @@ __global__ __launch_bounds__(256) void k_batch_prep(const FovParams p) {
         __syncthreads();
     }
     if (tid == 0) {
-        double* o = p.btab + kBatchStride * b;
+        double* o = p.btab + kBatchStride * (size_t)b;
         const EphemArgs& E = p.eph;
         const int hi_all = E.n_seg - 1;
         double S[3], Sd[3];
@@ -418,7 +419,7 @@ __device__ __forceinline__ int batch_of_rank(const FovParams& p, int64_t q) {
 // Frame f's number and cap at its rank in the order the joins read.
 __device__ __forceinline__ void frame_to_rank(const FovParams& p, int f, int64_t pos) {
     p.cell_frames[pos] = f;
-    const double* src = p.fcap + 8 * f;
+    const double* src = p.fcap + 8 * (size_t)f;
     double* dst = p.cell_caps + 8 * pos;
     for (int i = 0; i < 5; ++i) dst[i] = src[i];
     dst[5] = (double)f;
@@ -430,7 +431,7 @@ __global__ void k_frame_keys(const FovParams p, int32_t* __restrict__ qkey, int3
     if (q >= p.n_frames) return;
     const int lo = batch_of_rank(p, q);
     const int f = p.frame_order[q];
-    const double* c = p.fcap + 8 * f;
+    const double* c = p.fcap + 8 * (size_t)f;
     const int key = (int)(p.b_koff[lo] + cell_of(c, p.b_G[lo]));
     qkey[q] = key;
     p.frame_batch[f] = lo;
@@ -539,7 +540,7 @@ __device__ __forceinline__ bool state_bounds(const FovParams& p, int b, ObjBound
     if (!(isfinite(o.x[0]) && isfinite(o.x[1]) && isfinite(o.x[2]) && isfinite(o.v[0]) && isfinite(o.v[1]) &&
           isfinite(o.v[2])))
         return false;
-    const double* bt = p.btab + kBatchStride * b;
+    const double* bt = p.btab + kBatchStride * (size_t)b;
     const double mu = p.mu, cl = p.c_light;
     const double Dobs = bt[9], Delta = bt[10], cosRm = bt[11], sinRm = bt[12], Vsun = bt[13];
     double r0[3], v0[3];
@@ -1087,7 +1088,7 @@ __global__ __launch_bounds__(256, kJoinWaves) void k_fov_cells(const FovParams p
         const int cell = (int)(key - base);
         const int ix = cell / (G * G), iy = (cell / G) % G, iz = cell % G;
         const double tr = p.t_ref[b];
-        const double Asun = p.btab[kBatchStride * b + 14];
+        const double Asun = p.btab[kBatchStride * (size_t)b + 14];
         // frame ranges of the 27 neighbouring cells, one per lane, and their
         // offsets in the concatenated neighbourhood list
         int my_a0 = 0, my_len = 0;
@@ -1380,7 +1381,7 @@ __global__ __launch_bounds__(256, kJoinWaves) void k_fov_direct(const FovParams 
                 // (an object's frames of a batch may lie in several items)
                 if (f0 == __builtin_amdgcn_readlane(off, src)) n_over += __popcll(__ballot(live && o.overflow));
                 const double tr = p.t_ref[b];
-                const double Asun = p.btab[kBatchStride * b + 14];
+                const double Asun = p.btab[kBatchStride * (size_t)b + 14];
                 // global object index; bit 63 set: no linear test
                 const unsigned long long gtag =
                     (unsigned long long)(__builtin_amdgcn_readlane(obj0_l, src) + j) | (o.lin_ok ? 0ull : (1ull << 63));
@@ -1554,7 +1555,7 @@ __global__ __launch_bounds__(256, kJoinWaves) void k_fov_wide(const FovParams p)
         const int u0 = (int)((int64_t)n_units * k / parts), u1 = (int)((int64_t)n_units * (k + 1) / parts);
         const unsigned long long gobj = (unsigned long long)(p.b_obj0[b] + j);
         const double tr = p.t_ref[b];
-        const double Asun = p.btab[kBatchStride * b + 14];
+        const double Asun = p.btab[kBatchStride * (size_t)b + 14];
         int nq = 0;                              // queued frames, wave-uniform
         // queue the frames (cell ranks) of the lanes with `hit`; run the
         // linear test on every full 64
@@ -1870,7 +1871,7 @@ __global__ void k_frame_exact_rec(const FovParams p) {
     }
     const EphemArgs& E = p.eph;
     const double tf = p.ft[f];
-    const double* bt = p.btab + kBatchStride * b;
+    const double* bt = p.btab + kBatchStride * (size_t)b;
     const SunCubic S = sun_cubic(E.coef, 0, E.deg1, tf, E.t_start, E.seg_days, E.inv_seg, 0, E.n_seg - 1);
     R[0] = tf;
     R[1] = p.t_ref[b];

@@ -753,12 +753,14 @@ def test_fov_frame_counts(torch_cuda, n_frames):
     assert torch.equal(qo, po.repeat(c.shape[0])[keep]) and int(qs.abs().max()) == 0
 
 
-@pytest.mark.parametrize("n_frames", [1 << 27])
+@pytest.mark.parametrize("n_frames", [1 << 27, (1 << 28) + 3])
 def test_fov_very_many_frames(torch_cuda, n_frames):
-    """As many frames as pass the threads of one launch with 32 a frame (some
-    700 bytes a frame, inputs and workspace): all away from the one body but
-    a handful that hold it."""
+    """As many frames as pass the threads of one launch with 32 a frame, and
+    as many as pass 32 bits with eight values a frame (some 700 bytes a frame,
+    inputs and workspace): all away from the one body but a handful that hold
+    it."""
     torch, api = torch_cuda
+    torch.cuda.empty_cache()
     if torch.cuda.mem_get_info()[0] < 760 * n_frames:
         pytest.skip("not enough free device memory")
     case = synth.footprint_case(n_obj=1, n_frames=0, span=3.0)
