@@ -477,7 +477,7 @@ __device__ __forceinline__ void node_ephemeris8(const EphemArgs& E, const GroupC
     const int ngr = NB > 0 ? NGR : E.n_gr;
     const int deg1 = DEG1 > 0 ? DEG1 : E.deg1;
     const int cps = 3 * deg1, nc = 3 * nb, ngc = 3 * ngr;
-    const int bstride = E.n_seg * cps;
+    const size_t bstride = (size_t)E.n_seg * cps;     // (a table may pass 2^31 values)
     const double sc = 2.0 * E.inv_seg;
     auto chains = [&](int n, double tt, int c0, int cstep, int npass) {
         const int k = seg_index(tt, E.t_start, E.inv_seg, 0, E.n_seg - 1);

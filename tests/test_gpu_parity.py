@@ -468,6 +468,38 @@ def test_propagate_other_tables(torch_cuda, table, n):
     assert d < 1e-11
 
 
+def test_ephemeris_table_past_2_31_values(torch_cuda):
+    """The same segments in a table so long (19 GB) that the last bodies' lie
+    past 2^31 values: the same states and gradients."""
+    torch, api = torch_cuda
+    torch.cuda.empty_cache()
+    n_seg = 6_200_000
+    case = synth.survey_case(n_obj=2100, n_frames=0)
+    eph, far = (api.DeviceEphemeris.from_synth(case.ephem) for _ in range(2))
+    nb, ns, _, m = eph.coef.shape
+    assert (nb - 1) * n_seg * 3 * m > 2 ** 31
+    if torch.cuda.mem_get_info()[0] < 10 * nb * n_seg * 3 * m:
+        pytest.skip("not enough free device memory")
+    far.coef = torch.zeros((nb, n_seg, 3, m), dtype=torch.float64, device="cuda")
+    far.coef[:, :ns] = eph.coef
+    far.c.n_seg, far.c.coef = n_seg, far.coef.data_ptr()
+    x0 = _dev_x(torch, case.x0)
+    for n, lanes in ((40, 7), (2100, 7), (40, 8), (40, 1)):
+        o = api.default_opts(lanes_per_body=lanes)
+        x, s = api.propagate(eph, x0[:n], 0.0, [5.0, 30.0], o)
+        y, r = api.propagate(far, x0[:n], 0.0, [5.0, 30.0], o)
+        assert torch.equal(s, r) and torch.equal(x, y), (n, lanes)
+    t_obs = _dev_x(torch, np.tile([3.0, 9.0, 20.0], (40, 1)))
+    grads = []
+    for e in (eph, far):
+        ctx = api.AdjointContext(e, 0.0, 20.0, t_obs, _dev_x(torch, np.tile([1.0, 0.1, 0.0], (40, 3, 1))))
+        sky = ctx.forward(x0[:40])
+        grads.append((sky, ctx.backward(x0[:40], torch.ones_like(sky))))
+    assert torch.equal(grads[0][0], grads[1][0]) and torch.equal(grads[0][1], grads[1][1])
+    del far
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("n", [1, 8, 9, 200])
 @pytest.mark.parametrize("lanes", [0, 1, 7, 8])
 def test_propagate_all_objects_of_a_wavefront_fail(torch_cuda, n, lanes):
