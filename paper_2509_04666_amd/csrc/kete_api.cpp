@@ -889,7 +889,7 @@ int kete_fov_check(const kete_ephem_t* eph, const double* x_epoch, int32_t* stat
     hipStream_t s = (hipStream_t)stream;
     {
         TimedScope ts(kTimeFov, s);
-        P.direct = fov_is_direct((double)n_obj * (double)F, P.n_pairs_total);
+        P.direct = fov_is_direct((double)n_obj * (double)F, P.n_pairs_total, 0.0);
         FovClear clear = fov_clear_list(P, counters, n_obj, cnt, ocnt);
         clear.b_poff = b_poff;
         clear.b_obj0 = b_obj0;
@@ -1086,6 +1086,7 @@ struct BatchDims {
     int64_t F = 0, B = 0, NP = 0, nkeys = 0, cand_cap = 0, pairs_cap = 0, max_batch_obj = 0;
     int32_t n_tiles = 0, n_sub = 1;
     double obj_frames = 0.0;                    // sum over batches of objects x frames
+    double busy_items = 0.0;                    // and of 64 objects x 64 frames, objects rounded up
     std::vector<int2> tiles;
     std::vector<int64_t> b_poff, b_xoff, b_koff;
     std::vector<int32_t> b_obj0, b_G;
@@ -1153,6 +1154,7 @@ int batch_dims(const kete_ephem_t* eph, const kete_batch_t* bt, int64_t pairs_ca
             d.b_G[b] = G;
         }
         d.obj_frames += (double)J[j].n_obj * (double)nf;
+        d.busy_items += (double)((J[j].n_obj + kWave - 1) / kWave) * (double)nf / kWave;
         np += J[j].n_obj;
         nk += (int64_t)G * G * G + 1;
         d.max_batch_obj = std::max<int64_t>(d.max_batch_obj, J[j].n_obj);
@@ -1398,7 +1400,9 @@ int kete_batch_run(const kete_ephem_t* eph, const kete_batch_t* batch, int64_t p
     P.max_cells = 1024;
     P.sin_overflow = 0.5;
     TimedScope ts(kTimeFov, s);
-    P.direct = fov_is_direct(dc.obj_frames, dc.NP);
+    P.direct = fov_is_direct(dc.obj_frames, dc.NP,
+                             (double)((dc.F + kWave - 1) / kWave) * (double)((dc.max_batch_obj + kWave - 1) / kWave) -
+                                 dc.busy_items);
     HIPCHK(fov_clear(fov_clear_list(P, w.counters, std::max<int64_t>(batch->n_bodies, 1), w.cnt, w.ocnt), s));
     if (dc.B > 0 && dc.F > 0 && dc.NP > 0) {
         HIPCHK(fov_prepare(P, w.qkey, w.cnt, w.scan_scratch, s));

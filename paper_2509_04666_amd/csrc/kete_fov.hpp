@@ -130,9 +130,17 @@ struct FovParams {
 // object and frame, how the frames are spread over the batches matters
 // little.  obj_frames counts the (object, frame) combinations, n_pairs_total
 // the (object, batch) ones.
+//   The direct join's items are the ranks of all frames times the objects of
+// the largest batch, 64 by 64: where batches of many objects and few frames
+// meet others of few objects and many frames, most of them are idle.  An idle
+// one costs 0.65 ns, as much as 480 tests (500,000 objects x 10 frames with 100
+// lists of 10 objects x 10,000 frames: 80.7 ms, 3.1 by the sorted join).  The
+// first 65,536 cost less than the sorted join's launches.
 constexpr int64_t kDirectFrames = 96;
-inline bool fov_is_direct(double obj_frames, int64_t n_pairs_total) {
-    return obj_frames <= (double)kDirectFrames * (double)n_pairs_total;
+constexpr double kIdleItemTests = 480.0, kFreeIdleItems = 65536.0;
+inline bool fov_is_direct(double obj_frames, int64_t n_pairs_total, double idle_items) {
+    return obj_frames + kIdleItemTests * std::max(0.0, idle_items - kFreeIdleItems) <=
+           (double)kDirectFrames * (double)n_pairs_total;
 }
 
 // Frame caps, batch records and the frames in the order the joins read:

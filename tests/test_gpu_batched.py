@@ -271,3 +271,38 @@ def test_batched_lone_bodies(torch_cuda, sizes):
         d = (x[off:off + 6 * n * ep.size].reshape(ep.size, n, 6) - y).abs().max().item()
         _say(f"job of {n}: max |dx| vs its own run {d:.3e}")
         assert d < 4e-10, k
+
+
+@pytest.mark.parametrize("case", ["even", "uneven"])
+def test_batched_uneven_lists_choose_the_join(torch_cuda, case):
+    """Few frames a batch are joined directly, each object's wavefront visiting
+    every frame of its batch; not where a large list of few frames and small
+    lists of many would leave almost all of that join's items idle.  Either
+    way the pairs are those of each job's own call."""
+    import ctypes as C
+    from paper_2509_04666_amd import _lib
+    torch, api = torch_cuda
+    model = synth.PlanetModel.make()
+    ephem = synth.make_ephemeris(model, -8.0, 3)
+    rng = np.random.default_rng(75)
+    sizes = [(30000, 10)] + [(20, 30)] * 3 if case == "even" else [(30000, 10)] + [(20, 6000)] * 3
+    jobs = []
+    for n, f in sizes:
+        el = synth.main_belt_elements(rng, n)
+        fr = synth.frames_targeted(rng, model, el[:20], 1.0, 2.5, f)
+        jobs.append((synth.bodies_from_elements(model, el, 0.0), 0.0, fr))
+    eph = api.DeviceEphemeris.from_synth(ephem)
+    runner = api.BatchRunner(eph, jobs)
+    runner.run()
+    got = [a.clone() for a in runner.pairs()]
+    stats = (C.c_int64 * 8)()
+    _lib.lib().kete_fov_last_counts(stats)
+    direct = sum(-(-n // 64) * f for n, f in sizes)
+    _say(f"{case}: {got[0].numel()} pairs, {stats[3]} frame visits, {direct} of a direct join")
+    assert (stats[3] == direct) == (case == "even")
+    want = []
+    for k, (x0, t0, fr) in enumerate(jobs):
+        pf, ps, po, *_ = api.predict(eph, _dev(torch, x0), t0, api.DeviceFrames.from_synth(fr), fr.t)
+        want.append((pf + int(runner.frame_off[k]), ps, po + int(runner.obj_off[k])))
+    for a, b in zip(got, (torch.cat(w) for w in zip(*want))):
+        assert torch.equal(a, b)
