@@ -27,6 +27,7 @@ hipError_t launch_body_sort(const uint32_t* keys, int n, int n_class, int32_t* p
                             hipStream_t s);
 const int32_t* body_sort_first(const int32_t* counts, int n, int n_class);
 int solo_waves_for(int n, bool classes);
+double solo_class_steps(int n, int solo_waves, int lanes_per_body, double span);
 size_t bucket_scratch_ints(int64_t n_obj, int n_buckets);
 }  // namespace kete
 
@@ -636,7 +637,8 @@ int kete_propagate_nbody(const kete_ephem_t* eph, const double* x0, double t0, i
         // wavefronts of one object, all of them on the chip at once, need no order
         const bool sorted = ncls > 1 && P.solo_waves < n_obj;
         HIPCHK(launch_hpref_init(P.state_in, h_pref, sorted ? sorts.keys : nullptr, (int)n_obj, E.gm[0], dt_lo, dt_hi,
-                                 ncls, (int)(e1 - e0), kSoloSteps, s));
+                                 ncls, (int)(e1 - e0),
+                                 solo_class_steps((int)n_obj, P.solo_waves, opts->lanes_per_body, dt_hi - dt_lo), s));
         if (sorted) {
             HIPCHK(launch_body_sort(sorts.keys, (int)n_obj, ncls, perm, sorts.tmp, sorts.counts, s));
             P.n_solo = body_sort_first(sorts.counts, (int)n_obj, ncls);

@@ -180,7 +180,8 @@ constexpr int kMaxBuckets = 256;
 // Sort keys of the bodies of one integrator launch (k_hpref_init): the high
 // 16 bits hold the step class, the low 16 the time class; bodies are
 // ordered by class, then by time (two stable counting-sort passes).
-//   step class 0: bodies for a wavefront of their own (see solo_waves_for),
+//   step class 0: bodies for a wavefront of their own (see solo_waves_for and
+//     solo_class_steps),
 //     with more than kSoloSteps predicted steps shorter than kSoloMaxStep
 //     days, the most steps first (16 classes an octave): the bodies of fast
 //     orbits, not the slow ones of a long span;

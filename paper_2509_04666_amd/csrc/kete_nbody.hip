@@ -383,6 +383,23 @@ int solo_waves_for(int n, bool classes) {
     return classes && n <= kSoloSomeObj ? kSoloSome : 0;
 }
 
+// Predicted steps from which a body is in the solo class, ordered by their
+// number: kSoloSteps where the first of them get wavefronts of their own.
+// Elsewhere its bodies share wavefronts, and whether to line up their numbers
+// of steps or (as critical bodies, no solo class) their perihelion passages
+// goes by the launch:
+//   its longest wavefronts end it: the passages (eight lanes a body, 20,000
+//     bodies 2.0 ms for a year and 9.0 for five, by steps 3.6 and 18.3; one
+//     lane a body 30 and 123, by steps 49 and 244);
+//   many rounds of wavefronts on the chip and a span of several passages: the
+//     steps (400,000 bodies, seven lanes: one and a half years 12.5 ms either
+//     way, two years 16.5, by passages 17.8, five 41.5 and 53.3).
+constexpr double kManyPassages = 650.0;             // days
+double solo_class_steps(int n, int solo_waves, int lanes_per_body, double span) {
+    const bool rounds = lanes_per_body != 1 && n > kSoloSomeObj;
+    return solo_waves || (rounds && span > kManyPassages) ? kSoloSteps : HUGE_VAL;
+}
+
 // The grouped kernel with G lanes per object; the usual shapes of the
 // perturber table (bodies, bodies with the Eq. A.3 and A.4 terms) get an
 // unrolled force.

@@ -424,6 +424,32 @@ def test_lone_paired_and_grouped_objects(torch_cuda, n, span):
         assert d < 1e-10
 
 
+def test_shared_wavefronts_line_up_perihelion_passages(torch_cuda):
+    """Fast orbits that share wavefronts (eight lanes or one a body) pass
+    perihelion together: they take fewer shared steps than in the order of
+    their numbers of steps, in which each shortens the others' steps at times
+    of its own."""
+    torch, api = torch_cuda
+    rng = np.random.default_rng(95)
+    model = synth.PlanetModel.make()
+    eph = api.DeviceEphemeris.from_synth(synth.make_ephemeris(model, -8.0, 49))
+    el = synth.neo_elements(rng, 8000)
+    el = el[el[:, 0] < 1.0]                              # a passage or more a year
+    x = synth.bodies_from_elements(model, el, 0.0)
+    q = el[:, 0] * (1 - el[:, 1])
+    by_steps = np.argsort(q ** 1.5 / np.sqrt(1 + el[:, 1]))      # the predicted step at perihelion
+    steps = {}
+    for lanes in (8, 1):
+        for name, order, buckets in (("own", np.arange(len(x)), 16), ("by steps", by_steps, 1)):
+            opts = api.default_opts(lanes_per_body=lanes, n_buckets=buckets)
+            _, st, c = api.propagate(eph, _dev_x(torch, x[order]), 0.0, [365.0], opts, stats=True)
+            assert int(st.abs().max()) == 0
+            steps[lanes, name] = int(c[0])
+    _say(f"{len(x)} bodies, shared steps {steps}")
+    for lanes in (8, 1):
+        assert steps[lanes, "own"] < 0.97 * steps[lanes, "by steps"]
+
+
 @pytest.mark.parametrize("n,n_out", [(2049, 5), (9300, 3), (9300, 4), (9300, 70)])
 def test_many_epochs_of_a_day(torch_cuda, n, n_out):
     """Objects that cross the span in one step keep their order when their
