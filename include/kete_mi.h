@@ -92,7 +92,8 @@ typedef struct {
     double h_max;            /* largest step, 0 = unlimited */
     double c_light;          /* speed of light in au/day (173.144632674...) */
     double batch_span;       /* frame batch span in days (3.0, Sect. 2) */
-    double cell_chord;       /* FoV sky-grid cell size (chord units; 0 = auto: 0.10) */
+    double cell_chord;       /* FoV sky-grid cell size (chord units; 0 = auto: 0.10); calls of few
+                                frames a batch are joined without a grid (the size is still checked) */
     double lt_tol;           /* light-time convergence: last update in days (1e-15) */
     int32_t max_steps;       /* per object per call (2,000,000) */
     int32_t max_iter;        /* corrector iterations per step (12) */
@@ -104,7 +105,7 @@ typedef struct {
                                 window's end.  0 = auto (0: no windows for the grouped
                                 integrators and the adjoint, 2 with one lane per body) */
     int32_t lt_iter;         /* light-time updates at most (10) */
-    int32_t fov_block;       /* FoV threads per block: 64/128/256 (128) */
+    int32_t fov_block;       /* 64/128/256 (128): checked, but the FoV kernels' blocks are fixed */
     int32_t adj_seg_steps;   /* adjoint: steps per checkpoint segment at most (32) */
     int32_t persist_waves;   /* batched runs: resident waves per compute unit (8) */
     int32_t lanes_per_body;  /* integrator lanes per object: 1, 8 (8 objects a wavefront), or 7: 9 objects
@@ -430,8 +431,8 @@ int kete_batch_graph_destroy(void *graph);
 
 /* Autotuner for batched runs: coordinate descent, starting from `base`
  * (NULL = defaults), over n_buckets {1,4,8,16}, persist_waves {2,4,8,12},
- * window_segs {1,2,4}, fov_block {64,128,256} and cell_chord
- * {0.05,0.10,0.16}, in that order; each candidate is planned, run once to
+ * window_segs {0,1,2,4} and, where the batch's frames are joined by sky cell,
+ * cell_chord {0.05,0.10,0.16}, in that order; each candidate is planned, run once to
  * warm up and timed with HIP events over `reps` (1..100) runs of
  * kete_batch_run on `stream`.  Candidates whose workspace exceeds
  * ws_bytes are skipped.  progress (may be NULL) is called with user after

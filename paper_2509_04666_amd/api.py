@@ -342,6 +342,12 @@ def sky_residual_loss(sky: torch.Tensor, radec_obs: torch.Tensor) -> torch.Tenso
     return (r1 * r1 + r2 * r2).sum()
 
 
+# Part of the autotune cache's keys: raised when a tuned option changes its
+# meaning, so that results stored before are not taken for it.  2: window_segs
+# 0 stands for no forced step ends (it was the longest windows that fitted LDS).
+TUNE_REVISION = 2
+
+
 class BatchRunner:
     """Many independent jobs (bodies + frames) run as one batch: a
     persistent propagation launch over all jobs, then the field-of-view
@@ -442,10 +448,12 @@ class BatchRunner:
 
     def autotune(self, reps: int = 1, cache: Optional[str] = None, progress=None):
         """Pick launch parameters with the library's autotuner.  With `cache`
-        (a JSON file), a result stored under this device and batch is reused
-        and a new one is stored.  Returns (opts, ms per run, from_cache)."""
+        (a JSON file), a result stored under this device, batch and
+        TUNE_REVISION is reused and a new one is stored.  Returns (opts, ms
+        per run, from_cache)."""
         props = torch.cuda.get_device_properties(self.device)
-        key = f"{getattr(props, 'gcnArchName', props.name)}|cu{props.multi_processor_count}|{self.signature()}"
+        key = (f"{getattr(props, 'gcnArchName', props.name)}|cu{props.multi_processor_count}|r{TUNE_REVISION}|"
+               f"{self.signature()}")
         tuned = ("n_buckets", "persist_waves", "window_segs", "fov_block", "cell_chord")
         if cache and os.path.exists(cache):
             with open(cache) as fh:

@@ -1096,6 +1096,11 @@ struct BatchDims {
 
 constexpr int kSmallBatchFrames = 256;   // below this a batch's frames share one grid cell
 
+bool batch_is_direct(const BatchDims& d) {
+    const double items = (double)((d.F + kWave - 1) / kWave) * (double)((d.max_batch_obj + kWave - 1) / kWave);
+    return fov_is_direct(d.obj_frames, d.NP, items - d.busy_items);
+}
+
 int batch_dims(const kete_ephem_t* eph, const kete_batch_t* bt, int64_t pairs_cap, const kete_opts_t* o,
                bool tables, BatchDims& d) {
     if (!bt || !bt->jobs_host || bt->n_jobs < 0 || bt->n_batch < 0 || bt->n_bodies < 0)
@@ -1402,9 +1407,7 @@ int kete_batch_run(const kete_ephem_t* eph, const kete_batch_t* batch, int64_t p
     P.max_cells = 1024;
     P.sin_overflow = 0.5;
     TimedScope ts(kTimeFov, s);
-    P.direct = fov_is_direct(dc.obj_frames, dc.NP,
-                             (double)((dc.F + kWave - 1) / kWave) * (double)((dc.max_batch_obj + kWave - 1) / kWave) -
-                                 dc.busy_items);
+    P.direct = batch_is_direct(dc);
     HIPCHK(fov_clear(fov_clear_list(P, w.counters, std::max<int64_t>(batch->n_bodies, 1), w.cnt, w.ocnt), s));
     if (dc.B > 0 && dc.F > 0 && dc.NP > 0) {
         HIPCHK(fov_prepare(P, w.qkey, w.cnt, w.scan_scratch, s));
@@ -1553,20 +1556,21 @@ int kete_batch_autotune(const kete_ephem_t* eph, const kete_batch_t* batch, int6
     double cur_ms;
     int rc = trial(cur, cur_ms);
     if (!rc && !(cur_ms < HUGE_VAL)) rc = fail(KETE_EWORKSPACE, "workspace too small for the base options");
+    BatchDims dims;
+    if (!rc) rc = batch_dims(eph, batch, pairs_cap, &cur, false, dims);
     struct Axis { int which; double v[5]; int n; };
     const Axis axes[] = {
         {0, {1, 4, 8, 16}, 4},             // n_buckets
         {1, {2, 4, 8, 12}, 4},             // persist_waves
-        {2, {1, 2, 4}, 3},                 // window_segs
-        {3, {64, 128, 256}, 3},            // fov_block
-        {4, {0.05, 0.10, 0.16}, 3},        // cell_chord
+        {2, {0, 1, 2, 4}, 4},              // window_segs
+        // the sky cells, which a direct join has none of
+        {3, {0.05, 0.10, 0.16}, batch_is_direct(dims) ? 0 : 3},        // cell_chord
     };
     auto with = [](kete_opts_t o, int which, double v) {
         switch (which) {
             case 0: o.n_buckets = (int32_t)v; break;
             case 1: o.persist_waves = (int32_t)v; break;
             case 2: o.window_segs = (int32_t)v; break;
-            case 3: o.fov_block = (int32_t)v; break;
             default: o.cell_chord = v; break;
         }
         return o;

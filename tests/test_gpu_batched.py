@@ -306,3 +306,31 @@ def test_batched_uneven_lists_choose_the_join(torch_cuda, case):
         want.append((pf + int(runner.frame_off[k]), ps, po + int(runner.obj_off[k])))
     for a, b in zip(got, (torch.cat(w) for w in zip(*want))):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("n_frames", [60, 6000])
+def test_batched_autotune_tries_what_has_an_effect(torch_cuda, tmp_path, n_frames):
+    """From a base with windows the autotuner also tries none; it leaves out
+    the sky cells where the frames are joined without them, and fov_block.  A
+    result stored before the options' present meaning is not used."""
+    import json
+    torch, api = torch_cuda
+    rng = np.random.default_rng(76)
+    model = synth.PlanetModel.make()
+    eph = api.DeviceEphemeris.from_synth(synth.make_ephemeris(model, -8.0, 3))
+    el = synth.main_belt_elements(rng, 300)
+    job = (synth.bodies_from_elements(model, el, 0.0), 0.0, synth.frames_targeted(rng, model, el, 1.0, 2.5, n_frames))
+    runner = api.BatchRunner(eph, [job], api.default_opts(window_segs=4))
+    props = torch.cuda.get_device_properties(0)
+    old = dict(cell_chord=0.16, fov_block=256, ms=1.0, n_buckets=1, persist_waves=12, window_segs=4)
+    cache = tmp_path / "tune.json"
+    cache.write_text(json.dumps({f"{props.gcnArchName}|cu{props.multi_processor_count}|{runner.signature()}": old}))
+    tried = []
+    best, ms, hit = runner.autotune(reps=1, cache=str(cache), progress=lambda o, t: tried.append(o))
+    assert not hit
+    values = {k: {o[k] for o in tried} for k in tried[0]}
+    _say(f"{n_frames} frames: tried {values}")
+    assert values["window_segs"] == {0, 1, 2, 4}
+    assert values["fov_block"] == {128}
+    assert len(values["cell_chord"]) == (1 if n_frames == 60 else 4)
+    assert api.BatchRunner(eph, [job], api.default_opts(window_segs=4)).autotune(cache=str(cache))[2]
