@@ -695,7 +695,7 @@ __global__ __launch_bounds__(64, 2) void k_adj_back(const AdjParams p) {
         while (S.t < t_stop)
             g8_integrate<NB, NGR, NJ2, DEG1, kGroup>(
                 p, gc, T, M, lane, aligned_end(S.t, p.t_end, E.t_start, E.seg_days, E.inv_seg, p.window_segs), S, Cn,
-                store, true, t_stop);
+                store, t_stop);
         sweep(seg, 0, min(n, ns));
     }
     // observations at the start epoch

@@ -195,15 +195,15 @@ constexpr int kGroup = 8;
 
 // Lanes of a wavefront by body, G lanes per body.  G = 7: 9 bodies, lanes
 // 7g..7g+6 for body g, and lane 63 joins body 8 as its eighth lane.  G = 8:
-// 8 bodies, lanes 8g..8g+7.  G = 14, 28, 56: 4, 2 or 1 bodies with kLanes =
-// 2, 4 or 8 adjacent lanes per node, which share the node's force sum, and
+// 8 bodies, lanes 8g..8g+7.  G = 14, 56: 4 bodies or one with kLanes = 2 or
+// 8 adjacent lanes per node, which share the node's force sum, and
 // lanes 56..63 joining the last body.  gl is the lane's node less one; lanes
 // with gl = 7 repeat node 7, so every node has exactly one owning set of
 // lanes and the code below needs no other distinction.  sub numbers the
 // lanes of a node.
 template <int G>
 struct GroupMap {
-    static_assert(G == 7 || G == 8 || G == 14 || G == 28 || G == 56, "lanes per body");
+    static_assert(G == 7 || G == 8 || G == 14 || G == 56, "lanes per body");
     static constexpr int kLanes = G == 8 ? 1 : G / 7;
     static constexpr int kBodies = G == 8 ? 8 : 64 / G;      // bodies per wavefront
     int grp, gl, sub;
@@ -881,7 +881,6 @@ struct G8State {
     double hprev = 0.0;               // that step (0: none yet)
     double t, hw, hp_new;
     bool active, haveF0;
-    bool row0 = false;          // table row 0 holds the perturbers at t (node 0)
     int status;
 };
 struct G8Count {
@@ -901,14 +900,11 @@ struct G8NoVisit {
 // wavefront take the smallest step any of them asks for).  Correctors start
 // from the previous step extrapolated unless p.zero_start.
 // visit(ts, te, h, dn, S) is called by every lane after each accepted step,
-// before S moves to the step end te (dn: this lane's converged increment, T.e8:
-// the step's perturber table).  With need_node0 the table also holds node 0
-// (the step start) on every step.
+// before S moves to the step end te (dn: this lane's converged increment).
 template <int NB, int NGR, int NJ2, int DEG1, int G, class Params, class Visit = G8NoVisit>
 __device__ __forceinline__ void g8_integrate(const Params& p, const GroupConst& K, const G8Lds& T,
                                              const GroupMap<G>& M, int lane, double tb, G8State& S, G8Count& C,
-                                             Visit&& visit = Visit(), bool need_node0 = false,
-                                             double t_stop = kInf) {
+                                             Visit&& visit = Visit(), double t_stop = kInf) {
     constexpr int L = GroupMap<G>::kLanes;
     const EphemArgs& E = p.eph;
     const RadauConst& rc = p.rc;
@@ -930,11 +926,9 @@ __device__ __forceinline__ void g8_integrate(const Params& p, const GroupConst& 
             return;
         }
         const double t_end = uniform(landed ? tb : S.t + h);
-        // node 0 is evaluated before the first step; with need_node0 it is
-        // afterwards the previous step's end row, copied when that step is accepted
-        const int n0 = (S.haveF0 && (!need_node0 || S.row0)) ? 1 : 0;
+        // (node 0, for the force there, before the first step only)
+        const int n0 = S.haveF0 ? 1 : 0;
         node_ephemeris8<NB, NGR, DEG1>(E, K, T, S.t, h, t_end, n0 == 0, lane);
-        S.row0 = true;
         C.chain += (kNodes - n0) * E.n_gr * 3;
         C.vchain += (kNodes - n0) * (nb - E.n_gr) * 3;
         if (!S.haveF0) { accel8_group<L>(T.e8, T, E, S.x0, S.v0, gl, sub, S.F0); S.haveF0 = true; }
@@ -980,11 +974,6 @@ __device__ __forceinline__ void g8_integrate(const Params& p, const GroupConst& 
             S.status = KETE_ST_NONFINITE; S.active = false;
         }
         accel8_group<L>(T.e8 + 8 * T.row, T, E, S.x0, S.v0, gl, sub, S.F0);
-        if (need_node0) {
-            wave_lds_sync();
-            for (int i = lane; i < T.row; i += kWave) T.e8[i] = T.e8[8 * T.row + i];
-            wave_lds_sync();
-        }
         if (landed) {
             S.hw = uniform(fmin(S.hw, hn));
         } else {
@@ -1149,70 +1138,5 @@ __device__ __forceinline__ void dense_epochs(const GroupConst& K, double* __rest
         if (n < kDenseRound || ec.next >= ec.end) break;
     }
 }
-
-// Shared stepping state of one lane.
-struct Lane {
-    double x0[3], v0[3], F0[3];
-    bool active;
-    int status;
-};
-
-// Integrate one window [t, W.t_b] with wave-shared adaptive steps.  The
-// visitor is called after every accepted step with (t_prev, h, D).
-template <class Params, class Visit>
-__device__ __forceinline__ void integrate_window(const Params& p, const Window& W, double* coefL, int bstride,
-                                                 double* ephW, Lane& L, double& t, double& hw, bool& haveF0,
-                                                 long& wsteps, Visit&& visit) {
-    const EphemArgs& E = p.eph;
-    const RadauConst& rc = p.rc;
-    const int lane = threadIdx.x & 63;
-    const double tb = W.t_b;
-    unsigned long long dummy = 0;
-    if (__ballot(L.active) == 0ull) { t = tb; return; }
-    while (t != tb) {
-        const double dir = tb > t ? 1.0 : -1.0;
-        double hmag = hw;
-        if (p.h_max > 0.0 && hmag > p.h_max) hmag = p.h_max;
-        double h = dir * hmag;
-        bool landed = false;
-        if (fabs(h) >= fabs(tb - t)) { h = tb - t; landed = true; }
-        if (wsteps >= p.max_steps) {
-            if (L.active) { L.status = KETE_ST_MAX_STEPS; L.active = false; }
-            t = tb;
-            return;
-        }
-        const double t_end = landed ? tb : t + h;
-        node_ephemeris(coefL, bstride, E, rc, W.seg_lo, W.seg_hi, t, h, t_end, lane, ephW);
-        if (!haveF0) { accel(ephW, E, L.x0, L.v0, L.F0); haveF0 = true; }
-        double D[7][3], b6[3];
-        corrector(rc, E, ephW, L.x0, L.v0, L.F0, h, L.active, p.max_iter, D, b6, dummy);
-        double fm = 0.0, bm = 0.0;
-        for (int c = 0; c < 3; ++c) { fm = fmax(fm, fabs(D[6][c] + L.F0[c])); bm = fmax(bm, fabs(b6[c])); }
-        const double ebl = fm > 0.0 ? bm / fm : 0.0;
-        double hl = (ebl > 0.0 && ebl < kInf) ? fabs(h) * step_factor(p.eps / ebl) : fabs(h) / p.safety;
-        if (!L.active) hl = kInf;
-        if (L.active && hl < p.h_min) { L.status = KETE_ST_STEP_UNDERFLOW; L.active = false; hl = kInf; }
-        const double hn = wave_min(hl);
-        if (!(hn < kInf)) { t = tb; return; }
-        if (hn < p.safety * fabs(h)) { hw = hn; continue; }
-        visit(t, h, D, ephW);
-        const double hh = h * h;
-        for (int c = 0; c < 3; ++c) {
-            double ax = rc.half_s2[8] * L.F0[c], av = L.F0[c];
-            for (int m = 0; m < 7; ++m) { ax = fma(rc.A[8][m], D[m][c], ax); av = fma(rc.B[8][m], D[m][c], av); }
-            L.x0[c] = fma(hh, ax, fma(h, L.v0[c], L.x0[c]));
-            L.v0[c] = fma(h, av, L.v0[c]);
-        }
-        t = t_end;
-        ++wsteps;
-        if (L.active && !(isfinite(L.x0[0]) && isfinite(L.x0[1]) && isfinite(L.x0[2]) && isfinite(L.v0[0]) &&
-                          isfinite(L.v0[1]) && isfinite(L.v0[2]))) {
-            L.status = KETE_ST_NONFINITE; L.active = false;
-        }
-        accel(ephW + 8 * E.n_body * 6, E, L.x0, L.v0, L.F0);
-        hw = landed ? fmin(hw, hn) : fmin(hn, fabs(h) / p.safety);
-    }
-}
-
 
 }  // namespace kete
