@@ -229,3 +229,68 @@ def test_adjoint_observation_at_the_end_epoch(torch_cuda):
             assert torch.isfinite(skies[-1]).all() and torch.isfinite(grad).all(), (t0, t_end)
         assert (skies[0] - skies[1]).abs().max().item() < 1e-10
     assert below > 0
+
+
+def _fast_orbits(n, arc):
+    """Bodies within 2 au that pass perihelion, with their observations."""
+    import dataclasses
+    g = synth.gradient_case(n_obj=n, k_obs=9, arc=arc, neo_frac=1.0)
+    el = synth.neo_elements(np.random.default_rng(97), n)
+    el[:, 0], el[:, 1] = 0.8 + 0.1 * (np.arange(n) % 4), 0.6
+    return dataclasses.replace(g, x0=synth.bodies_from_elements(synth.PlanetModel.make(), el, 0.0))
+
+
+@pytest.mark.parametrize("n", [1, 8, 9, 70])
+def test_adjoint_steps_past_the_records(torch_cuda, n):
+    """Every body alone takes more steps than the forward records with
+    adj_seg_steps = 1 (8), so every wavefront recomputes; the gradients are
+    those of a run that records all of its steps."""
+    torch, api = torch_cuda
+    g = _fast_orbits(n, 100.0)
+    x0 = _t(torch, g.x0)
+    eph, ctx = _setup(torch, api, g, 5.0, adj_seg_steps=256)
+    for j in range(n):
+        _, _, c = api.propagate(eph, x0[j:j + 1], 0.0, [100.0], api.default_opts(lanes_per_body=8), stats=True)
+        assert int(c[0]) > 8, j
+    w = torch.full((n, 9, 2), 1e-3, dtype=torch.float64, device="cuda")
+    grads = []
+    for ckpt, steps in ((5.0, 256), (0.1, 1)):
+        eph, ctx = _setup(torch, api, g, ckpt, adj_seg_steps=steps)
+        ctx.workspace.fill_(255)
+        ctx.forward(x0)
+        grads.append(ctx.backward(x0, w))
+        assert int((ctx.status != 0).sum()) == 0
+    rel = ((grads[1] - grads[0]).norm(dim=1) / grads[0].norm(dim=1)).max().item()
+    _say(f"{n} fast orbits, recomputed vs recorded: max rel {rel:.3e}")
+    assert rel < 1e-9
+
+
+def test_adjoint_object_fails_in_a_recomputed_segment(torch_cuda):
+    """A body whose steps fall below h_min on the way to its perihelion fails
+    in the middle of wavefronts whose steps are recomputed: it gets a zero
+    gradient, and the others theirs as from a run that records all steps."""
+    torch, api = torch_cuda
+    n, fails = 16, [3, 12]
+    g = _fast_orbits(n, 100.0)
+    el = np.array([[1.2, 0.95, 0.1, 0.3, 0.2, 0.0]] * 2)
+    period = 2 * np.pi * np.sqrt(1.2 ** 3 / synth.GM_SUN)
+    el[:, 5] = -2 * np.pi * np.array([60.0, 70.0]) / period         # perihelion after 60 and 70 days
+    x0 = g.x0.copy()
+    x0[fails] = synth.bodies_from_elements(synth.PlanetModel.make(), el, 0.0)
+    x0 = _t(torch, x0)
+    w = torch.full((n, 9, 2), 1e-3, dtype=torch.float64, device="cuda")
+    grads = []
+    for ckpt, steps in ((5.0, 1024), (0.2, 6)):
+        eph, ctx = _setup(torch, api, g, ckpt, adj_seg_steps=steps, h_min=0.046)
+        ctx.workspace.fill_(255)
+        ctx.forward(x0)
+        before = ctx.status.clone()
+        grads.append(ctx.backward(x0, w))
+        assert torch.equal(ctx.status, before)
+        assert ctx.status.tolist() == [2 if j in fails else 0 for j in range(n)]
+        assert torch.all(grads[-1][fails] == 0)
+    _, _, c = api.propagate(eph, x0[:8], 0.0, [100.0], api.default_opts(lanes_per_body=8, h_min=0.046), stats=True)
+    ok = [j for j in range(n) if j not in fails]
+    rel = ((grads[1] - grads[0])[ok].norm(dim=1) / grads[0][ok].norm(dim=1)).max().item()
+    _say(f"{int(c[0])} steps of a wavefront, 48 recorded; recomputed vs recorded: max rel {rel:.3e}")
+    assert int(c[0]) > 96 and rel < 1e-9        # (half of them before the failure)

@@ -768,6 +768,45 @@ def test_fov_frames_outside_every_batch(torch_cuda, n_sub):
             assert torch.equal(a, c)
 
 
+@pytest.mark.parametrize("widest", [165.0, 180.0])
+def test_fov_sub_frames_far_apart(torch_cuda, orc, widest):
+    """Frames of two sub-frames 10 degrees apart and more, 120 to a batch.  Up
+    to 165 degrees, boxes that reach tangents of 12 about the frame's centre,
+    in the per-cell join; up to 180, frames without a box (a vertex outside
+    the centre's hemisphere), whose batch's bodies all take the wide join.
+    Every pair is the oracle's."""
+    torch, api = torch_cuda
+    rng = np.random.default_rng(96)
+    base = synth.tiny_case(n_obj=1500, n_frames=1, span=6.0)
+    F = 240
+    t = np.sort(rng.uniform(0.2, 5.8, F))
+    obs = synth.circular_observer(base.model, t)[:, :3]
+    lon, lat = rng.uniform(0, 2 * np.pi, F), rng.uniform(-0.1, 0.1, F)
+    sep = np.radians(np.resize(np.array([10.0, 60.0, 120.0, 150.0, 170.0, 175.0, 178.0, 180.0]) * (widest / 180.0), F))
+    subs = []
+    for a in (-0.5, 0.5):
+        c = np.stack([np.cos(lon + a * sep) * np.cos(lat), np.sin(lon + a * sep) * np.cos(lat), np.sin(lat)], axis=1)
+        h = np.full(F, np.radians(2.0))
+        subs.append(synth.rect_normals(c, *synth.tangent_basis(c), h, h))
+    fr = synth.Frames(t, obs, None, None, None, None, None, np.stack(subs, axis=1))
+    case = dataclasses.replace(base, frames=fr)
+    order, off, t_ref = orc.make_batches(t)
+    assert F > 96 * (len(off) - 1)
+    xe, st, _ = orc.propagate(case.ephem, case.x0, 0.0, t_ref)
+    opairs = orc.fov(case.ephem, xe, st, order, off, t_ref, t, obs, fr.normals)
+    *gp, stats = api.fov_check(api.DeviceEphemeris.from_synth(case.ephem), _dev_x(torch, xe),
+                               api.Batches.from_host(order.astype(np.int32), off.astype(np.int32), t_ref),
+                               api.DeviceFrames.from_synth(fr), return_stats=True)
+    gp = [a.cpu().numpy() for a in gp]
+    found = np.bincount(np.arange(F)[opairs[0]] % 8, minlength=8)
+    _say(f"{len(opairs[0])} pairs, by separation {found.tolist()}; {stats[2]} of 3000 without a bound")
+    assert found.min() > 0
+    assert stats[2] == 3000 if widest == 180.0 else stats[2] < 300
+    extra = _compare_pairs(gp, opairs[:3], opairs[3], "sub-frames far apart")
+    for p in extra:
+        assert abs(_edge_of(orc, case.ephem, xe, order, off, t_ref, fr, p)) < MAS
+
+
 @pytest.mark.parametrize("copies", [1, 31, 32, 33, 1023, 1025, 4097, 8193])
 def test_fov_pairs_of_a_frame_sorted(torch_cuda, copies):
     """Copies of one object, as many pairs in each frame that holds it: the
