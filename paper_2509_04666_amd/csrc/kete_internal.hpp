@@ -161,9 +161,9 @@ hipError_t launch_group_const(const RadauConst& rc, double* out, hipStream_t s);
 // Instantiation of the grouped kernels for a perturber table: 2 and 3 the
 // default model's shape (10 bodies, 3 with Eq. A.3, 2 of them with Eq. A.4)
 // and that of the Sun with two planets, whose force is unrolled; 1 any other
-// count with 13 coefficients, 0 any.
+// count with 13 coefficients, 0 any, also tables of 2^32 values a body.
 inline int group_shape(const EphemArgs& E) {
-    if (E.deg1 != 13) return 0;
+    if (E.deg1 != 13 || (uint64_t)E.n_seg * 3 * E.deg1 > UINT32_MAX) return 0;
     if (E.n_j2 != 2 || E.n_j2g != 2) return 1;
     return E.n_body == 10 && E.n_gr == 3 ? 2 : E.n_body == 3 && E.n_gr == 2 ? 3 : 1;
 }

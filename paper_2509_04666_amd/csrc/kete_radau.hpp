@@ -477,7 +477,12 @@ __device__ __forceinline__ void node_ephemeris8(const EphemArgs& E, const GroupC
     const int ngr = NB > 0 ? NGR : E.n_gr;
     const int deg1 = DEG1 > 0 ? DEG1 : E.deg1;
     const int cps = 3 * deg1, nc = 3 * nb, ngc = 3 * ngr;
-    const size_t bstride = (size_t)E.n_seg * cps;     // (a table may pass 2^31 values)
+    // A body's segments begin at a 64-bit offset (a table may pass 2^31 values),
+    // one multiply-add where a body has fewer than 2^32 (group_shape).
+    const size_t bstride = (size_t)E.n_seg * cps;
+    auto body_offset = [&](int b) {
+        return DEG1 > 0 ? (size_t)(unsigned)b * (unsigned)bstride : (size_t)b * bstride;
+    };
     const double sc = 2.0 * E.inv_seg;
     auto chains = [&](int n, double tt, int c0, int cstep, int npass) {
         const int k = seg_index(tt, E.t_start, E.inv_seg, 0, E.n_seg - 1);
@@ -486,7 +491,7 @@ __device__ __forceinline__ void node_ephemeris8(const EphemArgs& E, const GroupC
         double* row = T.e8 + n * T.row;
         auto at = [&](int c) {                     // coefficients of coordinate c
             const int qc = c < nc ? c : nc - 1, sl = qc / 3;
-            return cb + slot_body(E, sl) * bstride + (qc - 3 * sl) * deg1;
+            return cb + body_offset(slot_body(E, sl)) + (unsigned)((qc - 3 * sl) * deg1);
         };
 #pragma unroll 1
         for (int j = 0; j < npass; j += 2) {

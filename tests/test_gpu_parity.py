@@ -494,16 +494,21 @@ def test_propagate_other_tables(torch_cuda, table, n):
     assert d < 1e-11
 
 
-def test_ephemeris_table_past_2_31_values(torch_cuda):
-    """The same segments in a table so long (19 GB) that the last bodies' lie
-    past 2^31 values: the same states and gradients."""
+@pytest.mark.parametrize("bodies,n_seg", [(10, 6_200_000), (2, 2 ** 32 // 39 + 2)])
+def test_ephemeris_table_past_2_31_values(torch_cuda, bodies, n_seg):
+    """The same segments in a table so long that the last bodies' lie past
+    2^31 values (19 GB) and even one body has 2^32 (69 GB): the same states and
+    gradients, the latter's up to the rounding of another kernel shape."""
     torch, api = torch_cuda
     torch.cuda.empty_cache()
-    n_seg = 6_200_000
     case = synth.survey_case(n_obj=2100, n_frames=0)
-    eph, far = (api.DeviceEphemeris.from_synth(case.ephem) for _ in range(2))
+    e = case.ephem
+    e = dataclasses.replace(e, coef=e.coef[:bodies], gm=e.gm[:bodies], flags=e.flags[:bodies], names=e.names[:bodies],
+                            j2=e.j2[:bodies])
+    eph, far = (api.DeviceEphemeris.from_synth(e) for _ in range(2))
     nb, ns, _, m = eph.coef.shape
     assert (nb - 1) * n_seg * 3 * m > 2 ** 31
+    tol = 0.0 if bodies == 10 else 1e-13
     if torch.cuda.mem_get_info()[0] < 10 * nb * n_seg * 3 * m:
         pytest.skip("not enough free device memory")
     far.coef = torch.zeros((nb, n_seg, 3, m), dtype=torch.float64, device="cuda")
@@ -514,14 +519,15 @@ def test_ephemeris_table_past_2_31_values(torch_cuda):
         o = api.default_opts(lanes_per_body=lanes)
         x, s = api.propagate(eph, x0[:n], 0.0, [5.0, 30.0], o)
         y, r = api.propagate(far, x0[:n], 0.0, [5.0, 30.0], o)
-        assert torch.equal(s, r) and torch.equal(x, y), (n, lanes)
+        assert torch.equal(s, r) and (x - y).abs().max().item() <= tol, (n, lanes)
     t_obs = _dev_x(torch, np.tile([3.0, 9.0, 20.0], (40, 1)))
     grads = []
     for e in (eph, far):
         ctx = api.AdjointContext(e, 0.0, 20.0, t_obs, _dev_x(torch, np.tile([1.0, 0.1, 0.0], (40, 3, 1))))
         sky = ctx.forward(x0[:40])
         grads.append((sky, ctx.backward(x0[:40], torch.ones_like(sky))))
-    assert torch.equal(grads[0][0], grads[1][0]) and torch.equal(grads[0][1], grads[1][1])
+    for a, b in zip(*grads):
+        assert (a - b).abs().max().item() <= 1e3 * tol * b.abs().max().item()
     del far
     torch.cuda.empty_cache()
 
