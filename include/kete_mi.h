@@ -95,7 +95,8 @@ typedef struct {
     double cell_chord;       /* FoV sky-grid cell size (chord units; 0 = auto: 0.10); calls of few
                                 frames a batch are joined without a grid (the size is still checked) */
     double lt_tol;           /* light-time convergence: last update in days (1e-15) */
-    int32_t max_steps;       /* per object per call (2,000,000) */
+    int32_t max_steps;       /* per object per call (2,000,000); an object counts the steps of its
+                                wavefront, which the objects that share one take together */
     int32_t max_iter;        /* corrector iterations per step (12) */
     int32_t n_buckets;       /* step-size buckets (octaves of the predicted step), 1 = none (16) */
     int32_t block;           /* integrator threads per block: 64/128/256, 0 = auto (0: 64 for the

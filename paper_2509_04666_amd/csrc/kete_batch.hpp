@@ -20,7 +20,8 @@ struct BatchParams {
     int32_t n_tiles;
     int32_t all_solo;           // every body has a wavefront of its own (no order needed)
     int32_t pad_;
-    const int2* tiles;          // [n_tiles] (job, tile of KETE_BATCH_TILE bodies), longest first
+    const int2* tiles;          // [n_tiles] (job, tile of KETE_BATCH_TILE bodies), longest jobs first;
+                                // taken in this order only where the bodies are not sorted (else tile_order)
     unsigned int* tile_counter;
     const double* x0;           // [bodies][6]
     const double* epochs;       // concatenated epochs of all jobs

@@ -10,8 +10,10 @@
 // grid, and a persistent join pops work items (one per 64 narrow objects
 // of a cell) and scans the frames of the 27 neighbouring cells with
 // wave-uniform loops; the remaining ("wide") objects scan the cells their
-// cap touches, one wavefront per object.  Pairs that pass the cap test
-// and a linear-motion test with a rigorous remainder bound become
+// cap touches, one wavefront per object.  Batches of few frames are joined
+// without a grid, every object with every frame (k_fov_direct).  Pairs that
+// pass the cap or box test and that a linear-motion test with a rigorous
+// remainder bound leaves undecided become
 // candidates; the exact test (universal-variable hop with light time,
 // then n.d > 0 for every normal) decides membership.  Appends are staged
 // in LDS per wavefront and flushed to the global lists in chunks; the
@@ -770,9 +772,8 @@ __device__ __forceinline__ int nth_set_bit(unsigned long long w, int r) {
     return pos;
 }
 
-// Linear-motion test of an (object, frame) pair that passed the cap test
-// (and, with a linear test, the linear cap test),
-// with its remainder bound: the object moves on x + v dt within eps of its
+// Linear-motion test of an (object, frame) pair that passed a join's cap or
+// box test, with its remainder bound: the object moves on x + v dt within eps of its
 // true emission point, so with unit normals and ul = x + v dt - o a
 // sub-frame is out when some n . ul <= -2 eps, surely in when every
 // n . ul > 2 eps (the true direction's dot products then keep their
@@ -1028,9 +1029,9 @@ __device__ __forceinline__ void add_stats(const FovParams& p, unsigned long long
     }
 }
 
-// A frame's record for the per-cell join's broadcast loop: cap (centre,
-// cos and sin of the radius), cell rank, time and observer, as five
-// 16-byte LDS words.
+// A frame's record for the broadcast loops of the direct join and of the
+// per-cell join without locators: cap (centre, cos and sin of the radius),
+// cell rank, time and observer, as five 16-byte LDS words.
 struct __align__(16) FrameRec {
     double c[3], cosr, sinr, rank, t, o[3];
 };
@@ -1040,17 +1041,28 @@ constexpr int kLocChunk = 32;          // frame records staged at once where fra
 
 // Persistent join: every wavefront pops work items until none is left.
 // An item is up to 64 narrow objects of one (batch, cell), one per lane;
-// the frame records of the 27 neighbouring cells are read 64 at a time,
-// one per lane, and broadcast for the cap test.  (object, frame) pairs
-// that pass it are queued in LDS and take the linear-motion test 64 at a
-// time, one pair per lane, reading their object's data from the lane that
-// holds it.  The broadcast loop reads LDS only: after the motion-cap test
-// an object with a linear test takes the linear cap test there (the frame
-// record carries the frame's time and observer), and only objects without
-// one take the locator-box test, a global read.  Items are in (batch, cell) order; the waves of
-// one XCD start on their own slice of the list, so that neighbouring cells
-// share that XCD's L2, and help the other slices when theirs runs out.
-constexpr int kJoinWaves = 3;        // resident waves per SIMD of the join kernels (168 VGPRs, a few spilled)
+// the frame caps of the 27 neighbouring cells are read 64 at a time, one
+// per lane, and the frames whose cap meets a cap around all of the item's
+// objects are staged in LDS and broadcast.
+//   Frames with sub-frames (kLoc): their box records (the head of the
+// locator), kLocChunk at a time.  An object's straight line at the frame's
+// time, seen from the observer, has to lie above the planes through the
+// centre of projection and the four edges of the frame's box, less its bound
+// times their norm.  (The cap around a 7 x 7.3 degree footprint is 1.6 times
+// its box: 750,000 objects x 2,000,000 of them 55.5 ms by cap, now 48.)
+//   Frames without: their caps, which the straight line's direction has to
+// meet (lin_cap_hit).
+//   The few objects without a linear test take the frame's locator-box test,
+// a global read, or the motion-cap test.  (object, frame) pairs that pass are
+// queued in LDS and take the sub-frame tests 64 at a time, one pair per lane,
+// reading their object's data from the lane that holds it.  Items are in
+// (batch, cell) order; the waves of one XCD start on their own slice of the
+// list, so that neighbouring cells share that XCD's L2, and help the other
+// slices when theirs runs out.
+//   Resident waves per SIMD of the join kernels: three, with 168 registers
+// (the per-cell join with boxes keeps 40 more in scratch, the others 8 to 15).
+// Two or four took a step of that workload from 119 to 131 and 133 ms.
+constexpr int kJoinWaves = 3;
 template <bool kLoc>
 __global__ __launch_bounds__(256, kJoinWaves) void k_fov_cells(const FovParams p) {
     const int lane = threadIdx.x & 63, wv = (threadIdx.x >> 6) & 3;

@@ -168,7 +168,8 @@ inline int group_shape(const EphemArgs& E) {
     return E.n_body == 10 && E.n_gr == 3 ? 2 : E.n_body == 3 && E.n_gr == 2 ? 3 : 1;
 }
 
-// lanes_per_body: 1 (one lane per object) or 8 (an 8-lane group per object).
+// lanes_per_body: 1 (one lane per object), 8 (an 8-lane group per object) or 7
+// (see k_nbody_g8).
 hipError_t launch_nbody(const NbodyParams& p, int block, int lanes_per_body, hipStream_t s);
 
 // Stable counting sort of objects into step-size buckets.

@@ -1,13 +1,15 @@
 // n-body propagation of massless bodies on gfx950 (App. A force model,
 // Gauss-Radau collocation with the predictor removed, App. A.6).
 //
-// Two layouts share the force, the Chebyshev window staging and the step
-// control.  k_nbody_g8 (the default) spreads each object over an 8-lane
-// group, one collocation node per lane, so a wavefront integrates 8
-// objects; k_nbody keeps one object per lane (64 per wavefront).  The
-// objects of a wavefront share the time grid: the step size is the
-// smallest one any of them asks for, so the perturber states at the node
-// times of a step are evaluated once per wavefront and read from LDS.
+// Two layouts share the force and the step control.  k_nbody_g8 (the
+// default) spreads each object over a group of lanes, one or more per
+// collocation node: 7 lanes, 9 objects a wavefront, in long lists; 14 lanes,
+// 4 objects, in short ones; 56 lanes for an object that has a wavefront of its
+// own; or, on request, 8 lanes, 8 objects.  k_nbody keeps one object per lane
+// (64 per wavefront).  The objects of a wavefront share the time grid: the
+// step size is the smallest one any of them asks for, so the perturber states
+// at the node times of a step are evaluated once per wavefront and read from
+// LDS.
 // k_nbody stages the Chebyshev coefficients of the segments a window needs
 // in LDS once per workgroup; k_nbody_g8 reads them from L2 (see
 // node_ephemeris8).  Objects are sorted by predicted step size
@@ -366,17 +368,22 @@ __global__ void k_hpref_init(const double* __restrict__ x0, double* __restrict__
 
 // Wavefronts of one object each, for a launch of n objects of which the
 // device may name the heaviest (`classes`: they are sorted by predicted step).
-// Up to kSoloAll objects, two wavefronts a SIMD, all of them.  Up to
-// kSoloSomeObj, fewer than eight rounds of wavefronts on the chip, the
-// heaviest kSoloSome: with nine a wavefront the fast orbits took 3.3 ms of a
-// 100,000-object year whose other wavefronts were done in 2.4 ms (2.8 ms with
-// their own).  In a longer launch their wavefronts end among the others:
-// 750,000 objects take 17.1 ms either way.
+// Up to kSoloAll objects, two wavefronts a SIMD, all of them (63 objects over
+// a month: 55 -> 43 us).  Up to kSoloSomeObj, twelve rounds of wavefronts on
+// the chip, the heaviest kSoloSome: the fast orbits' wavefronts end a launch
+// of few rounds (5% fast orbits: 20,000 objects for a quarter of a year 0.99 ->
+// 0.84 ms, for five years 10.0 -> 6.7; 100,000 for five years 14.4 -> 12.2).
+// For a year, over which sharing wavefronts lines up their perihelion passages
+// (see solo_class_steps), it gains up to 50,000 objects (2.33 -> 1.79 ms) and
+// costs behind (100,000 2.55 -> 2.79, 220,000 4.72 -> 5.12).  In longer lists
+// it costs at either span (400,000: a year 8.3 -> 8.9 ms, five 41.5 -> 43.0).
 constexpr int kSoloSome = 1024, kSoloSomeObj = 220000;
 // Two lanes per node (4 objects a wavefront) up to here: at most two
-// wavefronts a SIMD, whose sweeps are half as long.
-//   (20,011 objects carried back five years, the heaviest 1,024 of them
-// alone: 14.9 -> 7.5 ms; 63 objects over a month: 55 -> 43 us.)
+// wavefronts a SIMD, whose sweeps are half as long (a quarter of a year: 3,000
+// objects 0.87 -> 0.73 ms, 9,000 1.10 -> 0.74; five years with 30% fast
+// orbits: 9,000 8.6 -> 7.0 ms, 3,000 6.06 either way).  Beyond it depends on
+// the orbits: 16,000 objects for a year would take 1.48 -> 1.52 ms with 5% fast
+// ones and 2.20 -> 1.69 with 30%.
 constexpr int kPairLanesObj = 8192;
 int solo_waves_for(int n, bool classes) {
     if (n <= kSoloAll) return n;
