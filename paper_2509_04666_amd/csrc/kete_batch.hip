@@ -273,7 +273,7 @@ __device__ __forceinline__ void batch_wave(const BatchParams& p, const GroupCons
 // job ended the launch: of 256 uneven jobs (500,000 bodies, up to ten years)
 // all but a hundred wavefronts were done in 9 ms and the last in 31.  With
 // the lone bodies 12.5 ms, and with the tiles by their steps instead of their
-// jobs' time spans 10.8, 9.4 of which every wavefront works.
+// jobs' time spans 10.8.
 template <int NB, int NGR, int NJ2, int DEG1>
 __global__ __launch_bounds__(64, 2) void k_batch_g8(const BatchParams p) {
     constexpr int G = KETE_BATCH_LANES;

@@ -340,8 +340,8 @@ constexpr double kKeplerLastStep = 1e-7;
 // update's root and quotient within a few ulp, and none after one of
 // kKeplerLastStep |chi|.  A max_iter below the default counts the updates of
 // the rule above, so there every hop goes by it.  With the next hop's start
-// carried along (lighttime) 3,000,017 pairs' magnitudes take 150 us, 165
-// without.  `quick` tells the caller.
+// carried along (lighttime) 3,000,017 pairs' magnitudes take 155 us, 168 by
+// the general solve.  `quick` tells the caller.
 __device__ __forceinline__ int kepler_uv(double mu, double smu, const double r0[3], const double v0[3],
                                          double dt, double& chi, double r[3], double v[3], int max_iter,
                                          bool& quick) {

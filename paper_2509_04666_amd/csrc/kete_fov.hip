@@ -1049,7 +1049,7 @@ constexpr int kLocChunk = 32;          // frame records staged at once where fra
 // time, seen from the observer, has to lie above the planes through the
 // centre of projection and the four edges of the frame's box, less its bound
 // times their norm.  (The cap around a 7 x 7.3 degree footprint is 1.6 times
-// its box: 750,000 objects x 2,000,000 of them 55.5 ms by cap, now 48.)
+// its box: 750,000 objects x 2,000,000 of them take 48 ms, by cap ten more.)
 //   Frames without: their caps, which the straight line's direction has to
 // meet (lin_cap_hit).
 //   The few objects without a linear test take the frame's locator-box test,
